@@ -1,7 +1,7 @@
-// fp32 scan kernels: one workgroup per (batch, head) recurrence, the K x V
-// state resident in LDS for all T steps, every contraction done with fp32
-// vector FMAs.  This is the path for float32 io (1e-5 parity class) and for
-// shapes the matrix-core kernels do not cover.
+// fp32 scan kernels for V = 128 (fp32 io, and bf16 io with K < 128): one workgroup
+// per (batch, head) recurrence, the K x V state resident in LDS for all T steps, every
+// contraction done with fp32 vector FMAs.  V <= 64 runs on m2rnn_quad_f32.hip, whose
+// waves hold a row's columns and W in registers; at V = 128 those would be 512 registers.
 //
 // Forward : recurrence equations / Algorithm 1 of the paper.
 // Backward: Algorithm 2 (BPTT) with the carried state gradient added to
@@ -19,9 +19,8 @@ namespace {
 constexpr int kMaxThreads = 1024;
 constexpr int kMaxPerThread = 16;  // 128*128 / 1024
 constexpr size_t kLdsBudget = 160 * 1024 - 2048;
-// unroll factor of the contraction loops: as far as the registers left by PT elements per
-// thread allow without spilling
-template <int PT> constexpr int kUnrollOf = PT <= 2 ? 8 : (PT <= 4 ? 2 : 1);
+constexpr int PT = kMaxPerThread;  // state (and dW) elements per thread
+constexpr int UN = 1;  // unroll factor of the contraction loops: PT elements leave no registers for more
 
 template <typename IO> __device__ __forceinline__ float to_f32(IO x);
 template <> __device__ __forceinline__ float to_f32<float>(float x) { return x; }
@@ -68,12 +67,11 @@ __device__ __forceinline__ float block_sum(float x, float *red) {
 // One step of the recurrence for the elements this thread owns.  Hs holds the
 // state before the step; the new values are returned in hn[] (and Z in z[] if
 // asked) and are NOT yet written back.
-template <bool kKeepZ, int PT>
+template <bool kKeepZ>
 __device__ __forceinline__ void step_elements(const float *Hs, const float *Wf, const float *ks,
                                               const float *vs, float f, int K, int V, int KV,
                                               float *hn, float *z) {
   const int tid = threadIdx.x, nt = blockDim.x;
-  constexpr int UN = kUnrollOf<PT>;
 #pragma unroll
   for (int m = 0; m < PT; ++m) {
     const int e = tid + m * nt;
@@ -90,15 +88,12 @@ __device__ __forceinline__ void step_elements(const float *Hs, const float *Wf, 
   }
 }
 
-// PT: state (and dW) elements per thread, the smallest power of two that covers the shape:
-// the per-thread arrays and the unrolled element loops are no longer than they must be.
 // WL: W[n] is copied to LDS (it fits next to the state) and read from there; a template
 // parameter, so that every access to W has one address space (with a run-time choice the
 // contraction reads W through generic-address loads, one wait per load).
-template <typename IO, bool WL, int PT>
+template <typename IO, bool WL>
 __global__ void __launch_bounds__(kMaxThreads) gen_fwd_kernel(FwdArgs a, const float *W32) {
   extern __shared__ float smem[];
-  constexpr int UN = kUnrollOf<PT>;
   const int K = a.K, V = a.V, KV = K * V, T = a.T, N = a.N;
   const int tid = threadIdx.x, nt = blockDim.x;
   float *Hs = smem;
@@ -133,7 +128,7 @@ __global__ void __launch_bounds__(kMaxThreads) gen_fwd_kernel(FwdArgs a, const f
     float f = a.f[((size_t)b * T + t) * N + n];
     if (a.gate_alpha) f = gate_psi(f, a.gate_alpha[n], a.gate_beta[n]);
     __syncthreads();
-    step_elements<false, PT>(Hs, Wf, ks, vs, f, K, V, KV, hn, nullptr);
+    step_elements<false>(Hs, Wf, ks, vs, f, K, V, KV, hn, nullptr);
     __syncthreads();
 #pragma unroll
     for (int m = 0; m < PT; ++m) {
@@ -158,13 +153,12 @@ __global__ void __launch_bounds__(kMaxThreads) gen_fwd_kernel(FwdArgs a, const f
 
 // Backward for one (b, n): chunks from last to first; per chunk a forward
 // recompute that parks the chunk's states in `states`, then the reverse sweep.
-template <typename IO, bool WL, int PT>
+template <typename IO, bool WL>
 __global__ void __launch_bounds__(kMaxThreads)
     gen_bwd_kernel(BwdArgs a, const float *W32, const float *WT32, float *states, float *dW_unit,
                    float *dq_heads, float *dk_heads) {
   extern __shared__ float smem[];
   __shared__ float red[kMaxThreads / 64];
-  constexpr int UN = kUnrollOf<PT>;
   const int K = a.K, V = a.V, KV = K * V, VV = V * V, T = a.T, N = a.N, C = a.C;
   const int tid = threadIdx.x, nt = blockDim.x;
   float *Hs = smem;        // state before the step
@@ -220,7 +214,7 @@ __global__ void __launch_bounds__(kMaxThreads)
       float f = a.f[((size_t)b * T + t) * N + n];
     if (a.gate_alpha) f = gate_psi(f, a.gate_alpha[n], a.gate_beta[n]);
       __syncthreads();
-      step_elements<false, PT>(Hs, Wf, ks, vs, f, K, V, KV, hn, nullptr);
+      step_elements<false>(Hs, Wf, ks, vs, f, K, V, KV, hn, nullptr);
       __syncthreads();
 #pragma unroll
       for (int m = 0; m < PT; ++m) {
@@ -247,7 +241,7 @@ __global__ void __launch_bounds__(kMaxThreads)
     if (a.gate_alpha) f = gate_psi(f, a.gate_alpha[n], a.gate_beta[n]);
       __syncthreads();
       // recompute Z_t and H_t exactly as the forward did
-      step_elements<true, PT>(Hs, Wf, ks, vs, f, K, V, KV, hn, z);
+      step_elements<true>(Hs, Wf, ks, vs, f, K, V, KV, hn, z);
 #pragma unroll
       for (int m = 0; m < PT; ++m) {
         const int e = tid + m * nt;
@@ -386,20 +380,13 @@ __global__ void head_group_sum_kernel(const float *per_head, IO *out, size_t BT,
 }
 
 struct GenericPlan {
-  int threads, per_thread;
   size_t lds_fwd, lds_bwd;
-  int w_lds_fwd, w_lds_bwd;
+  bool w_lds_fwd, w_lds_bwd;
 };
 
 GenericPlan make_plan(int K, int V) {
   GenericPlan p;
   const int KV = K * V, VV = V * V;
-  p.threads = KV < kMaxThreads ? KV : kMaxThreads;
-  // every thread must be able to own its share of dW (V*V elements) as well
-  while (p.threads < kMaxThreads && VV > p.threads * kMaxPerThread) p.threads *= 2;
-  const int big = KV > VV ? KV : VV;
-  p.per_thread = 1;
-  while (p.per_thread * p.threads < big) p.per_thread *= 2;
   const size_t base_f = (size_t)(KV + 2 * K + V) * 4;
   p.w_lds_fwd = base_f + (size_t)VV * 4 <= kLdsBudget;
   p.lds_fwd = base_f + (p.w_lds_fwd ? (size_t)VV * 4 : 0);
@@ -451,15 +438,10 @@ hipError_t run_fwd(const FwdArgs &a, hipStream_t s) {
   auto go = [&](auto kernel) {
     hipError_t e2 = set_max_lds_once(kernel, (int)kLdsBudget);  // (the need varies with the shape)
     if (e2 != hipSuccess) return e2;
-    hipLaunchKernelGGL(kernel, dim3(units), dim3(p.threads), p.lds_fwd, s, a, (const float *)W32);
+    hipLaunchKernelGGL(kernel, dim3(units), dim3(kMaxThreads), p.lds_fwd, s, a, (const float *)W32);
     return hipGetLastError();
   };
-#define M2RNN_GEN_FWD(PT_) \
-  if (p.per_thread == PT_)  \
-    return p.w_lds_fwd ? go(gen_fwd_kernel<IO, true, PT_>) : go(gen_fwd_kernel<IO, false, PT_>);
-  M2RNN_GEN_FWD(1) M2RNN_GEN_FWD(2) M2RNN_GEN_FWD(4) M2RNN_GEN_FWD(8) M2RNN_GEN_FWD(16)
-#undef M2RNN_GEN_FWD
-  return hipErrorInvalidValue;
+  return p.w_lds_fwd ? go(gen_fwd_kernel<IO, true>) : go(gen_fwd_kernel<IO, false>);
 }
 
 template <typename IO>
@@ -482,24 +464,15 @@ hipError_t run_bwd(const BwdArgs &a, hipStream_t s) {
     auto go = [&](auto kernel) {
       hipError_t e2 = set_max_lds_once(kernel, (int)kLdsBudget);
       if (e2 != hipSuccess) return e2;
-      hipLaunchKernelGGL(kernel, dim3(units), dim3(p.threads), p.lds_bwd, s, a, (const float *)W32,
+      hipLaunchKernelGGL(kernel, dim3(units), dim3(kMaxThreads), p.lds_bwd, s, a, (const float *)W32,
                          (const float *)WT32, states, dW_unit, dq_heads, dk_heads);
       return hipGetLastError();
     };
-    e = hipErrorInvalidValue;
-#define M2RNN_GEN_BWD(PT_) \
-  if (p.per_thread == PT_)  \
-    e = p.w_lds_bwd ? go(gen_bwd_kernel<IO, true, PT_>) : go(gen_bwd_kernel<IO, false, PT_>);
-    M2RNN_GEN_BWD(1) M2RNN_GEN_BWD(2) M2RNN_GEN_BWD(4) M2RNN_GEN_BWD(8) M2RNN_GEN_BWD(16)
-#undef M2RNN_GEN_BWD
+    e = p.w_lds_bwd ? go(gen_bwd_kernel<IO, true>) : go(gen_bwd_kernel<IO, false>);
     if (e != hipSuccess) return e;
-    if (shared && a.T > 0) {
-      const size_t total = (size_t)a.B * a.T * a.Nqk * a.K;
-      hipLaunchKernelGGL(head_group_sum_kernel<IO>, dim3(grid_for(total, 256)), dim3(256), 0, s,
-                         (const float *)dq_heads, (IO *)a.dq, (size_t)a.B * a.T, a.N, a.Nqk, a.K);
-      hipLaunchKernelGGL(head_group_sum_kernel<IO>, dim3(grid_for(total, 256)), dim3(256), 0, s,
-                         (const float *)dk_heads, (IO *)a.dk, (size_t)a.B * a.T, a.N, a.Nqk, a.K);
-      if ((e = hipGetLastError()) != hipSuccess) return e;
+    if (shared) {
+      if ((e = generic_head_group_sum(a, dq_heads, a.dq, s)) != hipSuccess) return e;
+      if ((e = generic_head_group_sum(a, dk_heads, a.dk, s)) != hipSuccess) return e;
     }
   }
   // B == 0 leaves dW = 0: the sum below runs over zero terms.
@@ -510,18 +483,33 @@ hipError_t run_bwd(const BwdArgs &a, hipStream_t s) {
 
 }  // namespace
 
+hipError_t generic_head_group_sum(const BwdArgs &a, const float *per_head, void *out, hipStream_t s) {
+  const size_t bt = (size_t)a.B * a.T, total = bt * a.Nqk * a.K;
+  if (total == 0) return hipSuccess;
+  if (a.io == 0)
+    hipLaunchKernelGGL(head_group_sum_kernel<float>, dim3(grid_for(total, 256)), dim3(256), 0, s, per_head,
+                       (float *)out, bt, a.N, a.Nqk, a.K);
+  else
+    hipLaunchKernelGGL(head_group_sum_kernel<__hip_bfloat16>, dim3(grid_for(total, 256)), dim3(256), 0, s,
+                       per_head, (__hip_bfloat16 *)out, bt, a.N, a.Nqk, a.K);
+  return hipGetLastError();
+}
+
 int generic_default_chunk(int, int) { return 16; }
 int generic_max_chunk(int, int) { return 256; }
 
 size_t generic_workspace_bytes(int B, int T, int N, int Nqk, int K, int V, int C, int bwd) {
+  if (quad_supported(K, V)) return quad_workspace_bytes(B, T, N, Nqk, K, V, C, bwd);
   return layout_ws(B, T, N, Nqk, K, V, C, bwd).total;
 }
 
 hipError_t generic_fwd(const FwdArgs &a, hipStream_t s) {
+  if (quad_supported(a.K, a.V)) return quad_fwd(a, s);  // (bf16 io with V <= 64 never gets here)
   return a.io == 0 ? run_fwd<float>(a, s) : run_fwd<__hip_bfloat16>(a, s);
 }
 
 hipError_t generic_bwd(const BwdArgs &a, hipStream_t s) {
+  if (quad_supported(a.K, a.V)) return quad_bwd(a, s);
   return a.io == 0 ? run_bwd<float>(a, s) : run_bwd<__hip_bfloat16>(a, s);
 }
 

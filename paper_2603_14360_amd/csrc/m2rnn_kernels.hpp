@@ -82,12 +82,21 @@ inline hipError_t set_max_lds_once(Fn kernel, int bytes) {
 }
 inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
-// ---- fp32 path (plain vector-ALU kernels; any supported shape, either io) ----
+// ---- fp32 path (any supported shape, either io) ----
 int generic_default_chunk(int K, int V);
 int generic_max_chunk(int K, int V);
 size_t generic_workspace_bytes(int B, int T, int N, int Nqk, int K, int V, int C, int bwd);
 hipError_t generic_fwd(const FwdArgs &a, hipStream_t s);
 hipError_t generic_bwd(const BwdArgs &a, hipStream_t s);
+
+// dq or dk (`out`, io dtype) = sum of the per-head fp32 values [B,T,N,K] over the heads that share a q/k head
+hipError_t generic_head_group_sum(const BwdArgs &a, const float *per_head, void *out, hipStream_t s);
+
+// fp32 kernels on the fp32 matrix instructions, V <= 64 (forward: fp32 io; backward: either io)
+bool quad_supported(int K, int V);
+size_t quad_workspace_bytes(int B, int T, int N, int Nqk, int K, int V, int C, int bwd);
+hipError_t quad_fwd(const FwdArgs &a, hipStream_t s);
+hipError_t quad_bwd(const BwdArgs &a, hipStream_t s);
 
 // dw_r[n][j] = sum over b, t of dy (.) v in a fixed order (two stages through `scratch`)
 size_t residual_dw_r_scratch_bytes(int N, int V);

@@ -1,0 +1,701 @@
+// fp32 scan kernels for V <= 64 on the fp32 matrix instructions: every operand, product and sum
+// is fp32 (the 1e-5 parity class), the state stays in registers from step to step, and no wave
+// waits for another one inside a chunk of steps.
+//
+// Which instruction, and why.  Row i of H W needs only row i of H, so what a wave must have at
+// hand for its rows is the whole of each row, in every lane that holds one of the row's columns.
+// v_mfma_f32_4x4x1 computes 16 independent 4 x 4 blocks and can broadcast one block's A operand
+// to a group of blocks (cbsz / abid): with A = 4 rows x 1 column of the state, broadcast, and
+// B = that row of W spread over the V columns, V such instructions are the product of 4 rows
+// with W, and the operand never leaves the registers.  One wave holds 4 rows x 64 columns,
+// 8 x 32 or 16 x 16: RW = 256 / V rows.  The rate (64 multiply-adds per clock and SIMD) is that of the
+// 16x16x4 form, and twice that of the vector ALU; the 16x16x4 form would spread a row over
+// V / 16 waves, with an exchange through LDS and a barrier in every step.
+// Layouts.  Accumulator ("D"): lane 4 b + n holds column 4 (b mod V/4) + n, register m row m of
+// the lane's group of 4 rows.  A operand: lane 4 b + m holds row m, register j column 4 b + j.
+// The two differ by a 4 x 4 transposition inside each group of four lanes (quad_transpose, eight
+// vector instructions).
+//
+// Measured against the vector-ALU kernels that these replace (one workgroup per state, state and
+// W in LDS, three barriers per step): B = 4, N = 8, K = V = 32, T = 512 forward 1.16 -> 0.24 ms,
+// backward 4.35 -> 0.58 ms.  What bounds it there: 128 waves on 1024 SIMDs, each a chain of some
+// 1100 cycles per step (forward: 256 of matrix instructions, the rest the 130 vector instructions
+// of a lone wave); LDS and HBM are idle.
+#include "m2rnn_kernels.hpp"
+
+#include <hip/hip_bf16.h>
+
+#include <type_traits>
+#include <utility>
+
+namespace m2rnn {
+namespace {
+
+typedef float f4_t __attribute__((ext_vector_type(4)));
+
+constexpr int TB = 16;  // steps per staged block (forward), per on-chip stash (backward)
+
+template <typename IO> __device__ __forceinline__ float to_f32(IO x);
+template <> __device__ __forceinline__ float to_f32<float>(float x) { return x; }
+template <> __device__ __forceinline__ float to_f32<__hip_bfloat16>(__hip_bfloat16 x) {
+  return __bfloat162float(x);
+}
+template <typename IO> __device__ __forceinline__ IO from_f32(float x);
+template <> __device__ __forceinline__ float from_f32<float>(float x) { return x; }
+template <> __device__ __forceinline__ __hip_bfloat16 from_f32<__hip_bfloat16>(float x) {
+  return __float2bfloat16(x);  // round to nearest even
+}
+
+template <int K_, int V_>
+struct Quad {
+  static constexpr int K = K_, V = V_;
+  static constexpr int CB = V / 4;                     // 4-column blocks per row group
+  static constexpr int GR = 16 / CB;                   // row groups per wave
+  static constexpr int RW = 4 * GR;                    // rows per wave
+  static constexpr int CBSZ = CB == 16 ? 4 : (CB == 8 ? 3 : 2);
+  static constexpr int NWU = K / RW;                   // waves per state
+  static constexpr int NW = NWU < 4 ? NWU : 4;         // waves per workgroup
+  static constexpr int P = NWU / NW;                   // workgroups per state
+  static constexpr int ROWS = NW * RW;
+  static constexpr int THREADS = NW * 64;
+  static constexpr int NQ = TB * ROWS / THREADS;       // staged values per thread: q, k ...
+  static constexpr int NV = (TB * V + THREADS - 1) / THREADS;  // ... v, dy
+  static_assert(NWU >= 1 && NWU % NW == 0 && (TB * ROWS) % THREADS == 0, "quad tile");
+};
+
+// tanh with a relative error below 2 ulp over the whole range: an odd polynomial (a weighted
+// least-squares fit of (tanh x - x) / x^3 on [0, 0.57], relative error 1.6e-9) below 0.55, and
+// (1 - e) / (1 + e) with e = 2^(-2 |x| log2 e) above, where 1 - e has no cancellation.  Branch-free,
+// 20 issue slots; the library's tanhf is about twice that.
+__device__ __forceinline__ float tanh_fast_f32(float x) {
+  const float e = __builtin_amdgcn_exp2f(-2.885390081777927f * __builtin_fabsf(x));
+  const float big = (1.f - e) * __builtin_amdgcn_rcpf(1.f + e);
+  const float x2 = x * x;
+  float p = fmaf(x2, -0.006123021710664034f, 0.02096743695437908f);
+  p = fmaf(x2, p, -0.05382782220840454f);
+  p = fmaf(x2, p, 0.13332362473011017f);
+  p = fmaf(x2, p, -0.3333331048488617f);
+  const float small = fmaf(x * x2, p, x);
+  return __builtin_fabsf(x) < 0.55f ? small : __builtin_copysignf(big, x);
+}
+
+template <int CTRL>
+__device__ __forceinline__ float quad_perm(float x) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, 0xF, 0xF, true));
+}
+// y[j] in lane m of a quad = x[m] of lane j: registers and lanes swapped one index bit at a time.
+// (Every lane runs the permutations, the selects come after: a permutation inside the select's
+// arms would run with part of the lanes switched off, and read nothing from those.)
+__device__ __forceinline__ f4_t quad_transpose(f4_t x, bool odd, bool high) {
+  const float p0 = quad_perm<0xB1>(x[0]), p1 = quad_perm<0xB1>(x[1]);  // lane xor 1
+  const float p2 = quad_perm<0xB1>(x[2]), p3 = quad_perm<0xB1>(x[3]);
+  const float a0 = odd ? p1 : x[0], a1 = odd ? x[1] : p0, a2 = odd ? p3 : x[2], a3 = odd ? x[3] : p2;
+  const float q0 = quad_perm<0x4E>(a0), q1 = quad_perm<0x4E>(a1);      // lane xor 2
+  const float q2 = quad_perm<0x4E>(a2), q3 = quad_perm<0x4E>(a3);
+  return f4_t{high ? q2 : a0, high ? q3 : a1, high ? a2 : q0, high ? a3 : q1};
+}
+
+// acc[k mod 4] += (column k of A) x (row k of B) for all k = 4 B0 + j of the blocks B0...: four
+// independent chains, because the result of a 4x4x1 is not ready for the next instruction's
+// accumulator
+template <int CBSZ, int V, int... B0>
+__device__ __forceinline__ f4_t contract_blocks(const f4_t &a, const float (&w)[V], f4_t init,
+                                                std::integer_sequence<int, B0...>) {
+  f4_t acc0 = init, acc1 = {0.f, 0.f, 0.f, 0.f}, acc2 = acc1, acc3 = acc1;
+  (
+      [&] {
+        acc0 = __builtin_amdgcn_mfma_f32_4x4x1f32(a[0], w[4 * B0 + 0], acc0, CBSZ, B0, 0);
+        acc1 = __builtin_amdgcn_mfma_f32_4x4x1f32(a[1], w[4 * B0 + 1], acc1, CBSZ, B0, 0);
+        acc2 = __builtin_amdgcn_mfma_f32_4x4x1f32(a[2], w[4 * B0 + 2], acc2, CBSZ, B0, 0);
+        acc3 = __builtin_amdgcn_mfma_f32_4x4x1f32(a[3], w[4 * B0 + 3], acc3, CBSZ, B0, 0);
+      }(),
+      ...);
+  return (acc0 + acc1) + (acc2 + acc3);
+}
+template <typename Q>
+__device__ __forceinline__ f4_t contract(const f4_t &a, const float (&w)[Q::V], f4_t init) {
+  return contract_blocks<Q::CBSZ, Q::V>(a, w, init, std::make_integer_sequence<int, Q::CB>{});
+}
+
+// Waits for a loaded value here: the first use sits in a loop, where the wait would be repeated
+// in every step, and would wait there for the prefetch as well.
+__device__ __forceinline__ void arrived(f4_t &x) { asm volatile("" : "+v"(x)); }
+
+// Per-lane position inside the workgroup's rows
+template <typename Q>
+struct LanePos {
+  int wave, lane, rg, col, row;  // row: first of the lane's 4 rows inside the workgroup
+  int arow, acol;                // row and first column of the lane's A operand
+  bool odd, high;
+  __device__ __forceinline__ LanePos() {
+    lane = threadIdx.x & 63;
+    wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int blk = lane >> 2;
+    rg = blk / Q::CB;
+    col = 4 * (blk % Q::CB) + (lane & 3);
+    row = wave * Q::RW + 4 * rg;
+    arow = row + (lane & 3);
+    acol = 4 * (blk % Q::CB);
+    odd = lane & 1;
+    high = lane & 2;
+  }
+};
+
+// ------------------------------------------------------------------ forward
+// One barrier per 16 steps.  q, k, v, f of the next 16 steps travel while the current ones are
+// computed.  A lane adds q_i H[i][j] over its 4 rows; the rest of the sum over rows goes through
+// LDS once per 16 steps, and over the workgroups of a state through parts_sum_kernel.
+template <typename Q>
+struct FwdLds {
+  alignas(16) float q[2][TB][Q::ROWS], k[2][TB][Q::ROWS], v[2][TB][Q::V], f[2][TB];
+  float y[2][TB][Q::NW][64];
+};
+
+template <typename Q, bool DO_Y>
+__global__ void __launch_bounds__(Q::THREADS, 2) quad_fwd_kernel(FwdArgs a, float *__restrict__ ypart) {
+  constexpr int V = Q::V, K = Q::K, ROWS = Q::ROWS, THREADS = Q::THREADS, NQ = Q::NQ, NV = Q::NV;
+  __shared__ FwdLds<Q> sm;
+  const int unit = blockIdx.x / Q::P, part = blockIdx.x % Q::P;
+  const int T = a.T, N = a.N, b = unit / N, n = unit - b * N, g = n / (N / a.Nqk);
+  const int tid = threadIdx.x, row_base = part * ROWS;
+  const LanePos<Q> p;
+  const float *qg = (const float *)a.q + ((size_t)b * T * a.Nqk + g) * K + row_base;
+  const float *kg = (const float *)a.k + ((size_t)b * T * a.Nqk + g) * K + row_base;
+  const float *vg = (const float *)a.v + ((size_t)b * T * N + n) * V;
+  const float *fg = a.f + (size_t)b * T * N + n;
+  const size_t qk_step = (size_t)a.Nqk * K, v_step = (size_t)N * V;
+
+  float w[V];
+#pragma unroll
+  for (int c = 0; c < V; ++c) w[c] = ((const float *)a.W)[((size_t)n * V + c) * V + p.col];
+  const size_t st_off = ((size_t)unit * K + row_base + p.row) * V + p.col;
+  f4_t h = {0.f, 0.f, 0.f, 0.f};
+  if (a.H0)
+#pragma unroll
+    for (int m = 0; m < 4; ++m) h[m] = a.H0[st_off + m * V];
+  arrived(h);
+
+  float rq[NQ], rk[NQ], rv[NV], rf = 0.f;
+  // (steps behind the end fetch the last step again and are never used)
+  auto load = [&](int t0) {
+#pragma unroll
+    for (int m = 0; m < NQ; ++m) {
+      const int idx = tid + m * THREADS, t = min(t0 + idx / ROWS, T - 1);
+      rq[m] = qg[t * qk_step + idx % ROWS];
+      rk[m] = kg[t * qk_step + idx % ROWS];
+    }
+#pragma unroll
+    for (int m = 0; m < NV; ++m) {
+      const int idx = tid + m * THREADS, t = min(t0 + idx / V, T - 1);
+      rv[m] = vg[t * v_step + idx % V];
+    }
+    rf = fg[(size_t)min(t0 + (tid & (TB - 1)), T - 1) * N];
+  };
+  auto store = [&](int buf) {
+#pragma unroll
+    for (int m = 0; m < NQ; ++m) {
+      const int idx = tid + m * THREADS;
+      (&sm.q[buf][0][0])[idx] = rq[m];
+      (&sm.k[buf][0][0])[idx] = rk[m];
+    }
+#pragma unroll
+    for (int m = 0; m < NV; ++m) {
+      const int idx = tid + m * THREADS;
+      if (TB * V % THREADS == 0 || idx < TB * V) (&sm.v[buf][0][0])[idx] = rv[m];
+    }
+    if (tid < TB) sm.f[buf][tid] = a.gate_alpha ? gate_psi(rf, a.gate_alpha[n], a.gate_beta[n]) : rf;
+  };
+  // y rows of one block out of the per-wave sums in LDS
+  auto flush = [&](int t0, int len, int buf) {
+    for (int idx = tid; idx < len * V; idx += THREADS) {
+      const int s = idx / V, j = idx % V;
+      float acc = 0.f;
+#pragma unroll
+      for (int i = 0; i < Q::NW * Q::GR; ++i) acc += (&sm.y[buf][s][0][0])[i * V + j];
+      const size_t off = (size_t)(t0 + s) * v_step + j;
+      if constexpr (Q::P == 1) {
+        if (a.w_r) acc = fmaf(((const float *)a.w_r)[n * V + j], vg[off], acc);  // (v in LDS may be overwritten already)
+        ((float *)a.y)[((size_t)b * T * N + n) * V + off] = acc;
+      } else {
+        ypart[(size_t)part * a.B * T * v_step + ((size_t)b * T * N + n) * V + off] = acc;
+      }
+    }
+  };
+
+  const int nblk = (T + TB - 1) / TB, nck = (T + a.C - 1) / a.C;
+  int next_ck = 0;
+  float *ckpt = a.ckpt ? a.ckpt + (size_t)unit * nck * K * V + (size_t)(row_base + p.row) * V + p.col : nullptr;
+  if (nblk > 0) {
+    load(0);
+    store(0);
+  }
+  __syncthreads();
+  for (int blk = 0; blk < nblk; ++blk) {
+    const int t0 = blk * TB, len = min(TB, T - t0), buf = blk & 1;
+    if (blk + 1 < nblk) load(t0 + TB);
+#pragma nounroll
+    for (int s = 0; s < len; ++s) {
+      if (ckpt && t0 + s == next_ck) {  // state before step t0 + s
+#pragma unroll
+        for (int m = 0; m < 4; ++m) ckpt[m * V] = h[m];
+        ckpt += (size_t)K * V;
+        next_ck += a.C;
+      }
+      const f4_t k4 = *(const f4_t *)&sm.k[buf][s][p.row];
+      const float vj = sm.v[buf][s][p.col], f = sm.f[buf][s], gm = 1.f - f;
+      const f4_t ha = quad_transpose(h, p.odd, p.high);
+      const f4_t sp = contract<Q>(ha, w, k4 * vj);
+#pragma unroll
+      for (int m = 0; m < 4; ++m) h[m] = fmaf(f, h[m], gm * tanh_fast_f32(sp[m]));
+      if constexpr (DO_Y) {
+        const f4_t q4 = *(const f4_t *)&sm.q[buf][s][p.row];
+        float y = q4[0] * h[0];
+#pragma unroll
+        for (int m = 1; m < 4; ++m) y = fmaf(q4[m], h[m], y);
+        // lanes of a row group are consecutive, so lane order is [row group][column]
+        sm.y[buf][s][p.wave][p.lane] = y;
+      }
+    }
+    if (blk + 1 < nblk) store(buf ^ 1);
+    // one barrier per block: it closes this block's y sums and the next block's vectors; the
+    // buffers of this block are written again only behind the next barrier
+    __syncthreads();
+    if constexpr (DO_Y) flush(t0, len, buf);
+  }
+  if (a.HT)
+#pragma unroll
+    for (int m = 0; m < 4; ++m) a.HT[st_off + m * V] = h[m];
+}
+
+// ------------------------------------------------------------------ backward
+// Per stash of up to 16 steps, last to first:
+//   recompute  the states from the checkpoint, H before each step and Z of each step to LDS
+//   sweep      in reverse: G = q dy^T + carry, dS = (1 - f) G (1 - Z^2) into Z's place,
+//              carry = f G + dS W^T; df on a 16x16x4 product with ones in column s
+//   finish     everything that contracts over more than a wave holds, for all 16 steps at once,
+//              out of LDS: dW += sum_s H^T dS (16x16x4 products over steps and rows), dq = H dy,
+//              dk = dS v, dv = dS^T k
+// Recompute and sweep are private to a wave (no barrier); two barriers per stash around `finish`.
+// H and dS lie row-major with the 16-column blocks of a row placed by (row xor block), so that the
+// 4 rows that a matrix operand reads at once fall on different banks.
+template <typename Q>
+struct BwdLds {
+  static constexpr int V = Q::V, ROWS = Q::ROWS;
+  alignas(16) float H[TB + 1][ROWS * V];
+  alignas(16) float D[TB][ROWS * V];
+  alignas(16) float q[TB][ROWS], k[TB][ROWS], v[TB][V], dy[TB][V], f[TB];
+  float df[Q::NW * 4][TB];
+};
+template <int V>
+__device__ __forceinline__ int sw(int row, int col) {  // element offset inside [ROWS][V]
+  const int x = V == 64 ? (row & 3) : (V == 32 ? ((row >> 1) & 1) : 0);
+  return row * V + (col ^ (16 * x));
+}
+
+struct QuadBwdWs {
+  float *sub;     // [units][P][THREADS * 4] x sub-chunk states, only when C > 16
+  float *dvp, *dfp;  // [P][B,T,N,V], [P][B,T,N]  (P > 1)
+  float *dWp;     // [B N P][V][V]
+  float *dqh, *dkh;  // [B,T,N,K] (Nqk != N)
+  int nsub;
+};
+
+template <typename IO, typename Q>
+__global__ void __launch_bounds__(Q::THREADS, Q::V < 64 ? 2 : 1) quad_bwd_kernel(BwdArgs a, QuadBwdWs ws) {
+  constexpr int V = Q::V, K = Q::K, ROWS = Q::ROWS, THREADS = Q::THREADS, NQ = Q::NQ, NV = Q::NV,
+                NW = Q::NW;
+  extern __shared__ __attribute__((aligned(16))) char lds[];
+  BwdLds<Q> &sm = *(BwdLds<Q> *)lds;
+  const int unit = blockIdx.x / Q::P, part = blockIdx.x % Q::P;
+  const int T = a.T, N = a.N, C = a.C, b = unit / N, n = unit - b * N, g = n / (N / a.Nqk);
+  const int tid = threadIdx.x, row_base = part * ROWS;
+  const LanePos<Q> p;
+  const size_t qk0 = ((size_t)b * T * a.Nqk + g) * K + row_base, v0 = ((size_t)b * T * N + n) * V,
+               f0 = (size_t)b * T * N + n;
+  const size_t qk_step = (size_t)a.Nqk * K, v_step = (size_t)N * V;
+  const IO *qg = (const IO *)a.q + qk0, *kg = (const IO *)a.k + qk0, *vg = (const IO *)a.v + v0,
+           *dyg = (const IO *)a.dy + v0;
+  const float *fg = a.f + f0;
+
+  float w[V], wt[V];
+#pragma unroll
+  for (int c = 0; c < V; ++c) {
+    w[c] = to_f32<IO>(((const IO *)a.W)[((size_t)n * V + c) * V + p.col]);
+    wt[c] = to_f32<IO>(((const IO *)a.W)[((size_t)n * V + p.col) * V + c]);
+  }
+  const size_t st_off = ((size_t)unit * K + row_base + p.row) * V + p.col;
+  f4_t carry = {0.f, 0.f, 0.f, 0.f};
+  if (a.dHT)
+#pragma unroll
+    for (int m = 0; m < 4; ++m) carry[m] = a.dHT[st_off + m * V];
+  arrived(carry);
+
+  // dW tiles of 16 x 16: with at least one per wave, wave w owns the NTW tiles w NTW ..; with
+  // fewer tiles than waves (V = 16) every wave adds its own share of the rows to the one tile
+  constexpr int CT = V / 16, NT = CT * CT, NTW = NT >= NW ? NT / NW : 1, SPLIT = NT >= NW ? 1 : NW;
+  f4_t dW[NTW];
+#pragma unroll
+  for (int i = 0; i < NTW; ++i) dW[i] = f4_t{0.f, 0.f, 0.f, 0.f};
+
+  float rq[NQ], rk[NQ], rv[NV], rdy[NV], rf = 0.f;
+  auto load = [&](int t0, int len) {
+#pragma unroll
+    for (int m = 0; m < NQ; ++m) {
+      const int idx = tid + m * THREADS, t = t0 + min(idx / ROWS, len - 1);
+      rq[m] = to_f32<IO>(qg[t * qk_step + idx % ROWS]);
+      rk[m] = to_f32<IO>(kg[t * qk_step + idx % ROWS]);
+    }
+#pragma unroll
+    for (int m = 0; m < NV; ++m) {
+      const int idx = tid + m * THREADS, t = t0 + min(idx / V, len - 1);
+      rv[m] = to_f32<IO>(vg[t * v_step + idx % V]);
+      rdy[m] = to_f32<IO>(dyg[t * v_step + idx % V]);
+    }
+    rf = fg[(size_t)(t0 + min(tid & (TB - 1), len - 1)) * N];
+  };
+  auto store = [&]() {
+#pragma unroll
+    for (int m = 0; m < NQ; ++m) {
+      (&sm.q[0][0])[tid + m * THREADS] = rq[m];
+      (&sm.k[0][0])[tid + m * THREADS] = rk[m];
+    }
+#pragma unroll
+    for (int m = 0; m < NV; ++m) {
+      const int idx = tid + m * THREADS;
+      if (TB * V % THREADS == 0 || idx < TB * V) {
+        (&sm.v[0][0])[idx] = rv[m];
+        (&sm.dy[0][0])[idx] = rdy[m];
+      }
+    }
+    if (tid < TB) sm.f[tid] = a.gate_alpha ? gate_psi(rf, a.gate_alpha[n], a.gate_beta[n]) : rf;
+  };
+  // one recomputed step of the recurrence; the state's A operand is returned for the stash
+  auto step = [&](f4_t &h, int s, f4_t &ha) __attribute__((always_inline)) {
+    const f4_t k4 = *(const f4_t *)&sm.k[s][p.row];
+    const float vj = sm.v[s][p.col], f = sm.f[s], gm = 1.f - f;
+    ha = quad_transpose(h, p.odd, p.high);
+    const f4_t sp = contract<Q>(ha, w, k4 * vj);
+    f4_t z;
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+      z[m] = tanh_fast_f32(sp[m]);
+      h[m] = fmaf(f, h[m], gm * z[m]);
+    }
+    return z;
+  };
+
+  const int nck = (T + C - 1) / C;
+  const int a_off = sw<V>(p.arow, p.acol);
+  if (nck > 0) {  // vectors of the last stash
+    const int t0 = (nck - 1) * C, len = T - t0, sub = (len - 1) / TB;
+    load(t0 + sub * TB, len - sub * TB);
+  }
+  for (int ck = nck - 1; ck >= 0; --ck) {
+    const int ck0 = ck * C, clen = min(C, T - ck0), nsub = (clen + TB - 1) / TB;
+    f4_t hck;
+    {
+      const float *src = a.ckpt + ((size_t)unit * nck + ck) * K * V + (size_t)(row_base + p.row) * V + p.col;
+#pragma unroll
+      for (int m = 0; m < 4; ++m) hck[m] = src[m * V];
+      arrived(hck);
+    }
+    // checkpoints further apart than a stash: a first pass leaves the state in front of each
+    // later stash in the workspace, at a place that only the same lane reads again
+    f4_t *const subst = (f4_t *)ws.sub + ((size_t)blockIdx.x * ws.nsub) * THREADS + tid;
+    if (nsub > 1) {
+      f4_t h = hck, ha;
+      for (int sub = 0; sub + 1 < nsub; ++sub) {
+        load(ck0 + sub * TB, TB);
+        __syncthreads();
+        store();
+        __syncthreads();
+#pragma nounroll
+        for (int s = 0; s < TB; ++s) step(h, s, ha);
+        subst[(size_t)sub * THREADS] = h;
+      }
+      load(ck0 + (nsub - 1) * TB, clen - (nsub - 1) * TB);
+      __syncthreads();
+    }
+    for (int sub = nsub - 1; sub >= 0; --sub) {
+      const int t0 = ck0 + sub * TB, len = min(TB, clen - sub * TB);
+      store();
+      f4_t h = sub > 0 ? subst[(size_t)(sub - 1) * THREADS] : hck, ha;
+      arrived(h);
+      __syncthreads();
+      // the next stash's vectors travel during this one
+      if (sub > 0) load(t0 - TB, TB);
+      else if (ck > 0 && C <= TB) load(ck0 - C, C);
+      // ---- recompute
+#pragma nounroll
+      for (int s = 0; s < len; ++s) {
+        const f4_t z = step(h, s, ha);
+        *(f4_t *)&sm.H[s][a_off] = ha;
+        ((f4_t *)sm.D[s])[tid] = z;  // (only this lane reads it again)
+      }
+      *(f4_t *)&sm.H[len][a_off] = quad_transpose(h, p.odd, p.high);
+      // ---- sweep
+      f4_t dfacc = {0.f, 0.f, 0.f, 0.f};
+#pragma nounroll
+      for (int s = len - 1; s >= 0; --s) {
+        const f4_t q4 = *(const f4_t *)&sm.q[s][p.row];
+        const float dyj = sm.dy[s][p.col], f = sm.f[s], gm = 1.f - f;
+        const f4_t z = ((const f4_t *)sm.D[s])[tid];
+        f4_t hp, G, dS;
+        float dfl = 0.f;
+#pragma unroll
+        for (int m = 0; m < 4; ++m) hp[m] = sm.H[s][sw<V>(p.row + m, p.col)];
+#pragma unroll
+        for (int m = 0; m < 4; ++m) {
+          G[m] = fmaf(q4[m], dyj, carry[m]);
+          dfl = fmaf(G[m], hp[m] - z[m], dfl);
+          dS[m] = gm * G[m] * fmaf(-z[m], z[m], 1.f);
+        }
+        const f4_t da = quad_transpose(dS, p.odd, p.high);
+        *(f4_t *)&sm.D[s][a_off] = da;
+        dfacc = __builtin_amdgcn_mfma_f32_16x16x4f32(dfl, (p.lane & 15) == s ? 1.f : 0.f, dfacc, 0, 0, 0);
+        const f4_t d = contract<Q>(da, wt, f4_t{0.f, 0.f, 0.f, 0.f});
+#pragma unroll
+        for (int m = 0; m < 4; ++m) carry[m] = fmaf(f, G[m], d[m]);
+        if (a.clip > 0.f)
+#pragma unroll
+          for (int m = 0; m < 4; ++m) carry[m] = __builtin_amdgcn_fmed3f(carry[m], -a.clip, a.clip);
+      }
+      // column s of dfacc: lane (s, i) holds four of its sixteen rows
+      sm.df[p.wave * 4 + (p.lane >> 4)][p.lane & 15] = (dfacc[0] + dfacc[1]) + (dfacc[2] + dfacc[3]);
+      __syncthreads();
+      // ---- finish: dW, 4 rows of one step per product
+#pragma unroll
+      for (int i = 0; i < NTW; ++i) {
+        const int tile = SPLIT > 1 ? 0 : p.wave * NTW + i, ci = tile / CT, cj = tile % CT;
+        const int kr = p.lane >> 4, c = p.lane & 15;
+        // (summed per stash first: one running sum over all steps would lose two bits)
+        f4_t acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = acc0;
+        const int r0 = SPLIT > 1 ? p.wave * Q::RW : 0;
+        constexpr int NR = SPLIT > 1 ? Q::RW : ROWS;
+        for (int s = 0; s < len; ++s) {
+#pragma unroll
+          for (int r = 0; r < NR; r += 8) {
+            const int ra = r0 + r + kr, rb = ra + 4;
+            acc0 = __builtin_amdgcn_mfma_f32_16x16x4f32(sm.H[s][sw<V>(ra, 16 * ci + c)],
+                                                        sm.D[s][sw<V>(ra, 16 * cj + c)], acc0, 0, 0, 0);
+            if (r + 4 < NR)
+              acc1 = __builtin_amdgcn_mfma_f32_16x16x4f32(sm.H[s][sw<V>(rb, 16 * ci + c)],
+                                                          sm.D[s][sw<V>(rb, 16 * cj + c)], acc1, 0, 0, 0);
+          }
+        }
+        dW[i] += acc0 + acc1;
+      }
+      // ---- finish: dq_s[i] = H_s dy_s, dk_s[i] = dS_s v_s, one (step, row) per thread
+      for (int idx = tid; idx < len * ROWS; idx += THREADS) {
+        const int s = idx / ROWS, i = idx % ROWS;
+        f4_t q4 = {0.f, 0.f, 0.f, 0.f}, k4 = q4;
+#pragma unroll 4
+        for (int c4 = 0; c4 < V / 4; ++c4) {
+          const int c = 4 * (c4 ^ ((i >> 2) & 3));  // (rows that share a swizzle start on other banks)
+          q4 += *(const f4_t *)&sm.H[s + 1][sw<V>(i, c)] * *(const f4_t *)&sm.dy[s][c];
+          k4 += *(const f4_t *)&sm.D[s][sw<V>(i, c)] * *(const f4_t *)&sm.v[s][c];
+        }
+        const float dq = (q4[0] + q4[1]) + (q4[2] + q4[3]), dk = (k4[0] + k4[1]) + (k4[2] + k4[3]);
+        if (ws.dqh) {
+          const size_t o = (((size_t)b * T + t0 + s) * N + n) * K + row_base + i;
+          ws.dqh[o] = dq;
+          ws.dkh[o] = dk;
+        } else {
+          const size_t o = qk0 + (size_t)(t0 + s) * qk_step + i;
+          ((IO *)a.dq)[o] = from_f32<IO>(dq);
+          ((IO *)a.dk)[o] = from_f32<IO>(dk);
+        }
+      }
+      // ---- finish: dv_s[j] = sum over the workgroup's rows of dS[i][j] k_i, one (step, column)
+      for (int idx = tid; idx < len * V; idx += THREADS) {
+        const int s = idx / V, j = idx % V;
+        float acc = 0.f;
+#pragma unroll 8
+        for (int i = 0; i < ROWS; ++i) acc = fmaf(sm.D[s][sw<V>(i, j)], sm.k[s][i], acc);
+        const size_t o = v0 + (size_t)(t0 + s) * v_step + j;
+        if constexpr (Q::P == 1) {
+          if (a.w_r) acc = fmaf(to_f32<IO>(((const IO *)a.w_r)[n * V + j]), sm.dy[s][j], acc);
+          ((IO *)a.dv)[o] = from_f32<IO>(acc);
+        } else {
+          ws.dvp[(size_t)part * a.B * T * v_step + o] = acc;
+        }
+      }
+      if (tid < len) {
+        float acc = 0.f;
+#pragma unroll
+        for (int i = 0; i < NW * 4; ++i) acc += sm.df[i][tid];
+        const size_t o = f0 + (size_t)(t0 + tid) * N;
+        if constexpr (Q::P == 1) a.df[o] = acc;
+        else ws.dfp[(size_t)part * a.B * T * N + o] = acc;
+      }
+      __syncthreads();
+    }
+  }
+  if (a.dH0)
+#pragma unroll
+    for (int m = 0; m < 4; ++m) a.dH0[st_off + m * V] = carry[m];
+  // dW of the workgroup: D layout of the 16x16 product, rows 4 (lane / 16) + r, column lane % 16
+  float *dst = ws.dWp + (size_t)blockIdx.x * V * V;
+  if constexpr (SPLIT > 1) {
+    f4_t *red = (f4_t *)sm.H;
+    __syncthreads();
+    red[tid] = dW[0];
+    __syncthreads();
+    if (p.wave == 0) {
+      f4_t s = red[p.lane];
+#pragma unroll
+      for (int i = 1; i < NW; ++i) s += red[i * 64 + p.lane];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) dst[(4 * (p.lane >> 4) + r) * V + (p.lane & 15)] = s[r];
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < NTW; ++i) {
+      const int tile = p.wave * NTW + i, ci = tile / CT, cj = tile % CT;
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        dst[(16 * ci + 4 * (p.lane >> 4) + r) * V + 16 * cj + (p.lane & 15)] = dW[i][r];
+    }
+  }
+}
+
+// out = sum over P parts in increasing order [+ w_r (.) x, the residual's term]
+template <typename IO>
+__global__ void parts_sum_kernel(const float *__restrict__ part, IO *__restrict__ out, size_t total, int P,
+                                 const IO *__restrict__ w_r, const IO *__restrict__ x, int NV) {
+  for (size_t e = blockIdx.x * (size_t)blockDim.x + threadIdx.x; e < total; e += (size_t)gridDim.x * blockDim.x) {
+    float s = part[e];
+    for (int p = 1; p < P; ++p) s += part[(size_t)p * total + e];
+    if (w_r) s = fmaf(to_f32<IO>(w_r[e % NV]), to_f32<IO>(x[e]), s);
+    out[e] = from_f32<IO>(s);
+  }
+}
+template <typename IO>
+hipError_t parts_sum(const float *part, IO *out, size_t total, int P, const IO *w_r, const IO *x, int NV,
+                     hipStream_t s) {
+  if (total == 0) return hipSuccess;
+  const size_t blocks = (total + 255) / 256;
+  hipLaunchKernelGGL(parts_sum_kernel<IO>, dim3((unsigned)(blocks > 8192 ? 8192 : blocks)), dim3(256), 0, s, part,
+                     out, total, P, w_r, x, NV);
+  return hipGetLastError();
+}
+
+// dW[n] = sum over b, then over the workgroups of a state, in increasing order
+__global__ void quad_dw_sum_kernel(const float *__restrict__ dWp, float *__restrict__ dW, int B, int N, int P, int VV) {
+  const size_t total = (size_t)N * VV;
+  for (size_t e = blockIdx.x * (size_t)blockDim.x + threadIdx.x; e < total; e += (size_t)gridDim.x * blockDim.x) {
+    const int n = e / VV, r = e % VV;
+    float s = 0.f;
+    for (int b = 0; b < B; ++b)
+      for (int p = 0; p < P; ++p) s += dWp[(((size_t)b * N + n) * P + p) * VV + r];
+    dW[e] = s;
+  }
+}
+
+template <typename Q>
+hipError_t launch_fwd(const FwdArgs &a, hipStream_t s) {
+  const int units = a.B * a.N;
+  if (units == 0) return hipSuccess;
+  float *ypart = (float *)a.ws;
+  if (a.write_y)
+    hipLaunchKernelGGL((quad_fwd_kernel<Q, true>), dim3(units * Q::P), dim3(Q::THREADS), 0, s, a, ypart);
+  else
+    hipLaunchKernelGGL((quad_fwd_kernel<Q, false>), dim3(units * Q::P), dim3(Q::THREADS), 0, s, a, ypart);
+  hipError_t e = hipGetLastError();
+  if (e == hipSuccess && Q::P > 1 && a.write_y)
+    e = parts_sum<float>(ypart, (float *)a.y, (size_t)a.B * a.T * a.N * a.V, Q::P, (const float *)a.w_r,
+                         (const float *)a.v, a.N * a.V, s);
+  return e;
+}
+
+struct QuadLayout {
+  size_t sub, dvp, dfp, dWp, heads, total;
+  int nsub;
+};
+QuadLayout quad_layout(int B, int T, int N, int Nqk, int K, int V, int C, int P, int threads) {
+  QuadLayout l;
+  const size_t units = (size_t)B * N;
+  l.nsub = (C - 1) / TB;
+  l.sub = align256(units * P * l.nsub * threads * 16);
+  l.dvp = P > 1 ? align256((size_t)P * units * T * V * 4) : 0;
+  l.dfp = P > 1 ? align256((size_t)P * units * T * 4) : 0;
+  l.dWp = align256(units * P * V * V * 4);
+  l.heads = Nqk != N ? align256(units * T * K * 4) : 0;
+  l.total = l.sub + l.dvp + l.dfp + l.dWp + 2 * l.heads;
+  return l;
+}
+
+template <typename IO, typename Q>
+hipError_t launch_bwd(const BwdArgs &a, hipStream_t s) {
+  const int units = a.B * a.N;
+  const QuadLayout l = quad_layout(a.B, a.T, a.N, a.Nqk, a.K, a.V, a.C, Q::P, Q::THREADS);
+  char *p = a.ws;
+  QuadBwdWs ws;
+  ws.nsub = l.nsub;
+  ws.sub = (float *)p; p += l.sub;
+  ws.dvp = (float *)p; p += l.dvp;
+  ws.dfp = (float *)p; p += l.dfp;
+  ws.dWp = (float *)p; p += l.dWp;
+  ws.dqh = l.heads ? (float *)p : nullptr; p += l.heads;
+  ws.dkh = l.heads ? (float *)p : nullptr;
+  hipError_t e;
+  if (units > 0) {
+    auto kernel = quad_bwd_kernel<IO, Q>;
+    if ((e = set_max_lds_once(kernel, (int)sizeof(BwdLds<Q>))) != hipSuccess) return e;
+    hipLaunchKernelGGL(kernel, dim3(units * Q::P), dim3(Q::THREADS), sizeof(BwdLds<Q>), s, a, ws);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    const size_t steps = (size_t)units * a.T;
+    if (Q::P > 1) {
+      e = parts_sum<IO>(ws.dvp, (IO *)a.dv, steps * a.V, Q::P, (const IO *)a.w_r, (const IO *)a.dy, a.N * a.V, s);
+      if (e == hipSuccess)
+        e = parts_sum<float>(ws.dfp, a.df, steps, Q::P, nullptr, nullptr, 1, s);
+      if (e != hipSuccess) return e;
+    }
+    if (l.heads) {
+      if ((e = generic_head_group_sum(a, ws.dqh, a.dq, s)) != hipSuccess) return e;
+      if ((e = generic_head_group_sum(a, ws.dkh, a.dk, s)) != hipSuccess) return e;
+    }
+  }
+  const size_t total = (size_t)a.N * a.V * a.V;
+  hipLaunchKernelGGL(quad_dw_sum_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, ws.dWp, a.dW, a.B,
+                     a.N, Q::P, a.V * a.V);
+  return hipGetLastError();
+}
+
+#define M2RNN_QUAD_CASES(X) \
+  X(16, 16) X(32, 16) X(64, 16) X(128, 16) X(16, 32) X(32, 32) X(64, 32) X(128, 32) X(16, 64) X(32, 64) X(64, 64) X(128, 64)
+
+}  // namespace
+
+bool quad_supported(int, int V) { return V <= 64; }
+
+size_t quad_workspace_bytes(int B, int T, int N, int Nqk, int K, int V, int C, int bwd) {
+#define X(K_, V_)                                                                                  \
+  if (K == K_ && V == V_) {                                                                        \
+    using Q = Quad<K_, V_>;                                                                        \
+    if (!bwd) return Q::P > 1 ? align256((size_t)Q::P * B * N * T * V * 4) : 0;                     \
+    return quad_layout(B, T, N, Nqk, K, V, C, Q::P, Q::THREADS).total;                              \
+  }
+  M2RNN_QUAD_CASES(X)
+#undef X
+  return 0;
+}
+
+hipError_t quad_fwd(const FwdArgs &a, hipStream_t s) {
+#define X(K_, V_) \
+  if (a.K == K_ && a.V == V_) return launch_fwd<Quad<K_, V_>>(a, s);
+  M2RNN_QUAD_CASES(X)
+#undef X
+  return hipErrorInvalidValue;
+}
+
+hipError_t quad_bwd(const BwdArgs &a, hipStream_t s) {
+#define X(K_, V_)                                                                        \
+  if (a.K == K_ && a.V == V_)                                                            \
+    return a.io == 0 ? launch_bwd<float, Quad<K_, V_>>(a, s) : launch_bwd<__hip_bfloat16, Quad<K_, V_>>(a, s);
+  M2RNN_QUAD_CASES(X)
+#undef X
+  return hipErrorInvalidValue;
+}
+
+}  // namespace m2rnn
