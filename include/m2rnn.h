@@ -251,7 +251,8 @@ m2rnn_status m2rnn_gated_rmsnorm_bwd(int32_t B, int32_t T, int32_t D, int32_t io
  * the same kernels as m2rnn_fwd_opt and gives the same bits.
  *   - A descriptor whose m2rnn_workspace_bytes(desc, 0) exceeds M2RNN_STATIC_SCRATCH_BYTES is
  *     rejected with M2RNN_ERR_WORKSPACE before anything is launched (e.g. B*T*N*V <= 2^19
- *     at K = V = 64 with few states; shapes whose forward needs no scratch always pass).
+ *     at K = V = 64 with few states; shapes whose forward needs no scratch always pass, and
+ *     so does fp32 io with V <= 64, which then runs the parts of a state in turn).
  *   - All calls on one GPU share that GPU's array: calls that overlap in time on one GPU
  *     (different streams or threads) race; serialise them.  Nothing in the array needs to
  *     start at zero: every part that is read in a call was written earlier in that call.

@@ -128,7 +128,7 @@ void *static_scratch_of_current_device() {
 m2rnn_status fwd_impl(const m2rnn_desc *desc, const m2rnn_opts *opts, const void *q,
                       const void *k, const void *v, const float *f, const void *W,
                       const float *H0, void *y, float *HT, float *ckpt, void *workspace,
-                      size_t workspace_bytes, void *hip_stream) {
+                      size_t workspace_bytes, void *hip_stream, size_t need) {
   m2rnn_status st = check_desc(desc);
   if (st != M2RNN_OK) return st;
   const int C = resolve_chunk(desc);
@@ -143,7 +143,6 @@ m2rnn_status fwd_impl(const m2rnn_desc *desc, const m2rnn_opts *opts, const void
   const void *ptrs[] = {q, k, v, f, W, H0, y, HT, ckpt, workspace, w_r, ga, gb};
   for (const void *p : ptrs)
     if (misaligned(p)) return M2RNN_ERR_ALIGN;
-  const size_t need = family_ws(desc, C, 0);
   if (need > 0 && (!workspace || workspace_bytes < need))
     return workspace ? M2RNN_ERR_WORKSPACE : M2RNN_ERR_NULL;
 
@@ -152,6 +151,7 @@ m2rnn_status fwd_impl(const m2rnn_desc *desc, const m2rnn_opts *opts, const void
   a.C = C; a.io = desc->io;
   a.q = q; a.k = k; a.v = v; a.W = W; a.f = f; a.H0 = H0;
   a.y = y; a.HT = HT; a.ckpt = ckpt; a.write_y = 1; a.ws = (char *)workspace;
+  a.ws_bytes = workspace_bytes;
   a.w_r = w_r; a.gate_alpha = ga; a.gate_beta = gb;
   hipStream_t s = (hipStream_t)hip_stream;
   const hipError_t e = run_fwd(desc, a, s);
@@ -242,7 +242,7 @@ m2rnn_status m2rnn_fwd_opt(const m2rnn_desc *desc, const m2rnn_opts *opts, const
                            const float *H0, void *y, float *HT, float *ckpt, void *workspace,
                            size_t workspace_bytes, void *hip_stream) {
   return fwd_impl(desc, opts, q, k, v, f, W, H0, y, HT, ckpt, workspace, workspace_bytes,
-                  hip_stream);
+                  hip_stream, m2rnn_workspace_bytes(desc, 0));
 }
 
 m2rnn_status m2rnn_fwd_static(const m2rnn_desc *desc, const m2rnn_opts *opts, const void *q,
@@ -253,7 +253,11 @@ m2rnn_status m2rnn_fwd_static(const m2rnn_desc *desc, const m2rnn_opts *opts, co
   if (st != M2RNN_OK) return st;
   const int C = resolve_chunk(desc);
   if (!C) return M2RNN_ERR_CHUNK;
-  const size_t need = family_ws(desc, C, 0);
+  size_t need = family_ws(desc, C, 0);
+  // (the fp32 kernels can do without room for all partial sums)
+  if (fwd_family_of(desc) == kGeneric && quad_supported(desc->K, desc->V) &&
+      need > (size_t)M2RNN_STATIC_SCRATCH_BYTES)
+    need = 256;
   if (need > (size_t)M2RNN_STATIC_SCRATCH_BYTES) return M2RNN_ERR_WORKSPACE;
   void *scratch_ptr = nullptr;
   if (need > 0 && desc->B > 0 && desc->T > 0) {
@@ -261,7 +265,7 @@ m2rnn_status m2rnn_fwd_static(const m2rnn_desc *desc, const m2rnn_opts *opts, co
     if (!scratch_ptr) return M2RNN_ERR_HIP;
   }
   return fwd_impl(desc, opts, q, k, v, f, W, H0, y, HT, ckpt, scratch_ptr,
-                  scratch_ptr ? (size_t)M2RNN_STATIC_SCRATCH_BYTES : 0, hip_stream);
+                  scratch_ptr ? (size_t)M2RNN_STATIC_SCRATCH_BYTES : 0, hip_stream, scratch_ptr ? need : 0);
 }
 
 m2rnn_status m2rnn_bwd(const m2rnn_desc *desc, const void *q, const void *k, const void *v,
@@ -314,7 +318,7 @@ m2rnn_status m2rnn_bwd_opt(const m2rnn_desc *desc, const m2rnn_opts *opts, const
     fa.B = desc->B; fa.T = desc->T; fa.N = desc->N; fa.Nqk = desc->Nqk; fa.K = desc->K;
     fa.V = desc->V; fa.C = C; fa.io = desc->io;
     fa.q = q; fa.k = k; fa.v = v; fa.W = W; fa.f = f; fa.H0 = H0;
-    fa.y = nullptr; fa.HT = nullptr; fa.ckpt = own; fa.write_y = 0; fa.ws = ws;
+    fa.y = nullptr; fa.HT = nullptr; fa.ckpt = own; fa.write_y = 0; fa.ws = ws; fa.ws_bytes = main_bytes;
     fa.w_r = nullptr; fa.gate_alpha = ga; fa.gate_beta = gb;
     const hipError_t e = run_fwd(desc, fa, s);
     if (e != hipSuccess) return M2RNN_ERR_HIP;

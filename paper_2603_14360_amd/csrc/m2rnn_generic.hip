@@ -499,7 +499,11 @@ int generic_default_chunk(int, int) { return 16; }
 int generic_max_chunk(int, int) { return 256; }
 
 size_t generic_workspace_bytes(int B, int T, int N, int Nqk, int K, int V, int C, int bwd) {
-  if (quad_supported(K, V)) return quad_workspace_bytes(B, T, N, Nqk, K, V, C, bwd);
+  if (quad_supported(K, V)) {
+    // (never zero: a workspace that is plainly too small stays an error, whatever the shape)
+    const size_t need = quad_workspace_bytes(B, T, N, Nqk, K, V, C, bwd);
+    return need > 256 ? need : 256;
+  }
   return layout_ws(B, T, N, Nqk, K, V, C, bwd).total;
 }
 

@@ -19,6 +19,7 @@ struct FwdArgs {
   float *HT, *ckpt;  // ckpt may be null (inference)
   int write_y;       // 0: checkpoint-only pass (the backward's pass 1)
   char *ws;          // workspace base (may be null when nothing is needed)
+  size_t ws_bytes;   // its size
   const void *w_r;   // [N,V] io dtype: y_t += w_r (.) v_t; null = no residual
   const float *gate_alpha, *gate_beta;  // [N] each: f holds the input of the gate function; null = f is the gate value
 };

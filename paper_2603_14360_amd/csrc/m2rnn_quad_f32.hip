@@ -151,11 +151,12 @@ struct FwdLds {
   float y[2][TB][Q::NW][64];
 };
 
-template <typename Q, bool DO_Y>
-__global__ void __launch_bounds__(Q::THREADS, 2) quad_fwd_kernel(FwdArgs a, float *__restrict__ ypart) {
+// SEQ: one workgroup runs the P parts of a state one after the other and adds up y in place, in
+// the order of parts_sum_kernel (same bits): for callers whose scratch cannot hold the partial sums.
+template <typename Q, bool DO_Y, bool SEQ>
+__device__ __forceinline__ void quad_fwd_part(const FwdArgs &a, float *__restrict__ ypart, FwdLds<Q> &sm,
+                                              int unit, int part) {
   constexpr int V = Q::V, K = Q::K, ROWS = Q::ROWS, THREADS = Q::THREADS, NQ = Q::NQ, NV = Q::NV;
-  __shared__ FwdLds<Q> sm;
-  const int unit = blockIdx.x / Q::P, part = blockIdx.x % Q::P;
   const int T = a.T, N = a.N, b = unit / N, n = unit - b * N, g = n / (N / a.Nqk);
   const int tid = threadIdx.x, row_base = part * ROWS;
   const LanePos<Q> p;
@@ -213,9 +214,12 @@ __global__ void __launch_bounds__(Q::THREADS, 2) quad_fwd_kernel(FwdArgs a, floa
 #pragma unroll
       for (int i = 0; i < Q::NW * Q::GR; ++i) acc += (&sm.y[buf][s][0][0])[i * V + j];
       const size_t off = (size_t)(t0 + s) * v_step + j;
-      if constexpr (Q::P == 1) {
-        if (a.w_r) acc = fmaf(((const float *)a.w_r)[n * V + j], vg[off], acc);  // (v in LDS may be overwritten already)
-        ((float *)a.y)[((size_t)b * T * N + n) * V + off] = acc;
+      if constexpr (Q::P == 1 || SEQ) {
+        float *dst = (float *)a.y + ((size_t)b * T * N + n) * V + off;
+        if (SEQ && part > 0) acc = *dst + acc;
+        // (v from memory: its place in LDS may be overwritten already)
+        if (a.w_r && part == Q::P - 1) acc = fmaf(((const float *)a.w_r)[n * V + j], vg[off], acc);
+        *dst = acc;
       } else {
         ypart[(size_t)part * a.B * T * v_step + ((size_t)b * T * N + n) * V + off] = acc;
       }
@@ -265,6 +269,19 @@ __global__ void __launch_bounds__(Q::THREADS, 2) quad_fwd_kernel(FwdArgs a, floa
   if (a.HT)
 #pragma unroll
     for (int m = 0; m < 4; ++m) a.HT[st_off + m * V] = h[m];
+}
+
+template <typename Q, bool DO_Y, bool SEQ>
+__global__ void __launch_bounds__(Q::THREADS, 2) quad_fwd_kernel(FwdArgs a, float *__restrict__ ypart) {
+  __shared__ FwdLds<Q> sm;
+  if constexpr (SEQ) {
+    for (int part = 0; part < Q::P; ++part) {
+      quad_fwd_part<Q, DO_Y, true>(a, ypart, sm, blockIdx.x, part);
+      __syncthreads();
+    }
+  } else {
+    quad_fwd_part<Q, DO_Y, false>(a, ypart, sm, blockIdx.x / Q::P, blockIdx.x % Q::P);
+  }
 }
 
 // ------------------------------------------------------------------ backward
@@ -593,15 +610,25 @@ __global__ void quad_dw_sum_kernel(const float *__restrict__ dWp, float *__restr
 }
 
 template <typename Q>
+size_t fwd_parts_bytes(int B, int T, int N) {
+  return Q::P > 1 ? align256((size_t)Q::P * B * N * T * Q::V * 4) : 0;
+}
+
+template <typename Q>
 hipError_t launch_fwd(const FwdArgs &a, hipStream_t s) {
   const int units = a.B * a.N;
   if (units == 0) return hipSuccess;
   float *ypart = (float *)a.ws;
-  if (a.write_y)
-    hipLaunchKernelGGL((quad_fwd_kernel<Q, true>), dim3(units * Q::P), dim3(Q::THREADS), 0, s, a, ypart);
-  else
-    hipLaunchKernelGGL((quad_fwd_kernel<Q, false>), dim3(units * Q::P), dim3(Q::THREADS), 0, s, a, ypart);
+  const bool seq = Q::P > 1 && a.write_y && a.ws_bytes < fwd_parts_bytes<Q>(a.B, a.T, a.N);
+  const dim3 grid(seq ? units : units * Q::P), block(Q::THREADS);
+  if (!a.write_y)
+    hipLaunchKernelGGL((quad_fwd_kernel<Q, false, false>), grid, block, 0, s, a, ypart);
+  else if (!seq)
+    hipLaunchKernelGGL((quad_fwd_kernel<Q, true, false>), grid, block, 0, s, a, ypart);
+  else if constexpr (Q::P > 1)
+    hipLaunchKernelGGL((quad_fwd_kernel<Q, true, true>), grid, block, 0, s, a, ypart);
   hipError_t e = hipGetLastError();
+  if (seq) return e;
   if (e == hipSuccess && Q::P > 1 && a.write_y)
     e = parts_sum<float>(ypart, (float *)a.y, (size_t)a.B * a.T * a.N * a.V, Q::P, (const float *)a.w_r,
                          (const float *)a.v, a.N * a.V, s);
@@ -673,7 +700,7 @@ size_t quad_workspace_bytes(int B, int T, int N, int Nqk, int K, int V, int C, i
 #define X(K_, V_)                                                                                  \
   if (K == K_ && V == V_) {                                                                        \
     using Q = Quad<K_, V_>;                                                                        \
-    if (!bwd) return Q::P > 1 ? align256((size_t)Q::P * B * N * T * V * 4) : 0;                     \
+    if (!bwd) return fwd_parts_bytes<Q>(B, T, N);                                                   \
     return quad_layout(B, T, N, Nqk, K, V, C, Q::P, Q::THREADS).total;                              \
   }
   M2RNN_QUAD_CASES(X)

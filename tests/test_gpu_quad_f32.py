@@ -31,3 +31,31 @@ def test_shapes(K, V):
 @pytest.mark.parametrize("K,V", [(32, 32), (64, 16), (64, 64)])
 def test_lengths_and_intervals(K, V, T, chunk):
     _check(1, T, 4, K, V, chunk, Nqk=2, clip=0.5 if T == 33 else 0.0)
+
+
+def test_parts_in_turn_give_the_same_bits():
+    """m2rnn_fwd_static with partial sums larger than its scratch: the parts of a state one after
+    the other, against the side-by-side kernel on a full workspace."""
+    import torch
+    from paper_2603_14360_amd import binding as mb
+    B, T, N, K, V = 1, 601, 16, 64, 64
+    desc = mb.make_desc(B, T, N, K, V, mb.M2RNN_F32)
+    need = mb.m2rnn_workspace_bytes(desc, 0)
+    assert need > mb.M2RNN_STATIC_SCRATCH_BYTES
+    print("case static fp32 forward", flush=True)
+    inp = make_inputs(Workload("t", B, T, N, K, V, "f32", 9, K ** -0.5, 1.0, use_H0=True))
+    dev = gu.to_device(inp, "f32")
+    stream = torch.cuda.current_stream().cuda_stream
+    w_r = torch.randn(N, V, device="cuda")
+    outs = []
+    for static in (False, True):
+        y, HT = torch.full((B, T, N, V), float("nan"), device="cuda"), torch.empty(B, N, K, V, device="cuda")
+        args = (dev["q"], dev["k"], dev["v"], dev["f"], dev["W"], dev["H0"], y, HT, None)
+        if static:
+            mb.m2rnn_fwd_static(desc, mb.make_opts(w_r=w_r), *args, stream=stream)
+        else:
+            ws = torch.empty(need, dtype=torch.uint8, device="cuda")
+            mb.m2rnn_fwd_opt(desc, mb.make_opts(w_r=w_r), *args, ws, stream=stream)
+        torch.cuda.synchronize()
+        outs.append((y, HT))
+    assert torch.equal(outs[0][0], outs[1][0]) and torch.equal(outs[0][1], outs[1][1])
