@@ -51,7 +51,7 @@ typedef enum {
   M2RNN_ERR_SHAPE = 2,     /* a dimension is out of the supported set               */
   M2RNN_ERR_DTYPE = 3,     /* desc.io is not a known dtype                          */
   M2RNN_ERR_ALIGN = 4,     /* a pointer is not 16-byte aligned                      */
-  M2RNN_ERR_WORKSPACE = 5, /* workspace_bytes < m2rnn_workspace_bytes()             */
+  M2RNN_ERR_WORKSPACE = 5, /* workspace_bytes < what the call needs                 */
   M2RNN_ERR_HIP = 6,       /* a HIP call (launch, attribute) failed                 */
   M2RNN_ERR_CHUNK = 7      /* desc.chunk is outside [0, m2rnn_max_chunk()]          */
 } m2rnn_status;
@@ -87,7 +87,9 @@ int32_t m2rnn_max_chunk(const m2rnn_desc *desc);
 
 /* Name of the kernel variant that serves this descriptor's forward (bwd = 0) or backward
  * (bwd != 0): "tile<K,V,RB>" (matrix-core kernel, a 16-row block spread over V/16 waves, RB
- * row blocks per workgroup), "rowwave<K,V>" (matrix-core forward, one wave per 16-row block),
+ * row blocks per workgroup; the forward under this name splits the state further, into 8-row
+ * blocks, where that is faster), "rowwave<K,V>" (matrix-core forward, one wave per 16-row block,
+ * or 8-row blocks for few states),
  * "decode<K,V>" (T = 1: the single-launch latency kernel of recurrent inference),
  * "generic<f32>" / "generic<bf16>" (the kernels in fp32 throughout), or "invalid descriptor".
  * Static storage.  For profiling and for tests that must reach every variant. */
@@ -101,7 +103,8 @@ const char *m2rnn_route_string(const m2rnn_desc *desc, int bwd);
 size_t m2rnn_ckpt_bytes(const m2rnn_desc *desc);
 
 /* Bytes of scratch a call needs for partial sums across workgroups:
- *   bwd = 0   the forward (may be 0);
+ *   bwd = 0   the forward (may be 0).  With all of it a forward of few states can split them over
+ *             more of the GPU; part of it can do, at less speed and with the same results;
  *   bwd = 1   the backward called WITH the forward's checkpoints (ckpt != NULL), the normal
  *             forward-then-backward use;
  *   bwd >= 2  the backward called with ckpt == NULL: bwd = 1 plus room for the checkpoints it
@@ -249,7 +252,7 @@ m2rnn_status m2rnn_gated_rmsnorm_bwd(int32_t B, int32_t T, int32_t D, int32_t io
  * M2RNN_STATIC_SCRATCH_BYTES bytes, which every GPU the library runs on holds until the
  * process ends.  The call allocates nothing, frees nothing and synchronises nothing; it runs
  * the same kernels as m2rnn_fwd_opt and gives the same bits.
- *   - A descriptor whose m2rnn_workspace_bytes(desc, 0) exceeds M2RNN_STATIC_SCRATCH_BYTES is
+ *   - A descriptor whose forward cannot do with M2RNN_STATIC_SCRATCH_BYTES of scratch is
  *     rejected with M2RNN_ERR_WORKSPACE before anything is launched (e.g. B*T*N*V <= 2^19
  *     at K = V = 64 with few states; shapes whose forward needs no scratch always pass, and
  *     so does fp32 io with V <= 64, which then runs the parts of a state in turn).

@@ -55,7 +55,7 @@ Family fwd_family_of(const m2rnn_desc *d) {
 hipError_t run_fwd(const m2rnn_desc *d, const FwdArgs &a, hipStream_t s) {
   switch (fwd_family_of(d)) {
     case kDecode: return decode_fwd(a, s);
-    case kRowWave: return rowwave_fwd(a, s);
+    case kRowWave: return half_serves(a.K, a.V, a.B * a.N) ? half_fwd(a, s) : rowwave_fwd(a, s);
     case kMfma: return mfma_fwd(a, s);
     default: return generic_fwd(a, s);
   }
@@ -83,9 +83,21 @@ size_t ckpt_bytes(const m2rnn_desc *d, int C) {
 
 size_t family_ws(const m2rnn_desc *d, int C, int bwd) {
   const Family fam = bwd ? family_of(d) : fwd_family_of(d);
-  if (fam == kRowWave || fam == kDecode) return 0;
-  return fam == kMfma ? mfma_workspace_bytes(d->B, d->T, d->N, d->Nqk, d->K, d->V, C, bwd)
-                      : generic_workspace_bytes(d->B, d->T, d->N, d->Nqk, d->K, d->V, C, bwd);
+  if (fam == kDecode) return 0;
+  if (fam == kGeneric) return generic_workspace_bytes(d->B, d->T, d->N, d->Nqk, d->K, d->V, C, bwd);
+  return bwd ? mfma_bwd_workspace_bytes(d->B, d->T, d->N, d->Nqk, d->K, d->V)
+             : fam == kRowWave && !half_serves(d->K, d->V, d->B * d->N)
+                   ? 0
+                   : mfma_fwd_workspace_bytes(d->B, d->T, d->N, d->K, d->V);
+}
+// The least workspace that the forward accepts.  (Where the query above asks for more, the
+// rest lets the launch split its states further.)
+size_t fwd_least_ws(const m2rnn_desc *d, int C) {
+  switch (fwd_family_of(d)) {
+    case kRowWave: return 0;
+    case kMfma: return mfma_fwd_least_bytes(d->B, d->T, d->N, d->K, d->V);
+    default: return family_ws(d, C, 0);
+  }
 }
 
 bool misaligned(const void *p) { return ((uintptr_t)p & 15u) != 0; }
@@ -241,8 +253,9 @@ m2rnn_status m2rnn_fwd_opt(const m2rnn_desc *desc, const m2rnn_opts *opts, const
                            const void *k, const void *v, const float *f, const void *W,
                            const float *H0, void *y, float *HT, float *ckpt, void *workspace,
                            size_t workspace_bytes, void *hip_stream) {
+  const int C = check_desc(desc) == M2RNN_OK ? resolve_chunk(desc) : 0;
   return fwd_impl(desc, opts, q, k, v, f, W, H0, y, HT, ckpt, workspace, workspace_bytes,
-                  hip_stream, m2rnn_workspace_bytes(desc, 0));
+                  hip_stream, C ? fwd_least_ws(desc, C) : 0);
 }
 
 m2rnn_status m2rnn_fwd_static(const m2rnn_desc *desc, const m2rnn_opts *opts, const void *q,
@@ -253,7 +266,7 @@ m2rnn_status m2rnn_fwd_static(const m2rnn_desc *desc, const m2rnn_opts *opts, co
   if (st != M2RNN_OK) return st;
   const int C = resolve_chunk(desc);
   if (!C) return M2RNN_ERR_CHUNK;
-  size_t need = family_ws(desc, C, 0);
+  size_t need = fwd_least_ws(desc, C);
   // (the fp32 kernels can do without room for all partial sums)
   if (fwd_family_of(desc) == kGeneric && quad_supported(desc->K, desc->V) &&
       need > (size_t)M2RNN_STATIC_SCRATCH_BYTES)

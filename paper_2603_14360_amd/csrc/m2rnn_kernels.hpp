@@ -124,9 +124,21 @@ int rowwave_bwd_max_chunk();
 bool mfma_supported(int K, int V);
 int mfma_default_chunk(int K, int V);
 int mfma_max_chunk(int K, int V);
-size_t mfma_workspace_bytes(int B, int T, int N, int Nqk, int K, int V, int C, int bwd);
+// Workspace of the matrix-core forward: what it cannot run without (16-row parts of the states),
+// and what its launch prefers (the 8-row split may be finer, and is taken where it fits).
+size_t mfma_fwd_least_bytes(int B, int T, int N, int K, int V);
+size_t mfma_fwd_workspace_bytes(int B, int T, int N, int K, int V);
+size_t mfma_bwd_workspace_bytes(int B, int T, int N, int Nqk, int K, int V);
 hipError_t mfma_fwd(const FwdArgs &a, hipStream_t s);
 hipError_t mfma_bwd(const BwdArgs &a, hipStream_t s);
+// y = bf16(1/c of the sum over the P partial readouts at a.ws [+ w_r (.) v])
+hipError_t y_parts_sum(const FwdArgs &a, int P, hipStream_t s);
+// does the forward on 8-row blocks serve a launch of this many states?
+bool half_serves(int K, int V, int units);
+// that forward, rb of them per workgroup, and the choice of rb for a launch whose
+// partial readouts (part_bytes for each of the K/(8 rb) parts of a state) must fit avail bytes
+int half_pick_rb(int K, int V, int units, size_t part_bytes, size_t avail);
+hipError_t half_fwd(const FwdArgs &a, hipStream_t s);
 int mfma_pick_rb(int K, int V, int units);  // row blocks per workgroup of the tile serving a launch (0: none)
 
 // ---- register-resident path (bf16 io, V <= 64): one wave per 16 state rows ----

@@ -4,9 +4,7 @@
 
 namespace m2rnn {
 
-int mfma_pick_rb(int K, int V, int units);
 int mfma_bwd_max_chunk(int K, int V);
-size_t mfma_bwd_workspace_bytes(int B, int T, int N, int Nqk, int K, int V);
 
 bool mfma_supported(int K, int V) { return mfma_pick_rb(K, V, 1 << 20) != 0; }
 
@@ -15,15 +13,22 @@ bool mfma_supported(int K, int V) { return mfma_pick_rb(K, V, 1 << 20) != 0; }
 int mfma_max_chunk(int K, int V) { return mfma_bwd_max_chunk(K, V); }
 int mfma_default_chunk(int K, int V) { return mfma_bwd_max_chunk(K, V); }
 
-size_t mfma_workspace_bytes(int B, int T, int N, int Nqk, int K, int V, int C, int bwd) {
-  (void)C;
+namespace {
+size_t part_bytes(int B, int T, int N, int V) { return (size_t)B * T * N * V * 4; }
+}  // namespace
+
+size_t mfma_fwd_least_bytes(int B, int T, int N, int K, int V) {
   const int rb = mfma_pick_rb(K, V, B * N);
-  if (rb == 0) return bwd ? mfma_bwd_workspace_bytes(B, T, N, Nqk, K, V) : 0;  // no tiling: the
-      // register-resident kernels serve the shape (their forward needs no workspace)
-  const int P = K / (16 * rb);
-  const size_t fwd = P > 1 ? align256((size_t)P * B * T * N * V * 4) : 0;
-  if (!bwd) return fwd;
-  return mfma_bwd_workspace_bytes(B, T, N, Nqk, K, V);
+  const int P = rb ? K / (16 * rb) : 1;
+  return P > 1 ? align256(P * part_bytes(B, T, N, V)) : 0;
+}
+
+size_t mfma_fwd_workspace_bytes(int B, int T, int N, int K, int V) {
+  const size_t least = mfma_fwd_least_bytes(B, T, N, K, V);
+  if (!half_serves(K, V, B * N)) return least;
+  const int P = K / (8 * half_pick_rb(K, V, B * N, 0, 0));
+  const size_t want = P > 1 ? align256(P * part_bytes(B, T, N, V)) : 0;
+  return want > least ? want : least;
 }
 
 }  // namespace m2rnn

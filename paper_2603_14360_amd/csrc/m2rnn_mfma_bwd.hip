@@ -56,49 +56,6 @@ __device__ __forceinline__ uint2 pack4_bf16(f4_t x) {
 // iteration earlier, in reverse order.  The slot B reads in a step is the one A fills in
 // the next step, so one spare slot is enough and the checkpoint interval C can be almost
 // twice what two separate buffers would allow (chunk boundaries cost several step times).
-// Fragment read through the transposing LDS load of gfx950 (ds_read_b64_tr_b16).  Within each
-// group of 16 lanes the 16 x 8 bytes that the lanes address are taken as 64 consecutive
-// fp16 values and lane d receives values d, 16 + d, 32 + d, 48 + d of them.  With the tile
-// stored as 8-byte items (column j, rows 4 i .. 4 i + 3) -- which is what a lane of the
-// accumulator layout holds -- at byte offset 32 j + 8 i, lane d addressing item
-// (column c0 + d / 4, rows 4 (d % 4) ..) receives row d, columns c0 .. c0 + 3: the A operand of
-// the 16-row MFMAs, with no scattered 2-byte writes and no padded rows.
-__device__ __forceinline__ h4_t lds_ld_tr(const lchar *p, int off) {
-  typedef short s4_t __attribute__((ext_vector_type(4)));
-  const s4_t v = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s4_t *)(p + off));
-  return __builtin_bit_cast(h4_t, v);
-}
-// Where the four items of a column sit inside the column's 32 bytes, and where a group of
-// four columns sits inside its 256-byte pair, is free (every lane of the transposing load
-// supplies its own address).  Item (column j, rows 4 i ..) goes to
-// a = 32 j + 8 ((i + j / 4) mod 4) and then to a xor (128 if bit 8 of a is set): the items a
-// lane group reads are still 128 contiguous bytes, but the four lane groups and the two
-// halves of a k = 32 fragment start on different banks.  In the plain order (32 j + 8 i) a
-// third of the LDS-active cycles of the backward are bank conflicts; placed like this, 1 %.
-// That is worth 6.5 % of the backward on the 128-wide tile (rotation alone 3.5 %); on the
-// 64-wide tiles, where the LDS is not what the step waits for, the time does not change.
-__device__ __forceinline__ int xch_item_off(int j, int i) {
-  const int a = 32 * j + 8 * ((i + (j >> 2)) & 3);
-  return a ^ ((a >> 1) & 128);
-}
-// Per-lane base offsets of a fragment read: lane (d, g) = (lane % 16, lane / 16) reads, for
-// the first half of its FE columns c0 = FE g .., item (column c0 + d / 4, rows 4 (d % 4) ..); the
-// second half (k = 32 fragments only) is the next group of 4 columns.
-template <bool X32>
-__device__ __forceinline__ int xch_frag_off(int d, int g, int half) {
-  constexpr int FE = X32 ? 8 : 4;
-  const int c0 = FE * g + 4 * half;
-  return xch_item_off(c0 + (d >> 2), d & 3);
-}
-template <bool X32>
-__device__ __forceinline__ typename Frag<X32>::type lds_ld_frag_tr(const lchar *p0, const lchar *p1, int off) {
-  if constexpr (X32) {
-    const h4_t lo = lds_ld_tr(p0, off), hi = lds_ld_tr(p1, off);
-    return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-  } else {
-    return lds_ld_tr(p0, off);
-  }
-}
 
 // The lane index computed on the spot (two instructions).  The chunk-boundary code derives
 // its per-lane offsets from this instead of from a lane index kept in a register since the

@@ -59,6 +59,19 @@ __device__ __forceinline__ uint32_t split_hi_lo(float h) {
   const f2_t pr = {hi, h - hi};
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(pr, h2_t));
 }
+// Two elements H' -> their fp16 (hi, lo) parts as two packed registers, {hi0, hi1} and {lo0, lo1}:
+// hi is H' rounded towards zero (the bits that split_hi_lo keeps), lo = fp16(H' - hi).  Four
+// instructions for two elements: the mixed-precision FMA subtracts the fp16 hi in fp32, so hi
+// needs no fp32 copy of its own.
+__device__ __forceinline__ u2_t split2_hi_lo(float h0, float h1) {
+  typedef float f2_t __attribute__((ext_vector_type(2)));
+  const uint32_t hi = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(h0, h1));
+  float l0, l1;
+  asm("v_fma_mix_f32 %0, %1, -1.0, %2 op_sel_hi:[1,0,0]" : "=v"(l0) : "v"(hi), "v"(h0));
+  asm("v_fma_mix_f32 %0, %1, -1.0, %2 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(l1) : "v"(hi), "v"(h1));
+  const f2_t lo = {l0, l1};
+  return u2_t{hi, __builtin_bit_cast(uint32_t, __builtin_convertvector(lo, h2_t))};
+}
 // the four hi halves of four packed pairs, as one MFMA fragment
 __device__ __forceinline__ h4_t hi_of_pairs(const uint32_t (&pk)[4]) {
   uint2 v;
@@ -169,6 +182,21 @@ __device__ __forceinline__ int ilog2f(float x) {
   return (int)((__builtin_bit_cast(uint32_t, x) >> 23) & 255u) - 127;
 }
 
+// Sum of a power of two of terms as a binary tree of neighbours.  A row block's readout is summed
+// this way inside a workgroup and over the workgroups of a state, so that y has the same bits
+// however a state is split.
+template <int M>
+__device__ __forceinline__ f4_t pairwise_sum(const f4_t (&x)[M]) {
+  if constexpr (M == 1) {
+    return x[0];
+  } else {
+    f4_t y[M / 2];
+#pragma unroll
+    for (int i = 0; i < M / 2; ++i) y[i] = x[2 * i] + x[2 * i + 1];
+    return pairwise_sum(y);
+  }
+}
+
 template <int K_, int V_, int RB_>
 struct Tile {
   static constexpr int K = K_, V = V_, RB = RB_;
@@ -188,6 +216,50 @@ struct Tile {
 template <bool X32> struct Frag { typedef h8_t type; };
 template <> struct Frag<false> { typedef h4_t type; };
 
+// Fragment read through the transposing LDS load of gfx950 (ds_read_b64_tr_b16).  Within each
+// group of 16 lanes the 16 x 8 bytes that the lanes address are taken as 64 consecutive
+// fp16 values and lane d receives values d, 16 + d, 32 + d, 48 + d of them.  With the tile
+// stored as 8-byte items (column j, rows 4 i .. 4 i + 3) -- which is what a lane of the
+// accumulator layout holds -- at byte offset 32 j + 8 i, lane d addressing item
+// (column c0 + d / 4, rows 4 (d % 4) ..) receives row d, columns c0 .. c0 + 3: the A operand of
+// the 16-row MFMAs, with no scattered 2-byte writes and no padded rows.
+__device__ __forceinline__ h4_t lds_ld_tr(const lchar *p, int off) {
+  typedef short s4_t __attribute__((ext_vector_type(4)));
+  const s4_t v = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s4_t *)(p + off));
+  return __builtin_bit_cast(h4_t, v);
+}
+// Where the four items of a column sit inside the column's 32 bytes, and where a group of
+// four columns sits inside its 256-byte pair, is free (every lane of the transposing load
+// supplies its own address).  Item (column j, rows 4 i ..) goes to
+// a = 32 j + 8 ((i + j / 4) mod 4) and then to a xor (128 if bit 8 of a is set): the items a
+// lane group reads are still 128 contiguous bytes, but the four lane groups and the two
+// halves of a k = 32 fragment start on different banks.  In the plain order (32 j + 8 i) a
+// third of the LDS-active cycles of the backward are bank conflicts; placed like this, 1 %.
+// That is worth 6.5 % of the backward on the 128-wide tile (rotation alone 3.5 %); on the
+// 64-wide tiles, where the LDS is not what the step waits for, the time does not change.
+__device__ __forceinline__ int xch_item_off(int j, int i) {
+  const int a = 32 * j + 8 * ((i + (j >> 2)) & 3);
+  return a ^ ((a >> 1) & 128);
+}
+// Per-lane base offsets of a fragment read: lane (d, g) = (lane % 16, lane / 16) reads, for
+// the first half of its FE columns c0 = FE g .., item (column c0 + d / 4, rows 4 (d % 4) ..); the
+// second half (k = 32 fragments only) is the next group of 4 columns.
+template <bool X32>
+__device__ __forceinline__ int xch_frag_off(int d, int g, int half) {
+  constexpr int FE = X32 ? 8 : 4;
+  const int c0 = FE * g + 4 * half;
+  return xch_item_off(c0 + (d >> 2), d & 3);
+}
+template <bool X32>
+__device__ __forceinline__ typename Frag<X32>::type lds_ld_frag_tr(const lchar *p0, const lchar *p1, int off) {
+  if constexpr (X32) {
+    const h4_t lo = lds_ld_tr(p0, off), hi = lds_ld_tr(p1, off);
+    return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+  } else {
+    return lds_ld_tr(p0, off);
+  }
+}
+
 // blockIdx -> (unit, part).  Workgroups are dealt round-robin to the 8 XCDs, so
 // all P parts of a (b, n) state get ids that are equal mod 8: they then share
 // one XCD's L2 for v_t, f_t and W.  Returns false for padding blocks.
@@ -205,6 +277,12 @@ inline int grid_blocks(int units, int P) { return 8 * P * ((units + 7) / 8); }
 // (K, V, RB) tilings that are instantiated
 #define M2RNN_TILE_CASES(X)                                                                      \
   X(64, 64, 2) X(64, 64, 1) X(128, 128, 1) X(32, 32, 2) X(32, 32, 1) X(16, 16, 1) X(64, 16, 1)
+
+// (K, V, RB) splits of the forward on 8-row blocks, per shape in increasing RB
+#define M2RNN_HALF_CASES(X)                                                                      \
+  X(64, 64, 1) X(64, 64, 2) X(64, 64, 4) X(128, 128, 1) X(128, 128, 2) X(32, 32, 1) X(32, 32, 2) \
+  X(32, 32, 4) X(16, 16, 1) X(16, 16, 2) X(64, 16, 1) X(64, 16, 2) X(64, 16, 4) X(64, 16, 8)                  \
+  X(32, 16, 1) X(32, 16, 2) X(32, 16, 4) X(64, 32, 1) X(64, 32, 2) X(64, 32, 4) X(64, 32, 8)
 
 // (K, V) shapes of the register-resident (one wave per row block) kernels
 #define M2RNN_ROWWAVE_CASES(X)                                                                  \

@@ -1,5 +1,7 @@
 // Matrix-core forward scan (Algorithm 1 of the paper; recurrence equations),
-// tiled variant: a 16-row block of one (b, n) state is spread over V/16 waves.
+// tiled variant: a 16-row block of one (b, n) state is spread over V/16 waves.  It serves
+// K = V = 128 with more states than the 8-row forward (m2rnn_half_fwd.hip) has CUs for; that
+// kernel is the faster one for every other tiled shape.
 //
 // Per workgroup: RB row blocks (16 rows each) of one state, all V columns, for
 // all T steps.  A wavefront owns one 16 x 16 tile; lane l holds row l % 16 and
@@ -273,9 +275,9 @@ __global__ void __launch_bounds__(TL::THREADS, 2)
   auto y_store = [&](f4_t ys, int t0, int len) __attribute__((always_inline)) {
     // lane (ig, jl) holds columns col0 + 4 ig + r of step t0 + jl
     if (jl < len) {
-      ys *= kInvC;
       const size_t yoff = (((size_t)b * T + t0 + jl) * N + n) * V + col0 + 4 * ig;
       if constexpr (TL::P == 1) {
+        ys *= kInvC;
         if (a.w_r) {  // residual w_r (.) v_t of the y equation
           const uint2 wv = *(const uint2 *)&((const bf16_raw *)a.w_r)[n * V + col0 + 4 * ig];
           const uint2 vv = *(const uint2 *)&vg[yoff];
@@ -358,15 +360,18 @@ __global__ void __launch_bounds__(TL::THREADS, 2)
   if (a.HT) *(f4_t *)&a.HT[st_off] = f4_t{h[0], h[1], h[2], h[3]} * kInvC;
 }
 
-// y = bf16( sum over parts, in increasing part order [+ w_r (.) v, the residual of the y
-// equation, when w_r is given] ); NV = N * V, the period of w_r along the flat index
+// y = bf16( 1/c of the sum over the P parts [+ w_r (.) v, the residual of the y equation,
+// when w_r is given] ); NV = N * V, the period of w_r along the flat index
+template <int P>
 __global__ void y_parts_sum_kernel(const float *__restrict__ part, bf16_raw *__restrict__ y,
-                                   size_t total, int P, const bf16_raw *__restrict__ w_r,
+                                   size_t total, const bf16_raw *__restrict__ w_r,
                                    const bf16_raw *__restrict__ v, int NV) {
   for (size_t e = (blockIdx.x * (size_t)blockDim.x + threadIdx.x) * 4; e < total;
        e += (size_t)gridDim.x * blockDim.x * 4) {
-    f4_t s = *(const f4_t *)&part[e];
-    for (int p = 1; p < P; ++p) s += *(const f4_t *)&part[(size_t)p * total + e];
+    f4_t x[P];
+#pragma unroll
+    for (int p = 0; p < P; ++p) x[p] = *(const f4_t *)&part[(size_t)p * total + e];
+    f4_t s = pairwise_sum(x) * kInvC;
     if (w_r) {
       const uint2 wv = *(const uint2 *)&w_r[e % (size_t)NV];
       const uint2 vv = *(const uint2 *)&v[e];
@@ -382,6 +387,27 @@ __global__ void y_parts_sum_kernel(const float *__restrict__ part, bf16_raw *__r
   }
 }
 
+}  // namespace
+
+hipError_t y_parts_sum(const FwdArgs &a, int P, hipStream_t s) {
+  const size_t total = (size_t)a.B * a.T * a.N * a.V;
+  size_t blocks = (total / 4 + 255) / 256;
+  if (blocks > 8192) blocks = 8192;
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(256), 0, s, (const float *)a.ws,
+                       (bf16_raw *)a.y, total, (const bf16_raw *)a.w_r, (const bf16_raw *)a.v, a.N * a.V);
+  };
+  switch (P) {
+    case 2: go(y_parts_sum_kernel<2>); break;
+    case 4: go(y_parts_sum_kernel<4>); break;
+    case 8: go(y_parts_sum_kernel<8>); break;
+    case 16: go(y_parts_sum_kernel<16>); break;
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+
+namespace {
 template <typename TL>
 hipError_t launch_fwd(const FwdArgs &a, hipStream_t s) {
   const int units = a.B * a.N;
@@ -395,15 +421,7 @@ hipError_t launch_fwd(const FwdArgs &a, hipStream_t s) {
                        dim3(TL::THREADS), 0, s, a, ypart);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  if (TL::P > 1 && a.write_y && a.T > 0) {
-    const size_t total = (size_t)a.B * a.T * a.N * a.V;
-    size_t blocks = (total / 4 + 255) / 256;
-    if (blocks > 8192) blocks = 8192;
-    hipLaunchKernelGGL(y_parts_sum_kernel, dim3((unsigned)blocks), dim3(256), 0, s,
-                       (const float *)ypart, (bf16_raw *)a.y, total, TL::P,
-                       (const bf16_raw *)a.w_r, (const bf16_raw *)a.v, a.N * a.V);
-    e = hipGetLastError();
-  }
+  if (TL::P > 1 && a.write_y && a.T > 0) e = y_parts_sum(a, TL::P, s);
   return e;
 }
 
@@ -422,11 +440,8 @@ int mfma_pick_rb(int K, int V, int units) {
 }
 
 hipError_t mfma_fwd(const FwdArgs &a, hipStream_t s) {
-  const int rb = mfma_pick_rb(a.K, a.V, a.B * a.N);
-#define X(K_, V_, RB_) \
-  if (a.K == K_ && a.V == V_ && rb == RB_) return launch_fwd<Tile<K_, V_, RB_>>(a, s);
-  M2RNN_TILE_CASES(X)
-#undef X
+  if (half_serves(a.K, a.V, a.B * a.N)) return half_fwd(a, s);
+  if (a.K == 128 && a.V == 128) return launch_fwd<Tile<128, 128, 1>>(a, s);
   return hipErrorInvalidValue;
 }
 
