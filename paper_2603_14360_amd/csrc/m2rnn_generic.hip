@@ -338,29 +338,6 @@ __global__ void dw_batch_sum_kernel(const float *dW_unit, float *dW, int B, int 
   }
 }
 
-// Gradient of the residual weight: dw_r[n][j] = sum over (b, t) of dy (.) v.  Stage 1: block s
-// adds the rows r = s, s + S, s + 2S, ... of the [B*T, N*V] tensors in increasing r; stage 2
-// adds the S partial rows in increasing s.  The order is fixed, so the result is reproducible.
-constexpr int kDwrStages = 1024;
-template <typename IO>
-__global__ void dwr_stage1_kernel(const IO *__restrict__ dy, const IO *__restrict__ v,
-                                  float *__restrict__ part, size_t BT, int NV) {
-  for (int c = threadIdx.x; c < NV; c += blockDim.x) {
-    float acc = 0.f;
-    for (size_t r = blockIdx.x; r < BT; r += gridDim.x)
-      acc = fmaf(to_f32<IO>(dy[r * NV + c]), to_f32<IO>(v[r * NV + c]), acc);
-    part[(size_t)blockIdx.x * NV + c] = acc;
-  }
-}
-__global__ void dwr_stage2_kernel(const float *__restrict__ part, float *__restrict__ dw_r, int S,
-                                  int NV) {
-  const int c = blockIdx.x * blockDim.x + threadIdx.x;
-  if (c >= NV) return;
-  float s = 0.f;
-  for (int p = 0; p < S; ++p) s += part[(size_t)p * NV + c];
-  dw_r[c] = s;
-}
-
 // dq/dk of a shared q/k head = sum over its heads, in increasing head index.
 template <typename IO>
 __global__ void head_group_sum_kernel(const float *per_head, IO *out, size_t BT, int N, int Nqk,
@@ -515,80 +492,6 @@ hipError_t generic_fwd(const FwdArgs &a, hipStream_t s) {
 hipError_t generic_bwd(const BwdArgs &a, hipStream_t s) {
   if (quad_supported(a.K, a.V)) return quad_bwd(a, s);
   return a.io == 0 ? run_bwd<float>(a, s) : run_bwd<__hip_bfloat16>(a, s);
-}
-
-// Chain rule through the gate function.  df holds dL/d(gate value) g; with u = x + beta,
-// psi = exp(-alpha softplus(u)):  dL/dx = dL/dbeta-term = -g alpha psi sigmoid(u),
-// dL/dalpha-term = -g psi softplus(u).  Stage 1: block s handles the (b, t) rows s, s + S, ...
-// in increasing order, thread n one head; stage 2 adds the S partial rows in increasing s.
-constexpr int kGateStages = 256;
-__global__ void gate_bwd_stage1_kernel(float *__restrict__ df, const float *__restrict__ x,
-                                       const float *__restrict__ alpha,
-                                       const float *__restrict__ beta, float *__restrict__ part,
-                                       size_t BT, int N) {
-  for (int n = threadIdx.x; n < N; n += blockDim.x) {
-    const float al = alpha[n], be = beta[n];
-    float sa = 0.f, sb = 0.f;
-    for (size_t r = blockIdx.x; r < BT; r += gridDim.x) {
-      const float u = x[r * N + n] + be;
-      const float sp = fmaxf(u, 0.f) + log1pf(expf(-fabsf(u)));
-      const float psi = expf(-al * sp);
-      const float g = df[r * N + n];
-      const float dx = -g * al * psi / (1.f + expf(-u));
-      sa = fmaf(-g * psi, sp, sa);
-      sb += dx;
-      df[r * N + n] = dx;
-    }
-    part[((size_t)blockIdx.x * 2 + 0) * N + n] = sa;
-    part[((size_t)blockIdx.x * 2 + 1) * N + n] = sb;
-  }
-}
-__global__ void gate_bwd_stage2_kernel(const float *__restrict__ part, float *__restrict__ dalpha,
-                                       float *__restrict__ dbeta, int S, int N) {
-  const int n = blockIdx.x * blockDim.x + threadIdx.x;
-  if (n >= N) return;
-  float sa = 0.f, sb = 0.f;
-  for (int p = 0; p < S; ++p) {
-    sa += part[((size_t)p * 2 + 0) * N + n];
-    sb += part[((size_t)p * 2 + 1) * N + n];
-  }
-  dalpha[n] = sa;
-  dbeta[n] = sb;
-}
-
-size_t gate_scratch_bytes(int N) { return align256((size_t)kGateStages * 2 * N * sizeof(float)); }
-
-hipError_t gate_backward(const BwdArgs &a, hipStream_t s) {
-  const size_t BT = (size_t)a.B * a.T;
-  const int S = BT < (size_t)kGateStages ? (int)BT : kGateStages;
-  if (S > 0)
-    hipLaunchKernelGGL(gate_bwd_stage1_kernel, dim3(S), dim3(a.N < 64 ? 64 : 128), 0, s, a.df,
-                       a.f, a.gate_alpha, a.gate_beta, a.gate_ws, BT, a.N);
-  hipLaunchKernelGGL(gate_bwd_stage2_kernel, dim3((a.N + 63) / 64), dim3(64), 0, s,
-                     (const float *)a.gate_ws, a.dgate_alpha, a.dgate_beta, S, a.N);
-  return hipGetLastError();
-}
-
-size_t residual_dw_r_scratch_bytes(int N, int V) {
-  return align256((size_t)kDwrStages * N * V * sizeof(float));
-}
-
-hipError_t residual_dw_r(const BwdArgs &a, hipStream_t s) {
-  const int NV = a.N * a.V;
-  const size_t BT = (size_t)a.B * a.T;
-  const int S = BT < (size_t)kDwrStages ? (int)BT : kDwrStages;
-  if (S > 0) {
-    if (a.io == 0)
-      hipLaunchKernelGGL(dwr_stage1_kernel<float>, dim3(S), dim3(256), 0, s, (const float *)a.dy,
-                         (const float *)a.v, a.dwr_ws, BT, NV);
-    else
-      hipLaunchKernelGGL(dwr_stage1_kernel<__hip_bfloat16>, dim3(S), dim3(256), 0, s,
-                         (const __hip_bfloat16 *)a.dy, (const __hip_bfloat16 *)a.v, a.dwr_ws, BT,
-                         NV);
-  }
-  hipLaunchKernelGGL(dwr_stage2_kernel, dim3((NV + 255) / 256), dim3(256), 0, s,
-                     (const float *)a.dwr_ws, a.dw_r, S, NV);
-  return hipGetLastError();
 }
 
 }  // namespace m2rnn
