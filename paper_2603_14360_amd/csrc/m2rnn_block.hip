@@ -12,23 +12,23 @@
 // each tensor makes one trip through HBM: x -> out, and (y, a) -> out.
 // Sums over tokens (dw, dbias) are two-stage and ordered: bit-reproducible, no atomics.
 #include "m2rnn_kernels.hpp"
+#include "m2rnn_mfma_common.hpp"
 
 #include <hip/hip_bf16.h>
 
 namespace m2rnn {
 namespace {
 
-typedef float f4_t __attribute__((ext_vector_type(4)));
-typedef uint32_t u4_t __attribute__((ext_vector_type(4)));
-
 __device__ __forceinline__ float bf16_bits_to_f32(uint32_t lo16) {
   return __builtin_bit_cast(float, lo16 << 16);
 }
-__device__ __forceinline__ uint32_t f32_to_bf16_bits(float x) {  // round to nearest even
-  uint32_t u = __builtin_bit_cast(uint32_t, x);
-  if ((u & 0x7fffffffu) > 0x7f800000u) return (u >> 16) | 0x40u;
-  u += 0x7fffu + ((u >> 16) & 1u);
-  return u >> 16;
+// two floats, rounded to nearest even, in one dword (one conversion instruction; done on integers
+// the six of each element were a third of the norm's vector work)
+__device__ __forceinline__ uint32_t pack2_bf16(float lo, float hi) {
+  typedef float f2_t __attribute__((ext_vector_type(2)));
+  typedef __bf16 b2_t __attribute__((ext_vector_type(2)));
+  const f2_t x = {lo, hi};
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(x, b2_t));
 }
 
 // eight consecutive elements of an io tensor <-> eight floats
@@ -75,7 +75,7 @@ template <> struct Vec8<__hip_bfloat16> {
   static __device__ __forceinline__ void store(void *base, size_t e, const float (&x)[8]) {
     u4_t w;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) w[i] = f32_to_bf16_bits(x[2 * i]) | (f32_to_bf16_bits(x[2 * i + 1]) << 16);
+    for (int i = 0; i < 4; ++i) w[i] = pack2_bf16(x[2 * i], x[2 * i + 1]);
     *(u4_t *)((unsigned short *)base + e) = w;
   }
 };
@@ -281,43 +281,68 @@ __global__ void __launch_bounds__(256)
   }
 }
 
-// Ordered sum of R partial rows of E floats, in two levels so that it is both parallel and
-// reproducible: group g (blockIdx.y) adds its rows g*per .. (g+1)*per - 1 in increasing order
-// into row g of `lvl` (kSumGroups rows behind the partials); the second level adds those.
+// Ordered sum of R partial rows of E floats.  A workgroup adds up to 32 columns with 32 walkers
+// (rows wl, wl + 32, ..., four loads in flight) and the walkers in LDS.  Up to kDirectRows rows
+// that is all; more are first added in groups of about kDirectRows / 4 (blockIdx.y) into rows
+// of `lvl` (kSumGroups rows behind the partials).  What bounds it is the chain of dependent
+// loads: 128 rows of 7360 took two launches, some 13 us, with one column per thread; 4.7 us now.
 constexpr int kSumGroups = 32;
-// Sum of p[r * stride] for r in [r0, r1) in a FIXED order that keeps eight loads in flight:
-// eight interleaved running sums (rows r0 + k, r0 + k + 8, ...), combined pairwise at the end.
-// (One running sum is a chain of dependent loads: these kernels are a few workgroups, and
-// with it each of them paid the memory latency once per row.)
-__device__ __forceinline__ float strided_sum8(const float *__restrict__ p, size_t stride, int r0, int r1) {
-  float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  int r = r0;
-  for (; r + 8 <= r1; r += 8) {
-    float x[8];
-#pragma unroll
-    for (int k = 0; k < 8; ++k) x[k] = p[(size_t)(r + k) * stride];
-#pragma unroll
-    for (int k = 0; k < 8; ++k) acc[k] += x[k];
+constexpr int kDirectRows = 512;
+
+// column e of a plain [D] result, and of the convolution's [C][4 taps, bias]
+struct PlainOut {
+  float *out;
+  __device__ __forceinline__ void put(int e, float s) const { out[e] = s; }
+};
+struct ConvOut {
+  float *dw, *dbias;
+  __device__ __forceinline__ void put(int e, float s) const {
+    const int c = e / (kTaps + 1), j = e - c * (kTaps + 1);
+    if (j < kTaps) dw[c * kTaps + j] = s;
+    else if (dbias) dbias[c] = s;
   }
-  for (int k = 0; r < r1; ++r, ++k) acc[k] += p[(size_t)r * stride];
-  return ((acc[0] + acc[1]) + (acc[2] + acc[3])) + ((acc[4] + acc[5]) + (acc[6] + acc[7]));
-}
-__global__ void ordered_sum_level1_kernel(const float *__restrict__ part, float *__restrict__ lvl,
-                                          int E, int R) {
-  const int e = blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= E) return;
-  const int per = (R + kSumGroups - 1) / kSumGroups;
+};
+template <typename Out>
+__global__ void __launch_bounds__(1024)
+    ordered_sum_kernel(const float *__restrict__ part, float *__restrict__ lvl, Out out, int E, int R) {
+  __shared__ float red[32][33];
+  const int cl = threadIdx.x & 31, wl = threadIdx.x >> 5, e = blockIdx.x * 32 + cl;
+  const int per = (R + gridDim.y - 1) / gridDim.y;
   const int r0 = blockIdx.y * per, r1 = r0 + per < R ? r0 + per : R;
-  lvl[(size_t)blockIdx.y * E + e] = strided_sum8(part + e, (size_t)E, r0, r1);
+  float s = 0.f;
+  if (e < E) {
+    int r = r0 + wl;
+    for (; r + 96 < r1; r += 128) {
+      float x[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) x[u] = part[(size_t)(r + 32 * u) * E + e];
+      s += (x[0] + x[1]) + (x[2] + x[3]);
+    }
+    for (; r < r1; r += 32) s += part[(size_t)r * E + e];
+  }
+  red[wl][cl] = s;
+  __syncthreads();
+  if (wl == 0 && e < E) {
+    float t = 0.f;
+#pragma unroll
+    for (int w = 0; w < 32; ++w) t += red[w][cl];
+    if (gridDim.y > 1) lvl[(size_t)blockIdx.y * E + e] = t;
+    else out.put(e, t);
+  }
 }
-__global__ void conv_sum_kernel(const float *__restrict__ lvl, float *__restrict__ dw,
-                                float *__restrict__ dbias, int C, int groups) {
-  const int e = blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= C * (kTaps + 1)) return;
-  const float s = strided_sum8(lvl + e, (size_t)C * (kTaps + 1), 0, groups);
-  const int c = e / (kTaps + 1), j = e - c * (kTaps + 1);
-  if (j < kTaps) dw[c * kTaps + j] = s;
-  else if (dbias) dbias[c] = s;
+template <typename Out>
+hipError_t ordered_sum(const float *part, float *lvl, const Out &out, int E, int R, hipStream_t s) {
+  const int bx = (E + 31) / 32;
+  if (R > kDirectRows) {
+    const int want = (R + kDirectRows / 4 - 1) / (kDirectRows / 4), G = want < kSumGroups ? want : kSumGroups;
+    hipLaunchKernelGGL(ordered_sum_kernel<Out>, dim3(bx, G), dim3(1024), 0, s, part, lvl, out, E, R);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    part = lvl;
+    R = G;
+  }
+  hipLaunchKernelGGL(ordered_sum_kernel<Out>, dim3(bx, 1), dim3(1024), 0, s, part, lvl, out, E, R);
+  return hipGetLastError();
 }
 
 // ------------------------------------------------------------------ gated RMSNorm
@@ -379,117 +404,96 @@ __global__ void __launch_bounds__(256)
   }
 }
 
-constexpr int kMaxVecPerLane = 8;  // D <= 8 * 64 * 8 = 4096
+constexpr int kMaxVecPerLane = 8;  // of the forward; waves per token of the backward: D <= 8 * 64 * 8 = 4096
 
 // Backward (appendix): p = w dout, r = sum p x, dx = s p - r s^3 x / d; dy = dx g,
-// da = dx y SiLU'(a); dw = sum over tokens of dout x s: per wave over the tokens it walks
-// (increasing), written to part[wave][D]; norm_sum_kernel adds the waves in order.
-template <typename IO, int NV>
-__global__ void __launch_bounds__(256)
+// da = dx y SiLU'(a); dw = sum over tokens of dout x s, per workgroup over the tokens it walks
+// (increasing), written to part[workgroup][D]; the column sums behind add the workgroups in order.
+//
+// Five tensors once: bound by memory if enough loads are in flight while the vector work goes
+// on.  A token is spread over W = ceil(D / 512) waves, so that a lane holds eight of its elements
+// whatever D is: 118 registers with the next token's vectors on the way, 16 waves per CU (at 96
+// registers, for 20 waves, it spills: 138 us with all launches against 94).  The
+// waves of a token meet once, at an LDS-only barrier that leaves the loads in flight.  (With a whole
+// token per wave the registers of D = 1344 left 8 waves per CU, and D > 2048 spilled.)
+// 32768 tokens, D = 1344, bf16, 440 MB: 172 -> 82 us.
+template <typename IO>
+__global__ void __launch_bounds__(512, 4)
     gated_rmsnorm_bwd_kernel(const void *__restrict__ y, const void *__restrict__ a,
                              const void *__restrict__ w, float eps, const float *__restrict__ s_in,
                              const void *__restrict__ dout, void *__restrict__ dy,
                              void *__restrict__ da, float *__restrict__ part, size_t tokens, int D) {
-  constexpr bool KEEP = sizeof(IO) == 2 || NV <= 4;
-  const int lane = threadIdx.x & 63, DV = D / 8;
-  const size_t wave = (blockIdx.x * (size_t)blockDim.x + threadIdx.x) >> 6;
-  const size_t nwaves = ((size_t)gridDim.x * blockDim.x) >> 6;
-  float dwacc[NV][8];
+  typedef typename Vec8<IO>::Raw Raw;
+  const int DV = D / 8, W = blockDim.x >> 6, lane = threadIdx.x & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const bool mine = (int)threadIdx.x < DV;
+  const size_t e0 = 8 * (size_t)(mine ? threadIdx.x : DV - 1);  // (clamped: loads are unconditional)
+  __shared__ float red[2][2][kMaxVecPerLane];  // [token parity][r, ss][wave]
+  float ww[8], dwacc[8];
+  Vec8<IO>::load(w, e0, ww);
 #pragma unroll
-  for (int q = 0; q < NV; ++q)
-#pragma unroll
-    for (int i = 0; i < 8; ++i) dwacc[q][i] = 0.f;
-  // The next token of this wave is fetched while the current one is worked on (a wave walks
-  // several tokens, and a token is two dependent phases with a wave-wide sum between them).
-  constexpr bool PF = NV * sizeof(IO) <= 8;  // (two sets of raw vectors must fit the registers)
-  typename Vec8<IO>::Raw ry[NV], ra[NV], rd[NV], ny[NV], na[NV], nd[NV];
-  auto fetch = [&](size_t tok, typename Vec8<IO>::Raw (&fy)[NV], typename Vec8<IO>::Raw (&fa)[NV],
-                   typename Vec8<IO>::Raw (&fd)[NV]) {
-#pragma unroll
-    for (int q = 0; q < NV; ++q) {
-      const int v = lane + 64 * q, vc = v < DV ? v : DV - 1;  // (clamped: loads are unconditional)
-      fy[q] = Vec8<IO>::load_raw(y, tok * D + 8 * vc);
-      fa[q] = Vec8<IO>::load_raw(a, tok * D + 8 * vc);
-      fd[q] = Vec8<IO>::load_raw(dout, tok * D + 8 * vc);
-    }
+  for (int i = 0; i < 8; ++i) dwacc[i] = 0.f;
+  Raw ny, na, nd;
+  float ns = 0.f;
+  auto fetch = [&](size_t tok) {
+    ny = Vec8<IO>::load_raw(y, tok * D + e0);
+    na = Vec8<IO>::load_raw(a, tok * D + e0);
+    nd = Vec8<IO>::load_raw(dout, tok * D + e0);
+    if (s_in) ns = s_in[tok];
   };
-  if (PF && wave < tokens) fetch(wave, ny, na, nd);
-  for (size_t tok = wave; tok < tokens; tok += nwaves) {
-    if constexpr (PF) {
-#pragma unroll
-      for (int q = 0; q < NV; ++q) { ry[q] = ny[q]; ra[q] = na[q]; rd[q] = nd[q]; }
-      const size_t nx = tok + nwaves < tokens ? tok + nwaves : tok;  // (last token: fetched again, unused)
-      fetch(nx, ny, na, nd);
-    } else {
-      fetch(tok, ry, ra, rd);
-    }
+  if (blockIdx.x < tokens) fetch(blockIdx.x);
+  int par = 0;
+  for (size_t tok = blockIdx.x; tok < tokens; tok += gridDim.x, par ^= 1) {
+    float yy[8], aa[8], dd[8], g[8], x[8];
+    Vec8<IO>::widen(ny, yy);
+    Vec8<IO>::widen(na, aa);
+    Vec8<IO>::widen(nd, dd);
+    float s = ns;
+    fetch(tok + gridDim.x < tokens ? tok + gridDim.x : tok);  // (last token: fetched again, unused)
     float ss = 0.f, r = 0.f;
 #pragma unroll
-    for (int q = 0; q < NV; ++q) {
-      const int v = lane + 64 * q;
-      if (v < DV) {
-        float yy[8], aa[8], dd[8], ww[8];
-        Vec8<IO>::widen(ry[q], yy);
-        Vec8<IO>::widen(ra[q], aa);
-        Vec8<IO>::widen(rd[q], dd);
-        Vec8<IO>::load(w, 8 * v, ww);
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          const float xi = yy[i] * (aa[i] * sigmoidf_(aa[i]));
-          ss = fmaf(xi, xi, ss);
-          r = fmaf(ww[i] * dd[i], xi, r);
-        }
+    for (int i = 0; i < 8; ++i) {
+      const float sg = sigmoidf_(aa[i]);
+      g[i] = aa[i] * sg;
+      aa[i] = sg * (1.f + aa[i] * (1.f - sg));  // SiLU'
+      x[i] = yy[i] * g[i];
+      ss = fmaf(x[i], x[i], ss);
+      r = fmaf(ww[i] * dd[i], x[i], r);
+    }
+    r = wave_sum(mine ? r : 0.f);
+    if (!s_in) ss = wave_sum(mine ? ss : 0.f);
+    if (W > 1) {  // the waves' sums, in increasing order
+      if (lane == 0) {
+        red[par][0][wv] = r;
+        red[par][1][wv] = ss;
+      }
+      lds_barrier();  // (the other parity's words are free again: every wave has read them)
+      r = red[par][0][0];
+      ss = red[par][1][0];
+      for (int u = 1; u < W; ++u) {
+        r += red[par][0][u];
+        ss += red[par][1][u];
       }
     }
-    r = wave_sum(r);
-    float s;
-    if (s_in) s = s_in[tok];
-    else s = 1.f / sqrtf(wave_sum(ss) / (float)D + eps);
+    if (!s_in) s = 1.f / sqrtf(ss / (float)D + eps);
     const float c3 = r * s * s * s / (float)D;
+    if (mine) {
+      float oy[8], oa[8];
 #pragma unroll
-    for (int q = 0; q < NV; ++q) {
-      const int v = lane + 64 * q;
-      if (v < DV) {
-        float yy[8], aa[8], dd[8], ww[8], oy[8], oa[8];
-        if constexpr (KEEP) {
-          Vec8<IO>::widen(ry[q], yy);
-          Vec8<IO>::widen(ra[q], aa);
-          Vec8<IO>::widen(rd[q], dd);
-        } else {
-          Vec8<IO>::load(y, tok * D + 8 * v, yy);
-          Vec8<IO>::load(a, tok * D + 8 * v, aa);
-          Vec8<IO>::load(dout, tok * D + 8 * v, dd);
-        }
-        Vec8<IO>::load(w, 8 * v, ww);
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          const float sg = sigmoidf_(aa[i]);
-          const float g = aa[i] * sg;
-          const float xi = yy[i] * g;
-          const float dxi = s * (ww[i] * dd[i]) - c3 * xi;
-          dwacc[q][i] = fmaf(dd[i] * xi, s, dwacc[q][i]);
-          oy[i] = dxi * g;
-          oa[i] = dxi * yy[i] * (sg * (1.f + aa[i] * (1.f - sg)));
-        }
-        Vec8<IO>::store(dy, tok * D + 8 * v, oy);
-        Vec8<IO>::store(da, tok * D + 8 * v, oa);
+      for (int i = 0; i < 8; ++i) {
+        const float dxi = s * (ww[i] * dd[i]) - c3 * x[i];
+        dwacc[i] = fmaf(dd[i] * x[i], s, dwacc[i]);
+        oy[i] = dxi * g[i];
+        oa[i] = dxi * yy[i] * aa[i];
       }
+      Vec8<IO>::store(dy, tok * D + e0, oy);
+      Vec8<IO>::store(da, tok * D + e0, oa);
     }
   }
-#pragma unroll
-  for (int q = 0; q < NV; ++q) {
-    const int v = lane + 64 * q;
-    if (v < DV) {
-      *(f4_t *)&part[wave * D + 8 * v] = f4_t{dwacc[q][0], dwacc[q][1], dwacc[q][2], dwacc[q][3]};
-      *(f4_t *)&part[wave * D + 8 * v + 4] = f4_t{dwacc[q][4], dwacc[q][5], dwacc[q][6], dwacc[q][7]};
-    }
+  if (mine) {
+    *(f4_t *)&part[blockIdx.x * (size_t)D + e0] = f4_t{dwacc[0], dwacc[1], dwacc[2], dwacc[3]};
+    *(f4_t *)&part[blockIdx.x * (size_t)D + e0 + 4] = f4_t{dwacc[4], dwacc[5], dwacc[6], dwacc[7]};
   }
-}
-
-__global__ void norm_sum_kernel(const float *__restrict__ lvl, float *__restrict__ dw, int D, int groups) {
-  const int e = blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= D) return;
-  dw[e] = strided_sum8(lvl + e, (size_t)D, 0, groups);
 }
 
 // Partial rows of the weight-gradient sums.  Many rows = many independent walkers (these
@@ -502,10 +506,15 @@ inline int conv_rows(int B, int T) {
   const long long rows = (long long)B * ((T + kSeg - 1) / kSeg);
   return (int)(rows < kConvRows ? (rows < 1 ? 1 : rows) : kConvRows);
 }
-// (a multiple of four: whole workgroups; waves beyond the tokens write zero rows)
+// Rows of the norm's scratch (callers size their workspace by this figure), and workgroups of a
+// launch = rows in use: what is resident with W waves per workgroup, four on each SIMD.
 inline int norm_waves(size_t tokens) {
   const size_t r = tokens < (size_t)kNormWaves ? (tokens < 1 ? 1 : tokens) : kNormWaves;
   return (int)((r + 3) / 4 * 4);
+}
+inline int norm_rows(size_t tokens, int W) {
+  const int resident = 256 * (16 / W), most = resident < kNormWaves ? resident : kNormWaves;
+  return tokens < (size_t)most ? (int)tokens : most;
 }
 
 }  // namespace
@@ -549,13 +558,7 @@ static hipError_t conv_bwd_t(int B, int T, int C, const void *x, const void *w, 
     if (e != hipSuccess) return e;
   }
   const int E = C * (kTaps + 1);
-  float *lvl = part + (size_t)RG * E;
-  if (any)
-    hipLaunchKernelGGL(ordered_sum_level1_kernel, dim3((E + 255) / 256, kSumGroups), dim3(256), 0, s,
-                       (const float *)part, lvl, E, RG);
-  hipLaunchKernelGGL(conv_sum_kernel, dim3((E + 255) / 256), dim3(256), 0, s, (const float *)lvl, dw,
-                     dbias, C, any ? kSumGroups : 0);
-  return hipGetLastError();
+  return ordered_sum(part, part + (size_t)RG * E, ConvOut{dw, dbias}, E, any ? RG : 0, s);
 }
 hipError_t conv_silu_bwd(int B, int T, int C, int io, const void *x, const void *w, const void *bias,
                          const void *dout, void *dx, float *dw, float *dbias, float *part,
@@ -577,7 +580,9 @@ static hipError_t norm_fwd_t(int B, int T, int D, const void *y, const void *a, 
                      w, eps, out, s_out, tokens, D)
   if (nv <= 1) M2RNN_GO(1);
   else if (nv <= 2) M2RNN_GO(2);
+  else if (nv <= 3) M2RNN_GO(3);
   else if (nv <= 4) M2RNN_GO(4);
+  else if (nv <= 6) M2RNN_GO(6);
   else M2RNN_GO(8);
 #undef M2RNN_GO
   return hipGetLastError();
@@ -593,27 +598,15 @@ static hipError_t norm_bwd_t(int B, int T, int D, const void *y, const void *a, 
                              const float *s_in, const void *dout, void *dy, void *da, float *dw,
                              float *part, hipStream_t s) {
   const size_t tokens = (size_t)B * T;
-  const int R = norm_waves(tokens);
+  const int W = (D / 8 + 63) / 64;
+  const int R = norm_rows(tokens, W);
   if (tokens > 0) {
-    const int nv = (D / 8 + 63) / 64;
-#define M2RNN_GO(NV_)                                                                              \
-  hipLaunchKernelGGL((gated_rmsnorm_bwd_kernel<IO, NV_>), dim3(R / 4), dim3(256), 0, s, y, a, w, eps,   \
-                     s_in, dout, dy, da, part, tokens, D)
-    if (nv <= 1) M2RNN_GO(1);
-    else if (nv <= 2) M2RNN_GO(2);
-    else if (nv <= 4) M2RNN_GO(4);
-    else M2RNN_GO(8);
-#undef M2RNN_GO
+    hipLaunchKernelGGL((gated_rmsnorm_bwd_kernel<IO>), dim3(R), dim3(64 * W), 0, s, y, a, w, eps, s_in, dout, dy,
+                       da, part, tokens, D);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
-  float *lvl = part + (size_t)R * D;
-  if (tokens > 0)
-    hipLaunchKernelGGL(ordered_sum_level1_kernel, dim3((D + 255) / 256, kSumGroups), dim3(256), 0, s,
-                       (const float *)part, lvl, D, R);
-  hipLaunchKernelGGL(norm_sum_kernel, dim3((D + 255) / 256), dim3(256), 0, s, (const float *)lvl, dw, D,
-                     tokens > 0 ? kSumGroups : 0);
-  return hipGetLastError();
+  return ordered_sum(part, part + (size_t)R * D, PlainOut{dw}, D, tokens > 0 ? R : 0, s);
 }
 hipError_t gated_rmsnorm_bwd(int B, int T, int D, int io, const void *y, const void *a, const void *w,
                              float eps, const float *s_in, const void *dout, void *dy, void *da,
