@@ -86,67 +86,120 @@ __device__ __forceinline__ float sigmoidf_(float u) {
 
 // ------------------------------------------------------------------ conv1d(4) + SiLU
 constexpr int kTaps = 4;
-constexpr int kSeg = 32;  // time steps per work item (3 halo rows are re-read: 9 %)
-constexpr int kBlk = 8;   // steps whose loads are issued together
+constexpr int kThreads = 256;
 
-// taps [8 channels][4] (32 consecutive elements of w [C,4]) and bias of channels c0 .. c0 + 7
+// four consecutive elements of an io tensor <-> four floats
+template <typename IO> struct Vec4;
+template <> struct Vec4<float> {
+  typedef f4_t Raw;
+  static __device__ __forceinline__ Raw load_raw(const void *base, size_t e) {
+    return *(const f4_t *)((const float *)base + e);
+  }
+  static __device__ __forceinline__ void widen(const Raw &w, float (&x)[4]) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) x[i] = w[i];
+  }
+  static __device__ __forceinline__ void store(void *base, size_t e, const float (&x)[4]) {
+    *(f4_t *)((float *)base + e) = f4_t{x[0], x[1], x[2], x[3]};
+  }
+};
+template <> struct Vec4<__hip_bfloat16> {
+  typedef uint32_t Raw __attribute__((ext_vector_type(2)));
+  static __device__ __forceinline__ Raw load_raw(const void *base, size_t e) {
+    return *(const Raw *)((const unsigned short *)base + e);
+  }
+  static __device__ __forceinline__ void widen(const Raw &w, float (&x)[4]) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      x[2 * i] = bf16_bits_to_f32(w[i] & 0xFFFFu);
+      x[2 * i + 1] = __builtin_bit_cast(float, w[i] & 0xFFFF0000u);
+    }
+  }
+  static __device__ __forceinline__ void store(void *base, size_t e, const float (&x)[4]) {
+    *(Raw *)((unsigned short *)base + e) = Raw{pack2_bf16(x[0], x[1]), pack2_bf16(x[2], x[3])};
+  }
+};
+
+// taps [4 channels][4] (16 consecutive elements of w [C,4]) and bias of channels c0 .. c0 + 3
 template <typename IO>
-__device__ __forceinline__ void load_taps(const void *w, const void *bias, int c0, float (&wt)[8][kTaps],
-                                          float (&bs)[8]) {
-  float wv[4][8];
+__device__ __forceinline__ void load_taps(const void *w, const void *bias, int c0, float (&wt)[4][kTaps],
+                                          float (&bs)[4]) {
 #pragma unroll
-  for (int q = 0; q < 4; ++q) Vec8<IO>::load(w, (size_t)c0 * kTaps + 8 * q, wv[q]);
-#pragma unroll
-  for (int i = 0; i < 8; ++i)
-#pragma unroll
-    for (int j = 0; j < kTaps; ++j) wt[i][j] = wv[(i * kTaps + j) / 8][(i * kTaps + j) % 8];
-  if (bias) Vec8<IO>::load(bias, c0, bs);
+  for (int i = 0; i < 4; ++i) Vec4<IO>::widen(Vec4<IO>::load_raw(w, ((size_t)c0 + i) * kTaps), wt[i]);
+  if (bias) Vec4<IO>::widen(Vec4<IO>::load_raw(bias, c0), bs);
   else
 #pragma unroll
-    for (int i = 0; i < 8; ++i) bs[i] = 0.f;
+    for (int i = 0; i < 4; ++i) bs[i] = 0.f;
 }
 
-// One work item = 8 channels x kSeg steps of one batch row.  Items are numbered with the
-// channel vector fastest, so a wave reads 1 KB (bf16) of one time step at a time.
+// How a launch is dealt out.  A work item is four channels x `seg` steps of one batch row; a
+// workgroup is `cw` channel vectors (at most 64, gx workgroups side by side) x kThreads / cw walkers,
+// and walker w of rg workgroup rows takes the rows w, w + walkers, ... of the B * nseg segments.
+//
+// Four channels, not eight: taps, windows and sums are half the registers, 4 waves per SIMD in the
+// backward instead of 2, whose arithmetic and loads then overlap.  cw is a multiple of eight where
+// it can be: with 31 instead of 32 vectors side by side the forward of 1472 channels took 48 us, not
+// 37.  Long segments read fewer halo rows twice, short ones fill the chip with a short tensor: the
+// longest segment is taken that still gives kConvItems items (262144, every thread resident:
+// 8 x 4000 x 520 in 48 us backward, 39 with this).  Forward / backward, bf16, before and now:
+//   8 x 4096 x 1472   42 / 101 -> 36 / 79 us        2 x 150 x 1016   20 / 37 -> 5 / 11 us
+struct ConvPlan {
+  int seg, nseg, cw, gx, walkers, rg;
+};
+constexpr long long kConvItems = 160 * 1024;
+
+inline ConvPlan conv_plan(int B, int T, int C, int most_rows) {
+  ConvPlan p;
+  const int CV = C / 4;
+  p.gx = (CV + 63) / 64;
+  p.cw = ((CV + p.gx - 1) / p.gx + 7) & ~7;
+  if (p.cw > CV) p.cw = CV;
+  p.walkers = kThreads / p.cw;
+  p.seg = 64;
+  while (p.seg > 8 && (long long)B * ((T + p.seg - 1) / p.seg) * CV < kConvItems) p.seg /= 2;
+  p.nseg = (T + p.seg - 1) / p.seg;
+  const long long want = ((long long)B * p.nseg + p.walkers - 1) / p.walkers;
+  p.rg = (int)(want < 1 ? 1 : want < most_rows ? want : most_rows);
+  return p;
+}
+
 template <typename IO>
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(kThreads)
     conv_silu_fwd_kernel(const void *__restrict__ x, const void *__restrict__ w,
-                         const void *__restrict__ bias, void *__restrict__ out, int B, int T, int C) {
-  const int CV = C / 8, nseg = (T + kSeg - 1) / kSeg;
-  const size_t items = (size_t)B * nseg * CV;
-  for (size_t it = blockIdx.x * (size_t)blockDim.x + threadIdx.x; it < items;
-       it += (size_t)gridDim.x * blockDim.x) {
-    const int cv = it % CV;
-    const size_t r = it / CV;
-    const int seg = r % nseg, b = r / nseg;
-    const int c0 = cv * 8, t0 = seg * kSeg, t1 = t0 + kSeg < T ? t0 + kSeg : T;
-    float wt[8][kTaps], bs[8];
-    load_taps<IO>(w, bias, c0, wt, bs);
-    float win[kTaps - 1][8];  // steps t-3, t-2, t-1
+                         const void *__restrict__ bias, void *__restrict__ out, int B, int T, int C, ConvPlan p) {
+  constexpr int BLK = 8;  // steps whose loads are issued together
+  const int wl = threadIdx.x / p.cw, cl = threadIdx.x - wl * p.cw;
+  const int bx = blockIdx.x % p.gx, rgi = blockIdx.x / p.gx;
+  const int cv = bx * p.cw + cl, rows = B * p.nseg;
+  if (wl >= p.walkers || cv >= C / 4) return;
+  const int c0 = cv * 4;
+  float wt[4][kTaps], bs[4];
+  load_taps<IO>(w, bias, c0, wt, bs);
+  for (long long r = (long long)rgi * p.walkers + wl; r < rows; r += (long long)p.rg * p.walkers) {
+    const int seg = (int)r % p.nseg, b = (int)r / p.nseg;
+    const int t0 = seg * p.seg, t1 = t0 + p.seg < T ? t0 + p.seg : T;
+    const size_t base = (size_t)b * T * C + c0;
+    float win[kTaps - 1][4];  // steps t-3, t-2, t-1
 #pragma unroll
     for (int j = 0; j < kTaps - 1; ++j) {
       const int ts = t0 - (kTaps - 1) + j;
-      if (ts >= 0) Vec8<IO>::load(x, ((size_t)b * T + ts) * C + c0, win[j]);
+      if (ts >= 0) Vec4<IO>::widen(Vec4<IO>::load_raw(x, base + (size_t)ts * C), win[j]);
       else
 #pragma unroll
-        for (int i = 0; i < 8; ++i) win[j][i] = 0.f;
+        for (int i = 0; i < 4; ++i) win[j][i] = 0.f;
     }
-    // kBlk steps at a time: their loads are all in flight before the first is used (one load
-    // per iteration would expose the memory latency kSeg times per item)
-    for (int tb = t0; tb < t1; tb += kBlk) {
-      typename Vec8<IO>::Raw raw[kBlk];
+    for (int tb = t0; tb < t1; tb += BLK) {
+      typename Vec4<IO>::Raw raw[BLK];
 #pragma unroll
-      for (int u = 0; u < kBlk; ++u) {
-        const int t = tb + u < t1 ? tb + u : t1 - 1;  // (clamped: every load is unconditional)
-        raw[u] = Vec8<IO>::load_raw(x, ((size_t)b * T + t) * C + c0);
-      }
+      for (int u = 0; u < BLK; ++u)  // (clamped: every load is unconditional)
+        raw[u] = Vec4<IO>::load_raw(x, base + (size_t)(tb + u < t1 ? tb + u : t1 - 1) * C);
 #pragma unroll
-      for (int u = 0; u < kBlk; ++u) {
+      for (int u = 0; u < BLK; ++u) {
         if (tb + u < t1) {
-          float cur[8], o[8];
-          Vec8<IO>::widen(raw[u], cur);
+          float cur[4], o[4];
+          Vec4<IO>::widen(raw[u], cur);
 #pragma unroll
-          for (int i = 0; i < 8; ++i) {
+          for (int i = 0; i < 4; ++i) {
             const float a = bs[i] + wt[i][0] * win[0][i] + wt[i][1] * win[1][i] + wt[i][2] * win[2][i] +
                             wt[i][3] * cur[i];
             o[i] = a * sigmoidf_(a);
@@ -154,7 +207,7 @@ __global__ void __launch_bounds__(256)
             win[1][i] = win[2][i];
             win[2][i] = cur[i];
           }
-          Vec8<IO>::store(out, ((size_t)b * T + tb + u) * C + c0, o);
+          Vec4<IO>::store(out, base + (size_t)(tb + u) * C, o);
         }
       }
     }
@@ -164,118 +217,113 @@ __global__ void __launch_bounds__(256)
 // Backward.  A work item recomputes the pre-activation of its own steps and of the three
 // after them (their gradients reach back into its steps), forms da = dout SiLU'(a), and
 // finishes dx of step t-3 as soon as da of step t is known.  dw and dbias of its OWN steps are
-// summed per thread over the items it walks (row r, r + R, ...: increasing time inside a batch
-// row, increasing batch row) and written to part[row][C][5]; conv_sum_kernel adds the rows.
+// summed per walker over the items it walks (increasing time inside a batch row, increasing
+// batch row), the walkers of a workgroup through LDS (increasing), and written to
+// part[workgroup row][C][5]; the ordered sum behind adds those.
 template <typename IO>
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(kThreads, 4)
     conv_silu_bwd_kernel(const void *__restrict__ x, const void *__restrict__ w,
                          const void *__restrict__ bias, const void *__restrict__ dout,
-                         void *__restrict__ dx, float *__restrict__ part, int B, int T, int C, int R) {
-  // A workgroup = 8 walker rows x 32 channel vectors; its 8 partial sums per channel are added
-  // through LDS (increasing row) before they leave, so part has R / 8 rows.
-  const int CV = C / 8, nseg = (T + kSeg - 1) / kSeg;
-  const int rows = B * nseg;
-  const int CVB = (CV + 31) / 32;
-  const int cvl = threadIdx.x & 31, rl = threadIdx.x >> 5;
-  const int cvb = blockIdx.x % CVB, rg = blockIdx.x / CVB;
-  const int cv = cvb * 32 + cvl, row0 = rg * 8 + rl;
-  const bool walker = cv < CV && row0 < R;
-  const int c0 = (cv < CV ? cv : CV - 1) * 8;
-  __shared__ float red[8][32][8 * (kTaps + 1)];
-  float wt[8][kTaps], bs[8], dwacc[8][kTaps], dbacc[8];
+                         void *__restrict__ dx, float *__restrict__ part, int B, int T, int C, ConvPlan p) {
+  constexpr int BLK = sizeof(IO) == 4 ? 4 : 8;  // steps whose loads are issued together
+  constexpr int PER = 4 * (kTaps + 1);          // sums per channel vector: [4 channels][4 taps, bias]
+  __shared__ float red[kThreads][PER + 1];
+  const int wl = threadIdx.x / p.cw, cl = threadIdx.x - wl * p.cw;
+  const int bx = blockIdx.x % p.gx, rgi = blockIdx.x / p.gx;
+  const int cv = bx * p.cw + cl, rows = B * p.nseg;
+  const bool walker = wl < p.walkers && cv < C / 4;
+  const int c0 = (cv < C / 4 ? cv : C / 4 - 1) * 4;
+  float wt[4][kTaps], bs[4], dwacc[4][kTaps], dbacc[4];
   load_taps<IO>(w, bias, c0, wt, bs);
 #pragma unroll
-  for (int i = 0; i < 8; ++i) {
+  for (int i = 0; i < 4; ++i) {
 #pragma unroll
     for (int j = 0; j < kTaps; ++j) dwacc[i][j] = 0.f;
     dbacc[i] = 0.f;
   }
-  for (int r = walker ? row0 : rows; r < rows; r += R) {
-    const int seg = r % nseg, b = r / nseg;
-    const int t0 = seg * kSeg, t1 = t0 + kSeg < T ? t0 + kSeg : T;
-    float win[kTaps - 1][8], dawin[kTaps - 1][8];  // x and da of steps t-3, t-2, t-1
+  for (long long r = walker ? (long long)rgi * p.walkers + wl : rows; r < rows; r += (long long)p.rg * p.walkers) {
+    const int seg = (int)r % p.nseg, b = (int)r / p.nseg;
+    const int t0 = seg * p.seg, t1 = t0 + p.seg < T ? t0 + p.seg : T;
+    const size_t base = (size_t)b * T * C + c0;
+    float win[kTaps - 1][4], dawin[kTaps - 1][4];  // x and da of steps t-3, t-2, t-1
 #pragma unroll
     for (int j = 0; j < kTaps - 1; ++j) {
       const int ts = t0 - (kTaps - 1) + j;
-      if (ts >= 0) Vec8<IO>::load(x, ((size_t)b * T + ts) * C + c0, win[j]);
+      if (ts >= 0) Vec4<IO>::widen(Vec4<IO>::load_raw(x, base + (size_t)ts * C), win[j]);
       else
 #pragma unroll
-        for (int i = 0; i < 8; ++i) win[j][i] = 0.f;
+        for (int i = 0; i < 4; ++i) win[j][i] = 0.f;
 #pragma unroll
-      for (int i = 0; i < 8; ++i) dawin[j][i] = 0.f;   // da of earlier steps does not reach mine
+      for (int i = 0; i < 4; ++i) dawin[j][i] = 0.f;  // da of earlier steps does not reach mine
     }
-    // (BLK steps at a time, loads first: see the forward)
-    constexpr int BLK = sizeof(IO) == 4 ? kBlk / 2 : kBlk;
-    const int tend = t1 + (kTaps - 1);
+    const int tend = t1 + (kTaps - 1), tlast = (tend < T ? tend : T) - 1;
     for (int tb = t0; tb < tend; tb += BLK) {
-     typename Vec8<IO>::Raw rx[BLK], rd[BLK];
+      typename Vec4<IO>::Raw rx[BLK], rd[BLK];
 #pragma unroll
-     for (int u = 0; u < BLK; ++u) {
-       const int tc = tb + u < T ? tb + u : T - 1;
-       rx[u] = Vec8<IO>::load_raw(x, ((size_t)b * T + tc) * C + c0);
-       rd[u] = Vec8<IO>::load_raw(dout, ((size_t)b * T + tc) * C + c0);
-     }
+      for (int u = 0; u < BLK; ++u) {  // (clamped: every load is unconditional)
+        const size_t e = base + (size_t)(tb + u < tlast ? tb + u : tlast) * C;
+        rx[u] = Vec4<IO>::load_raw(x, e);
+        rd[u] = Vec4<IO>::load_raw(dout, e);
+      }
 #pragma unroll
-     for (int u = 0; u < BLK; ++u) {
-      const int t = tb + u;
-      if (t >= tend) break;
-      float cur[8], da[8];
-      if (t < T) {
-        float dd[8];
-        Vec8<IO>::widen(rx[u], cur);
-        Vec8<IO>::widen(rd[u], dd);
+      for (int u = 0; u < BLK; ++u) {
+        const int t = tb + u;
+        if (t >= tend) break;
+        float cur[4], da[4];
+        if (t < T) {
+          float dd[4];
+          Vec4<IO>::widen(rx[u], cur);
+          Vec4<IO>::widen(rd[u], dd);
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          const float a = bs[i] + wt[i][0] * win[0][i] + wt[i][1] * win[1][i] + wt[i][2] * win[2][i] +
-                          wt[i][3] * cur[i];
-          const float sg = sigmoidf_(a);
-          da[i] = dd[i] * (sg * (1.f + a * (1.f - sg)));
-        }
-        if (t < t1) {  // my own step: its share of dw, dbias
-#pragma unroll
-          for (int i = 0; i < 8; ++i) {
-            dwacc[i][0] = fmaf(da[i], win[0][i], dwacc[i][0]);
-            dwacc[i][1] = fmaf(da[i], win[1][i], dwacc[i][1]);
-            dwacc[i][2] = fmaf(da[i], win[2][i], dwacc[i][2]);
-            dwacc[i][3] = fmaf(da[i], cur[i], dwacc[i][3]);
-            dbacc[i] += da[i];
+          for (int i = 0; i < 4; ++i) {
+            const float a = bs[i] + wt[i][0] * win[0][i] + wt[i][1] * win[1][i] + wt[i][2] * win[2][i] +
+                            wt[i][3] * cur[i];
+            const float sg = sigmoidf_(a);
+            da[i] = dd[i] * (sg * (1.f + a * (1.f - sg)));
           }
+          if (t < t1) {  // my own step: its share of dw, dbias
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+              dwacc[i][0] = fmaf(da[i], win[0][i], dwacc[i][0]);
+              dwacc[i][1] = fmaf(da[i], win[1][i], dwacc[i][1]);
+              dwacc[i][2] = fmaf(da[i], win[2][i], dwacc[i][2]);
+              dwacc[i][3] = fmaf(da[i], cur[i], dwacc[i][3]);
+              dbacc[i] += da[i];
+            }
+          }
+        } else {
+#pragma unroll
+          for (int i = 0; i < 4; ++i) { cur[i] = 0.f; da[i] = 0.f; }
         }
-      } else {
+        const int td = t - (kTaps - 1);  // dx of this step is complete now
+        if (td >= t0) {
+          float o[4];
 #pragma unroll
-        for (int i = 0; i < 8; ++i) { cur[i] = 0.f; da[i] = 0.f; }
-      }
-      const int td = t - (kTaps - 1);  // dx of this step is complete now
-      if (td >= t0) {
-        float o[8];
+          for (int i = 0; i < 4; ++i)
+            o[i] = wt[i][3] * dawin[0][i] + wt[i][2] * dawin[1][i] + wt[i][1] * dawin[2][i] + wt[i][0] * da[i];
+          Vec4<IO>::store(dx, base + (size_t)td * C, o);
+        }
 #pragma unroll
-        for (int i = 0; i < 8; ++i)
-          o[i] = wt[i][3] * dawin[0][i] + wt[i][2] * dawin[1][i] + wt[i][1] * dawin[2][i] + wt[i][0] * da[i];
-        Vec8<IO>::store(dx, ((size_t)b * T + td) * C + c0, o);
+        for (int i = 0; i < 4; ++i) {
+          win[0][i] = win[1][i]; win[1][i] = win[2][i]; win[2][i] = cur[i];
+          dawin[0][i] = dawin[1][i]; dawin[1][i] = dawin[2][i]; dawin[2][i] = da[i];
+        }
       }
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        win[0][i] = win[1][i]; win[1][i] = win[2][i]; win[2][i] = cur[i];
-        dawin[0][i] = dawin[1][i]; dawin[1][i] = dawin[2][i]; dawin[2][i] = da[i];
-      }
-     }
     }
   }
-  constexpr int PER = 8 * (kTaps + 1);  // floats per channel vector: [8 channels][4 taps, bias]
 #pragma unroll
-  for (int i = 0; i < 8; ++i) {
+  for (int i = 0; i < 4; ++i) {
 #pragma unroll
-    for (int j = 0; j < kTaps; ++j) red[rl][cvl][i * (kTaps + 1) + j] = dwacc[i][j];
-    red[rl][cvl][i * (kTaps + 1) + kTaps] = dbacc[i];
+    for (int j = 0; j < kTaps; ++j) red[threadIdx.x][i * (kTaps + 1) + j] = dwacc[i][j];
+    red[threadIdx.x][i * (kTaps + 1) + kTaps] = dbacc[i];
   }
   __syncthreads();
-  float *dst = part + ((size_t)rg * C + (size_t)cvb * 32 * 8) * (kTaps + 1);
-  for (int o = threadIdx.x; o < 32 * PER; o += 256) {
-    const int cl = o / PER, j = o - cl * PER;
-    if (cvb * 32 + cl < CV) {
-      float acc = red[0][cl][j];
-#pragma unroll
-      for (int q = 1; q < 8; ++q) acc += red[q][cl][j];
+  float *dst = part + ((size_t)rgi * C + (size_t)bx * p.cw * 4) * (kTaps + 1);
+  for (int o = threadIdx.x; o < p.cw * PER; o += kThreads) {
+    const int c = o / PER, j = o - c * PER;
+    if (bx * p.cw + c < C / 4) {
+      float acc = red[c][j];
+      for (int q = 1; q < p.walkers; ++q) acc += red[q * p.cw + c][j];
       dst[o] = acc;
     }
   }
@@ -502,8 +550,10 @@ __global__ void __launch_bounds__(512, 4)
 constexpr int kConvRows = 2048;  // of the convolution's dw / dbias sums
 constexpr int kNormWaves = 4096; // of the norm's dw sum
 
+// Rows of the convolution's scratch (callers size their workspace by this figure): workgroup rows of
+// a launch stay within it (its walkers take more items each where that binds).
 inline int conv_rows(int B, int T) {
-  const long long rows = (long long)B * ((T + kSeg - 1) / kSeg);
+  const long long rows = (long long)B * ((T + 31) / 32);
   return (int)(rows < kConvRows ? (rows < 1 ? 1 : rows) : kConvRows);
 }
 // Rows of the norm's scratch (callers size their workspace by this figure), and workgroups of a
@@ -530,11 +580,10 @@ int gated_rmsnorm_max_features() { return kMaxVecPerLane * 64 * 8; }
 template <typename IO>
 static hipError_t conv_fwd_t(int B, int T, int C, const void *x, const void *w, const void *bias,
                              void *out, hipStream_t s) {
-  const size_t items = (size_t)B * ((T + kSeg - 1) / kSeg) * (C / 8);
-  if (items == 0) return hipSuccess;
-  size_t blocks = (items + 255) / 256;
-  if (blocks > 65536) blocks = 65536;
-  hipLaunchKernelGGL((conv_silu_fwd_kernel<IO>), dim3((unsigned)blocks), dim3(256), 0, s, x, w, bias, out, B, T, C);
+  if ((size_t)B * T == 0) return hipSuccess;
+  const ConvPlan p = conv_plan(B, T, C, 16384);
+  hipLaunchKernelGGL((conv_silu_fwd_kernel<IO>), dim3((unsigned)(p.gx * p.rg)), dim3(kThreads), 0, s, x, w, bias,
+                     out, B, T, C, p);
   return hipGetLastError();
 }
 hipError_t conv_silu_fwd(int B, int T, int C, int io, const void *x, const void *w, const void *bias,
@@ -547,18 +596,16 @@ template <typename IO>
 static hipError_t conv_bwd_t(int B, int T, int C, const void *x, const void *w, const void *bias,
                              const void *dout, void *dx, float *dw, float *dbias, float *part,
                              hipStream_t s) {
-  const int R = conv_rows(B, T);
-  const int RG = (R + 7) / 8;  // partial rows that leave the kernel
+  const ConvPlan p = conv_plan(B, T, C, conv_rows(B, T));
   const bool any = (size_t)B * T > 0;
   if (any) {
-    const int CVB = (C / 8 + 31) / 32;
-    hipLaunchKernelGGL((conv_silu_bwd_kernel<IO>), dim3((unsigned)(CVB * RG)), dim3(256), 0, s,
-                       x, w, bias, dout, dx, part, B, T, C, R);
+    hipLaunchKernelGGL((conv_silu_bwd_kernel<IO>), dim3((unsigned)(p.gx * p.rg)), dim3(kThreads), 0, s,
+                       x, w, bias, dout, dx, part, B, T, C, p);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
   const int E = C * (kTaps + 1);
-  return ordered_sum(part, part + (size_t)RG * E, ConvOut{dw, dbias}, E, any ? RG : 0, s);
+  return ordered_sum(part, part + (size_t)p.rg * E, ConvOut{dw, dbias}, E, any ? p.rg : 0, s);
 }
 hipError_t conv_silu_bwd(int B, int T, int C, int io, const void *x, const void *w, const void *bias,
                          const void *dout, void *dx, float *dw, float *dbias, float *part,
