@@ -36,3 +36,44 @@ def test_conv_edges(io, B, T, C, bias):
 @pytest.mark.parametrize("B,T,C,bias", [(3, 1399, 4000, True), (3, 2799, 4000, False), (17, 3901, 1024, True)])
 def test_conv_long_segments(B, T, C, bias):
     conv_case("bf16", B, T, C, bias)
+
+
+@pytest.mark.parametrize("io", ["f32", "bf16"])
+def test_a_nan_stays_where_it_belongs(io):
+    """A NaN reaches the outputs that depend on it and no other: lanes and rows that a launch
+    only pads with clamped loads must not leak into sums or neighbours."""
+    import torch
+    from paper_2603_14360_amd import binding as mb
+    print("case nan", io, flush=True)
+    B, T, C = 2, 70, 1048   # a last wave (norm) and a last workgroup (conv) that are nearly empty
+    g = torch.Generator(device="cuda").manual_seed(3)
+    dt = torch.float32 if io == "f32" else torch.bfloat16
+    x, a, dout = (torch.randn(B, T, C, generator=g, device="cuda").to(dt) for _ in range(3))
+    w4, b4, w = (torch.randn(*s, generator=g, device="cuda").to(dt) for s in ((C, 4), (C,), (C,)))
+    st = torch.cuda.current_stream().cuda_stream
+
+    def run(x):
+        out, dx, o2, dy, da = (torch.empty_like(x) for _ in range(5))
+        dw, db, dw2, s = (torch.empty(sh, device="cuda") for sh in ((C, 4), (C,), (C,), (B, T)))
+        ws = torch.empty(max(mb.m2rnn_conv_silu_workspace_bytes(B, T, C), mb.m2rnn_gated_rmsnorm_workspace_bytes(B, T, C)),
+                         dtype=torch.uint8, device="cuda")
+        mb.m2rnn_conv_silu_fwd(x, w4, b4, out, stream=st)
+        mb.m2rnn_conv_silu_bwd(x, w4, b4, dout, dx, dw, db, ws, stream=st)
+        mb.m2rnn_gated_rmsnorm_fwd(x, a, w, 1e-5, o2, s, stream=st)
+        mb.m2rnn_gated_rmsnorm_bwd(x, a, w, 1e-5, s, dout, dy, da, dw2, ws, stream=st)
+        return out, dx, dw, db, o2, dy, da, s
+
+    clean = run(x)
+    bad = x.clone()
+    bad[0, 20, C - 1] = float("nan")
+    # conv: the channel's next three steps and, backward, three steps around them; norm: the token
+    hit = [torch.zeros_like(t, dtype=torch.bool) for t in clean]
+    hit[0][0, 20:24, C - 1] = True
+    hit[1][0, 17:24, C - 1] = True
+    hit[2][C - 1] = True
+    hit[3][C - 1] = True
+    for i in (4, 5, 6, 7):
+        hit[i][0, 20] = True
+    for got, ref, h in zip(run(bad), clean, hit):
+        assert torch.equal(got[~h], ref[~h])
+        assert got[h].isnan().all()
