@@ -163,7 +163,7 @@ m2rnn_status fwd_impl(const m2rnn_desc *desc, const m2rnn_opts *opts, const void
   a.C = C; a.io = desc->io;
   a.q = q; a.k = k; a.v = v; a.W = W; a.f = f; a.H0 = H0;
   a.y = y; a.HT = HT; a.ckpt = ckpt; a.write_y = 1; a.ws = (char *)workspace;
-  a.ws_bytes = workspace_bytes;
+  a.ws_bytes = workspace ? workspace_bytes : 0;  // (what a split may use: nothing without a pointer)
   a.w_r = w_r; a.gate_alpha = ga; a.gate_beta = gb;
   hipStream_t s = (hipStream_t)hip_stream;
   const hipError_t e = run_fwd(desc, a, s);
