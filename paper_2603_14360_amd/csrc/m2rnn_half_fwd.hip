@@ -20,9 +20,11 @@
 //   R  S' = c (H W), hi and lo rows
 //   E  s' = S'_hi + S'_lo + (c k_i) v_j, gate_tanh_step, split; the lane's two rows are ONE
 //      8-byte item {hi0, hi1, lo0, lo1} of the exchange layout; barrier (V > 16)
-//   Y  readout y_t = H_t^T q_t: the item is, as it stands, the A operand of a 16x16x16 MFMA
-//      over the rows (hi and lo both count), B = q_t in column t mod 16 only, so that a
-//      16-step accumulator collects y.
+//   Y  readout y_t = H_t^T q_t: the item is, as it stands, the B operand of a 16x16x16 MFMA
+//      over the rows (hi and lo both count), A = q_t in every row; row t mod 16 of the product
+//      is kept, one register of 16 lanes per step, so that 16 steps of y collect in four registers.
+//      (Kept by a select: with zeros in the other rows of A and a running sum, 0 x NaN would
+//      carry a NaN of the state into the y of earlier steps.)
 // q, k, v, f for 16 steps at a time are staged through LDS, the next block's global loads in
 // flight behind the current block.
 #include "m2rnn_kernels.hpp"
@@ -212,26 +214,30 @@ __global__ void __launch_bounds__(HF::THREADS, 2) half_fwd_kernel(FwdArgs a, flo
     x.v = sm.vS[sb][s][col0 + jl];
     if constexpr (DO_Y) x.q = *(const uint32_t *)&sm.qS[sb][s][rowb + 2 * ig];
   };
+  // lane (ig, jl) of a block's readout holds steps 4 ig + r of column col0 + jl
+  const size_t row = (size_t)N * V, y_lane = ((size_t)b * T + 4 * ig) * row + (size_t)n * V + col0 + jl;
   auto y_store = [&](f4_t ys, int t0, int len) __attribute__((always_inline)) {
-    // lane (ig, jl) holds columns col0 + 4 ig + r of step t0 + jl
-    if (jl < len) {
-      const size_t yoff = (((size_t)b * T + t0 + jl) * N + n) * V + col0 + 4 * ig;
-      if constexpr (HF::P == 1) {
-        ys *= kInvC;
-        if (a.w_r) {  // residual w_r (.) v_t of the y equation
-          const uint2 wv = *(const uint2 *)&((const bf16_raw *)a.w_r)[n * V + col0 + 4 * ig];
-          const uint2 vv = *(const uint2 *)&vg[yoff];
-          ys[0] = fmaf(bf16_to_f32(wv.x & 0xFFFFu), bf16_to_f32(vv.x & 0xFFFFu), ys[0]);
-          ys[1] = fmaf(bf16_to_f32(wv.x >> 16), bf16_to_f32(vv.x >> 16), ys[1]);
-          ys[2] = fmaf(bf16_to_f32(wv.y & 0xFFFFu), bf16_to_f32(vv.y & 0xFFFFu), ys[2]);
-          ys[3] = fmaf(bf16_to_f32(wv.y >> 16), bf16_to_f32(vv.y >> 16), ys[3]);
+    const size_t yoff = y_lane + t0 * row;
+    if constexpr (HF::P == 1) {
+      ys *= kInvC;
+      const float wr = a.w_r ? bf16_to_f32(((const bf16_raw *)a.w_r)[n * V + col0 + jl]) : 0.f;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        if (4 * ig + r < len) {
+          // residual w_r (.) v_t of the y equation
+          if (a.w_r) ys[r] = fmaf(wr, bf16_to_f32(vg[yoff + r * row]), ys[r]);
+          yg[yoff + r * row] = f32_to_bf16(ys[r]);
         }
-        uint2 p2;
-        p2.x = (uint32_t)f32_to_bf16(ys[0]) | ((uint32_t)f32_to_bf16(ys[1]) << 16);
-        p2.y = (uint32_t)f32_to_bf16(ys[2]) | ((uint32_t)f32_to_bf16(ys[3]) << 16);
-        *(uint2 *)&yg[yoff] = p2;
+      }
+    } else {
+      float *dst = ypart_ws + (size_t)part * a.B * T * row + yoff;
+      if (len == TB) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) dst[r * row] = ys[r];
       } else {
-        *(f4_t *)&ypart_ws[(size_t)part * a.B * T * N * V + yoff] = ys;
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          if (4 * ig + r < len) dst[r * row] = ys[r];
       }
     }
   };
@@ -243,7 +249,7 @@ __global__ void __launch_bounds__(HF::THREADS, 2) half_fwd_kernel(FwdArgs a, flo
     // Unconditional (the last block fetches itself again): behind a condition the compiler
     // merges old and new registers with copies that wait for the loads at once.
     stage_load(blk + 1 < nblk ? t0 + TB : t0);
-    f4_t yacc = zero4;  // D[m = column][n = s] = c * y partial of step t0 + s
+    f4_t yacc = zero4;  // [step t0 + 4 ig + r][column col0 + jl]: c * y partial
     StepRegs nx;
     step_L(nx, 0, sb, 0);
     auto step = [&](int s, bool last) __attribute__((always_inline)) {
@@ -264,8 +270,9 @@ __global__ void __launch_bounds__(HF::THREADS, 2) half_fwd_kernel(FwdArgs a, flo
       step_barrier();
       if (!last) step_L(nx, s + 1, sb, (s + 1) & 1);
       if constexpr (DO_Y) {
-        const uint32_t qs = jl == s ? x.q : 0u;
-        yacc = mfma_k16(__builtin_bit_cast(h4_t, it), __builtin_bit_cast(h4_t, u2_t{qs, qs}), yacc);
+        const f4_t yd = mfma_k16(__builtin_bit_cast(h4_t, u2_t{x.q, x.q}), __builtin_bit_cast(h4_t, it), zero4);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) yacc[r] = 4 * ig + r == s ? yd[r] : yacc[r];
       }
     };
     if (len == TB) {

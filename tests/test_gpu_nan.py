@@ -1,0 +1,38 @@
+"""GPU: a NaN in the scan reaches the outputs that depend on it and no other.  y_t depends on the
+inputs of steps <= t; dq, dk, dv, df of step t on dy of steps >= t (and on the state, which is finite
+here).  Inputs hold one NaN; every output that cannot depend on it keeps its bits."""
+import pytest
+
+from paper_2603_14360_amd import binding as mb
+from paper_2603_14360_amd.synth_inputs import Workload, make_inputs
+import gpu_util as gu
+
+pytestmark = pytest.mark.gpu
+
+T = 37
+# (K, V, states): the splits of the 8-row forward, and its neighbours
+FORWARD = [(64, 64, 2), (64, 64, 130), (128, 128, 2), (32, 32, 3), (32, 32, 300), (16, 16, 3), (64, 16, 3),
+           (64, 16, 140), (64, 32, 3), (64, 32, 150), (32, 16, 3), (32, 16, 200), (64, 64, 600), (128, 32, 3)]
+
+
+def _device(K, V, units, io):
+    wl = Workload("t", units, T, 1, K, V, io, 50 + K + V, K ** -0.5, 1.0, use_H0=True, use_dHT=True)
+    return gu.to_device(make_inputs(wl), io)
+
+
+@pytest.mark.parametrize("io,K,V,units", [("bf16",) + c for c in FORWARD] +
+                         [("f32", K, V, 2) for K in (16, 64) for V in (16, 32, 64)])
+@pytest.mark.parametrize("t", [5, 21])
+def test_y_of_earlier_steps(io, K, V, units, t):
+    import torch
+    print("case", io, K, V, units, t, flush=True)
+    dev = _device(K, V, units, io)
+    scan = mb.Scan(units, T, 1, K, V, io, backward=False)
+    args = lambda: (dev["q"], dev["k"], dev["v"], dev["f"], dev["W"], dev["H0"])
+    clean, H = (x.clone() for x in scan.fwd(*args()))
+    dev["v"][0, t, 0, 3] = float("nan")
+    y, HT = scan.fwd(*args())
+    torch.cuda.synchronize()
+    assert torch.equal(y[0, :t], clean[0, :t])
+    assert torch.equal(y[1:], clean[1:]) and torch.equal(HT[1:], H[1:])
+    assert y[0, t:, 0, 3].isnan().all() and y[0, t + 1:].isnan().all() and HT[0].isnan().all()
