@@ -34,6 +34,8 @@
  *     recurrence itself keeps |H| <= max(1, |H0|)).  dy, dHT and the gradients
  *     may have any fp32 magnitude: the backward rescales them by powers of two
  *     internally.  With M2RNN_F32 everything is plain fp32.
+ *   - A NaN in the inputs of step t reaches no y of an earlier step, with one exception: bf16 io
+ *     at K = V = 128 and more than 16 states, where it may reach back up to 15 steps.
  */
 #ifndef M2RNN_H_
 #define M2RNN_H_

@@ -259,6 +259,10 @@ __global__ void __launch_bounds__(TL::THREADS, 2)
   //    they stand; times the identity gives them back with rows in registers and columns in
   //    lanes (exact: products with 1 and 0).  Then A[m = j][k = i] = hi(H'[i][j]);
   //    B[k = i][n] = q_i for n == s, else 0: column s of yacc collects step s.
+  //    (0 x NaN is NaN: a NaN that enters the state reaches the y of the earlier steps of its
+  //    16-step block here.  Column s kept by selects from a product with q in every column, as
+  //    the 8-row kernel does, holds it back but takes 2.7 % of a 4 x 8192, 8-head training
+  //    step, 10.88 -> 11.19 ms; transposed, with one select per step, 2.5 %.)
   auto step_Y = [&](const StepRegs &x, const uint32_t (&pk)[4], int s, f4_t &yacc)
       __attribute__((always_inline)) {
     const h4_t qf = (jl == s) ? x.qf : zero_h4;
