@@ -288,7 +288,9 @@ __global__ void __launch_bounds__(Q::THREADS, 2) quad_fwd_kernel(FwdArgs a, floa
 // Per stash of up to 16 steps, last to first:
 //   recompute  the states from the checkpoint, H before each step and Z of each step to LDS
 //   sweep      in reverse: G = q dy^T + carry, dS = (1 - f) G (1 - Z^2) into Z's place,
-//              carry = f G + dS W^T; df on a 16x16x4 product with ones in column s
+//              carry = f G + dS W^T; df from a 16x16x4 product with ones, each step's sum kept by
+//              one lane of 16 (ones in column s alone and a running sum would let a NaN or an
+//              infinity of one step into the df of all others of the stash: 0 x NaN is NaN)
 //   finish     everything that contracts over more than a wave holds, for all 16 steps at once,
 //              out of LDS: dW += sum_s H^T dS (16x16x4 products over steps and rows), dq = H dy,
 //              dk = dS v, dv = dS^T k
@@ -451,7 +453,7 @@ __global__ void __launch_bounds__(Q::THREADS, Q::V < 64 ? 2 : 1) quad_bwd_kernel
       }
       *(f4_t *)&sm.H[len][a_off] = quad_transpose(h, p.odd, p.high);
       // ---- sweep
-      f4_t dfacc = {0.f, 0.f, 0.f, 0.f};
+      float dfacc = 0.f;
 #pragma nounroll
       for (int s = len - 1; s >= 0; --s) {
         const f4_t q4 = *(const f4_t *)&sm.q[s][p.row];
@@ -469,16 +471,17 @@ __global__ void __launch_bounds__(Q::THREADS, Q::V < 64 ? 2 : 1) quad_bwd_kernel
         }
         const f4_t da = quad_transpose(dS, p.odd, p.high);
         *(f4_t *)&sm.D[s][a_off] = da;
-        dfacc = __builtin_amdgcn_mfma_f32_16x16x4f32(dfl, (p.lane & 15) == s ? 1.f : 0.f, dfacc, 0, 0, 0);
+        const f4_t df4 = __builtin_amdgcn_mfma_f32_16x16x4f32(dfl, 1.f, f4_t{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
         const f4_t d = contract<Q>(da, wt, f4_t{0.f, 0.f, 0.f, 0.f});
 #pragma unroll
         for (int m = 0; m < 4; ++m) carry[m] = fmaf(f, G[m], d[m]);
+        // every column of df4 is the same: lane (j, i) holds the sums of 4 of the 16 rows i' = 4 i + r
+        dfacc = (p.lane & 15) == s ? (df4[0] + df4[1]) + (df4[2] + df4[3]) : dfacc;
         if (a.clip > 0.f)
 #pragma unroll
           for (int m = 0; m < 4; ++m) carry[m] = __builtin_amdgcn_fmed3f(carry[m], -a.clip, a.clip);
       }
-      // column s of dfacc: lane (s, i) holds four of its sixteen rows
-      sm.df[p.wave * 4 + (p.lane >> 4)][p.lane & 15] = (dfacc[0] + dfacc[1]) + (dfacc[2] + dfacc[3]);
+      sm.df[p.wave * 4 + (p.lane >> 4)][p.lane & 15] = dfacc;  // lane (s, i): its rows' sum of step s
       __syncthreads();
       // ---- finish: dW, 4 rows of one step per product
 #pragma unroll

@@ -36,3 +36,34 @@ def test_y_of_earlier_steps(io, K, V, units, t):
     assert torch.equal(y[0, :t], clean[0, :t])
     assert torch.equal(y[1:], clean[1:]) and torch.equal(HT[1:], H[1:])
     assert y[0, t:, 0, 3].isnan().all() and y[0, t + 1:].isnan().all() and HT[0].isnan().all()
+
+
+# the backwards in fp32 throughout, V <= 64 and V = 128 (fp32 io, and bf16 io of the shapes without
+# a matrix-core backward)
+FP32_BACKWARD = [("f32", K, V) for K in (16, 64) for V in (16, 32, 64)] + [("f32", 32, 128)]
+FP32_BACKWARD += [("bf16", 64, 32), ("bf16", 128, 64), ("bf16", 16, 64)]
+
+
+@pytest.mark.parametrize("io,K,V", FP32_BACKWARD)
+@pytest.mark.parametrize("t,bad", [(5, "nan"), (21, "nan"), (21, "inf")])
+def test_gradients_of_later_steps(io, K, V, t, bad):
+    """dy of step t holds one NaN or infinity: the gradients of the steps behind t, which do not
+    depend on it, keep their bits; those of the steps up to t are spoiled."""
+    import torch
+    units = 2
+    print("case", io, K, V, t, bad, flush=True)
+    dev = _device(K, V, units, io)
+    scan = mb.Scan(units, T, 1, K, V, io)
+    args = [dev[n] for n in ("q", "k", "v", "f", "W", "H0")]
+    scan.fwd(*args)
+    grads = lambda: [x.clone() for x in scan.bwd(*args, dev["dy"], dev["dHT"])]
+    clean = grads()
+    dev["dy"][0, t, 0, 3] = float(bad)
+    got = grads()
+    torch.cuda.synchronize()
+    for name, g, c in zip(gu.GRAD_NAMES[:4], got, clean):
+        assert torch.equal(g[0, t + 1:], c[0, t + 1:]), name
+        assert torch.equal(g[1:], c[1:]), name
+    dq, dk, dv, df = got[:4]
+    assert not df[0, :t + 1].isfinite().any() and not dv[0, :t, 0].isfinite().any()
+    assert torch.equal(got[5][1:], clean[5][1:]) and not got[4].isfinite().any()
