@@ -99,9 +99,9 @@ __device__ __forceinline__ f4_t quad_transpose(f4_t x, bool odd, bool high) {
 // independent chains, because the result of a 4x4x1 is not ready for the next instruction's
 // accumulator
 template <int CBSZ, int V, int... B0>
-__device__ __forceinline__ f4_t contract_blocks(const f4_t &a, const float (&w)[V], f4_t init,
+__device__ __forceinline__ f4_t contract_blocks(const f4_t &a, const float (&w)[V],
                                                 std::integer_sequence<int, B0...>) {
-  f4_t acc0 = init, acc1 = {0.f, 0.f, 0.f, 0.f}, acc2 = acc1, acc3 = acc1;
+  f4_t acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = acc0, acc2 = acc0, acc3 = acc0;
   (
       [&] {
         acc0 = __builtin_amdgcn_mfma_f32_4x4x1f32(a[0], w[4 * B0 + 0], acc0, CBSZ, B0, 0);
@@ -113,8 +113,18 @@ __device__ __forceinline__ f4_t contract_blocks(const f4_t &a, const float (&w)[
   return (acc0 + acc1) + (acc2 + acc3);
 }
 template <typename Q>
-__device__ __forceinline__ f4_t contract(const f4_t &a, const float (&w)[Q::V], f4_t init) {
-  return contract_blocks<Q::CBSZ, Q::V>(a, w, init, std::make_integer_sequence<int, Q::CB>{});
+__device__ __forceinline__ f4_t contract(const f4_t &a, const float (&w)[Q::V]) {
+  return contract_blocks<Q::CBSZ, Q::V>(a, w, std::make_integer_sequence<int, Q::CB>{});
+}
+// Pre-activation of a step, H W + k v^T: the outer product joins last, by an FMA on the finished sum.
+// (As the start of one of the four chains it is rounded once more, and so is every sum behind it:
+// state error against 64 bits, 512 steps, 1.2e-7 for 0.9e-7 at V = 32, 1.4e-7 for 0.9e-7 at 64.)
+template <typename Q>
+__device__ __forceinline__ f4_t preactivation(const f4_t &ha, const float (&w)[Q::V], const f4_t &k4, float vj) {
+  f4_t sp = contract<Q>(ha, w);
+#pragma unroll
+  for (int m = 0; m < 4; ++m) sp[m] = fmaf(k4[m], vj, sp[m]);
+  return sp;
 }
 
 // Waits for a loaded value here: the first use sits in a loop, where the wait would be repeated
@@ -248,7 +258,7 @@ __device__ __forceinline__ void quad_fwd_part(const FwdArgs &a, float *__restric
       const f4_t k4 = *(const f4_t *)&sm.k[buf][s][p.row];
       const float vj = sm.v[buf][s][p.col], f = sm.f[buf][s], gm = 1.f - f;
       const f4_t ha = quad_transpose(h, p.odd, p.high);
-      const f4_t sp = contract<Q>(ha, w, k4 * vj);
+      const f4_t sp = preactivation<Q>(ha, w, k4, vj);
 #pragma unroll
       for (int m = 0; m < 4; ++m) h[m] = fmaf(f, h[m], gm * tanh_fast_f32(sp[m]));
       if constexpr (DO_Y) {
@@ -393,7 +403,7 @@ __global__ void __launch_bounds__(Q::THREADS, Q::V < 64 ? 2 : 1) quad_bwd_kernel
     const f4_t k4 = *(const f4_t *)&sm.k[s][p.row];
     const float vj = sm.v[s][p.col], f = sm.f[s], gm = 1.f - f;
     ha = quad_transpose(h, p.odd, p.high);
-    const f4_t sp = contract<Q>(ha, w, k4 * vj);
+    const f4_t sp = preactivation<Q>(ha, w, k4, vj);
     f4_t z;
 #pragma unroll
     for (int m = 0; m < 4; ++m) {
@@ -472,7 +482,7 @@ __global__ void __launch_bounds__(Q::THREADS, Q::V < 64 ? 2 : 1) quad_bwd_kernel
         const f4_t da = quad_transpose(dS, p.odd, p.high);
         *(f4_t *)&sm.D[s][a_off] = da;
         const f4_t df4 = __builtin_amdgcn_mfma_f32_16x16x4f32(dfl, 1.f, f4_t{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
-        const f4_t d = contract<Q>(da, wt, f4_t{0.f, 0.f, 0.f, 0.f});
+        const f4_t d = contract<Q>(da, wt);
 #pragma unroll
         for (int m = 0; m < 4; ++m) carry[m] = fmaf(f, G[m], d[m]);
         // every column of df4 is the same: lane (j, i) holds the sums of 4 of the 16 rows i' = 4 i + r
