@@ -36,3 +36,46 @@ def test_state_error(K, V):
     err = np.linalg.norm(HT.double().cpu().numpy() - ref) / np.linalg.norm(ref)
     print("state error %.3e" % err, flush=True)
     assert err < 1.05e-7
+
+
+# bounds: half an ulp of the result's own rounding and, below 1, the rounding of x^3 p(x^2), which
+# is at most a quarter of the result (half an ulp of it, doubled for its two factors): 0.5 + 0.5; from
+# 1 on the rounding of 2 e / (1 + e), at most 0.24 of the result with some two ulp of it (exponential,
+# sum, product) and an ulp that is twice as fine as that of 1: 0.5 + 0.24 x 2 x 1.5
+TANH = [(1e-6, 1e-3, 0.6), (1e-3, 0.3, 0.75), (0.3, 0.55, 1.0), (0.55, 0.7, 1.0), (0.7, 1, 1.0), (1, 1.5, 1.25),
+        (1.5, 3, 1.0), (3, 12, 0.6), (12, 3e38, 0.6)]
+
+
+@pytest.mark.parametrize("lo,hi,bound", TANH)
+@pytest.mark.parametrize("K,V", [(128, 16), (128, 32), (128, 64)])
+def test_tanh(K, V, lo, hi, bound):
+    """One step with W = 0, f = 0 and v = 1: the state is tanh(k), k in [lo, hi] in both signs; in
+    one head all of a wave's values are of the range, in the other a few among small ones."""
+    import torch
+    print("case", K, V, lo, hi, flush=True)
+    B = 512
+    g = torch.Generator(device="cuda").manual_seed(11)
+    u = torch.rand(B, 1, 2, K, generator=g, device="cuda", dtype=torch.float64)
+    k = (lo + (hi - lo) * u).float().clamp(lo, hi)
+    k[:, :, :, ::3] *= -1
+    k[:, :, 1, 1::2] = 0.25
+    z = lambda *s: torch.zeros(*s, device="cuda")
+    scan = mb.Scan(B, 1, 2, K, V, "f32", backward=False)
+    _, HT = scan.fwd(k, k, z(B, 1, 2, V) + 1, z(B, 1, 2), z(2, V, V))
+    assert torch.equal(HT, HT[..., :1].expand_as(HT))
+    ref = torch.tanh(k[:, 0].double())
+    ulp = torch.exp2(torch.floor(torch.log2(ref.abs())) - 23)
+    err = float(((HT[..., 0].double() - ref) / ulp).abs().max())
+    print("tanh error %.2f ulp" % err, flush=True)
+    assert err <= bound
+
+
+def test_tanh_of_no_number():
+    import torch
+    k = torch.full((1, 1, 1, 16), 0.5, device="cuda")
+    k[0, 0, 0, :4] = torch.tensor([float("inf"), -float("inf"), float("nan"), 1e38], device="cuda")
+    z = lambda *s: torch.zeros(*s, device="cuda")
+    _, HT = mb.Scan(1, 1, 1, 16, 16, "f32", backward=False).fwd(k, k, z(1, 1, 1, 16) + 1, z(1, 1, 1), z(1, 16, 16))
+    col = HT[0, 0, :, 0]
+    assert col[0] == 1 and col[1] == -1 and col[2].isnan() and col[3] == 1
+    assert (col[4:] - 0.46211716).abs().max() < 1e-7 and torch.equal(HT[0, 0, :2, :], col[:2, None].expand(2, 16))
