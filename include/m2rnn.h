@@ -104,15 +104,24 @@ const char *m2rnn_route_string(const m2rnn_desc *desc, int bwd);
  * descriptor or T == 0. */
 size_t m2rnn_ckpt_bytes(const m2rnn_desc *desc);
 
-/* Bytes of scratch a call needs for partial sums across workgroups:
- *   bwd = 0   the forward (may be 0).  With all of it a forward of few states can split them over
- *             more of the GPU; part of it can do, at less speed and with the same results;
+/* Bytes of scratch with which a call runs at its best (partial sums across workgroups):
+ *   bwd = 0   the forward (may be 0);
  *   bwd = 1   the backward called WITH the forward's checkpoints (ckpt != NULL), the normal
  *             forward-then-backward use;
  *   bwd >= 2  the backward called with ckpt == NULL: bwd = 1 plus room for the checkpoints it
  *             then recomputes itself (m2rnn_ckpt_bytes more).
  * The backward figures include the two-stage sums of the option gradients (dw_r,
- * dgate_alpha, dgate_beta); the same size serves the plain and the _opt calls. */
+ * dgate_alpha, dgate_beta); the same size serves the plain and the _opt calls.
+ * This size always serves.  Two kinds of call also run on less, more slowly and with the same
+ * results (dW, whose sum takes another order, to rounding); M2RNN_ERR_WORKSPACE below that:
+ *   - the bf16 forward of few states, on the parts of a state that it has room for: down to the
+ *     partial sums of 16-row parts, or to nothing where one workgroup can hold a state;
+ *   - the kernels in fp32 throughout with V <= 64 (m2rnn_route_string), which then run the parts of
+ *     a state in turn: the forward from 8 N V^2 bytes, the backward from
+ *     8 N V^2 + 4 B N ((C + 1) K V + V^2) [+ 8 B T N K if Nqk != N] + 4096 N V + 2048 N bytes, or the
+ *     query where that is less.  (C: the checkpoint interval; N V^2, N K V, B T N K terms each rounded
+ *     up to 256 bytes.)  At B = 8, T = 4096, N = 16, K = V = 64 that is 0.5 MB and 42 MB, where the
+ *     query asks for 537 MB and 558 MB and takes 0.4 and 0.54 of the time. */
 size_t m2rnn_workspace_bytes(const m2rnn_desc *desc, int bwd);
 
 /*
@@ -124,7 +133,7 @@ size_t m2rnn_workspace_bytes(const m2rnn_desc *desc, int bwd);
  *   HT     [B,N,K,V] fp32, out, final state; NULL if not wanted
  *   ckpt   out, m2rnn_ckpt_bytes() bytes, written for a later m2rnn_bwd with the
  *          same descriptor; NULL for inference (no checkpoints are written)
- *   workspace / workspace_bytes  scratch of at least m2rnn_workspace_bytes(desc,0)
+ *   workspace / workspace_bytes  scratch, m2rnn_workspace_bytes(desc,0) (what less does is said there)
  * Returns M2RNN_OK or the first validation / launch error.
  */
 m2rnn_status m2rnn_fwd(const m2rnn_desc *desc, const void *q, const void *k,
@@ -145,7 +154,7 @@ m2rnn_status m2rnn_fwd(const m2rnn_desc *desc, const void *q, const void *k,
  *   dv     [B,T,N,V] io, out   df [B,T,N] fp32, out (gradient w.r.t. the gate value)
  *   dW     [N,V,V] fp32, out (summed over the batch)
  *   dH0    [B,N,K,V] fp32, out; NULL if not wanted
- *   workspace / workspace_bytes  at least m2rnn_workspace_bytes(desc, ckpt ? 1 : 2)
+ *   workspace / workspace_bytes  m2rnn_workspace_bytes(desc, ckpt ? 1 : 2) (what less does is said there)
  */
 m2rnn_status m2rnn_bwd(const m2rnn_desc *desc, const void *q, const void *k,
                        const void *v, const float *f, const void *W,

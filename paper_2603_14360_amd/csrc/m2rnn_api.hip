@@ -96,8 +96,13 @@ size_t fwd_least_ws(const m2rnn_desc *d, int C) {
   switch (fwd_family_of(d)) {
     case kRowWave: return 0;
     case kMfma: return mfma_fwd_least_bytes(d->B, d->T, d->N, d->K, d->V);
-    default: return family_ws(d, C, 0);
+    case kGeneric: return generic_least_bytes(d->B, d->T, d->N, d->Nqk, d->K, d->V, C, 0);
+    default: return 0;
   }
+}
+size_t bwd_least_ws(const m2rnn_desc *d, int C) {
+  return family_of(d) == kGeneric ? generic_least_bytes(d->B, d->T, d->N, d->Nqk, d->K, d->V, C, 1)
+                                  : family_ws(d, C, 1);
 }
 
 bool misaligned(const void *p) { return ((uintptr_t)p & 15u) != 0; }
@@ -107,9 +112,10 @@ bool misaligned(const void *p) { return ((uintptr_t)p & 15u) != 0; }
 struct BwdWsLayout {
   size_t main, ckpt, dwr, gate, total;
 };
-BwdWsLayout bwd_ws(const m2rnn_desc *d, int C, bool own_ckpt) {
+BwdWsLayout bwd_ws(const m2rnn_desc *d, int C, bool own_ckpt, bool least) {
   BwdWsLayout w;
-  const size_t b = family_ws(d, C, 1), f = own_ckpt ? family_ws(d, C, 0) : 0;  // pass 1 borrows `main`
+  const size_t b = least ? bwd_least_ws(d, C) : family_ws(d, C, 1);
+  const size_t f = !own_ckpt ? 0 : least ? fwd_least_ws(d, C) : family_ws(d, C, 0);  // pass 1 borrows `main`
   w.main = align256(b > f ? b : f);
   w.ckpt = own_ckpt ? align256(ckpt_bytes(d, C)) : 0;
   w.dwr = residual_dw_r_scratch_bytes(d->N, d->V);
@@ -239,7 +245,7 @@ size_t m2rnn_workspace_bytes(const m2rnn_desc *desc, int bwd) {
   if (check_desc(desc) != M2RNN_OK) return 0;
   const int C = resolve_chunk(desc);
   if (!C) return 0;
-  return bwd ? bwd_ws(desc, C, bwd >= 2).total : family_ws(desc, C, 0);
+  return bwd ? bwd_ws(desc, C, bwd >= 2, false).total : family_ws(desc, C, 0);
 }
 
 m2rnn_status m2rnn_fwd(const m2rnn_desc *desc, const void *q, const void *k, const void *v,
@@ -312,7 +318,8 @@ m2rnn_status m2rnn_bwd_opt(const m2rnn_desc *desc, const m2rnn_opts *opts, const
                         dv, df, dW, dH0, workspace, w_r, dw_r, ga,  gb,  dga, dgb};
   for (const void *p : ptrs)
     if (misaligned(p)) return M2RNN_ERR_ALIGN;
-  const BwdWsLayout wl = bwd_ws(desc, C, /*own_ckpt=*/ckpt == nullptr);
+  BwdWsLayout wl = bwd_ws(desc, C, /*own_ckpt=*/ckpt == nullptr, /*least=*/false);
+  if (workspace_bytes < wl.total) wl = bwd_ws(desc, C, ckpt == nullptr, /*least=*/true);
   const size_t need = wl.total;
   if (need > 0 && (!workspace || workspace_bytes < need))
     return workspace ? M2RNN_ERR_WORKSPACE : M2RNN_ERR_NULL;
@@ -341,7 +348,7 @@ m2rnn_status m2rnn_bwd_opt(const m2rnn_desc *desc, const m2rnn_opts *opts, const
   a.B = desc->B; a.T = desc->T; a.N = desc->N; a.Nqk = desc->Nqk; a.K = desc->K; a.V = desc->V;
   a.C = C; a.io = desc->io;
   a.q = q; a.k = k; a.v = v; a.W = W; a.dy = dy; a.f = f; a.H0 = H0; a.ckpt = ckpt; a.dHT = dHT;
-  a.dq = dq; a.dk = dk; a.dv = dv; a.df = df; a.dW = dW; a.dH0 = dH0; a.ws = ws;
+  a.dq = dq; a.dk = dk; a.dv = dv; a.df = df; a.dW = dW; a.dH0 = dH0; a.ws = ws; a.ws_bytes = main_bytes;
   a.w_r = w_r; a.dw_r = dw_r; a.dwr_ws = (float *)(ws + need - gate_bytes - dwr_bytes);
   a.clip = opts ? opts->grad_clip : 0.f;
   a.gate_alpha = ga; a.gate_beta = gb; a.dgate_alpha = dga; a.dgate_beta = dgb;

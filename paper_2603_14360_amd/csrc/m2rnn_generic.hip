@@ -484,6 +484,17 @@ size_t generic_workspace_bytes(int B, int T, int N, int Nqk, int K, int V, int C
   return layout_ws(B, T, N, Nqk, K, V, C, bwd).total;
 }
 
+// V <= 64 can do with less than the query: without room for the partial sums of a state's parts they
+// run in turn.  The line is the room that one workgroup per state with W and the states in memory
+// takes (the layout of the V = 128 kernels): callers that sized a fixed buffer by that stay served.
+// It holds what the parts in turn need: carried gradients and inner states are at most
+// (C - 1) / 16 + 1 states of each recurrence against C + 1, the sums of dW and of shared heads are the same.
+size_t generic_least_bytes(int B, int T, int N, int Nqk, int K, int V, int C, int bwd) {
+  const size_t full = generic_workspace_bytes(B, T, N, Nqk, K, V, C, bwd);
+  const size_t one = layout_ws(B, T, N, Nqk, K, V, C, bwd).total;
+  return full < one ? full : one;
+}
+
 hipError_t generic_fwd(const FwdArgs &a, hipStream_t s) {
   if (quad_supported(a.K, a.V)) return quad_fwd(a, s);  // (bf16 io with V <= 64 never gets here)
   return a.io == 0 ? run_fwd<float>(a, s) : run_fwd<__hip_bfloat16>(a, s);

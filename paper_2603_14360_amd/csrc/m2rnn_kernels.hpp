@@ -30,7 +30,8 @@ struct BwdArgs {
   const float *f, *H0, *ckpt, *dHT;
   void *dq, *dk, *dv;
   float *df, *dW, *dH0;
-  char *ws;
+  char *ws;          // workspace base
+  size_t ws_bytes;   // its size (the scan kernels' part of the caller's)
   const void *w_r;   // residual weight (dv_t += w_r (.) dy_t); null = none
   float *dw_r;       // [N,V] fp32 out, with w_r
   float *dwr_ws;     // scratch of residual_dw_r_scratch_bytes() for dw_r
@@ -87,6 +88,7 @@ inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 int generic_default_chunk(int K, int V);
 int generic_max_chunk(int K, int V);
 size_t generic_workspace_bytes(int B, int T, int N, int Nqk, int K, int V, int C, int bwd);
+size_t generic_least_bytes(int B, int T, int N, int Nqk, int K, int V, int C, int bwd);  // what it cannot run without
 hipError_t generic_fwd(const FwdArgs &a, hipStream_t s);
 hipError_t generic_bwd(const BwdArgs &a, hipStream_t s);
 

@@ -150,6 +150,12 @@ __device__ __forceinline__ f4_t preactivation(const f4_t &ha, const float (&w)[Q
 // in every step, and would wait there for the prefetch as well.
 __device__ __forceinline__ void arrived(f4_t &x) { asm volatile("" : "+v"(x)); }
 
+// four elements of a column
+template <int V>
+__device__ __forceinline__ f4_t load_rows(const float *p) {
+  return f4_t{p[0], p[V], p[2 * V], p[3 * V]};
+}
+
 // Per-lane position inside the workgroup's rows
 template <typename Q>
 struct LanePos {
@@ -342,24 +348,30 @@ __device__ __forceinline__ int sw(int row, int col) {  // element offset inside 
 }
 
 struct QuadBwdWs {
-  float *sub;     // [units][P][THREADS * 4] x sub-chunk states, only when C > 16
-  float *dvp, *dfp;  // [P][B,T,N,V], [P][B,T,N]  (P > 1)
-  float *dWp;     // [B N P][V][V]
+  float *sub;     // [units][P][nsub (+ 1)][THREADS * 4]: states in front of the later stashes of a chunk
+                  // (C > 16), and, the parts in turn, each part's carried gradient
+  float *dvp, *dfp;  // [P][B,T,N,V], [P][B,T,N]  (P > 1, the parts side by side)
+  float *dWp;     // [B N P][V][V], the parts in turn [B N][V][V]
   float *dqh, *dkh;  // [B,T,N,K] (Nqk != N)
   int nsub;
 };
 
-template <typename IO, typename Q>
+// SEQ: one workgroup runs the P parts of a state one after the other inside every stash, their dv and
+// df added up in registers in the order of parts_sum_kernel (same bits; dW is added in another
+// order): for callers whose workspace cannot hold the partial sums.
+template <typename IO, typename Q, bool SEQ>
 __global__ void __launch_bounds__(Q::THREADS, Q::V < 64 ? 2 : 1) quad_bwd_kernel(BwdArgs a, QuadBwdWs ws) {
   constexpr int V = Q::V, K = Q::K, ROWS = Q::ROWS, THREADS = Q::THREADS, NQ = Q::NQ, NV = Q::NV,
                 NW = Q::NW;
   extern __shared__ __attribute__((aligned(16))) char lds[];
   BwdLds<Q> &sm = *(BwdLds<Q> *)lds;
-  const int unit = blockIdx.x / Q::P, part = blockIdx.x % Q::P;
+  constexpr int TURNS = SEQ ? Q::P : 1;
+  const int unit = SEQ ? blockIdx.x : blockIdx.x / Q::P;
+  int part = SEQ ? 0 : blockIdx.x % Q::P, row_base = part * ROWS;
   const int T = a.T, N = a.N, C = a.C, b = unit / N, n = unit - b * N, g = n / (N / a.Nqk);
-  const int tid = threadIdx.x, row_base = part * ROWS;
+  const int tid = threadIdx.x;
   const LanePos<Q> p;
-  const size_t qk0 = ((size_t)b * T * a.Nqk + g) * K + row_base, v0 = ((size_t)b * T * N + n) * V,
+  const size_t qk0 = ((size_t)b * T * a.Nqk + g) * K + (SEQ ? 0 : row_base), v0 = ((size_t)b * T * N + n) * V,
                f0 = (size_t)b * T * N + n;
   const size_t qk_step = (size_t)a.Nqk * K, v_step = (size_t)N * V;
   const IO *qg = (const IO *)a.q + qk0, *kg = (const IO *)a.k + qk0, *vg = (const IO *)a.v + v0,
@@ -372,12 +384,23 @@ __global__ void __launch_bounds__(Q::THREADS, Q::V < 64 ? 2 : 1) quad_bwd_kernel
     w[c] = to_f32<IO>(((const IO *)a.W)[((size_t)n * V + c) * V + p.col]);
     wt[c] = to_f32<IO>(((const IO *)a.W)[((size_t)n * V + p.col) * V + c]);
   }
-  const size_t st_off = ((size_t)unit * K + row_base + p.row) * V + p.col;
+  auto st_off = [&]() __attribute__((always_inline)) { return ((size_t)unit * K + row_base + p.row) * V + p.col; };
+  // a part's slots in the workspace: a place that only the same lane reads again
+  const int slots = SEQ ? ws.nsub + 1 : ws.nsub;
+  auto slot = [&](int i) __attribute__((always_inline)) { return (f4_t *)ws.sub + (((size_t)unit * Q::P + part) * slots + i) * THREADS + tid; };
+  auto turn = [&](int i) __attribute__((always_inline)) {
+    if constexpr (SEQ) {
+      part = i;
+      row_base = i * ROWS;
+    }
+  };
   f4_t carry = {0.f, 0.f, 0.f, 0.f};
-  if (a.dHT)
-#pragma unroll
-    for (int m = 0; m < 4; ++m) carry[m] = a.dHT[st_off + m * V];
-  arrived(carry);
+  for (int i = 0; i < TURNS; ++i) {
+    turn(i);
+    if (a.dHT) carry = load_rows<V>(a.dHT + st_off());
+    arrived(carry);
+    if constexpr (SEQ) *slot(ws.nsub) = carry;
+  }
 
   // dW tiles of 16 x 16: with at least one per wave, wave w owns the NTW tiles w NTW ..; with
   // fewer tiles than waves (V = 16) every wave adds its own share of the rows to the one tile
@@ -391,8 +414,8 @@ __global__ void __launch_bounds__(Q::THREADS, Q::V < 64 ? 2 : 1) quad_bwd_kernel
 #pragma unroll
     for (int m = 0; m < NQ; ++m) {
       const int idx = tid + m * THREADS, t = t0 + min(idx / ROWS, len - 1);
-      rq[m] = to_f32<IO>(qg[t * qk_step + idx % ROWS]);
-      rk[m] = to_f32<IO>(kg[t * qk_step + idx % ROWS]);
+      rq[m] = to_f32<IO>(qg[t * qk_step + idx % ROWS + (SEQ ? row_base : 0)]);
+      rk[m] = to_f32<IO>(kg[t * qk_step + idx % ROWS + (SEQ ? row_base : 0)]);
     }
 #pragma unroll
     for (int m = 0; m < NV; ++m) {
@@ -432,155 +455,184 @@ __global__ void __launch_bounds__(Q::THREADS, Q::V < 64 ? 2 : 1) quad_bwd_kernel
 
   const int nck = (T + C - 1) / C;
   const int a_off = sw<V>(p.arow, p.acol);
-  if (nck > 0) {  // vectors of the last stash
+  if (!SEQ && nck > 0) {  // vectors of the last stash
     const int t0 = (nck - 1) * C, len = T - t0, sub = (len - 1) / TB;
     load(t0 + sub * TB, len - sub * TB);
   }
   for (int ck = nck - 1; ck >= 0; --ck) {
     const int ck0 = ck * C, clen = min(C, T - ck0), nsub = (clen + TB - 1) / TB;
-    f4_t hck;
-    {
-      const float *src = a.ckpt + ((size_t)unit * nck + ck) * K * V + (size_t)(row_base + p.row) * V + p.col;
-#pragma unroll
-      for (int m = 0; m < 4; ++m) hck[m] = src[m * V];
-      arrived(hck);
-    }
+    auto checkpoint = [&]() __attribute__((always_inline)) {
+      f4_t h = load_rows<V>(a.ckpt + ((size_t)unit * nck + ck) * K * V + (size_t)(row_base + p.row) * V + p.col);
+      arrived(h);
+      return h;
+    };
+    f4_t hck = {0.f, 0.f, 0.f, 0.f};
+    if constexpr (!SEQ) hck = checkpoint();
     // checkpoints further apart than a stash: a first pass leaves the state in front of each
-    // later stash in the workspace, at a place that only the same lane reads again
-    f4_t *const subst = (f4_t *)ws.sub + ((size_t)blockIdx.x * ws.nsub) * THREADS + tid;
+    // later stash in the workspace
     if (nsub > 1) {
-      f4_t h = hck, ha;
-      for (int sub = 0; sub + 1 < nsub; ++sub) {
-        load(ck0 + sub * TB, TB);
-        __syncthreads();
-        store();
-        __syncthreads();
+      for (int i = 0; i < TURNS; ++i) {
+        turn(i);
+        if constexpr (SEQ) hck = checkpoint();
+        f4_t h = hck, ha;
+        for (int sub = 0; sub + 1 < nsub; ++sub) {
+          load(ck0 + sub * TB, TB);
+          __syncthreads();
+          store();
+          __syncthreads();
 #pragma nounroll
-        for (int s = 0; s < TB; ++s) step(h, s, ha);
-        subst[(size_t)sub * THREADS] = h;
+          for (int s = 0; s < TB; ++s) step(h, s, ha);
+          *slot(sub) = h;
+        }
       }
-      load(ck0 + (nsub - 1) * TB, clen - (nsub - 1) * TB);
+      if constexpr (!SEQ) load(ck0 + (nsub - 1) * TB, clen - (nsub - 1) * TB);
       __syncthreads();
     }
     for (int sub = nsub - 1; sub >= 0; --sub) {
       const int t0 = ck0 + sub * TB, len = min(TB, clen - sub * TB);
-      store();
-      f4_t h = sub > 0 ? subst[(size_t)(sub - 1) * THREADS] : hck, ha;
-      arrived(h);
-      __syncthreads();
-      // the next stash's vectors travel during this one
-      if (sub > 0) load(t0 - TB, TB);
-      else if (ck > 0 && C <= TB) load(ck0 - C, C);
-      // ---- recompute
-#pragma nounroll
-      for (int s = 0; s < len; ++s) {
-        const f4_t z = step(h, s, ha);
-        *(f4_t *)&sm.H[s][a_off] = ha;
-        ((f4_t *)sm.D[s])[tid] = z;  // (only this lane reads it again)
-      }
-      *(f4_t *)&sm.H[len][a_off] = quad_transpose(h, p.odd, p.high);
-      // ---- sweep
-      float dfacc = 0.f;
-#pragma nounroll
-      for (int s = len - 1; s >= 0; --s) {
-        const f4_t q4 = *(const f4_t *)&sm.q[s][p.row];
-        const float dyj = sm.dy[s][p.col], f = sm.f[s], gm = 1.f - f;
-        const f4_t z = ((const f4_t *)sm.D[s])[tid];
-        f4_t hp, G, dS;
-        float dfl = 0.f;
-#pragma unroll
-        for (int m = 0; m < 4; ++m) hp[m] = sm.H[s][sw<V>(p.row + m, p.col)];
-#pragma unroll
-        for (int m = 0; m < 4; ++m) {
-          G[m] = fmaf(q4[m], dyj, carry[m]);
-          dfl = fmaf(G[m], hp[m] - z[m], dfl);
-          dS[m] = gm * G[m] * fmaf(-z[m], z[m], 1.f);
+      float dvsum[NV], dfsum = 0.f;  // (the parts in turn)
+      for (int i = 0; i < TURNS; ++i) {
+        turn(i);
+        if constexpr (SEQ) {
+          load(t0, len);
+          carry = *slot(ws.nsub);
+          if (sub == 0) hck = checkpoint();
         }
-        const f4_t da = quad_transpose(dS, p.odd, p.high);
-        *(f4_t *)&sm.D[s][a_off] = da;
-        const f4_t df4 = __builtin_amdgcn_mfma_f32_16x16x4f32(dfl, 1.f, f4_t{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
-        const f4_t d = contract<Q>(da, wt);
-#pragma unroll
-        for (int m = 0; m < 4; ++m) carry[m] = fmaf(f, G[m], d[m]);
-        // every column of df4 is the same: lane (j, i) holds the sums of 4 of the 16 rows i' = 4 i + r
-        dfacc = (p.lane & 15) == s ? (df4[0] + df4[1]) + (df4[2] + df4[3]) : dfacc;
-        if (a.clip > 0.f)
-#pragma unroll
-          for (int m = 0; m < 4; ++m) carry[m] = __builtin_amdgcn_fmed3f(carry[m], -a.clip, a.clip);
-      }
-      sm.df[p.wave * 4 + (p.lane >> 4)][p.lane & 15] = dfacc;  // lane (s, i): its rows' sum of step s
-      __syncthreads();
-      // ---- finish: dW, 4 rows of one step per product
-#pragma unroll
-      for (int i = 0; i < NTW; ++i) {
-        const int tile = SPLIT > 1 ? 0 : p.wave * NTW + i, ci = tile / CT, cj = tile % CT;
-        const int kr = p.lane >> 4, c = p.lane & 15;
-        // (summed per stash first: one running sum over all steps would lose two bits)
-        f4_t acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = acc0;
-        const int r0 = SPLIT > 1 ? p.wave * Q::RW : 0;
-        constexpr int NR = SPLIT > 1 ? Q::RW : ROWS;
+        store();
+        f4_t h = sub > 0 ? *slot(sub - 1) : hck, ha;
+        arrived(h);
+        __syncthreads();
+        // the next stash's vectors travel during this one
+        if constexpr (!SEQ) {
+          if (sub > 0) load(t0 - TB, TB);
+          else if (ck > 0 && C <= TB) load(ck0 - C, C);
+        }
+        // ---- recompute
+#pragma nounroll
         for (int s = 0; s < len; ++s) {
+          const f4_t z = step(h, s, ha);
+          *(f4_t *)&sm.H[s][a_off] = ha;
+          ((f4_t *)sm.D[s])[tid] = z;  // (only this lane reads it again)
+        }
+        *(f4_t *)&sm.H[len][a_off] = quad_transpose(h, p.odd, p.high);
+        // ---- sweep
+        float dfacc = 0.f;
+#pragma nounroll
+        for (int s = len - 1; s >= 0; --s) {
+          const f4_t q4 = *(const f4_t *)&sm.q[s][p.row];
+          const float dyj = sm.dy[s][p.col], f = sm.f[s], gm = 1.f - f;
+          const f4_t z = ((const f4_t *)sm.D[s])[tid];
+          f4_t hp, G, dS;
+          float dfl = 0.f;
 #pragma unroll
-          for (int r = 0; r < NR; r += 8) {
-            const int ra = r0 + r + kr, rb = ra + 4;
-            acc0 = __builtin_amdgcn_mfma_f32_16x16x4f32(sm.H[s][sw<V>(ra, 16 * ci + c)],
-                                                        sm.D[s][sw<V>(ra, 16 * cj + c)], acc0, 0, 0, 0);
-            if (r + 4 < NR)
-              acc1 = __builtin_amdgcn_mfma_f32_16x16x4f32(sm.H[s][sw<V>(rb, 16 * ci + c)],
-                                                          sm.D[s][sw<V>(rb, 16 * cj + c)], acc1, 0, 0, 0);
+          for (int m = 0; m < 4; ++m) hp[m] = sm.H[s][sw<V>(p.row + m, p.col)];
+#pragma unroll
+          for (int m = 0; m < 4; ++m) {
+            G[m] = fmaf(q4[m], dyj, carry[m]);
+            dfl = fmaf(G[m], hp[m] - z[m], dfl);
+            dS[m] = gm * G[m] * fmaf(-z[m], z[m], 1.f);
+          }
+          const f4_t da = quad_transpose(dS, p.odd, p.high);
+          *(f4_t *)&sm.D[s][a_off] = da;
+          const f4_t df4 = __builtin_amdgcn_mfma_f32_16x16x4f32(dfl, 1.f, f4_t{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+          const f4_t d = contract<Q>(da, wt);
+#pragma unroll
+          for (int m = 0; m < 4; ++m) carry[m] = fmaf(f, G[m], d[m]);
+          // every column of df4 is the same: lane (j, i) holds the sums of 4 of the 16 rows i' = 4 i + r
+          dfacc = (p.lane & 15) == s ? (df4[0] + df4[1]) + (df4[2] + df4[3]) : dfacc;
+          if (a.clip > 0.f)
+#pragma unroll
+            for (int m = 0; m < 4; ++m) carry[m] = __builtin_amdgcn_fmed3f(carry[m], -a.clip, a.clip);
+        }
+        sm.df[p.wave * 4 + (p.lane >> 4)][p.lane & 15] = dfacc;  // lane (s, i): its rows' sum of step s
+        __syncthreads();
+        // ---- finish: dW, 4 rows of one step per product
+#pragma unroll
+        for (int i = 0; i < NTW; ++i) {
+          const int tile = SPLIT > 1 ? 0 : p.wave * NTW + i, ci = tile / CT, cj = tile % CT;
+          const int kr = p.lane >> 4, c = p.lane & 15;
+          // (summed per stash first: one running sum over all steps would lose two bits)
+          f4_t acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = acc0;
+          const int r0 = SPLIT > 1 ? p.wave * Q::RW : 0;
+          constexpr int NR = SPLIT > 1 ? Q::RW : ROWS;
+          for (int s = 0; s < len; ++s) {
+#pragma unroll
+            for (int r = 0; r < NR; r += 8) {
+              const int ra = r0 + r + kr, rb = ra + 4;
+              acc0 = __builtin_amdgcn_mfma_f32_16x16x4f32(sm.H[s][sw<V>(ra, 16 * ci + c)],
+                                                          sm.D[s][sw<V>(ra, 16 * cj + c)], acc0, 0, 0, 0);
+              if (r + 4 < NR)
+                acc1 = __builtin_amdgcn_mfma_f32_16x16x4f32(sm.H[s][sw<V>(rb, 16 * ci + c)],
+                                                            sm.D[s][sw<V>(rb, 16 * cj + c)], acc1, 0, 0, 0);
+            }
+          }
+          dW[i] += acc0 + acc1;
+        }
+        // ---- finish: dq_s[i] = H_s dy_s, dk_s[i] = dS_s v_s, one (step, row) per thread
+        for (int idx = tid; idx < len * ROWS; idx += THREADS) {
+          const int s = idx / ROWS, i = idx % ROWS;
+          f4_t q4 = {0.f, 0.f, 0.f, 0.f}, k4 = q4;
+#pragma unroll 4
+          for (int c4 = 0; c4 < V / 4; ++c4) {
+            const int c = 4 * (c4 ^ ((i >> 2) & 3));  // (rows that share a swizzle start on other banks)
+            q4 += *(const f4_t *)&sm.H[s + 1][sw<V>(i, c)] * *(const f4_t *)&sm.dy[s][c];
+            k4 += *(const f4_t *)&sm.D[s][sw<V>(i, c)] * *(const f4_t *)&sm.v[s][c];
+          }
+          const float dq = (q4[0] + q4[1]) + (q4[2] + q4[3]), dk = (k4[0] + k4[1]) + (k4[2] + k4[3]);
+          if (ws.dqh) {
+            const size_t o = (((size_t)b * T + t0 + s) * N + n) * K + row_base + i;
+            ws.dqh[o] = dq;
+            ws.dkh[o] = dk;
+          } else {
+            const size_t o = qk0 + (size_t)(t0 + s) * qk_step + i + (SEQ ? row_base : 0);
+            ((IO *)a.dq)[o] = from_f32<IO>(dq);
+            ((IO *)a.dk)[o] = from_f32<IO>(dk);
           }
         }
-        dW[i] += acc0 + acc1;
-      }
-      // ---- finish: dq_s[i] = H_s dy_s, dk_s[i] = dS_s v_s, one (step, row) per thread
-      for (int idx = tid; idx < len * ROWS; idx += THREADS) {
-        const int s = idx / ROWS, i = idx % ROWS;
-        f4_t q4 = {0.f, 0.f, 0.f, 0.f}, k4 = q4;
-#pragma unroll 4
-        for (int c4 = 0; c4 < V / 4; ++c4) {
-          const int c = 4 * (c4 ^ ((i >> 2) & 3));  // (rows that share a swizzle start on other banks)
-          q4 += *(const f4_t *)&sm.H[s + 1][sw<V>(i, c)] * *(const f4_t *)&sm.dy[s][c];
-          k4 += *(const f4_t *)&sm.D[s][sw<V>(i, c)] * *(const f4_t *)&sm.v[s][c];
-        }
-        const float dq = (q4[0] + q4[1]) + (q4[2] + q4[3]), dk = (k4[0] + k4[1]) + (k4[2] + k4[3]);
-        if (ws.dqh) {
-          const size_t o = (((size_t)b * T + t0 + s) * N + n) * K + row_base + i;
-          ws.dqh[o] = dq;
-          ws.dkh[o] = dk;
-        } else {
-          const size_t o = qk0 + (size_t)(t0 + s) * qk_step + i;
-          ((IO *)a.dq)[o] = from_f32<IO>(dq);
-          ((IO *)a.dk)[o] = from_f32<IO>(dk);
-        }
-      }
-      // ---- finish: dv_s[j] = sum over the workgroup's rows of dS[i][j] k_i, one (step, column)
-      for (int idx = tid; idx < len * V; idx += THREADS) {
-        const int s = idx / V, j = idx % V;
-        float acc = 0.f;
+        // ---- finish: dv_s[j] = sum over the workgroup's rows of dS[i][j] k_i, one (step, column)
+        const bool last_part = Q::P == 1 || (SEQ && part == Q::P - 1);
+        auto finish_dv = [&](int idx, float &sum) __attribute__((always_inline)) {
+          const int s = idx / V, j = idx % V;
+          float acc = 0.f;
 #pragma unroll 8
-        for (int i = 0; i < ROWS; ++i) acc = fmaf(sm.D[s][sw<V>(i, j)], sm.k[s][i], acc);
-        const size_t o = v0 + (size_t)(t0 + s) * v_step + j;
-        if constexpr (Q::P == 1) {
-          if (a.w_r) acc = fmaf(to_f32<IO>(((const IO *)a.w_r)[n * V + j]), sm.dy[s][j], acc);
-          ((IO *)a.dv)[o] = from_f32<IO>(acc);
-        } else {
-          ws.dvp[(size_t)part * a.B * T * v_step + o] = acc;
-        }
-      }
-      if (tid < len) {
-        float acc = 0.f;
+          for (int r = 0; r < ROWS; ++r) acc = fmaf(sm.D[s][sw<V>(r, j)], sm.k[s][r], acc);
+          const size_t o = v0 + (size_t)(t0 + s) * v_step + j;
+          if constexpr (SEQ) acc = sum = part ? sum + acc : acc;
+          if (last_part) {
+            if (a.w_r) acc = fmaf(to_f32<IO>(((const IO *)a.w_r)[n * V + j]), sm.dy[s][j], acc);
+            ((IO *)a.dv)[o] = from_f32<IO>(acc);
+          } else if constexpr (!SEQ) {
+            ws.dvp[(size_t)part * a.B * T * v_step + o] = acc;
+          }
+        };
+        if constexpr (SEQ) {
 #pragma unroll
-        for (int i = 0; i < NW * 4; ++i) acc += sm.df[i][tid];
-        const size_t o = f0 + (size_t)(t0 + tid) * N;
-        if constexpr (Q::P == 1) a.df[o] = acc;
-        else ws.dfp[(size_t)part * a.B * T * N + o] = acc;
+          for (int m = 0; m < NV; ++m)
+            if (tid + m * THREADS < len * V) finish_dv(tid + m * THREADS, dvsum[m]);
+        } else {
+          for (int idx = tid; idx < len * V; idx += THREADS) finish_dv(idx, dvsum[0]);
+        }
+        if (tid < len) {
+          float acc = 0.f;
+#pragma unroll
+          for (int r = 0; r < NW * 4; ++r) acc += sm.df[r][tid];
+          const size_t o = f0 + (size_t)(t0 + tid) * N;
+          if constexpr (SEQ) acc = dfsum = part ? dfsum + acc : acc;
+          if (last_part) a.df[o] = acc;
+          else if constexpr (!SEQ) ws.dfp[(size_t)part * a.B * T * N + o] = acc;
+        }
+        if constexpr (SEQ) *slot(ws.nsub) = carry;
+        __syncthreads();
       }
-      __syncthreads();
     }
   }
   if (a.dH0)
+    for (int i = 0; i < TURNS; ++i) {
+      turn(i);
+      if constexpr (SEQ) carry = *slot(ws.nsub);
 #pragma unroll
-    for (int m = 0; m < 4; ++m) a.dH0[st_off + m * V] = carry[m];
+      for (int m = 0; m < 4; ++m) a.dH0[st_off() + m * V] = carry[m];
+    }
   // dW of the workgroup: D layout of the 16x16 product, rows 4 (lane / 16) + r, column lane % 16
   float *dst = ws.dWp + (size_t)blockIdx.x * V * V;
   if constexpr (SPLIT > 1) {
@@ -669,23 +721,25 @@ struct QuadLayout {
   size_t sub, dvp, dfp, dWp, heads, total;
   int nsub;
 };
-QuadLayout quad_layout(int B, int T, int N, int Nqk, int K, int V, int C, int P, int threads) {
+// seq: the parts of a state in turn
+QuadLayout quad_layout(int B, int T, int N, int Nqk, int K, int V, int C, int P, int threads, bool seq) {
   QuadLayout l;
   const size_t units = (size_t)B * N;
+  const bool side = P > 1 && !seq;
   l.nsub = (C - 1) / TB;
-  l.sub = align256(units * P * l.nsub * threads * 16);
-  l.dvp = P > 1 ? align256((size_t)P * units * T * V * 4) : 0;
-  l.dfp = P > 1 ? align256((size_t)P * units * T * 4) : 0;
-  l.dWp = align256(units * P * V * V * 4);
+  l.sub = align256(units * P * (l.nsub + (seq ? 1 : 0)) * threads * 16);
+  l.dvp = side ? align256((size_t)P * units * T * V * 4) : 0;
+  l.dfp = side ? align256((size_t)P * units * T * 4) : 0;
+  l.dWp = align256(units * (seq ? 1 : P) * V * V * 4);
   l.heads = Nqk != N ? align256(units * T * K * 4) : 0;
   l.total = l.sub + l.dvp + l.dfp + l.dWp + 2 * l.heads;
   return l;
 }
 
-template <typename IO, typename Q>
-hipError_t launch_bwd(const BwdArgs &a, hipStream_t s) {
+template <typename IO, typename Q, bool SEQ>
+hipError_t launch_bwd_as(const BwdArgs &a, const QuadLayout &l, hipStream_t s) {
+  constexpr bool side = Q::P > 1 && !SEQ;
   const int units = a.B * a.N;
-  const QuadLayout l = quad_layout(a.B, a.T, a.N, a.Nqk, a.K, a.V, a.C, Q::P, Q::THREADS);
   char *p = a.ws;
   QuadBwdWs ws;
   ws.nsub = l.nsub;
@@ -697,12 +751,12 @@ hipError_t launch_bwd(const BwdArgs &a, hipStream_t s) {
   ws.dkh = l.heads ? (float *)p : nullptr;
   hipError_t e;
   if (units > 0) {
-    auto kernel = quad_bwd_kernel<IO, Q>;
+    auto kernel = quad_bwd_kernel<IO, Q, SEQ>;
     if ((e = set_max_lds_once(kernel, (int)sizeof(BwdLds<Q>))) != hipSuccess) return e;
-    hipLaunchKernelGGL(kernel, dim3(units * Q::P), dim3(Q::THREADS), sizeof(BwdLds<Q>), s, a, ws);
+    hipLaunchKernelGGL(kernel, dim3(SEQ ? units : units * Q::P), dim3(Q::THREADS), sizeof(BwdLds<Q>), s, a, ws);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     const size_t steps = (size_t)units * a.T;
-    if (Q::P > 1) {
+    if (side) {
       e = parts_sum<IO>(ws.dvp, (IO *)a.dv, steps * a.V, Q::P, (const IO *)a.w_r, (const IO *)a.dy, a.N * a.V, s);
       if (e == hipSuccess)
         e = parts_sum<float>(ws.dfp, a.df, steps, Q::P, nullptr, nullptr, 1, s);
@@ -715,8 +769,17 @@ hipError_t launch_bwd(const BwdArgs &a, hipStream_t s) {
   }
   const size_t total = (size_t)a.N * a.V * a.V;
   hipLaunchKernelGGL(quad_dw_sum_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, ws.dWp, a.dW, a.B,
-                     a.N, Q::P, a.V * a.V);
+                     a.N, SEQ ? 1 : Q::P, a.V * a.V);
   return hipGetLastError();
+}
+template <typename IO, typename Q>
+hipError_t launch_bwd(const BwdArgs &a, hipStream_t s) {
+  auto layout = [&](bool seq) { return quad_layout(a.B, a.T, a.N, a.Nqk, a.K, a.V, a.C, Q::P, Q::THREADS, seq); };
+  const QuadLayout side = layout(false), turns = layout(true);
+  if (a.ws_bytes >= side.total) return launch_bwd_as<IO, Q, false>(a, side, s);
+  if constexpr (Q::P > 1)
+    if (a.ws_bytes >= turns.total) return launch_bwd_as<IO, Q, true>(a, turns, s);
+  return hipErrorInvalidValue;
 }
 
 #define M2RNN_QUAD_CASES(X) \
@@ -731,7 +794,7 @@ size_t quad_workspace_bytes(int B, int T, int N, int Nqk, int K, int V, int C, i
   if (K == K_ && V == V_) {                                                                        \
     using Q = Quad<K_, V_>;                                                                        \
     if (!bwd) return fwd_parts_bytes<Q>(B, T, N);                                                   \
-    return quad_layout(B, T, N, Nqk, K, V, C, Q::P, Q::THREADS).total;                              \
+    return quad_layout(B, T, N, Nqk, K, V, C, Q::P, Q::THREADS, false).total;                              \
   }
   M2RNN_QUAD_CASES(X)
 #undef X

@@ -34,3 +34,42 @@ def test_a_missing_workspace_is_never_written(K, V, units):
     assert [l["kernel"].split("<")[0] for l in null["launches"]] in (["half_fwd_kernel"], ["rowwave_fwd_kernel"])
     for l in full["launches"]:
         assert l["partial"] in (None, WS)
+
+
+def one_workgroup_per_state(desc, bwd):
+    """Scratch of the fp32 scan with one workgroup per state: W and its transpose in fp32, and
+    backward a chunk's states, a dW per state and, for shared heads, dq and dk of every head."""
+    a = lambda x: (x + 255) // 256 * 256
+    B, T, N, K, V = (desc[k] for k in "BTNKV")
+    C = desc.get("chunk") or mb.m2rnn_default_chunk(mb.make_desc(**desc))
+    n = 2 * a(N * V * V * 4)
+    if bwd:
+        heads = a(B * T * N * K * 4) if desc.get("Nqk", N) != N else 0
+        n += a(B * N * (C + 1) * K * V * 4) + a(B * N * V * V * 4) + 2 * heads
+        n += a(1024 * N * V * 4) + a(256 * 2 * N * 4)   # sums of the options' gradients
+    return n
+
+
+IN_TURN = [(K, V, io) for K, V in ((128, 16), (64, 32), (128, 32), (32, 64), (64, 64), (128, 64)) for io in (F32, BF16)]
+
+
+@pytest.mark.parametrize("K,V,io", IN_TURN)
+@pytest.mark.parametrize("B,T,N,chunk,Nqk", [(8, 4096, 16, 0, 16), (1, 65536, 32, 1, 32), (2, 100, 4, 256, 2), (3, 5000, 4, 17, 1)])
+def test_fp32_kernels_without_room_for_partial_sums(K, V, io, B, T, N, chunk, Nqk):
+    """The fp32 kernels of V <= 64 accept what one workgroup per state takes and then run the parts
+    of a state in turn; below that they refuse."""
+    desc = d(B, T, N, K, V, io, chunk=chunk, Nqk=Nqk)
+    for call in ("fwd", "bwd"):
+        bwd = int(call == "bwd")
+        if mb.m2rnn_route_string(mb.make_desc(**desc), bwd)[:4] not in ("gene", "quad"):
+            continue   # (bf16 io: matrix-core kernels)
+        least, full = one_workgroup_per_state(desc, bwd), ws_bytes(desc, bwd)
+        c = dict(call=call, desc=desc, ws=WS, ckpt=1, opts=1)
+        under, at, query = lr.launches([dict(c, ws_bytes=min(least, full) - 1), dict(c, ws_bytes=least), dict(c, ws_bytes=full)])
+        assert under["rc"] == 5 and not under["launches"]
+        assert at["rc"] == 0 and query["rc"] == 0
+        kern = [r["launches"][0] for r in (at, query)]
+        assert kern[1]["kernel"].startswith("quad_%s_kernel" % call)
+        if full > least:
+            assert kern[0]["kernel"] == kern[1]["kernel"].replace(", false>", ", true>")
+            assert kern[0]["grid"] == B * N and kern[1]["grid"] == B * N * (K * V // 1024)

@@ -59,3 +59,55 @@ def test_parts_in_turn_give_the_same_bits():
         torch.cuda.synchronize()
         outs.append((y, HT))
     assert torch.equal(outs[0][0], outs[1][0]) and torch.equal(outs[0][1], outs[1][1])
+
+
+TURNS = [(128, 16, 35, 0, 2), (64, 32, 37, 5, 4), (128, 32, 50, 33, 1), (32, 64, 16, 16, 2), (64, 64, 49, 17, 4),
+         (128, 64, 70, 256, 2), (128, 64, 1, 0, 4)]
+# (bf16 io: the shapes without a matrix-core backward)
+TURNS = [("f32",) + c for c in TURNS] + [("bf16",) + c for c in TURNS if c[:2] not in ((128, 16), (64, 64))]
+
+
+@pytest.mark.parametrize("io,K,V,T,chunk,Nqk", TURNS)
+def test_backward_parts_in_turn(io, K, V, T, chunk, Nqk):
+    """A workspace without room for the partial sums of a state's parts: the parts one after the other
+    against the side-by-side kernel and the oracle.  Only dW is added in another order."""
+    import torch
+    from paper_2603_14360_amd import binding as mb
+    B, N = 2, 4
+    desc = mb.make_desc(B, T, N, K, V, mb.M2RNN_F32 if io == "f32" else mb.M2RNN_BF16, Nqk=Nqk, chunk=chunk)
+    print("case in turn", io, K, V, T, chunk, Nqk, flush=True)
+    C = chunk or mb.m2rnn_default_chunk(desc)
+    full = mb.m2rnn_workspace_bytes(desc, 1)
+    al = lambda x: (x + 255) // 256 * 256
+    inp = make_inputs(Workload("t", B, T, N, K, V, io, 9 + K + T, K ** -0.5, 1.0, use_H0=True, use_dHT=True, Nqk=Nqk))
+    dev = gu.to_device(inp, io)
+    dt = torch.float32 if io == "f32" else torch.bfloat16
+    w_r = torch.linspace(-1, 1, N * V, device="cuda").reshape(N, V).to(dt)
+    scan = mb.Scan(B, T, N, K, V, io, Nqk=Nqk, chunk=chunk)
+    args = [dev[n] for n in ("q", "k", "v", "f", "W", "H0")]
+    scan.fwd(*args, w_r=w_r)
+    # the least: the layout of one workgroup per state, and what sits behind it
+    least = 2 * al(N * V * V * 4) + al(B * N * (C + 1) * K * V * 4) + al(B * N * V * V * 4)
+    least += (2 * al(B * T * N * K * 4) if Nqk != N else 0) + al(1024 * N * V * 4) + al(256 * 2 * N * 4)
+    least = min(least, full - 256)
+    outs = []
+    for n in (full, least):
+        new = lambda *s, dtype=torch.float32: torch.full(s, float("nan"), dtype=dtype, device="cuda")
+        g = [new(B, T, Nqk, K, dtype=dt), new(B, T, Nqk, K, dtype=dt), new(B, T, N, V, dtype=dt), new(B, T, N),
+             new(N, V, V), new(B, N, K, V)]
+        dw_r = new(N, V)
+        ws = torch.full((n + 4096,), 0xFF, dtype=torch.uint8, device="cuda")   # (a guard behind the workspace)
+        rc = mb.m2rnn_bwd_opt(desc, mb.make_opts(w_r, dw_r, 0.7), *args, scan.ckpt, dev["dy"], dev["dHT"], *g, ws[:n],
+                              stream=torch.cuda.current_stream().cuda_stream, check=False)
+        torch.cuda.synchronize()
+        if rc != 0:
+            assert rc == 5 and n == full - 256   # no less than the query is accepted here: nothing to compare
+            break
+        assert (ws[n:] == 0xFF).all()
+        outs.append(g + [dw_r])
+    ref = gu.run_oracle(dict(inp, w_r=w_r.double().cpu().numpy()), grad_clip=0.7)
+    for g in outs:
+        got = {name: gu.to_np(x) for name, x in zip(gu.GRAD_NAMES + ("dw_r",), g)}
+        gu.compare(got, {n: ref[n] for n in got}, gu.TOL[io], label="in turn")
+    for name, x, y in zip(gu.GRAD_NAMES, *[g[:6] for g in (outs[0], outs[-1])]):
+        assert name == "dW" or torch.equal(x, y), name
