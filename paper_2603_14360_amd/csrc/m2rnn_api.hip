@@ -114,9 +114,9 @@ struct BwdWsLayout {
 };
 BwdWsLayout bwd_ws(const m2rnn_desc *d, int C, bool own_ckpt, bool least) {
   BwdWsLayout w;
-  const size_t b = least ? bwd_least_ws(d, C) : family_ws(d, C, 1);
-  const size_t f = !own_ckpt ? 0 : least ? fwd_least_ws(d, C) : family_ws(d, C, 0);  // pass 1 borrows `main`
-  w.main = align256(b > f ? b : f);
+  // (the pass that recomputes checkpoints borrows `main`: it writes no y and so has no partial sums;
+  // the copies of W that the V = 128 kernels take lie at the head of the backward's own layout)
+  w.main = align256(least ? bwd_least_ws(d, C) : family_ws(d, C, 1));
   w.ckpt = own_ckpt ? align256(ckpt_bytes(d, C)) : 0;
   w.dwr = residual_dw_r_scratch_bytes(d->N, d->V);
   w.gate = gate_scratch_bytes(d->N);

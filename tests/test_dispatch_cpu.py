@@ -73,3 +73,22 @@ def test_fp32_kernels_without_room_for_partial_sums(K, V, io, B, T, N, chunk, Nq
         if full > least:
             assert kern[0]["kernel"] == kern[1]["kernel"].replace(", false>", ", true>")
             assert kern[0]["grid"] == B * N and kern[1]["grid"] == B * N * (K * V // 1024)
+
+
+SHAPES = [(64, 64, 84), (64, 64, 4), (128, 128, 8), (32, 32, 8), (16, 16, 3), (64, 16, 84), (64, 32, 8), (32, 16, 8),
+          (128, 32, 4), (64, 128, 4)]
+
+
+@pytest.mark.parametrize("io", [BF16, F32])
+@pytest.mark.parametrize("K,V,N", SHAPES)
+@pytest.mark.parametrize("B,T", [(4, 777), (1, 512)])
+def test_backward_without_checkpoints_needs_room_for_them_and_no_more(K, V, N, B, T, io):
+    """The pass that recomputes checkpoints writes no y: it adds the checkpoints to what the backward
+    takes with the forward's, and nothing for partial sums of y."""
+    desc = d(B, T, N, K, V, io)
+    ck = (mb.m2rnn_ckpt_bytes(mb.make_desc(**desc)) + 255) // 256 * 256
+    need = ws_bytes(desc, 2)
+    assert need == ws_bytes(desc, 1) + ck
+    (got,) = lr.launches([dict(call="bwd", desc=desc, ws=WS, ws_bytes=need)])
+    assert got["rc"] == 0
+    assert not any("y_parts_sum" in l["kernel"] for l in got["launches"])
