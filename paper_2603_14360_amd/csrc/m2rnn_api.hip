@@ -279,6 +279,8 @@ m2rnn_status m2rnn_fwd_static(const m2rnn_desc *desc, const m2rnn_opts *opts, co
     need = 256;
   if (need > (size_t)M2RNN_STATIC_SCRATCH_BYTES) return M2RNN_ERR_WORKSPACE;
   void *scratch_ptr = nullptr;
+  // (a forward that can do without scratch gets none, also where it could split further with some:
+  // such calls share nothing)
   if (need > 0 && desc->B > 0 && desc->T > 0) {
     scratch_ptr = static_scratch_of_current_device();
     if (!scratch_ptr) return M2RNN_ERR_HIP;

@@ -341,6 +341,13 @@ hipError_t launch(const FwdArgs &a, hipStream_t s) {
 //   32 x 32, with checkpoints: 16 states, T 333 69 / 74 / 85;  128, T 2048 458 / 431 / 499;
 //   512, T 1024 408 / 355 / 336
 //   64 x 16, T 777: 84 states 131 / 146 / 119 / 137;  336 252 / 233 / 184 / 216;  504 273 / 246 / 229 / 217
+namespace {
+// waves on the fullest SIMD
+long long half_load(int K, int V, int units, int rb) {
+  const long long groups = (long long)units * (K / (8 * rb));
+  return ((groups + 255) / 256 * rb * (V / 16) + 3) / 4;
+}
+}  // namespace
 int half_pick_rb(int K, int V, int units, size_t part_bytes, size_t avail) {
   int best = 0;
   long long best_load = 0;
@@ -348,8 +355,7 @@ int half_pick_rb(int K, int V, int units, size_t part_bytes, size_t avail) {
   auto consider = [&](int rb) {  // (in increasing rb)
     const int P = K / (8 * rb);
     if (P > 1 && (size_t)P * part_bytes > avail) return;
-    const long long groups = (long long)units * P;
-    const long long load = ((groups + 255) / 256 * rb * (V / 16) + 3) / 4;
+    const long long groups = (long long)units * P, load = half_load(K, V, units, rb);
     if (!best || load < best_load || (load == best_load && !best_fits))
       best = rb, best_load = load, best_fits = groups <= 256;
   };
@@ -365,9 +371,22 @@ int half_pick_rb(int K, int V, int units, size_t part_bytes, size_t avail) {
 // faster.  128 x 128 only while twice as many workgroups have a CU each: T = 2048 with checkpoints,
 // 16-row tile -> RB = 1: 8 states 933 -> 655 us, 16 states 947 -> 686, but 32 states 982 -> 1381
 // (RB = 2: 1037; the exchange traffic of sixteen waves meets in one LDS).
+// Shapes with V = 32 have a 16-row kernel whose waves the same number of states fills evenly (one or two
+// on every SIMD for each 256 of them); 8-row waves are half of one, and from six on a SIMD, where latency
+// no longer counts, the fullest SIMD's odd wave decides.  T = 512, us, 16-row kernel -> this one:
+//   64 x 32, row-wave: 200 states 219 -> 180, 257 302 -> 231, 384 310 -> 271, 400 306 -> 296 (load 7),
+//   450 308 -> 356 (8).  Without a workspace (one part per state): 200 217 -> 180, but 257 to 448 305 -> 350.
+//   32 x 32, tile: 512 193 -> 169, 513 241 -> 231 (5), 700 247 -> 269 (6), 900 327 -> 329 (8).  Without a
+//   workspace: 384 192 -> 171, but 513 to 640 241 -> 267.
+//   32 x 16, row-wave: 200 140 -> 86, 511 182 -> 98, 1023 179 -> 145, without a workspace the same.
+// (The choice does not look at the workspace: a call's bits do not depend on its room.)
 bool half_serves(int K, int V, int units) {
-  if (!half_pick_rb(K, V, units, 0, 0)) return false;
-  return K == 128 ? (long long)units * (K / 8) <= 256 : (long long)units * (K / 16) < 2048;
+  const int rb = half_pick_rb(K, V, units, 0, 0);
+  if (!rb) return false;
+  if (K == 128) return (long long)units * (K / 8) <= 256;
+  if ((long long)units * (K / 16) >= 2048) return false;
+  const long long load = half_load(K, V, units, rb), even = (long long)(K / 8) * (V / 16) / 4 * ((units + 255) / 256);
+  return V != 32 || load <= 5 || load < even;
 }
 
 hipError_t half_fwd(const FwdArgs &a, hipStream_t s) {

@@ -1,9 +1,11 @@
 // Matrix-core forward scan (Algorithm 1 of the paper; recurrence equations),
 // tiled variant: a 16-row block of one (b, n) state is spread over V/16 waves.  It serves
-// K = V = 128 with more states than the 8-row forward (m2rnn_half_fwd.hip) has CUs for; that
-// kernel is the faster one for every other tiled shape.
+// K = V = 128 with more states than the 8-row forward (m2rnn_half_fwd.hip) has CUs for, and
+// the state counts of 32 x 32 that fill the SIMDs with its waves and not with that kernel's
+// (half_serves); that kernel is the faster one otherwise.
 //
-// Per workgroup: one block of 16 rows of a state, all V columns, for all T steps.  A wavefront owns one 16 x 16 tile; lane l holds row l % 16 and
+// Per workgroup: RB row blocks (16 rows each) of one state, all V columns, for
+// all T steps.  A wavefront owns one 16 x 16 tile; lane l holds row l % 16 and
 // the four columns 4 (l / 16) + r of it.  The contraction is computed
 // transposed, (H W)^T = W^T H^T: W^T is the MFMA A operand (fragments stay in
 // registers) and the state tile is the B operand, whose register layout (lane =
@@ -29,8 +31,8 @@
 //      A = hi of the transposed tile (k = rows) and B = q placed in column
 //      (t mod 16) only.  The accumulator is kept for 16 steps, so column s of
 //      it collects c sum_i q_i H[i][j] of step s; nothing is read back per step.
-//      Every 16 steps 16 rows of the block's partial y are stored; y_parts_sum
-//      adds the blocks of a state.
+//      Every 16 steps the row blocks are summed through LDS and 16 rows of y
+//      are stored.
 // q, k, v, f for 16 steps at a time are staged through LDS; the next block's
 // global loads are in flight while the current block is computed.
 #include "m2rnn_kernels.hpp"
@@ -43,11 +45,12 @@ constexpr int TB = 16;  // steps per staging / readout block (= MFMA N)
 
 template <typename TL>
 struct FwdSmem {
-  alignas(16) u4_t Hx[2][TL::CT][64];              // (hi, lo) state fragments, one per tile and lane
+  alignas(16) u4_t Hx[2][TL::RB][TL::CT][64];      // (hi, lo) state fragments, one per tile and lane
   alignas(16) float kS[2][TB][TL::ROWS];           // c * k
   alignas(16) _Float16 qS[2][TB][TL::ROWS];
   alignas(16) float vS[2][TB][TL::V];
   alignas(16) float fS[2][TB][4];                  // f, c(1-f), unused, unused
+  alignas(16) f4_t yB[TL::RB][TL::CT][64];         // readout accumulators of one block
 };
 
 // (Second launch bound: at least two waves per SIMD, i.e. at most 256 registers.  With the
@@ -58,9 +61,8 @@ struct FwdSmem {
 template <typename TL, bool DO_Y>
 __global__ void __launch_bounds__(TL::THREADS, 2)
     mfma_fwd_kernel(FwdArgs a, float *__restrict__ ypart_ws) {
-  constexpr int K = TL::K, V = TL::V, CT = TL::CT, ROWS = TL::ROWS;
+  constexpr int K = TL::K, V = TL::V, RB = TL::RB, CT = TL::CT, ROWS = TL::ROWS;
   constexpr int THREADS = TL::THREADS;
-  static_assert(TL::RB == 1 && TL::P > 1 && CT > 1, "one row block per workgroup, summed by y_parts_sum");
   constexpr int NQ = (TB * ROWS + THREADS - 1) / THREADS;
   constexpr int NV = (TB * V + THREADS - 1) / THREADS;
 
@@ -72,9 +74,10 @@ __global__ void __launch_bounds__(TL::THREADS, 2)
   const int tid = threadIdx.x, lane = tid & 63;
   // wave-level indices as scalars: branches on them must be real (uniform) branches, because
   // a matrix-core instruction that is merely predicated off still executes
-  const int ct = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int rb = wave / CT, ct = wave - rb * CT;
   const int jl = lane & 15, ig = lane >> 4;
-  const int col0 = ct * 16;
+  const int col0 = ct * 16, rowb = rb * 16;
   const int row_base = part * ROWS;
 
   __shared__ FwdSmem<TL> sm;
@@ -104,8 +107,8 @@ __global__ void __launch_bounds__(TL::THREADS, 2)
     }
   }
 
-  // ---- state tile, scaled by c: row jl of the block, columns col0 + 4 ig + r
-  const size_t st_off = (size_t)unit * K * V + (size_t)(row_base + jl) * V + col0 + 4 * ig;
+  // ---- state tile, scaled by c: row rowb + jl, columns col0 + 4 ig + r
+  const size_t st_off = (size_t)unit * K * V + (size_t)(row_base + rowb + jl) * V + col0 + 4 * ig;
   float h[4];
   {
     const f4_t h0 = a.H0 ? *(const f4_t *)&a.H0[st_off] : f4_t{0.f, 0.f, 0.f, 0.f};
@@ -121,12 +124,12 @@ __global__ void __launch_bounds__(TL::THREADS, 2)
   u4_t own;
 #pragma unroll
   for (int r = 0; r < 4; ++r) own[r] = split_hi_lo(h[r]);
-  sm.Hx[0][ct][lane] = own;
+  sm.Hx[0][rb][ct][lane] = own;
   f4_t acc_own = mfma_k32(wf[0], __builtin_bit_cast(h8_t, own), zero4);
   // LDS byte offsets of the other tiles' fragments (exchange buffer 0)
   int hx_off[CT];
 #pragma unroll
-  for (int d = 0; d < CT; ++d) hx_off[d] = ((ct + d) % CT * 64 + lane) * 16;
+  for (int d = 0; d < CT; ++d) hx_off[d] = ((rb * CT + (ct + d) % CT) * 64 + lane) * 16;
   // identity operand of the transposing MFMA: B[k = 4 ig + r][n = jl] = (k == n)
   h4_t ident;
 #pragma unroll
@@ -200,6 +203,7 @@ __global__ void __launch_bounds__(TL::THREADS, 2)
   const int nblk = (T + TB - 1) / TB;
   const int nck = (T + a.C - 1) / a.C;
   int next_ck = 0, ck_idx = 0;
+  bf16_raw *__restrict__ yg = (bf16_raw *)a.y;
   const h4_t zero_h4 = {(_Float16)0.f, (_Float16)0.f, (_Float16)0.f, (_Float16)0.f};
 
   // Pieces of one step.  `s` is the step inside the 16-step block; the block loop calls
@@ -216,14 +220,14 @@ __global__ void __launch_bounds__(TL::THREADS, 2)
   auto ckpt_store = [&](int t) __attribute__((always_inline)) {
     if (a.ckpt && t == next_ck) {  // state before step t
       float *dst = a.ckpt + ((size_t)unit * nck + ck_idx) * K * V +
-                   (size_t)(row_base + jl) * V + col0 + 4 * ig;
+                   (size_t)(row_base + rowb + jl) * V + col0 + 4 * ig;
       *(f4_t *)dst = f4_t{h[0], h[1], h[2], h[3]} * kInvC;
       next_ck += a.C;
       ++ck_idx;
     }
   };
-  lchar *const hx = (lchar *)&sm.Hx[0][0][0];
-  constexpr int HXBUF = CT * 64 * 16;  // bytes of one exchange buffer
+  lchar *const hx = (lchar *)&sm.Hx[0][0][0][0];
+  constexpr int HXBUF = RB * CT * 64 * 16;  // bytes of one exchange buffer
   // L: the other tiles' fragments from exchange buffer `buf` and this step's vectors.
   //    Issued right after the barrier that completes the buffer, ahead of the previous
   //    step's readout, so that the readout runs while the fragments are on their way.
@@ -232,9 +236,9 @@ __global__ void __launch_bounds__(TL::THREADS, 2)
     for (int d = 1; d < CT; ++d) x.hf[d] = lds_ld<h8_t>(hx + hx_off[d], buf * HXBUF);
     x.f = sm.fS[sb][s][0];
     x.gp = sm.fS[sb][s][1];
-    x.kk = sm.kS[sb][s][jl];
+    x.kk = sm.kS[sb][s][rowb + jl];
     x.v4 = *(const f4_t *)&sm.vS[sb][s][col0 + 4 * ig];
-    if constexpr (DO_Y) x.qf = *(const h4_t *)&sm.qS[sb][s][4 * ig];
+    if constexpr (DO_Y) x.qf = *(const h4_t *)&sm.qS[sb][s][rowb + 4 * ig];
   };
   // R: the contraction (the own tile's product was started in the previous step's E)
   auto step_R = [&](StepRegs &x) __attribute__((always_inline)) {
@@ -260,24 +264,47 @@ __global__ void __launch_bounds__(TL::THREADS, 2)
   //    lanes (exact: products with 1 and 0).  Then A[m = j][k = i] = hi(H'[i][j]);
   //    B[k = i][n] = q_i for n == s, else 0: column s of yacc collects step s.
   //    (0 x NaN is NaN: a NaN that enters the state reaches the y of the earlier steps of its
-  //    16-step block here.  Column s kept by selects from a product with q in every column, as
-  //    the 8-row kernel does, holds it back but takes 2.7 % of a 4 x 8192, 8-head training
-  //    step, 10.88 -> 11.19 ms; transposed, with one select per step, 2.5 %.)
+  //    16-step block so.  V < 128 holds it back: q in every column, column s kept by selects.  At
+  //    V = 128 those take 2.7 % of a 4 x 8192, 8-head training step, 10.88 -> 11.19 ms; transposed,
+  //    with one select per step, 2.5 %.)
   auto step_Y = [&](const StepRegs &x, const uint32_t (&pk)[4], int s, f4_t &yacc)
       __attribute__((always_inline)) {
-    const h4_t qf = (jl == s) ? x.qf : zero_h4;
+    // (masked up here: behind the transposing product it takes 8 % of the kernel at V = 128)
+    const h4_t qf = V < 128 || jl == s ? x.qf : zero_h4;
     uint2 hv;
     hv.x = __builtin_amdgcn_perm(pk[1], pk[0], 0x05040100u);
     hv.y = __builtin_amdgcn_perm(pk[3], pk[2], 0x05040100u);
     const f4_t tr = mfma_k16(__builtin_bit_cast(h4_t, hv), ident, zero4);
     const h4_t ht = {(_Float16)tr[0], (_Float16)tr[1], (_Float16)tr[2], (_Float16)tr[3]};
-    yacc = mfma_k16(ht, qf, yacc);
+    if constexpr (V < 128) {
+      const f4_t yd = mfma_k16(ht, qf, zero4);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) yacc[r] = jl == s ? yd[r] : yacc[r];
+    } else {
+      yacc = mfma_k16(ht, qf, yacc);
+    }
   };
   auto y_store = [&](f4_t ys, int t0, int len) __attribute__((always_inline)) {
     // lane (ig, jl) holds columns col0 + 4 ig + r of step t0 + jl
     if (jl < len) {
       const size_t yoff = (((size_t)b * T + t0 + jl) * N + n) * V + col0 + 4 * ig;
-      *(f4_t *)&ypart_ws[(size_t)part * a.B * T * N * V + yoff] = ys;
+      if constexpr (TL::P == 1) {
+        ys *= kInvC;
+        if (a.w_r) {  // residual w_r (.) v_t of the y equation
+          const uint2 wv = *(const uint2 *)&((const bf16_raw *)a.w_r)[n * V + col0 + 4 * ig];
+          const uint2 vv = *(const uint2 *)&vg[yoff];
+          ys[0] = fmaf(bf16_to_f32(wv.x & 0xFFFFu), bf16_to_f32(vv.x & 0xFFFFu), ys[0]);
+          ys[1] = fmaf(bf16_to_f32(wv.x >> 16), bf16_to_f32(vv.x >> 16), ys[1]);
+          ys[2] = fmaf(bf16_to_f32(wv.y & 0xFFFFu), bf16_to_f32(vv.y & 0xFFFFu), ys[2]);
+          ys[3] = fmaf(bf16_to_f32(wv.y >> 16), bf16_to_f32(vv.y >> 16), ys[3]);
+        }
+        uint2 p2;
+        p2.x = (uint32_t)f32_to_bf16(ys[0]) | ((uint32_t)f32_to_bf16(ys[1]) << 16);
+        p2.y = (uint32_t)f32_to_bf16(ys[2]) | ((uint32_t)f32_to_bf16(ys[3]) << 16);
+        *(uint2 *)&yg[yoff] = p2;
+      } else {
+        *(f4_t *)&ypart_ws[(size_t)part * a.B * T * N * V + yoff] = ys;
+      }
     }
   };
 
@@ -327,7 +354,19 @@ __global__ void __launch_bounds__(TL::THREADS, 2)
         asm volatile("" : : "v"(rf));
       }
       settle(yacc);
-      if constexpr (DO_Y) y_store(yacc, t0, len);
+      if constexpr (DO_Y) {
+        // ---- block flush: sum the row blocks, store the block's rows of y
+        if constexpr (RB > 1) {
+          if (rb > 0) sm.yB[rb][ct][lane] = yacc;
+          lds_barrier();
+          if (rb == 0) {
+#pragma unroll
+            for (int r2 = 1; r2 < RB; ++r2) yacc += sm.yB[r2][ct][lane];
+          }
+          // (yB is written again only 16 steps, i.e. at least 16 barriers, later)
+        }
+        if (rb == 0) y_store(yacc, t0, len);
+      }
     }
   }
   if (a.HT) *(f4_t *)&a.HT[st_off] = f4_t{h[0], h[1], h[2], h[3]} * kInvC;
@@ -394,7 +433,7 @@ hipError_t launch_fwd(const FwdArgs &a, hipStream_t s) {
                        dim3(TL::THREADS), 0, s, a, ypart);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  if (a.write_y && a.T > 0) e = y_parts_sum(a, TL::P, s);
+  if (TL::P > 1 && a.write_y && a.T > 0) e = y_parts_sum(a, TL::P, s);
   return e;
 }
 
@@ -415,6 +454,7 @@ int mfma_pick_rb(int K, int V, int units) {
 hipError_t mfma_fwd(const FwdArgs &a, hipStream_t s) {
   if (half_serves(a.K, a.V, a.B * a.N)) return half_fwd(a, s);
   if (a.K == 128 && a.V == 128) return launch_fwd<Tile<128, 128, 1>>(a, s);
+  if (a.K == 32 && a.V == 32) return launch_fwd<Tile<32, 32, 2>>(a, s);
   return hipErrorInvalidValue;
 }
 

@@ -92,3 +92,26 @@ def test_backward_without_checkpoints_needs_room_for_them_and_no_more(K, V, N, B
     (got,) = lr.launches([dict(call="bwd", desc=desc, ws=WS, ws_bytes=need)])
     assert got["rc"] == 0
     assert not any("y_parts_sum" in l["kernel"] for l in got["launches"])
+
+
+# states around the lines of the forward's choice between the 8-row kernel and the 16-row ones
+CHOICE = [(32, 32, 640, "half"), (32, 32, 641, "mfma"), (32, 32, 768, "mfma"), (32, 32, 769, "half"), (32, 32, 896, "half"),
+          (32, 32, 897, "mfma"), (32, 32, 1023, "mfma"), (32, 32, 1024, "rowwave"), (64, 32, 448, "half"), (64, 32, 449, "rowwave"),
+          (64, 32, 511, "rowwave"), (64, 32, 512, "rowwave"), (32, 16, 1023, "half"), (32, 16, 1024, "rowwave"),
+          (64, 64, 511, "half"), (64, 64, 512, "rowwave"), (64, 16, 511, "half"), (64, 16, 512, "rowwave"),
+          (16, 16, 2047, "half"), (16, 16, 2048, "rowwave"), (128, 128, 16, "half"), (128, 128, 17, "mfma")]
+
+
+@pytest.mark.parametrize("K,V,units,kernel", CHOICE)
+def test_forward_kernel_choice(K, V, units, kernel):
+    """The kernel follows from the shape and the states alone; the workspace decides at most between
+    splits of the same kernel (whose bits are the same), and the query is what the choice needs."""
+    desc = d(units, 40, 1, K, V, BF16)
+    full = ws_bytes(desc, 0)
+    calls = [dict(call="fwd", desc=desc, ws=WS, ws_bytes=n) for n in {full, 0, full + 4096, 1 << 40}]
+    for r in lr.launches(calls):
+        assert r["rc"] in (0, 5)
+        if r["rc"] == 0:
+            assert r["launches"][0]["kernel"].startswith(kernel + "_fwd_kernel")
+    (r,) = lr.launches([dict(call="fwd", desc=desc, ws=WS, ws_bytes=full)])
+    assert r["rc"] == 0

@@ -10,8 +10,8 @@ import gpu_util as gu
 pytestmark = pytest.mark.gpu
 
 # state counts at which the launch rule turns from one split to the next
-SHAPES = [(64, 64, (1, 32, 33, 65, 130)), (128, 128, (1, 16, 17)), (32, 32, (1, 65, 300)),
-          (16, 16, (1, 130)), (64, 16, (1, 70, 140)), (64, 32, (1, 40, 70, 150)), (32, 16, (3, 100, 200))]
+SHAPES = [(64, 64, (1, 32, 33, 65, 130)), (128, 128, (1, 16, 17)), (32, 32, (1, 65, 300, 641, 769)),
+          (16, 16, (1, 130)), (64, 16, (1, 70, 140)), (64, 32, (1, 40, 70, 150, 257, 449)), (32, 16, (3, 100, 200))]
 CASES = [(K, V, n) for K, V, counts in SHAPES for n in counts]
 
 
