@@ -16,6 +16,8 @@
 
 #include <hip/hip_bf16.h>
 
+#include <algorithm>
+
 namespace m2rnn {
 namespace {
 
@@ -556,6 +558,12 @@ inline int conv_rows(int B, int T) {
   const long long rows = (long long)B * ((T + 31) / 32);
   return (int)(rows < kConvRows ? (rows < 1 ? 1 : rows) : kConvRows);
 }
+// Workgroup rows of a backward launch, beyond those that fill the chip: with many sequences of a few steps
+// a row has less to read than the partial sums it writes and the sum behind reads again.
+// bf16, us, without the limit -> with it (the kernel with eight channels per lane before): 4096 x 1 x 1024
+// 33.3 -> 20.9 (22.6), 8192 x 1 x 1024 58.5 -> 32.1 (33.7), 4096 x 4 x 512 25.5 -> 19.7 (23.7);
+// 512 rows instead of 256: 24.8, 35.3, 19.7.
+inline int conv_bwd_most_rows(int gx) { return std::max(256, (1024 + gx - 1) / gx); }
 // Rows of the norm's scratch (callers size their workspace by this figure), and workgroups of a
 // launch = rows in use: what is resident with W waves per workgroup, four on each SIMD.
 inline int norm_waves(size_t tokens) {
@@ -596,7 +604,8 @@ template <typename IO>
 static hipError_t conv_bwd_t(int B, int T, int C, const void *x, const void *w, const void *bias,
                              const void *dout, void *dx, float *dw, float *dbias, float *part,
                              hipStream_t s) {
-  const ConvPlan p = conv_plan(B, T, C, conv_rows(B, T));
+  ConvPlan p = conv_plan(B, T, C, conv_rows(B, T));
+  p.rg = std::min(p.rg, conv_bwd_most_rows(p.gx));
   const bool any = (size_t)B * T > 0;
   if (any) {
     hipLaunchKernelGGL((conv_silu_bwd_kernel<IO>), dim3((unsigned)(p.gx * p.rg)), dim3(kThreads), 0, s,

@@ -32,6 +32,13 @@ def test_conv_edges(io, B, T, C, bias):
     conv_case(io, B, T, C, bias)
 
 
+# many sequences of a few steps: more segments than workgroup rows, several to a walker
+@pytest.mark.parametrize("io", ["f32", "bf16"])
+@pytest.mark.parametrize("B,T,C", [(4200, 1, 1024), (2300, 3, 1016), (4096, 4, 520)])
+def test_conv_many_short_sequences(io, B, T, C):
+    conv_case(io, B, T, C, True)
+
+
 # the longer segments, taken by launches that fill the chip: 16, 32 and 64 steps, ragged ends
 @pytest.mark.parametrize("B,T,C,bias", [(3, 1399, 4000, True), (3, 2799, 4000, False), (17, 3901, 1024, True)])
 def test_conv_long_segments(B, T, C, bias):
