@@ -679,17 +679,31 @@ hipError_t parts_sum(const float *part, IO *out, size_t total, int P, const IO *
   return hipGetLastError();
 }
 
-// dW[n] = sum over b, then over the workgroups of a state, in increasing order
-__global__ void quad_dw_sum_kernel(const float *__restrict__ dWp, float *__restrict__ dW, int B, int N, int P, int VV) {
-  const size_t total = (size_t)N * VV;
-  for (size_t e = blockIdx.x * (size_t)blockDim.x + threadIdx.x; e < total; e += (size_t)gridDim.x * blockDim.x) {
-    const int n = e / VV, r = e % VV;
-    float s = 0.f;
-    for (int b = 0; b < B; ++b)
-      for (int p = 0; p < P; ++p) s += dWp[(((size_t)b * N + n) * P + p) * VV + r];
-    dW[e] = s;
+// dW[n] = sum over the batch and the workgroups of a state: a workgroup adds 64 elements of one head,
+// its W waves the rows (b, p) w, w + W, ... with four loads in flight, and the waves' sums in increasing
+// order.  W grows with the rows (quad_dw_waves): one chain over all of them took most of a launch of
+// many short sequences.
+__global__ void __launch_bounds__(1024)
+    quad_dw_sum_kernel(const float *__restrict__ dWp, float *__restrict__ dW, int N, int P, int VV, int R) {
+  __shared__ float red[16][64];
+  const int W = blockDim.x >> 6, w = threadIdx.x >> 6, cl = threadIdx.x & 63;
+  const int n = blockIdx.x / (VV / 64), e = (blockIdx.x % (VV / 64)) * 64 + cl;
+  auto row = [&](int r) { return dWp[(((size_t)(r / P) * N + n) * P + r % P) * VV + e]; };
+  float s = 0.f;
+  int r = w;
+  for (; r + 3 * W < R; r += 4 * W) {
+    const float x0 = row(r), x1 = row(r + W), x2 = row(r + 2 * W), x3 = row(r + 3 * W);
+    s = (((s + x0) + x1) + x2) + x3;
+  }
+  for (; r < R; r += W) s += row(r);
+  red[w][cl] = s;
+  __syncthreads();
+  if (w == 0) {
+    for (int i = 1; i < W; ++i) s += red[i][cl];
+    dW[(size_t)n * VV + e] = s;
   }
 }
+int quad_dw_waves(int rows) { return rows <= 16 ? 1 : rows <= 64 ? 4 : 16; }
 
 template <typename Q>
 size_t fwd_parts_bytes(int B, int T, int N) {
@@ -767,9 +781,9 @@ hipError_t launch_bwd_as(const BwdArgs &a, const QuadLayout &l, hipStream_t s) {
       if ((e = generic_head_group_sum(a, ws.dkh, a.dk, s)) != hipSuccess) return e;
     }
   }
-  const size_t total = (size_t)a.N * a.V * a.V;
-  hipLaunchKernelGGL(quad_dw_sum_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, ws.dWp, a.dW, a.B,
-                     a.N, SEQ ? 1 : Q::P, a.V * a.V);
+  const int VV = a.V * a.V, P = SEQ ? 1 : Q::P, rows = a.B * P;
+  hipLaunchKernelGGL(quad_dw_sum_kernel, dim3((unsigned)(a.N * (VV / 64))), dim3(64 * quad_dw_waves(rows)), 0, s,
+                     ws.dWp, a.dW, a.N, P, VV, rows);
   return hipGetLastError();
 }
 template <typename IO, typename Q>
