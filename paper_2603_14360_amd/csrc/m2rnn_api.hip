@@ -55,7 +55,7 @@ Family fwd_family_of(const m2rnn_desc *d) {
 hipError_t run_fwd(const m2rnn_desc *d, const FwdArgs &a, hipStream_t s) {
   switch (fwd_family_of(d)) {
     case kDecode: return decode_fwd(a, s);
-    case kRowWave: return half_serves(a.K, a.V, a.B * a.N) ? half_fwd(a, s) : rowwave_fwd(a, s);
+    case kRowWave: return half_serves(a.K, a.V, a.B * a.N, a.T) ? half_fwd(a, s) : rowwave_fwd(a, s);
     case kMfma: return mfma_fwd(a, s);
     default: return generic_fwd(a, s);
   }
@@ -86,7 +86,7 @@ size_t family_ws(const m2rnn_desc *d, int C, int bwd) {
   if (fam == kDecode) return 0;
   if (fam == kGeneric) return generic_workspace_bytes(d->B, d->T, d->N, d->Nqk, d->K, d->V, C, bwd);
   return bwd ? mfma_bwd_workspace_bytes(d->B, d->T, d->N, d->Nqk, d->K, d->V)
-             : fam == kRowWave && !half_serves(d->K, d->V, d->B * d->N)
+             : fam == kRowWave && !half_serves(d->K, d->V, d->B * d->N, d->T)
                    ? 0
                    : mfma_fwd_workspace_bytes(d->B, d->T, d->N, d->K, d->V);
 }

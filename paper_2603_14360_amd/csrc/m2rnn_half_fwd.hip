@@ -30,6 +30,8 @@
 #include "m2rnn_kernels.hpp"
 #include "m2rnn_mfma_common.hpp"
 
+#include <limits.h>
+
 namespace m2rnn {
 namespace {
 
@@ -220,14 +222,20 @@ __global__ void __launch_bounds__(HF::THREADS, 2) half_fwd_kernel(FwdArgs a, flo
     const size_t yoff = y_lane + t0 * row;
     if constexpr (HF::P == 1) {
       ys *= kInvC;
-      const float wr = a.w_r ? bf16_to_f32(((const bf16_raw *)a.w_r)[n * V + col0 + jl]) : 0.f;
+      if (a.w_r) {  // residual w_r (.) v_t of the y equation
+        const float wr = bf16_to_f32(((const bf16_raw *)a.w_r)[n * V + col0 + jl]);
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        if (4 * ig + r < len) {
-          // residual w_r (.) v_t of the y equation
-          if (a.w_r) ys[r] = fmaf(wr, bf16_to_f32(vg[yoff + r * row]), ys[r]);
-          yg[yoff + r * row] = f32_to_bf16(ys[r]);
-        }
+        for (int r = 0; r < 4; ++r)
+          if (4 * ig + r < len) ys[r] = fmaf(wr, bf16_to_f32(vg[yoff + r * row]), ys[r]);
+      }
+      bf16_raw *dst = yg + yoff;
+      if (len == TB) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) dst[r * row] = __builtin_bit_cast(bf16_raw, (__bf16)ys[r]);
+      } else {
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          if (4 * ig + r < len) dst[r * row] = __builtin_bit_cast(bf16_raw, (__bf16)ys[r]);
       }
     } else {
       float *dst = ypart_ws + (size_t)part * a.B * T * row + yoff;
@@ -334,7 +342,12 @@ hipError_t launch(const FwdArgs &a, hipStream_t s) {
 // dealt evenly over 256 CUs; a step takes as long as the waves of the fullest SIMD need for it).
 // Among equals the smallest workgroup that still gives every workgroup a CU (the row blocks of a
 // workgroup wait for each other), else the largest (fewer partial sums of y).  Only splits whose
-// partial sums fit `avail` bytes; 0 if there is none.  Measured (us, forward, no checkpoints
+// partial sums fit `avail` bytes; 0 if there is none.  Parts of a state cost a second launch
+// for the sum of their y, some 2.5 us, and save 0.01 us a step, 0.05 more for every wave that the fullest
+// SIMD has less: where one workgroup can hold a state, they are taken from the T on that repays the launch.
+// One part / parts, us: 64 x 32, 8 states, T = 4 8.2 / 11.2, 17 10.3 / 11.1, 24 13.4 / 11.1; 32 x 32, 8 states,
+// T = 32 11.3 / 11.2, 48 15.3 / 14.1, 200 53.9 / 43.6; 16 x 16, 8 states, T = 128 22.7 / 22.6, 256 46 / 40.1.
+// Measured (us, forward, no checkpoints
 // unless stated, RB = 1 / 2 / 4 / 8):
 //   64 x 64, T 8192: 32 states 1772 / 2122 / 2938;  T 4096: 64 states 1105 / 1097 / 1491, 96 states
 //   1388 / 1518 / 1510;  T 2048 with checkpoints: 128 states 862 / 787 / 772
@@ -348,8 +361,8 @@ long long half_load(int K, int V, int units, int rb) {
   return ((groups + 255) / 256 * rb * (V / 16) + 3) / 4;
 }
 }  // namespace
-int half_pick_rb(int K, int V, int units, size_t part_bytes, size_t avail) {
-  int best = 0;
+int half_pick_rb(int K, int V, int units, size_t part_bytes, size_t avail, int T) {
+  int best = 0, whole = 0;  // whole: one workgroup per state
   long long best_load = 0;
   bool best_fits = false;
   auto consider = [&](int rb) {  // (in increasing rb)
@@ -358,12 +371,14 @@ int half_pick_rb(int K, int V, int units, size_t part_bytes, size_t avail) {
     const long long groups = (long long)units * P, load = half_load(K, V, units, rb);
     if (!best || load < best_load || (load == best_load && !best_fits))
       best = rb, best_load = load, best_fits = groups <= 256;
+    if (P == 1) whole = rb;
   };
 #define X(K_, V_, RB_) \
   if (K == K_ && V == V_) consider(RB_);
   M2RNN_HALF_CASES(X)
 #undef X
-  return best;
+  if (!whole || whole == best) return best;
+  return T * (4 * (half_load(K, V, units, whole) - best_load) + 1) < 224 ? whole : best;
 }
 
 // Which launches: below two 16-row blocks per SIMD (1024 SIMDs) of all shapes that have a split;
@@ -372,27 +387,28 @@ int half_pick_rb(int K, int V, int units, size_t part_bytes, size_t avail) {
 // 16-row tile -> RB = 1: 8 states 933 -> 655 us, 16 states 947 -> 686, but 32 states 982 -> 1381
 // (RB = 2: 1037; the exchange traffic of sixteen waves meets in one LDS).
 // Shapes with V = 32 have a 16-row kernel whose waves the same number of states fills evenly (one or two
-// on every SIMD for each 256 of them); 8-row waves are half of one, and from six on a SIMD, where latency
-// no longer counts, the fullest SIMD's odd wave decides.  T = 512, us, 16-row kernel -> this one:
-//   64 x 32, row-wave: 200 states 219 -> 180, 257 302 -> 231, 384 310 -> 271, 400 306 -> 296 (load 7),
-//   450 308 -> 356 (8).  Without a workspace (one part per state): 200 217 -> 180, but 257 to 448 305 -> 350.
-//   32 x 32, tile: 512 193 -> 169, 513 241 -> 231 (5), 700 247 -> 269 (6), 900 327 -> 329 (8).  Without a
-//   workspace: 384 192 -> 171, but 513 to 640 241 -> 267.
-//   32 x 16, row-wave: 200 140 -> 86, 511 182 -> 98, 1023 179 -> 145, without a workspace the same.
+// on every SIMD for each 256 of them); 8-row waves are half of one, and from five on a SIMD, where latency
+// no longer counts, the fullest SIMD's odd wave decides.  us, 16-row kernel -> this one:
+//   64 x 32, row-wave, T = 512: 200 states 219 -> 180, 257 302 -> 231, 384 310 -> 271 (load 6), 400 306 -> 296
+//   (7; T = 48 31.5 -> 35.8), 450 308 -> 356 (8); without a workspace (one part per state) 200 217 -> 180, but
+//   257 to 384 305 -> 350; 300 states, T = 48 31.3 -> 30.5, 24 18.5 -> 21.2, 8 9.3 -> 15.6.
+//   32 x 32, tile: T = 512: 512 states 193 -> 169 (4), 513 241 -> 231 (5), 700 247 -> 269 (6), 900 327 -> 329;
+//   600 states, T = 100 52.7 -> 55.4, 32 19.3 -> 22.1.
+//   32 x 16, row-wave, T = 512: 200 140 -> 86, 511 182 -> 98, 1023 179 -> 145, without a workspace the same.
 // (The choice does not look at the workspace: a call's bits do not depend on its room.)
-bool half_serves(int K, int V, int units) {
-  const int rb = half_pick_rb(K, V, units, 0, 0);
+bool half_serves(int K, int V, int units, int T) {
+  const int rb = half_pick_rb(K, V, units, 0, 0, INT_MAX);
   if (!rb) return false;
   if (K == 128) return (long long)units * (K / 8) <= 256;
   if ((long long)units * (K / 16) >= 2048) return false;
-  const long long load = half_load(K, V, units, rb), even = (long long)(K / 8) * (V / 16) / 4 * ((units + 255) / 256);
-  return V != 32 || load <= 5 || load < even;
+  const long long load = half_load(K, V, units, rb);
+  return V != 32 || load <= 4 || (K == 64 && load <= 6 && T >= 32);
 }
 
 hipError_t half_fwd(const FwdArgs &a, hipStream_t s) {
   // (a pass that only writes checkpoints has no partial sums)
   const size_t part = a.write_y ? (size_t)a.B * a.T * a.N * a.V * 4 : 0;
-  const int rb = half_pick_rb(a.K, a.V, a.B * a.N, part, a.ws_bytes);
+  const int rb = half_pick_rb(a.K, a.V, a.B * a.N, part, a.ws_bytes, a.write_y ? a.T : INT_MAX);
 #define X(K_, V_, RB_) \
   if (a.K == K_ && a.V == V_ && rb == RB_) return launch<Half<K_, V_, RB_>>(a, s);
   M2RNN_HALF_CASES(X)

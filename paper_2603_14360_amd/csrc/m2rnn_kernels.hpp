@@ -135,11 +135,11 @@ hipError_t mfma_fwd(const FwdArgs &a, hipStream_t s);
 hipError_t mfma_bwd(const BwdArgs &a, hipStream_t s);
 // y = bf16(1/c of the sum over the P partial readouts at a.ws [+ w_r (.) v])
 hipError_t y_parts_sum(const FwdArgs &a, int P, hipStream_t s);
-// does the forward on 8-row blocks serve a launch of this many states?
-bool half_serves(int K, int V, int units);
-// that forward, rb of them per workgroup, and the choice of rb for a launch whose
+// does the forward on 8-row blocks serve a launch of this many states and steps?
+bool half_serves(int K, int V, int units, int T);
+// that forward, rb of them per workgroup, and the choice of rb for a launch of T steps whose
 // partial readouts (part_bytes for each of the K/(8 rb) parts of a state) must fit avail bytes
-int half_pick_rb(int K, int V, int units, size_t part_bytes, size_t avail);
+int half_pick_rb(int K, int V, int units, size_t part_bytes, size_t avail, int T);
 hipError_t half_fwd(const FwdArgs &a, hipStream_t s);
 int mfma_pick_rb(int K, int V, int units);  // row blocks per workgroup of the tile serving a launch (0: none)
 

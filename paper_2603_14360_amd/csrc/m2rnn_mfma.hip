@@ -25,8 +25,8 @@ size_t mfma_fwd_least_bytes(int B, int T, int N, int K, int V) {
 
 size_t mfma_fwd_workspace_bytes(int B, int T, int N, int K, int V) {
   const size_t least = mfma_fwd_least_bytes(B, T, N, K, V);
-  if (!half_serves(K, V, B * N)) return least;
-  const int P = K / (8 * half_pick_rb(K, V, B * N, 0, 0));
+  if (!half_serves(K, V, B * N, T)) return least;
+  const int P = K / (8 * half_pick_rb(K, V, B * N, 0, 0, T));
   const size_t want = P > 1 ? align256(P * part_bytes(B, T, N, V)) : 0;
   return want > least ? want : least;
 }

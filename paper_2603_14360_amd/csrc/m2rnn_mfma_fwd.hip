@@ -452,7 +452,7 @@ int mfma_pick_rb(int K, int V, int units) {
 }
 
 hipError_t mfma_fwd(const FwdArgs &a, hipStream_t s) {
-  if (half_serves(a.K, a.V, a.B * a.N)) return half_fwd(a, s);
+  if (half_serves(a.K, a.V, a.B * a.N, a.T)) return half_fwd(a, s);
   if (a.K == 128 && a.V == 128) return launch_fwd<Tile<128, 128, 1>>(a, s);
   if (a.K == 32 && a.V == 32) return launch_fwd<Tile<32, 32, 2>>(a, s);
   return hipErrorInvalidValue;

@@ -95,18 +95,20 @@ def test_backward_without_checkpoints_needs_room_for_them_and_no_more(K, V, N, B
 
 
 # states around the lines of the forward's choice between the 8-row kernel and the 16-row ones
-CHOICE = [(32, 32, 640, "half"), (32, 32, 641, "mfma"), (32, 32, 768, "mfma"), (32, 32, 769, "half"), (32, 32, 896, "half"),
-          (32, 32, 897, "mfma"), (32, 32, 1023, "mfma"), (32, 32, 1024, "rowwave"), (64, 32, 448, "half"), (64, 32, 449, "rowwave"),
+CHOICE = [(32, 32, 512, "half"), (32, 32, 513, "mfma"), (32, 32, 1023, "mfma"), (32, 32, 1024, "rowwave"), (64, 32, 384, "half"), (64, 32, 385, "rowwave"),
           (64, 32, 511, "rowwave"), (64, 32, 512, "rowwave"), (32, 16, 1023, "half"), (32, 16, 1024, "rowwave"),
           (64, 64, 511, "half"), (64, 64, 512, "rowwave"), (64, 16, 511, "half"), (64, 16, 512, "rowwave"),
           (16, 16, 2047, "half"), (16, 16, 2048, "rowwave"), (128, 128, 16, "half"), (128, 128, 17, "mfma")]
 
 
-@pytest.mark.parametrize("K,V,units,kernel", CHOICE)
-def test_forward_kernel_choice(K, V, units, kernel):
-    """The kernel follows from the shape and the states alone; the workspace decides at most between
-    splits of the same kernel (whose bits are the same), and the query is what the choice needs."""
-    desc = d(units, 40, 1, K, V, BF16)
+CHOICE = [c + (40,) for c in CHOICE] + [(64, 32, 256, "half", 2), (64, 32, 257, "rowwave", 31), (64, 32, 257, "half", 32)]
+
+
+@pytest.mark.parametrize("K,V,units,kernel,T", CHOICE)
+def test_forward_kernel_choice(K, V, units, kernel, T):
+    """The kernel follows from the shape, the states and the steps alone; the workspace decides at most
+    between splits of the same kernel (whose bits are the same), and the query is what the choice needs."""
+    desc = d(units, T, 1, K, V, BF16)
     full = ws_bytes(desc, 0)
     calls = [dict(call="fwd", desc=desc, ws=WS, ws_bytes=n) for n in {full, 0, full + 4096, 1 << 40}]
     for r in lr.launches(calls):
