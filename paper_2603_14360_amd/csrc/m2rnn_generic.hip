@@ -88,10 +88,8 @@ __device__ __forceinline__ void step_elements(const float *Hs, const float *Wf, 
   }
 }
 
-// WL: W[n] is copied to LDS (it fits next to the state) and read from there; a template
-// parameter, so that every access to W has one address space (with a run-time choice the
-// contraction reads W through generic-address loads, one wait per load).
-template <typename IO, bool WL>
+// W[n] is copied to LDS, where it fits next to the state at every K and V.
+template <typename IO>
 __global__ void __launch_bounds__(kMaxThreads) gen_fwd_kernel(FwdArgs a, const float *W32) {
   extern __shared__ float smem[];
   const int K = a.K, V = a.V, KV = K * V, T = a.T, N = a.N;
@@ -104,9 +102,7 @@ __global__ void __launch_bounds__(kMaxThreads) gen_fwd_kernel(FwdArgs a, const f
   const int unit = blockIdx.x, b = unit / N, n = unit - b * N;
   const int g = n / (N / a.Nqk);
   const float *Wg = W32 + (size_t)n * V * V;
-  if constexpr (WL)
-    for (int e = tid; e < V * V; e += nt) Wl[e] = Wg[e];
-  const float *Wf = WL ? Wl : Wg;
+  for (int e = tid; e < V * V; e += nt) Wl[e] = Wg[e];
   for (int e = tid; e < KV; e += nt) Hs[e] = a.H0 ? a.H0[(size_t)unit * KV + e] : 0.f;
   __syncthreads();
   const int nck = (T + a.C - 1) / a.C;
@@ -128,7 +124,7 @@ __global__ void __launch_bounds__(kMaxThreads) gen_fwd_kernel(FwdArgs a, const f
     float f = a.f[((size_t)b * T + t) * N + n];
     if (a.gate_alpha) f = gate_psi(f, a.gate_alpha[n], a.gate_beta[n]);
     __syncthreads();
-    step_elements<false>(Hs, Wf, ks, vs, f, K, V, KV, hn, nullptr);
+    step_elements<false>(Hs, Wl, ks, vs, f, K, V, KV, hn, nullptr);
     __syncthreads();
 #pragma unroll
     for (int m = 0; m < PT; ++m) {
@@ -153,6 +149,9 @@ __global__ void __launch_bounds__(kMaxThreads) gen_fwd_kernel(FwdArgs a, const f
 
 // Backward for one (b, n): chunks from last to first; per chunk a forward
 // recompute that parks the chunk's states in `states`, then the reverse sweep.
+// WL: W and its transpose are copied to LDS (they fit next to the state) and read from there; a
+// template parameter, so that every access to W has one address space (with a run-time choice the
+// contraction reads W through generic-address loads, one wait per load).
 template <typename IO, bool WL>
 __global__ void __launch_bounds__(kMaxThreads)
     gen_bwd_kernel(BwdArgs a, const float *W32, const float *WT32, float *states, float *dW_unit,
@@ -358,15 +357,13 @@ __global__ void head_group_sum_kernel(const float *per_head, IO *out, size_t BT,
 
 struct GenericPlan {
   size_t lds_fwd, lds_bwd;
-  bool w_lds_fwd, w_lds_bwd;
+  bool w_lds_bwd;
 };
 
 GenericPlan make_plan(int K, int V) {
   GenericPlan p;
   const int KV = K * V, VV = V * V;
-  const size_t base_f = (size_t)(KV + 2 * K + V) * 4;
-  p.w_lds_fwd = base_f + (size_t)VV * 4 <= kLdsBudget;
-  p.lds_fwd = base_f + (p.w_lds_fwd ? (size_t)VV * 4 : 0);
+  p.lds_fwd = (size_t)(KV + 2 * K + V + VV) * 4;
   const size_t base_b = (size_t)(2 * KV + 2 * K + 2 * V) * 4;
   p.w_lds_bwd = base_b + (size_t)2 * VV * 4 <= kLdsBudget;
   p.lds_bwd = base_b + (p.w_lds_bwd ? (size_t)2 * VV * 4 : 0);
@@ -418,7 +415,7 @@ hipError_t run_fwd(const FwdArgs &a, hipStream_t s) {
     hipLaunchKernelGGL(kernel, dim3(units), dim3(kMaxThreads), p.lds_fwd, s, a, (const float *)W32);
     return hipGetLastError();
   };
-  return p.w_lds_fwd ? go(gen_fwd_kernel<IO, true>) : go(gen_fwd_kernel<IO, false>);
+  return go(gen_fwd_kernel<IO>);
 }
 
 template <typename IO>

@@ -330,7 +330,9 @@ hipError_t launch(const FwdArgs &a, hipStream_t s) {
   float *ypart = (float *)a.ws;
   const dim3 grid(grid_blocks(units, HF::P)), block(HF::THREADS);
   if (a.write_y) hipLaunchKernelGGL((half_fwd_kernel<HF, true>), grid, block, 0, s, a, ypart);
-  else hipLaunchKernelGGL((half_fwd_kernel<HF, false>), grid, block, 0, s, a, ypart);
+  else if constexpr (HF::K < 128 || HF::RB == 1)  // (that split is taken for want of room, and no y needs none)
+    hipLaunchKernelGGL((half_fwd_kernel<HF, false>), grid, block, 0, s, a, ypart);
+  else return hipErrorInvalidValue;
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess || HF::P == 1 || !a.write_y || a.T == 0) return e;
   return y_parts_sum(a, HF::P, s);

@@ -824,12 +824,21 @@ hipError_t quad_fwd(const FwdArgs &a, hipStream_t s) {
   return hipErrorInvalidValue;
 }
 
+// bf16 io: the shapes without a matrix-core backward
+#define M2RNN_QUAD_BF16_CASES(X) X(16, 32) X(64, 32) X(128, 32) X(16, 64) X(32, 64) X(128, 64)
+
 hipError_t quad_bwd(const BwdArgs &a, hipStream_t s) {
-#define X(K_, V_)                                                                        \
-  if (a.K == K_ && a.V == V_)                                                            \
-    return a.io == 0 ? launch_bwd<float, Quad<K_, V_>>(a, s) : launch_bwd<__hip_bfloat16, Quad<K_, V_>>(a, s);
-  M2RNN_QUAD_CASES(X)
+  if (a.io == 0) {
+#define X(K_, V_) \
+  if (a.K == K_ && a.V == V_) return launch_bwd<float, Quad<K_, V_>>(a, s);
+    M2RNN_QUAD_CASES(X)
 #undef X
+  } else {
+#define X(K_, V_) \
+  if (a.K == K_ && a.V == V_) return launch_bwd<__hip_bfloat16, Quad<K_, V_>>(a, s);
+    M2RNN_QUAD_BF16_CASES(X)
+#undef X
+  }
   return hipErrorInvalidValue;
 }
 
