@@ -89,11 +89,12 @@ int32_t m2rnn_max_chunk(const m2rnn_desc *desc);
 
 /* Name of the kernel variant that serves this descriptor's forward (bwd = 0) or backward
  * (bwd != 0): "tile<K,V,RB>" (matrix-core kernel, a 16-row block spread over V/16 waves, RB
- * row blocks per workgroup; the forward under this name splits the state further, into 8-row
- * blocks, where that is faster), "rowwave<K,V>" (matrix-core forward, one wave per 16-row block,
- * or 8-row blocks for few states),
+ * row blocks per workgroup), "half<K,V,RB>" (matrix-core forward on 8-row blocks, RB of them per
+ * workgroup on a full workspace), "rowwave<K,V>" (matrix-core forward, one wave per 16-row block),
+ * "rowwave_bwd<K,16>" (matrix-core backward of V = 16, likewise),
  * "decode<K,V>" (T = 1: the single-launch latency kernel of recurrent inference),
- * "generic<f32>" / "generic<bf16>" (the kernels in fp32 throughout), or "invalid descriptor".
+ * "quad<K,V>" (fp32 throughout on the 4x4x1 matrix instructions, V <= 64), "generic<f32>" /
+ * "generic<bf16>" (fp32 throughout on the vector ALUs, V = 128), or "invalid descriptor".
  * Static storage.  For profiling and for tests that must reach every variant. */
 const char *m2rnn_route_string(const m2rnn_desc *desc, int bwd);
 

@@ -211,6 +211,13 @@ size_t m2rnn_ckpt_bytes(const m2rnn_desc *desc) {
 const char *m2rnn_route_string(const m2rnn_desc *desc, int bwd) {
   if (check_desc(desc) != M2RNN_OK) return "invalid descriptor";
   const Family fam = bwd ? family_of(desc) : fwd_family_of(desc);
+  if (fam == kGeneric && quad_supported(desc->K, desc->V)) {
+#define X(K_, V_) \
+  if (desc->K == K_ && desc->V == V_) return "quad<" #K_ "," #V_ ">";
+    M2RNN_ROWWAVE_CASES(X)
+#undef X
+    return "quad<?>";
+  }
   if (fam == kGeneric) return desc->io == M2RNN_F32 ? "generic<f32>" : "generic<bf16>";
   if (fam == kDecode) {
 #define X(K_, V_) \
@@ -218,6 +225,15 @@ const char *m2rnn_route_string(const m2rnn_desc *desc, int bwd) {
     M2RNN_ROWWAVE_CASES(X)
 #undef X
     return "decode<?>";
+  }
+  const int units = desc->B * desc->N;
+  if (!bwd && half_serves(desc->K, desc->V, units, desc->T)) {
+    const int rb = half_pick_rb(desc->K, desc->V, units, 0, 0, desc->T);
+#define X(K_, V_, RB_) \
+  if (desc->K == K_ && desc->V == V_ && rb == RB_) return "half<" #K_ "," #V_ "," #RB_ ">";
+    M2RNN_HALF_CASES(X)
+#undef X
+    return "half<?>";
   }
   if (fam == kRowWave) {
 #define X(K_, V_) \
@@ -233,7 +249,7 @@ const char *m2rnn_route_string(const m2rnn_desc *desc, int bwd) {
     if (desc->K == 128) return "rowwave_bwd<128,16>";
     return "rowwave_bwd<?>";
   }
-  const int rb = mfma_pick_rb(desc->K, desc->V, desc->B * desc->N);
+  const int rb = mfma_pick_rb(desc->K, desc->V, units);
 #define X(K_, V_, RB_) \
   if (desc->K == K_ && desc->V == V_ && rb == RB_) return "tile<" #K_ "," #V_ "," #RB_ ">";
   M2RNN_TILE_CASES(X)

@@ -155,40 +155,6 @@ def test_static_scratch_entry_rejects_oversized_shapes_on_the_host():
     assert "#define M2RNN_STATIC_SCRATCH_BYTES (8u << 20)" in text
 
 
-def test_every_kernel_instantiation_has_a_parity_case():
-    """Host logic: every tiling and every one-wave-per-row-block shape the sources
-    instantiate is reached by a case of tests/test_gpu_instantiations.py, and the dispatcher
-    really routes that case's descriptor to it."""
-    import importlib.util
-    import sys
-    sys.path.insert(0, os.path.join(ROOT, "tests"))
-    spec = importlib.util.spec_from_file_location(
-        "inst_cases", os.path.join(ROOT, "tests", "test_gpu_instantiations.py"))
-    mod = importlib.util.module_from_spec(spec)
-    spec.loader.exec_module(mod)
-    src = open(os.path.join(ROOT, "paper_2603_14360_amd", "csrc", "m2rnn_mfma_common.hpp")).read()
-    src = src.replace("\\\n", " ")
-    tiles = re.search(r"#define M2RNN_TILE_CASES\(X\)(.*)", src).group(1)
-    rows = re.search(r"#define M2RNN_ROWWAVE_CASES\(X\)(.*)", src).group(1)
-    want = {"tile<%s,%s,%s>" % t for t in re.findall(r"X\((\d+), (\d+), (\d+)\)", tiles)}
-    want_rw = {"rowwave<%s,%s>" % t for t in re.findall(r"X\((\d+), (\d+)\)", rows)}
-    assert len(want) >= 7 and len(want_rw) >= 12
-    fwd_seen, bwd_seen = set(), set()
-    for K, V, B, N, Nqk, fr, br in mod.CASES:
-        d = mb.make_desc(B, 35, N, K, V, mb.M2RNN_BF16, Nqk=(Nqk or None))
-        assert mb.m2rnn_route_string(d, 0) == fr and mb.m2rnn_route_string(d, 1) == br
-        fwd_seen.add(fr)
-        bwd_seen.add(br)
-    # V = 16 tilings exist for the forward only: their backward is the register-resident one
-    rwb_src = open(os.path.join(ROOT, "paper_2603_14360_amd", "csrc", "m2rnn_rowwave_bwd.hip")).read()
-    rwb = re.search(r"#define M2RNN_ROWWAVE_BWD_CASES\(X\)(.*)", rwb_src).group(1)
-    want_rwb = {"rowwave_bwd<%s,16>" % k for k in re.findall(r"X\((\d+)\)", rwb)}
-    assert len(want_rwb) >= 2
-    want_bwd = {t for t in want if not t.split(",")[1] == "16"} | want_rwb
-    assert want <= fwd_seen and want_bwd <= bwd_seen, (want - fwd_seen, want_bwd - bwd_seen)
-    assert want_rw <= fwd_seen, want_rw - fwd_seen
-
-
 def test_block_neighbours_validate_on_the_host():
     """conv1d(4) + SiLU and gated RMSNorm entry points: sizes and refusals without a GPU."""
     buf = FakeBuf(1 << 20, 1 << 30)

@@ -117,3 +117,68 @@ def test_forward_kernel_choice(K, V, units, kernel, T):
             assert r["launches"][0]["kernel"].startswith(kernel + "_fwd_kernel")
     (r,) = lr.launches([dict(call="fwd", desc=desc, ws=WS, ws_bytes=full)])
     assert r["rc"] == 0
+
+
+SCAN_KERNELS = ("half_fwd", "mfma_fwd", "rowwave_fwd", "quad_fwd", "gen_fwd", "decode", "mfma_bwd_overlap", "rowwave_bwd",
+                "quad_bwd", "gen_bwd")
+
+
+def test_every_scan_kernel_has_a_parity_case():
+    """Every kernel of the scan that is compiled into the library is launched by a case of the GPU
+    parity tests, and the route string of each case names the kernel that runs."""
+    import test_gpu_half_fwd as half
+    import test_gpu_instantiations as inst
+    import test_gpu_quad_f32 as quad
+
+    calls, routes = [], []
+
+    def add(desc, bwd=False, room=None, route=None, **kw):
+        n = ws_bytes(desc, (1 if kw.get("ckpt") else 2) if bwd else 0) if room is None else room
+        calls.append(dict(call="bwd" if bwd else "fwd", desc=desc, ws=WS, ws_bytes=n, **kw))
+        routes.append(mb.m2rnn_route_string(mb.make_desc(**desc), int(bwd)) if route is None else route)
+
+    for K, V, B, N, Nqk, fr, br in inst.CASES:
+        desc = d(B, 35, N, K, V, BF16, Nqk=Nqk or N)
+        add(desc, route=fr, ckpt=1)
+        add(desc, bwd=True, route=br, ckpt=1)
+        add(desc, bwd=True, route="")
+    for K, V, B, N, Nqk, fr, br in inst.CLIPPED:
+        add(d(B, 35, N, K, V, BF16, Nqk=Nqk or N), bwd=True, route=br, ckpt=1, opts=1)
+    for K, V, B, N, T, route in inst.SPLITS:
+        add(d(B, T, N, K, V, BF16), route=route)
+    for K, V, units in inst.CHECKPOINT_PASS:
+        add(d(units, 35, 1, K, V, BF16), bwd=True, route="")
+    for K, V in inst.DECODE:
+        add(d(5, 1, 3, K, V, BF16))
+    for K, V in inst.GENERIC_F32 + quad.SHAPES:
+        add(d(2, 35, 3, K, V, F32), ckpt=1)
+        add(d(2, 35, 3, K, V, F32), bwd=True, ckpt=1)
+    for K, V in quad.SHAPES:
+        add(d(2, 35, 3, K, V, F32), bwd=True, route="")
+    for io, K, V, T, chunk, Nqk in quad.TURNS:
+        desc = d(1, T, 4, K, V, F32 if io == "f32" else BF16, chunk=chunk, Nqk=Nqk)
+        assert one_workgroup_per_state(desc, 1) < ws_bytes(desc, 1)
+        add(desc, bwd=True, route="", ckpt=1, room=one_workgroup_per_state(desc, 1))
+    for io, K, V in quad.FORWARD_TURNS:
+        desc = d(1, 601, 16, K, V, F32)
+        add(desc, route="", room=min(one_workgroup_per_state(desc, 0), ws_bytes(desc, 0)))
+    for K, V, units in half.ROOMS:
+        desc = d(units, 261, 1, K, V, BF16)
+        for P in (16, 8, 4, 2, 1):
+            add(desc, route="", room=P * units * 261 * V * 4)
+
+    seen = set()
+    for c, route, r in zip(calls, routes, lr.launches(calls)):
+        assert r["rc"] in ((0, 5) if route == "" else (0,)), (c, r)
+        names = [l["kernel"] for l in r["launches"]]
+        scan = [n for n in names if n.split("_kernel")[0] in SCAN_KERNELS]
+        seen |= set(scan)
+        if route:
+            family, shape = route[:-1].split("<")
+            want = {"tile": "mfma_bwd_overlap" if c["call"] == "bwd" else "mfma_fwd", "half": "half_fwd", "rowwave": "rowwave_fwd",
+                    "rowwave_bwd": "rowwave_bwd", "decode": "decode", "generic": "gen_" + c["call"], "quad": "quad_" + c["call"]}[family]
+            assert len(scan) == 1 and scan[0].startswith(want + "_kernel<"), (route, scan)
+            if family in ("tile", "half", "rowwave", "decode", "quad"):
+                assert "<%s>" % shape.replace(",", ", ") in scan[0], (route, scan)
+    every = {k for k in lr.kernels() if k.split("_kernel")[0] in SCAN_KERNELS}
+    assert len(every) > 100 and not every - seen, sorted(every - seen)

@@ -30,8 +30,10 @@ def test_splits_against_oracle(K, V, units, T):
     assert errs["y"] <= 2 ** -8 and errs["HT"] <= 2e-6, errs
 
 
-@pytest.mark.parametrize("K,V,units", [(64, 64, 3), (64, 64, 40), (128, 128, 2), (32, 32, 2), (64, 16, 5),
-                                       (64, 32, 5), (32, 16, 3), (16, 16, 2)])
+ROOMS = [(64, 64, 3), (64, 64, 40), (128, 128, 2), (32, 32, 2), (64, 16, 5), (64, 32, 5), (32, 16, 3), (16, 16, 2)]
+
+
+@pytest.mark.parametrize("K,V,units", ROOMS)
 def test_same_bits_on_a_smaller_workspace(K, V, units):
     """Every workspace size from the least accepted to the full query: same outputs, bit for bit."""
     import torch
