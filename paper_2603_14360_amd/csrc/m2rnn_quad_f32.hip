@@ -63,39 +63,26 @@ struct Quad {
   static_assert(NWU >= 1 && NWU % NW == 0 && (TB * ROWS) % THREADS == 0, "quad tile");
 };
 
-// tanh of four values, in place.  Below 1 an odd polynomial x + x^3 p(x^2) (a minimax fit of
-// (tanh x - x) / x^3 with every coefficient a float, error 0.5e-9 relative to tanh); from 1 on
-// 1 - 2 e / (1 + e) with e = 2^(-2 |x| log2 e), whose subtrahend is small: the argument of the exponential in
-// two parts, one Newton step on the reciprocal.  Measured error, against the library's tanhf (max / rms
-// ulp): below 0.55 0.71 / 0.30 (0.78 / 0.30), 0.55 to 1 0.88 / 0.32 (1.41 / 0.47), 1 to 1.5 1.16 / 0.33
-// (1.00 / 0.33), beyond 0.71 / 0.29 (0.66 / 0.29).  A wave takes the second branch only if one of its
-// values needs it; infinities give +-1, a NaN stays with the polynomial and is one.
-__device__ __forceinline__ float tanh_from_1(float x) {
-  constexpr float kL = 2.885390043258667f, kLlo = 3.8519e-8f;  // 2 log2 e in two parts
-  const float ax = fminf(__builtin_fabsf(x), 16.f);
-  const float hi = -kL * ax, lo = fmaf(-kL, ax, -hi) - kLlo * ax;
-  const float e0 = __builtin_amdgcn_exp2f(hi), e = fmaf(e0 * 0.69314718f, lo, e0), d = 1.f + e;
-  const float r0 = __builtin_amdgcn_rcpf(d), r = fmaf(fmaf(-d, r0, 1.f), r0, r0);
-  return __builtin_copysignf(fmaf(-2.f * e, r, 1.f), x);
-}
-__device__ __forceinline__ f4_t tanh4(const f4_t &x) {
-  constexpr float c[8] = {-0.33333328366f,  0.13333174586f,   -0.05395071581f,   0.02177435532f,
-                          -0.008571075276f, 0.003048127051f, -0.0008212084067f, 0.0001162105109f};
-  f4_t z;
-  bool far = false;
+// tanh.  Below 1 an odd polynomial x + x^3 p(x^2) (a minimax fit of (tanh x - x) / x^3 with every
+// coefficient a float, error 4.7e-9 relative to tanh); from 1 on 1 - 2 / (1 + e^(2 |x|)), whose
+// subtrahend is below a quarter.  Branch-free, 17 issue slots.  Error, max / rms ulp, here and of the library's
+// tanhf: below 0.55 0.77 / 0.30 (0.78 / 0.30), 0.55 to 1 0.88 / 0.32 (1.41 / 0.47), 1 to
+// 1.5 1.33 / 0.37 (1.00 / 0.33), 1.5 to 2 0.93 / 0.31 (0.66 / 0.29), beyond 0.66 / 0.29 (0.57 / 0.29).
+// (With the argument in two parts and a Newton step the second form is as near as tanhf from 1 on too; the
+// state's error does not change, and a state that saturates pays: B 4, N 8, T 512, W of gain one, forward 246 ->
+// 292 us, although only waves that need it took it.)
+// Infinities give +-1; a NaN goes through the polynomial and stays one.
+__device__ __forceinline__ float tanh_f32(float x) {
+  constexpr float c[7] = {-0.33333295583724976f, 0.13332346081733704f,  -0.05387984961271286f, 0.02148670330643654f,
+                          -0.007946079596877098f, 0.0023012934252619743f, -0.0003584200458135456f};
+  const float x2 = x * x;
+  float p = c[6];
 #pragma unroll
-  for (int m = 0; m < 4; ++m) {
-    const float x2 = x[m] * x[m];
-    float p = c[7];
-#pragma unroll
-    for (int i = 6; i >= 0; --i) p = fmaf(x2, p, c[i]);
-    z[m] = fmaf(x[m] * x2, p, x[m]);
-    far |= __builtin_fabsf(x[m]) >= 1.f;
-  }
-  if (__any(far))
-#pragma unroll
-    for (int m = 0; m < 4; ++m) z[m] = __builtin_fabsf(x[m]) >= 1.f ? tanh_from_1(x[m]) : z[m];
-  return z;
+  for (int i = 5; i >= 0; --i) p = fmaf(x2, p, c[i]);
+  const float near = fmaf(x * x2, p, x);
+  const float e = __builtin_amdgcn_exp2f(2.885390081777927f * __builtin_fabsf(x));
+  const float far = __builtin_copysignf(fmaf(-2.f, __builtin_amdgcn_rcpf(1.f + e), 1.f), x);
+  return __builtin_fabsf(x) >= 1.f ? far : near;
 }
 
 template <int CTRL>
@@ -284,9 +271,8 @@ __device__ __forceinline__ void quad_fwd_part(const FwdArgs &a, float *__restric
       const float vj = sm.v[buf][s][p.col], f = sm.f[buf][s], gm = 1.f - f;
       const f4_t ha = quad_transpose(h, p.odd, p.high);
       const f4_t sp = preactivation<Q>(ha, w, k4, vj);
-      const f4_t z = tanh4(sp);
 #pragma unroll
-      for (int m = 0; m < 4; ++m) h[m] = fmaf(f, h[m], gm * z[m]);
+      for (int m = 0; m < 4; ++m) h[m] = fmaf(f, h[m], gm * tanh_f32(sp[m]));
       if constexpr (DO_Y) {
         const f4_t q4 = *(const f4_t *)&sm.q[buf][s][p.row];
         float y = q4[0] * h[0];
@@ -447,9 +433,12 @@ __global__ void __launch_bounds__(Q::THREADS, Q::V < 64 ? 2 : 1) quad_bwd_kernel
     const float vj = sm.v[s][p.col], f = sm.f[s], gm = 1.f - f;
     ha = quad_transpose(h, p.odd, p.high);
     const f4_t sp = preactivation<Q>(ha, w, k4, vj);
-    const f4_t z = tanh4(sp);
+    f4_t z;
 #pragma unroll
-    for (int m = 0; m < 4; ++m) h[m] = fmaf(f, h[m], gm * z[m]);
+    for (int m = 0; m < 4; ++m) {
+      z[m] = tanh_f32(sp[m]);
+      h[m] = fmaf(f, h[m], gm * z[m]);
+    }
     return z;
   };
 
