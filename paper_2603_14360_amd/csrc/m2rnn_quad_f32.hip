@@ -17,10 +17,10 @@
 // vector instructions).
 //
 // Measured against the vector-ALU kernels that these replace (one workgroup per state, state and
-// W in LDS, three barriers per step): B = 4, N = 8, K = V = 32, T = 512 forward 1.16 -> 0.24 ms,
-// backward 4.35 -> 0.58 ms.  What bounds it there: 128 waves on 1024 SIMDs, each a chain of some
-// 1100 cycles per step (forward: 256 of matrix instructions, the rest the 130 vector instructions
-// of a lone wave); LDS and HBM are idle.
+// W in LDS, three barriers per step): B = 4, N = 8, K = V = 32, T = 512 forward 1.13 -> 0.245 ms,
+// backward 4.34 -> 0.59 ms.  What bounds it there: 128 waves on 1024 SIMDs, each a chain of some
+// 1150 cycles per step (forward: 256 of matrix instructions, the rest the 165 vector instructions
+// of a lone wave); vector ALU 7 %, matrix cores 3 %, HBM 0.06 TB/s.
 #include "m2rnn_kernels.hpp"
 
 #include <hip/hip_bf16.h>
