@@ -70,6 +70,11 @@ def test_fp32_kernels_without_room_for_partial_sums(K, V, io, B, T, N, chunk, Nq
         assert at["rc"] == 0 and query["rc"] == 0
         kern = [r["launches"][0] for r in (at, query)]
         assert kern[1]["kernel"].startswith("quad_%s_kernel" % call)
+        if bwd:   # ... and without the forward's checkpoints, with room for them on top
+            ck = (mb.m2rnn_ckpt_bytes(mb.make_desc(**desc)) + 255) // 256 * 256
+            c = dict(c, ckpt=0)
+            short, enough = lr.launches([dict(c, ws_bytes=min(least, full) + ck - 1), dict(c, ws_bytes=least + ck)])
+            assert short["rc"] == 5 and enough["rc"] == 0 and enough["launches"][-1] == at["launches"][-1]
         if full > least:
             assert kern[0]["kernel"] == kern[1]["kernel"].replace(", false>", ", true>")
             assert kern[0]["grid"] == B * N and kern[1]["grid"] == B * N * (K * V // 1024)
