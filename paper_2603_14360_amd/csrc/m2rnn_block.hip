@@ -11,76 +11,15 @@
 // that stages the same q, k, v rows would add exactly the instructions that bind it.  Here
 // each tensor makes one trip through HBM: x -> out, and (y, a) -> out.
 // Sums over tokens (dw, dbias) are two-stage and ordered: bit-reproducible, no atomics.
+#include "m2rnn_io.hpp"
 #include "m2rnn_kernels.hpp"
 #include "m2rnn_mfma_common.hpp"
-
-#include <hip/hip_bf16.h>
 
 #include <algorithm>
 
 namespace m2rnn {
 namespace {
 
-__device__ __forceinline__ float bf16_bits_to_f32(uint32_t lo16) {
-  return __builtin_bit_cast(float, lo16 << 16);
-}
-// two floats, rounded to nearest even, in one dword (one conversion instruction; done on integers
-// the six of each element were a third of the norm's vector work)
-__device__ __forceinline__ uint32_t pack2_bf16(float lo, float hi) {
-  typedef float f2_t __attribute__((ext_vector_type(2)));
-  typedef __bf16 b2_t __attribute__((ext_vector_type(2)));
-  const f2_t x = {lo, hi};
-  return __builtin_bit_cast(uint32_t, __builtin_convertvector(x, b2_t));
-}
-
-// eight consecutive elements of an io tensor <-> eight floats
-template <typename IO> struct Vec8;
-template <> struct Vec8<float> {
-  struct Raw { f4_t a, b; };
-  static __device__ __forceinline__ Raw load_raw(const void *base, size_t e) {
-    return Raw{*(const f4_t *)((const float *)base + e), *(const f4_t *)((const float *)base + e + 4)};
-  }
-  static __device__ __forceinline__ void widen(const Raw &r, float (&x)[8]) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) { x[i] = r.a[i]; x[4 + i] = r.b[i]; }
-  }
-  static __device__ __forceinline__ void load(const void *base, size_t e, float (&x)[8]) {
-    const f4_t a = *(const f4_t *)((const float *)base + e), b = *(const f4_t *)((const float *)base + e + 4);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) { x[i] = a[i]; x[4 + i] = b[i]; }
-  }
-  static __device__ __forceinline__ void store(void *base, size_t e, const float (&x)[8]) {
-    *(f4_t *)((float *)base + e) = f4_t{x[0], x[1], x[2], x[3]};
-    *(f4_t *)((float *)base + e + 4) = f4_t{x[4], x[5], x[6], x[7]};
-  }
-};
-template <> struct Vec8<__hip_bfloat16> {
-  typedef u4_t Raw;
-  static __device__ __forceinline__ Raw load_raw(const void *base, size_t e) {
-    return *(const u4_t *)((const unsigned short *)base + e);
-  }
-  static __device__ __forceinline__ void widen(const Raw &w, float (&x)[8]) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      x[2 * i] = bf16_bits_to_f32(w[i] & 0xFFFFu);
-      x[2 * i + 1] = __builtin_bit_cast(float, w[i] & 0xFFFF0000u);
-    }
-  }
-  static __device__ __forceinline__ void load(const void *base, size_t e, float (&x)[8]) {
-    const u4_t w = *(const u4_t *)((const unsigned short *)base + e);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      x[2 * i] = bf16_bits_to_f32(w[i] & 0xFFFFu);
-      x[2 * i + 1] = __builtin_bit_cast(float, w[i] & 0xFFFF0000u);
-    }
-  }
-  static __device__ __forceinline__ void store(void *base, size_t e, const float (&x)[8]) {
-    u4_t w;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) w[i] = pack2_bf16(x[2 * i], x[2 * i + 1]);
-    *(u4_t *)((unsigned short *)base + e) = w;
-  }
-};
 // 1 / (1 + e^-u) on the hardware's exp2 and reciprocal (1 ulp each; e^-u = inf gives 0)
 __device__ __forceinline__ float sigmoidf_(float u) {
   return __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(-1.4426950408889634f * u));
@@ -89,38 +28,6 @@ __device__ __forceinline__ float sigmoidf_(float u) {
 // ------------------------------------------------------------------ conv1d(4) + SiLU
 constexpr int kTaps = 4;
 constexpr int kThreads = 256;
-
-// four consecutive elements of an io tensor <-> four floats
-template <typename IO> struct Vec4;
-template <> struct Vec4<float> {
-  typedef f4_t Raw;
-  static __device__ __forceinline__ Raw load_raw(const void *base, size_t e) {
-    return *(const f4_t *)((const float *)base + e);
-  }
-  static __device__ __forceinline__ void widen(const Raw &w, float (&x)[4]) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) x[i] = w[i];
-  }
-  static __device__ __forceinline__ void store(void *base, size_t e, const float (&x)[4]) {
-    *(f4_t *)((float *)base + e) = f4_t{x[0], x[1], x[2], x[3]};
-  }
-};
-template <> struct Vec4<__hip_bfloat16> {
-  typedef uint32_t Raw __attribute__((ext_vector_type(2)));
-  static __device__ __forceinline__ Raw load_raw(const void *base, size_t e) {
-    return *(const Raw *)((const unsigned short *)base + e);
-  }
-  static __device__ __forceinline__ void widen(const Raw &w, float (&x)[4]) {
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      x[2 * i] = bf16_bits_to_f32(w[i] & 0xFFFFu);
-      x[2 * i + 1] = __builtin_bit_cast(float, w[i] & 0xFFFF0000u);
-    }
-  }
-  static __device__ __forceinline__ void store(void *base, size_t e, const float (&x)[4]) {
-    *(Raw *)((unsigned short *)base + e) = Raw{pack2_bf16(x[0], x[1]), pack2_bf16(x[2], x[3])};
-  }
-};
 
 // taps [4 channels][4] (16 consecutive elements of w [C,4]) and bias of channels c0 .. c0 + 3
 template <typename IO>
@@ -355,27 +262,10 @@ struct ConvOut {
 template <typename Out>
 __global__ void __launch_bounds__(1024)
     ordered_sum_kernel(const float *__restrict__ part, float *__restrict__ lvl, Out out, int E, int R) {
-  __shared__ float red[32][33];
-  const int cl = threadIdx.x & 31, wl = threadIdx.x >> 5, e = blockIdx.x * 32 + cl;
-  const int per = (R + gridDim.y - 1) / gridDim.y;
+  const int e = blockIdx.x * 32 + (threadIdx.x & 31), per = (R + gridDim.y - 1) / gridDim.y;
   const int r0 = blockIdx.y * per, r1 = r0 + per < R ? r0 + per : R;
-  float s = 0.f;
-  if (e < E) {
-    int r = r0 + wl;
-    for (; r + 96 < r1; r += 128) {
-      float x[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) x[u] = part[(size_t)(r + 32 * u) * E + e];
-      s += (x[0] + x[1]) + (x[2] + x[3]);
-    }
-    for (; r < r1; r += 32) s += part[(size_t)r * E + e];
-  }
-  red[wl][cl] = s;
-  __syncthreads();
-  if (wl == 0 && e < E) {
-    float t = 0.f;
-#pragma unroll
-    for (int w = 0; w < 32; ++w) t += red[w][cl];
+  const float t = column_sum(part, E, e, r0, r1);
+  if (threadIdx.x < 32 && e < E) {
     if (gridDim.y > 1) lvl[(size_t)blockIdx.y * E + e] = t;
     else out.put(e, t);
   }

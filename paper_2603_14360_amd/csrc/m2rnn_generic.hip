@@ -9,9 +9,8 @@
 //           H_full cache of every state, the forward stores one fp32 checkpoint
 //           every C steps and the backward recomputes a chunk of C states into
 //           a per-recurrence scratch that stays in L2.
+#include "m2rnn_io.hpp"
 #include "m2rnn_kernels.hpp"
-
-#include <hip/hip_bf16.h>
 
 namespace m2rnn {
 namespace {
@@ -22,16 +21,6 @@ constexpr size_t kLdsBudget = 160 * 1024 - 2048;
 constexpr int PT = kMaxPerThread;  // state (and dW) elements per thread
 constexpr int UN = 1;  // unroll factor of the contraction loops: PT elements leave no registers for more
 
-template <typename IO> __device__ __forceinline__ float to_f32(IO x);
-template <> __device__ __forceinline__ float to_f32<float>(float x) { return x; }
-template <> __device__ __forceinline__ float to_f32<__hip_bfloat16>(__hip_bfloat16 x) {
-  return __bfloat162float(x);
-}
-template <typename IO> __device__ __forceinline__ IO from_f32(float x);
-template <> __device__ __forceinline__ float from_f32<float>(float x) { return x; }
-template <> __device__ __forceinline__ __hip_bfloat16 from_f32<__hip_bfloat16>(float x) {
-  return __float2bfloat16(x);  // round to nearest even
-}
 
 // fp32 copies of W[n] and its transpose, so that both contractions of the
 // backward read with unit stride.

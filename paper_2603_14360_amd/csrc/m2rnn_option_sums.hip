@@ -7,6 +7,7 @@
 // walkers are added in LDS and the workgroups by rows_sum_kernel.  Every order is fixed.
 // B T = 32000, N = 16, V = 64, bf16: dw_r 299 -> 29 us (131 MB of dy and v), gate 164 -> 12 us;
 // one column per thread and a serial second stage over 1024 rows took the longer times.
+#include "m2rnn_io.hpp"
 #include "m2rnn_kernels.hpp"
 #include "m2rnn_mfma_common.hpp"
 
@@ -17,21 +18,6 @@ constexpr int kThreads = 256;
 constexpr int kAhead = 4;  // rows of a walker whose loads are issued together
 constexpr int kDwrStages = 1024, kGateStages = 256;  // most partial rows (the scratch is sized for them)
 constexpr int kBlocks = 1024;  // workgroups that fill the chip (four on each CU)
-
-// eight consecutive elements as they come from memory, and as floats
-template <typename IO> struct Eight;
-template <> struct Eight<float> {
-  f4_t a, b;
-  __device__ __forceinline__ void load(const float *p) { a = *(const f4_t *)p; b = *(const f4_t *)(p + 4); }
-  __device__ __forceinline__ float at(int i) const { return i < 4 ? a[i] : b[i - 4]; }
-};
-template <> struct Eight<bf16_raw> {
-  u4_t w;
-  __device__ __forceinline__ void load(const bf16_raw *p) { w = *(const u4_t *)p; }
-  __device__ __forceinline__ float at(int i) const {
-    return __builtin_bit_cast(float, i & 1 ? w[i / 2] & 0xFFFF0000u : w[i / 2] << 16);
-  }
-};
 
 // part[s][c] = sum over the rows of workgroup row s of dy[r][c] v[r][c]; cw = column vectors of
 // eight per workgroup (NV is a multiple of 16, the tensors are 16-byte aligned)
@@ -46,25 +32,24 @@ __global__ void __launch_bounds__(kThreads)
   float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   if (wl < walkers && c < NV) {
     size_t r = (size_t)blockIdx.y * walkers + wl;
+    auto add = [&](const typename Vec8<IO>::Raw &rx, const typename Vec8<IO>::Raw &ry) {
+      float x[8], y[8];
+      Vec8<IO>::widen(rx, x);
+      Vec8<IO>::widen(ry, y);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) acc[i] = fmaf(x[i], y[i], acc[i]);
+    };
     for (; r + (kAhead - 1) * step < BT; r += kAhead * step) {
-      Eight<IO> x[kAhead], y[kAhead];
+      typename Vec8<IO>::Raw x[kAhead], y[kAhead];
 #pragma unroll
       for (int u = 0; u < kAhead; ++u) {
-        x[u].load(dy + (r + u * step) * NV + c);
-        y[u].load(v + (r + u * step) * NV + c);
+        x[u] = Vec8<IO>::load_raw(dy, (r + u * step) * NV + c);
+        y[u] = Vec8<IO>::load_raw(v, (r + u * step) * NV + c);
       }
 #pragma unroll
-      for (int u = 0; u < kAhead; ++u)
-#pragma unroll
-        for (int i = 0; i < 8; ++i) acc[i] = fmaf(x[u].at(i), y[u].at(i), acc[i]);
+      for (int u = 0; u < kAhead; ++u) add(x[u], y[u]);
     }
-    for (; r < BT; r += step) {
-      Eight<IO> x, y;
-      x.load(dy + r * NV + c);
-      y.load(v + r * NV + c);
-#pragma unroll
-      for (int i = 0; i < 8; ++i) acc[i] = fmaf(x.at(i), y.at(i), acc[i]);
-    }
+    for (; r < BT; r += step) add(Vec8<IO>::load_raw(dy, r * NV + c), Vec8<IO>::load_raw(v, r * NV + c));
   }
   *(f4_t *)&red[threadIdx.x][0] = f4_t{acc[0], acc[1], acc[2], acc[3]};
   *(f4_t *)&red[threadIdx.x][4] = f4_t{acc[4], acc[5], acc[6], acc[7]};
@@ -123,29 +108,13 @@ __global__ void __launch_bounds__(kThreads)
   }
 }
 
-// Column sums of part [S][E]; columns from `split` on go to out1.  32 columns x 32 walkers.
+// Column sums of part [S][E]; columns from `split` on go to out1.
 __global__ void __launch_bounds__(1024)
     rows_sum_kernel(const float *__restrict__ part, int S, int E, float *__restrict__ out0, int split,
                     float *__restrict__ out1) {
-  __shared__ float red[32][33];
-  const int cl = threadIdx.x & 31, wl = threadIdx.x >> 5, c = blockIdx.x * 32 + cl;
-  float s = 0.f;
-  if (c < E) {
-    int r = wl;
-    for (; r + 96 < S; r += 128) {
-      float x[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) x[u] = part[(size_t)(r + 32 * u) * E + c];
-      s += (x[0] + x[1]) + (x[2] + x[3]);
-    }
-    for (; r < S; r += 32) s += part[(size_t)r * E + c];
-  }
-  red[wl][cl] = s;
-  __syncthreads();
-  if (wl == 0 && c < E) {
-    float t = 0.f;
-#pragma unroll
-    for (int w = 0; w < 32; ++w) t += red[w][cl];
+  const int c = blockIdx.x * 32 + (threadIdx.x & 31);
+  const float t = column_sum(part, E, c, 0, S);
+  if (threadIdx.x < 32 && c < E) {
     if (c < split) out0[c] = t;
     else out1[c - split] = t;
   }
@@ -200,7 +169,7 @@ size_t residual_dw_r_scratch_bytes(int N, int V) {
 }
 
 hipError_t residual_dw_r(const BwdArgs &a, hipStream_t s) {
-  return a.io == 0 ? dwr<float>(a, s) : dwr<bf16_raw>(a, s);
+  return a.io == 0 ? dwr<float>(a, s) : dwr<__hip_bfloat16>(a, s);
 }
 
 }  // namespace m2rnn

@@ -21,30 +21,15 @@
 // backward 4.34 -> 0.59 ms.  What bounds it there: 128 waves on 1024 SIMDs, each a chain of some
 // 1150 cycles per step (forward: 256 of matrix instructions, the rest the 165 vector instructions
 // of a lone wave); vector ALU 7 %, matrix cores 3 %, HBM 0.06 TB/s.
+#include "m2rnn_io.hpp"
 #include "m2rnn_kernels.hpp"
 
-#include <hip/hip_bf16.h>
-
-#include <type_traits>
 #include <utility>
 
 namespace m2rnn {
 namespace {
 
-typedef float f4_t __attribute__((ext_vector_type(4)));
-
 constexpr int TB = 16;  // steps per staged block (forward), per on-chip stash (backward)
-
-template <typename IO> __device__ __forceinline__ float to_f32(IO x);
-template <> __device__ __forceinline__ float to_f32<float>(float x) { return x; }
-template <> __device__ __forceinline__ float to_f32<__hip_bfloat16>(__hip_bfloat16 x) {
-  return __bfloat162float(x);
-}
-template <typename IO> __device__ __forceinline__ IO from_f32(float x);
-template <> __device__ __forceinline__ float from_f32<float>(float x) { return x; }
-template <> __device__ __forceinline__ __hip_bfloat16 from_f32<__hip_bfloat16>(float x) {
-  return __float2bfloat16(x);  // round to nearest even
-}
 
 template <int K_, int V_>
 struct Quad {

@@ -57,16 +57,18 @@ def test_parts_in_turn_give_the_same_bits(io, K, V):
     outs = []
     for room in rooms:
         y, HT = torch.full((B, T, N, V), float("nan"), device="cuda"), torch.empty(B, N, K, V, device="cuda")
-        args = (dev["q"], dev["k"], dev["v"], dev["f"], dev["W"], dev["H0"], y, HT, None)
+        ckpt = torch.full((mb.m2rnn_ckpt_bytes(desc) // 4,), float("nan"), device="cuda")
+        args = (dev["q"], dev["k"], dev["v"], dev["f"], dev["W"], dev["H0"], y, HT, ckpt)
         if room is None:
             mb.m2rnn_fwd_static(desc, mb.make_opts(w_r=w_r), *args, stream=stream)
         else:
             ws = torch.empty(room, dtype=torch.uint8, device="cuda")
             mb.m2rnn_fwd_opt(desc, mb.make_opts(w_r=w_r), *args, ws, stream=stream)
         torch.cuda.synchronize()
-        outs.append((y, HT))
-    for y, HT in outs[1:]:
-        assert torch.equal(outs[0][0], y) and torch.equal(outs[0][1], HT)
+        outs.append((y, HT, ckpt))
+    for out in outs[1:]:
+        assert all(torch.equal(a, b) for a, b in zip(outs[0], out))
+    assert all(torch.isfinite(a).all() for a in outs[0])
 
 
 # long enough that the query is more than the room of one workgroup per state; checkpoint intervals
