@@ -64,8 +64,8 @@ __global__ void __launch_bounds__(DC::THREADS, 2) decode_kernel(FwdArgs a) {
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         const _Float16 w = (_Float16)bf16_to_f32(Wn[(size_t)(16 * ct + 4 * ig + e) * V + 16 * jt + jl]);
-        wf[jt][ct][2 * e] = w;
-        wf[jt][ct][2 * e + 1] = w;
+        wf[jt][ct][pair_slot(e)] = w;
+        wf[jt][ct][pair_slot(e) + 2] = w;
       }
 
   if (a.ckpt) {  // checkpoint 0 = the state before the step (a later m2rnn_bwd starts from it)
@@ -83,26 +83,18 @@ __global__ void __launch_bounds__(DC::THREADS, 2) decode_kernel(FwdArgs a) {
   for (int jt = 0; jt < CT; ++jt) acc[jt] = f4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
   for (int ct = 0; ct < CT; ++ct) {
-    u4_t pk;
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      h[ct][r] = kC * h0[ct][r];
-      pk[r] = split_hi_lo(h[ct][r]);
-    }
-    const h8_t hf = __builtin_bit_cast(h8_t, pk);
+    for (int r = 0; r < 4; ++r) h[ct][r] = kC * h0[ct][r];
+    const h8_t hf = __builtin_bit_cast(h8_t, split4_hi_lo(h[ct]));
 #pragma unroll
     for (int jt = 0; jt < CT; ++jt) acc[jt] = mfma_k32(wf[jt][ct], hf, acc[jt]);
   }
 
   // ---- tanh, gate, readout
-  // identity fragment of the transposing MFMA: both slots of column 4 ig + e when that is n
+  // identity fragment of the transposing MFMA: both slots of a column when that is n
   h8_t ident;
 #pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    const _Float16 one = (4 * ig + e == jl) ? (_Float16)1.0f : (_Float16)0.0f;
-    ident[2 * e] = one;
-    ident[2 * e + 1] = one;
-  }
+  for (int e = 0; e < 8; ++e) ident[e] = (_Float16)(4 * ig + pair_row(e) == jl ? 1.f : 0.f);
   h4_t qfr;
   qfr[0] = (_Float16)bf16_to_f32((bf16_raw)(qraw.x & 0xFFFFu));
   qfr[1] = (_Float16)bf16_to_f32((bf16_raw)(qraw.x >> 16));
@@ -112,12 +104,10 @@ __global__ void __launch_bounds__(DC::THREADS, 2) decode_kernel(FwdArgs a) {
   for (int ct = 0; ct < CT; ++ct) {
     const float v4[4] = {bf16_to_f32((bf16_raw)(vraw[ct].x & 0xFFFFu)), bf16_to_f32((bf16_raw)(vraw[ct].x >> 16)),
                          bf16_to_f32((bf16_raw)(vraw[ct].y & 0xFFFFu)), bf16_to_f32((bf16_raw)(vraw[ct].y >> 16))};
-    u4_t pk;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const float sp = fmaf(ki, v4[r], acc[ct][r]);
       h[ct][r] = gate_tanh_step(fg, gp, h[ct][r], sp);
-      pk[r] = split_hi_lo(h[ct][r]);
     }
     if (a.HT) {
       f4_t x;
@@ -129,7 +119,7 @@ __global__ void __launch_bounds__(DC::THREADS, 2) decode_kernel(FwdArgs a) {
       // transpose on the matrix core (D[m = i][n = j] = hi + lo of H'[i][j]), then
       // D[m = j][*] = c sum_i q_i H[i][j] over the 16 rows of this block
       typedef float f2_t __attribute__((ext_vector_type(2)));
-      const f4_t tr = mfma_k32(__builtin_bit_cast(h8_t, pk), ident, f4_t{0.f, 0.f, 0.f, 0.f});
+      const f4_t tr = mfma_k32(__builtin_bit_cast(h8_t, split4_hi_lo(h[ct])), ident, f4_t{0.f, 0.f, 0.f, 0.f});
       const f2_t a01 = {tr[0], tr[1]}, a23 = {tr[2], tr[3]};
       uint2 tp;
       tp.x = __builtin_bit_cast(uint32_t, __builtin_convertvector(a01, h2_t));

@@ -717,14 +717,7 @@ __global__ void __launch_bounds__(2 * TL::THREADS, 2) mfma_bwd_overlap_kernel(Bw
       const bool mine = jlB == s;
       // k_s in row s of the A operand only: the other lanes read zeros
       const h4_t kfr = lds_ld<h4_t>(mine ? bR2 + (L::KH_ + s * ROWS * 2) : bZero + L::ZERO_, 0);
-      // H' - Z' in packed fp16 (its inputs are fp16 stash values).  dS = (1-f) G (1 - Z^2) is
-      // formed as  (1-f) G - G w,  w = (1-f) Z^2 : only the SMALL term w is packed fp16, the
-      // leading term keeps 1 - f and G in fp32, and one mixed-precision FMA rounds the sum
-      // straight to the fp16 MFMA operand.  (With the whole factor (1-f)(1 - Z^2) in fp16,
-      // which is one vector multiply per element cheaper, the rounded factor is biased: Z^2
-      // is mostly below one fp16 ulp of 1 - f, so the factor rounds up to fp16(1 - f) more
-      // often than down, by 2.4e-5 on average; compounded through the W path of the Jacobian
-      // that is +1 % on a gradient carried over 4096 steps, several % where memory is long.)
+      // H' - Z' and w = (1-f) Z^2 in packed fp16 (their inputs are fp16 stash values)
       const h4_t m4 = __builtin_bit_cast(h4_t, m4u);
       const h4_t hz = hown - zp;
       const h4_t ug = (zp * m4) * zp;   // = -w
@@ -734,20 +727,7 @@ __global__ void __launch_bounds__(2 * TL::THREADS, 2) mfma_bwd_overlap_kernel(Bw
         G[r] = fmaf(q4[r], dyj, carry[r]);
         dfl = fmaf(G[r], (float)hz[r], dfl);
       }
-      uint2 dsu;
-      {
-        const uint2 ugu = __builtin_bit_cast(uint2, ug);
-        const float g0 = gm * G[0], g1 = gm * G[1], g2 = gm * G[2], g3 = gm * G[3];
-        asm("v_fma_mixlo_f16 %0, %1, %2, %3 op_sel_hi:[0,1,0]"
-            : "=v"(dsu.x) : "v"(G[0]), "v"(ugu.x), "v"(g0));
-        asm("v_fma_mixhi_f16 %0, %1, %2, %3 op_sel:[0,1,0] op_sel_hi:[0,1,0]"
-            : "+v"(dsu.x) : "v"(G[1]), "v"(ugu.x), "v"(g1));
-        asm("v_fma_mixlo_f16 %0, %1, %2, %3 op_sel_hi:[0,1,0]"
-            : "=v"(dsu.y) : "v"(G[2]), "v"(ugu.y), "v"(g2));
-        asm("v_fma_mixhi_f16 %0, %1, %2, %3 op_sel:[0,1,0] op_sel_hi:[0,1,0]"
-            : "+v"(dsu.y) : "v"(G[3]), "v"(ugu.y), "v"(g3));
-      }
-      const h4_t dsp = __builtin_bit_cast(h4_t, dsu);
+      const h4_t dsp = ds_of(G, ug, gm);
       lds_st<h4_t>(bDw, L::DX + wr * ROWS * V * 2, dsp);
 #pragma unroll
       for (int c2 = 0; c2 < CT; ++c2) {

@@ -14,8 +14,8 @@
 // sensitive to the forward trajectory (the backward amplifies a trajectory
 // error of 2e-4 into gradient errors of several percent), so the state enters
 // its contraction as an fp16 pair (hi, lo) with hi + lo = H' to ~21 bits.  The
-// pair occupies two adjacent k-slots of the 16x16x32 MFMA and the W fragment
-// holds each row of W twice.  All other matrix-core operands (dS, the stash
+// pair occupies two k-slots of the 16x16x32 MFMA (or two of its rows) and the W
+// fragment holds each row of W twice.  All other matrix-core operands (dS, the stash
 // copies of H and Z, q, k, v, dy) are single fp16 values.
 //
 // Scaled state.  tanh(x) = 1 - 2/(1 + 2^(c x)) with c = 2*log2(e).  The kernels
@@ -51,18 +51,11 @@ __device__ __forceinline__ bf16_raw f32_to_bf16(float x) {
   return (bf16_raw)(u >> 16);
 }
 
-// H' -> fp16 pair packed in one dword: hi (H' truncated to 11 significant
-// bits, exact in fp16) in the low half, lo = fp16(H' - hi) in the high half.
-__device__ __forceinline__ uint32_t split_hi_lo(float h) {
-  typedef float f2_t __attribute__((ext_vector_type(2)));
-  const float hi = __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, h) & 0xFFFFE000u);
-  const f2_t pr = {hi, h - hi};
-  return __builtin_bit_cast(uint32_t, __builtin_convertvector(pr, h2_t));
-}
 // Two elements H' -> their fp16 (hi, lo) parts as two packed registers, {hi0, hi1} and {lo0, lo1}:
-// hi is H' rounded towards zero (the bits that split_hi_lo keeps), lo = fp16(H' - hi).  Four
-// instructions for two elements: the mixed-precision FMA subtracts the fp16 hi in fp32, so hi
-// needs no fp32 copy of its own.
+// hi is H' rounded towards zero to 11 significant bits, lo = fp16(H' - hi).  Four instructions for
+// two elements: the mixed-precision FMA subtracts the fp16 hi in fp32, so hi needs no fp32 copy of
+// its own.  (v_fma_mixlo/mixhi_f16 would round to fp16 in the same instruction, but take 8.3 cycles
+// a wave where v_fma_mix_f32 and the packing conversion take 4.3.)
 __device__ __forceinline__ u2_t split2_hi_lo(float h0, float h1) {
   typedef float f2_t __attribute__((ext_vector_type(2)));
   const uint32_t hi = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(h0, h1));
@@ -72,13 +65,15 @@ __device__ __forceinline__ u2_t split2_hi_lo(float h0, float h1) {
   const f2_t lo = {l0, l1};
   return u2_t{hi, __builtin_bit_cast(uint32_t, __builtin_convertvector(lo, h2_t))};
 }
-// the four hi halves of four packed pairs, as one MFMA fragment
-__device__ __forceinline__ h4_t hi_of_pairs(const uint32_t (&pk)[4]) {
-  uint2 v;
-  v.x = (pk[0] & 0xFFFFu) | (pk[1] << 16);
-  v.y = (pk[2] & 0xFFFFu) | (pk[3] << 16);
-  return __builtin_bit_cast(h4_t, v);
+// Four elements of a lane as the operand of a 16x16x32 MFMA that contracts 16 columns, hi and lo
+// parts both: slots {hi0, hi1, lo0, lo1, hi2, hi3, lo2, lo3}.  Slot e meets W's row pair_row(e).
+__device__ __forceinline__ u4_t split4_hi_lo(const float (&h)[4]) {
+  const u2_t a = split2_hi_lo(h[0], h[1]), b = split2_hi_lo(h[2], h[3]);
+  return u4_t{a.x, a.y, b.x, b.y};
 }
+__device__ __forceinline__ constexpr int pair_row(int e) { return 2 * (e >> 2) + (e & 1); }
+// the first of the two slots that row r takes (the other one is 2 further)
+__device__ __forceinline__ constexpr int pair_slot(int r) { return r + (r & 2); }
 
 // One state element through the non-linearity and the gate of the recurrence equations, on the
 // scaled state:  H' <- f H' + gp tanh(s),  gp = c (1 - f),  sp = c s = 2 log2(e) s.
@@ -98,6 +93,26 @@ __device__ __forceinline__ float gate_tanh_step(float f, float gp, float h, floa
   const float n = fmaf(-gp, e, gp);                      // gp (1 - e) >= 0
   const float ns = __builtin_copysignf(n, sp);
   return fmaf(ns, rr, f * h);
+}
+
+// dS = G ((1-f) - w) as an fp16 operand, from ug = -w = -(1-f) Z^2 in fp16: only the small term w
+// is fp16, the leading term 1 - f and G stay fp32.  (With the whole factor (1-f)(1 - Z^2) in fp16 the
+// rounded factor is biased: Z^2 is mostly below one fp16 ulp of 1 - f, so the factor rounds up to
+// fp16(1 - f) more often than down, by 2.4e-5 on average; compounded through the W path of the
+// Jacobian that is +1 % on a gradient carried over 4096 steps.)  The factor does not depend on G, so
+// it is off the chain of the carried gradient; v_fma_mixlo/mixhi_f16, which would form and round
+// (1-f) G - w G at once, take 8.3 cycles a wave against 4.3 here.
+__device__ __forceinline__ h4_t ds_of(const float (&G)[4], h4_t ug, float gm) {
+  typedef float f4v_t __attribute__((ext_vector_type(4)));
+  const u2_t u = __builtin_bit_cast(u2_t, ug);
+  const uint32_t u0 = u.x, u1 = u.y;
+  float t[4];
+  asm("v_fma_mix_f32 %0, %1, 1.0, %2 op_sel_hi:[1,0,0]" : "=v"(t[0]) : "v"(u0), "v"(gm));
+  asm("v_fma_mix_f32 %0, %1, 1.0, %2 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(t[1]) : "v"(u0), "v"(gm));
+  asm("v_fma_mix_f32 %0, %1, 1.0, %2 op_sel_hi:[1,0,0]" : "=v"(t[2]) : "v"(u1), "v"(gm));
+  asm("v_fma_mix_f32 %0, %1, 1.0, %2 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(t[3]) : "v"(u1), "v"(gm));
+  const f4v_t d = {G[0] * t[0], G[1] * t[1], G[2] * t[2], G[3] * t[3]};
+  return __builtin_convertvector(d, h4_t);
 }
 
 // Workgroup barrier that orders LDS traffic only.  __syncthreads() also drains

@@ -101,8 +101,8 @@ __global__ void __launch_bounds__(TL::THREADS, 2)
       for (int e = 0; e < 4; ++e) {
         const int c = 16 * m + 4 * ig + e;
         const _Float16 w = (_Float16)bf16_to_f32(Wn[(size_t)c * V + col0 + jl]);
-        wf[d][2 * e] = w;
-        wf[d][2 * e + 1] = w;
+        wf[d][pair_slot(e)] = w;
+        wf[d][pair_slot(e) + 2] = w;
       }
     }
   }
@@ -121,9 +121,7 @@ __global__ void __launch_bounds__(TL::THREADS, 2)
   }
   // the own tile as the next contraction's B fragment, and that contraction started with it
   const f4_t zero4 = {0.f, 0.f, 0.f, 0.f};
-  u4_t own;
-#pragma unroll
-  for (int r = 0; r < 4; ++r) own[r] = split_hi_lo(h[r]);
+  const u4_t own = split4_hi_lo(h);
   sm.Hx[0][rb][ct][lane] = own;
   f4_t acc_own = mfma_k32(wf[0], __builtin_bit_cast(h8_t, own), zero4);
   // LDS byte offsets of the other tiles' fragments (exchange buffer 0)
@@ -248,14 +246,13 @@ __global__ void __launch_bounds__(TL::THREADS, 2)
     settle(x.acc);
   };
   // E: tanh, gate, split, fragment into exchange buffer `buf`, own-tile product of the next step
-  auto step_E = [&](const StepRegs &x, uint32_t (&pk)[4], int buf) __attribute__((always_inline)) {
+  auto step_E = [&](const StepRegs &x, u4_t &fr, int buf) __attribute__((always_inline)) {
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const float sp = fmaf(x.kk, x.v4[r], x.acc[r]);
       h[r] = gate_tanh_step(x.f, x.gp, h[r], sp);
-      pk[r] = split_hi_lo(h[r]);
     }
-    const u4_t fr = {pk[0], pk[1], pk[2], pk[3]};
+    fr = split4_hi_lo(h);
     lds_st<u4_t>(hx + hx_off[0], buf * HXBUF, fr);
     acc_own = mfma_k32(wf[0], __builtin_bit_cast(h8_t, fr), zero4);
   };
@@ -267,13 +264,11 @@ __global__ void __launch_bounds__(TL::THREADS, 2)
   //    16-step block so.  V < 128 holds it back: q in every column, column s kept by selects.  At
   //    V = 128 those take 2.7 % of a 4 x 8192, 8-head training step, 10.88 -> 11.19 ms; transposed,
   //    with one select per step, 2.5 %.)
-  auto step_Y = [&](const StepRegs &x, const uint32_t (&pk)[4], int s, f4_t &yacc)
+  auto step_Y = [&](const StepRegs &x, const u4_t &fr, int s, f4_t &yacc)
       __attribute__((always_inline)) {
     // (masked up here: behind the transposing product it takes 8 % of the kernel at V = 128)
     const h4_t qf = V < 128 || jl == s ? x.qf : zero_h4;
-    uint2 hv;
-    hv.x = __builtin_amdgcn_perm(pk[1], pk[0], 0x05040100u);
-    hv.y = __builtin_amdgcn_perm(pk[3], pk[2], 0x05040100u);
+    const u2_t hv = {fr[0], fr[2]};
     const f4_t tr = mfma_k16(__builtin_bit_cast(h4_t, hv), ident, zero4);
     const h4_t ht = {(_Float16)tr[0], (_Float16)tr[1], (_Float16)tr[2], (_Float16)tr[3]};
     if constexpr (V < 128) {
@@ -334,12 +329,12 @@ __global__ void __launch_bounds__(TL::THREADS, 2)
         // through a block then uses the fetched registers, and the compiler puts no wait for
         // them -- which would also wait for the stores in flight -- at the head of the next.)
         if (s == TB / 2) stage_store(sb ^ 1);
-        uint32_t pk[4];
-        step_E(x, pk, (s & 1) ^ 1);  // every block but the last has 16 steps: parity of s
+        u4_t fr;
+        step_E(x, fr, (s & 1) ^ 1);  // every block but the last has 16 steps: parity of s
         lds_barrier();
         // after the barrier: fetch the next step's operands, then the readout MFMAs
         if (!last) step_L(nx, s + 1, sb, (s + 1) & 1);
-        if constexpr (DO_Y) step_Y(x, pk, s, yacc);
+        if constexpr (DO_Y) step_Y(x, fr, s, yacc);
       };
       if (len == TB) {
 #pragma unroll

@@ -130,7 +130,7 @@ __global__ void __launch_bounds__(RW::THREADS, 3) rowwave_bwd_kernel(BwdArgs a, 
   //      = W[j][j'];  carry:  (dS W^T)^T[j'][i] = sum_j W[j'][j] dS[i][j]  -> A[m = j'][k = j] = W[j'][j].
   //      Lane (m, k-group) = (jl, ig) holds k = 4 ig + e.
   //      The recomputed state enters its contraction as an fp16 pair (hi, lo), as in the
-  //      forward kernels (16x16x32 MFMA, the pair in adjacent k-slots against a fragment that
+  //      forward kernels (16x16x32 MFMA, the pair in two k-slots against a fragment that
   //      holds each row of W twice): a recurrence that expands (transition gain above one)
   //      amplifies the operand's rounding inside a chunk, 1.4^16 at gain 3.
   h8_t wfT;
@@ -138,12 +138,9 @@ __global__ void __launch_bounds__(RW::THREADS, 3) rowwave_bwd_kernel(BwdArgs a, 
   {
     const bf16_raw *Wn = (const bf16_raw *)a.W + (size_t)n * V * V;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const _Float16 w = (_Float16)bf16_to_f32(Wn[(size_t)(4 * ig + e) * V + jl]);
-      wfT[2 * e] = w;
-      wfT[2 * e + 1] = w;
-      wfW[e] = (_Float16)bf16_to_f32(Wn[(size_t)jl * V + 4 * ig + e]);
-    }
+    for (int e = 0; e < 8; ++e) wfT[e] = (_Float16)bf16_to_f32(Wn[(size_t)(4 * ig + pair_row(e)) * V + jl]);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) wfW[e] = (_Float16)bf16_to_f32(Wn[(size_t)jl * V + 4 * ig + e]);
   }
   const h4_t zero_h4 = {(_Float16)0.f, (_Float16)0.f, (_Float16)0.f, (_Float16)0.f};
   const f4_t zero4 = {0.f, 0.f, 0.f, 0.f};
@@ -355,10 +352,7 @@ __global__ void __launch_bounds__(RW::THREADS, 3) rowwave_bwd_kernel(BwdArgs a, 
           const float cki = lds_ld<float>(bRow4, RW::OFF_CK + s * K * 4);
           const h4_t v4 = lds_ld<h4_t>(bCol2, RW::OFF_VH + s * V * 2);
           lds_st<h4_t>(hsw, s * 512, hcur);
-          u4_t pk;
-#pragma unroll
-          for (int r = 0; r < 4; ++r) pk[r] = split_hi_lo(h[r]);
-          const f4_t acc = mfma_k32(wfT, __builtin_bit_cast(h8_t, pk), zero4);
+          const f4_t acc = mfma_k32(wfT, __builtin_bit_cast(h8_t, split4_hi_lo(h)), zero4);
           float z[4];
 #pragma unroll
           for (int r = 0; r < 4; ++r) {
@@ -401,8 +395,7 @@ __global__ void __launch_bounds__(RW::THREADS, 3) rowwave_bwd_kernel(BwdArgs a, 
           const bool mine = jlo == s;
           const h4_t vfr = lds_ld<h4_t>(mine ? bCol2 + (RW::OFF_VH + s * V * 2) : bZero + RW::OFF_ZERO, 0);
           const h4_t kfr = lds_ld<h4_t>(mine ? bRow2 + (RW::OFF_KH + s * K * 2) : bZero + RW::OFF_ZERO, 0);
-          // H' - Z' and w = (1-f) Z^2 in packed fp16;  dS = (1-f) G - G w  with the leading term
-          // in fp32 and one mixed-precision FMA rounding the sum to the fp16 operand
+          // H' - Z' and w = (1-f) Z^2 in packed fp16
           const h4_t hz = hown - zp;
           const h4_t ug = (zp * m4) * zp;  // = -w
           float G[4];
@@ -412,25 +405,7 @@ __global__ void __launch_bounds__(RW::THREADS, 3) rowwave_bwd_kernel(BwdArgs a, 
             G[r] = fmaf(qs, dy4[r], carry[r]);
             dfl = fmaf(G[r], (float)hz[r], dfl);
           }
-          uint2 dsu;
-          {
-            const uint2 ugu = __builtin_bit_cast(uint2, ug);
-            const float g0 = gm * G[0], g1 = gm * G[1], g2 = gm * G[2], g3 = gm * G[3];
-            asm("v_fma_mixlo_f16 %0, %1, %2, %3 op_sel_hi:[0,1,0]"
-                : "=v"(dsu.x) : "v"(G[0]), "v"(ugu.x), "v"(g0));
-            asm("v_fma_mixhi_f16 %0, %1, %2, %3 op_sel:[0,1,0] op_sel_hi:[0,1,0]"
-                : "+v"(dsu.x) : "v"(G[1]), "v"(ugu.x), "v"(g1));
-            asm("v_fma_mixlo_f16 %0, %1, %2, %3 op_sel_hi:[0,1,0]"
-                : "=v"(dsu.y) : "v"(G[2]), "v"(ugu.y), "v"(g2));
-            asm("v_fma_mixhi_f16 %0, %1, %2, %3 op_sel:[0,1,0] op_sel_hi:[0,1,0]"
-                : "+v"(dsu.y) : "v"(G[3]), "v"(ugu.y), "v"(g3));
-            // The next instruction to read dS is an MFMA.  The compiler does not count wait
-            // states behind inline assembly, and without them the matrix core reads the
-            // register pair before the two high halves have landed (seen as a carry built
-            // from half of dS).
-            asm volatile("s_nop 3" : "+v"(dsu.x), "+v"(dsu.y));
-          }
-          const h4_t dsp = __builtin_bit_cast(h4_t, dsu);
+          const h4_t dsp = ds_of(G, ug, gm);
           // chain: carry <- f G + W dS^T
           const f4_t d = mfma_k16(wfW, dsp, zero4);
           // off the chain: the two tiles with rows in the registers, for dW and dv

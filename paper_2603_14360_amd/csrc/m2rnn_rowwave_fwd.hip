@@ -7,7 +7,7 @@
 // wave's state.  The problem is run transposed, S^T = W^T H^T, because then the
 // MFMA accumulator layout (lane = state row i, 4 consecutive columns per
 // register group) IS the B-operand layout of the next step's MFMA: after the
-// elementwise update the packed (hi, lo) fp16 pairs of a 16 x 16 tile feed the
+// elementwise update the packed (hi, lo) fp16 parts of a 16 x 16 tile feed the
 // next contraction directly.  No LDS exchange and no barrier sit on the
 // step-to-step dependency chain (an LDS round trip on this chip costs ~400
 // cycles per step, more than the arithmetic).
@@ -16,7 +16,7 @@
 //   E   s' = acc[ct] + (c k_i) v_j ; H' <- c [f H + (1-f) tanh(s)] (gate_tanh_step) ;
 //       (hi, lo) = split(H')
 //   M   for every output tile jt: acc'[jt] += W^T[jt][ct] (hi, lo)[ct]
-//       (16x16x32 MFMA: the pair occupies adjacent k-slots, the W fragment
+//       (16x16x32 MFMA: the pair occupies two k-slots, the W fragment
 //        holds each row of W twice) -- these run on the matrix core while the
 //       vector ALU does E of the next tile.
 // Readout y_t = H_t^T q_t contracts over the rows, which are the lane index in
@@ -78,8 +78,8 @@ __global__ void __launch_bounds__(RW::THREADS, 2) rowwave_fwd_kernel(FwdArgs a) 
   const float *__restrict__ fg = a.f;
   bf16_raw *__restrict__ yg = (bf16_raw *)a.y;
 
-  // ---- W fragments (A operand of S^T = W^T H^T): slots 2e, 2e+1 of the MFMA for
-  //      (jt, ct) hold W[16 ct + 4 ig + e][16 jt + jl]; they meet the (hi, lo) pair.
+  // ---- W fragments (A operand of S^T = W^T H^T): slot e of the MFMA for (jt, ct) holds
+  //      W[16 ct + 4 ig + pair_row(e)][16 jt + jl]; each row meets the hi and the lo part.
   h8_t wf[CT][CT];
   {
     const bf16_raw *Wn = (const bf16_raw *)a.W + (size_t)n * V * V;
@@ -88,21 +88,13 @@ __global__ void __launch_bounds__(RW::THREADS, 2) rowwave_fwd_kernel(FwdArgs a) 
 #pragma unroll
       for (int ct = 0; ct < CT; ++ct)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const _Float16 w =
-              (_Float16)bf16_to_f32(Wn[(size_t)(16 * ct + 4 * ig + e) * V + 16 * jt + jl]);
-          wf[jt][ct][2 * e] = w;
-          wf[jt][ct][2 * e + 1] = w;
-        }
+        for (int e = 0; e < 8; ++e)
+          wf[jt][ct][e] = (_Float16)bf16_to_f32(Wn[(size_t)(16 * ct + 4 * ig + pair_row(e)) * V + 16 * jt + jl]);
   }
-  // identity fragment: B[slot][n] = 1 for both slots of column 4 ig + e when that column is n
+  // identity fragment: B[slot][n] = 1 for both slots of a column when that column is n
   h8_t ident;
 #pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    const _Float16 one = (4 * ig + e == jl) ? (_Float16)1.0f : (_Float16)0.0f;
-    ident[2 * e] = one;
-    ident[2 * e + 1] = one;
-  }
+  for (int e = 0; e < 8; ++e) ident[e] = (_Float16)(4 * ig + pair_row(e) == jl ? 1.f : 0.f);
 
   // ---- state: lane (row, ig) holds columns 16 ct + 4 ig + r, scaled by c
   const size_t st_off = (size_t)unit * K * V + (size_t)row * V + 4 * ig;
@@ -170,14 +162,7 @@ __global__ void __launch_bounds__(RW::THREADS, 2) rowwave_fwd_kernel(FwdArgs a) 
   stage_load(0);
   stage_store(0);
 
-  auto frag_of = [&](const float *hc) {
-    uint4 pk;
-    pk.x = split_hi_lo(hc[0]);
-    pk.y = split_hi_lo(hc[1]);
-    pk.z = split_hi_lo(hc[2]);
-    pk.w = split_hi_lo(hc[3]);
-    return __builtin_bit_cast(h8_t, pk);
-  };
+  auto frag_of = [&](const float (&hc)[4]) { return __builtin_bit_cast(h8_t, split4_hi_lo(hc)); };
 
   // ---- contraction for the first step from the initial state, all tiles but the last;
   //      the last tile's slice is added at the top of the step (software pipeline)
