@@ -60,17 +60,22 @@ struct RowWaveB {
   // the end-of-chunk partials
   static constexpr int OFF_Q = 0;                       // float q     [CB][K]
   static constexpr int OFF_CK = OFF_Q + CB * K * 4;     // float c k   [CB][K]
-  static constexpr int OFF_KH = OFF_CK + CB * K * 4;    // half  k     [CB][K]
-  static constexpr int OFF_VH = OFF_KH + CB * K * 2;    // half  v     [CB][V]
+  // Operands of the products over two steps: 16-byte items (4 values; zeros), in odd steps (zeros; 4
+  // values), the items of a step's dy (scaled), v and k in a row.  A lane whose row of the operand is
+  // another step's reads zeros at the same offsets behind OFF_ZERO.
+  static constexpr int OP_V = 64, OP_K = 128, OP_STEP = OP_K + 4 * K;
+  static constexpr int OFF_OP = OFF_CK + CB * K * 4;    // half dy, v, k [CB][OP_STEP bytes]
+  static constexpr int OFF_ZERO = OFF_OP + CB * OP_STEP;  // [OP_STEP] zero bytes
+  static constexpr int OFF_VH = OFF_ZERO + OP_STEP;     // half  v     [CB][V]
   static constexpr int OFF_DY = OFF_VH + CB * V * 2;    // float dy    [CB][V]
-  static constexpr int OFF_DYH = OFF_DY + CB * V * 4;   // half  dy scaled per step [CB][V]
-  static constexpr int OFF_F = OFF_DYH + CB * V * 2;    // per step: f, c(1-f), 1-f, f16x2 -(1-f)/c^2,
+  static constexpr int OFF_F = OFF_DY + CB * V * 4;     // per step: f, c(1-f), 1-f, f16x2 -(1-f)/c^2,
                                                         //           1/(dy scale), 3 pad (8 floats)
-  static constexpr int OFF_ZERO = OFF_F + CB * 32;      // 16 zero bytes (masked operand reads)
-  static constexpr int OFF_HS = OFF_ZERO + 16;          // [NW][CB][512] stash of H'_{t-1} (fp16 tiles)
+  static constexpr int OFF_HS = OFF_F + CB * 32;        // [NW][CB][512] stash of H'_{t-1} (fp16 tiles)
   static constexpr int OFF_TR = OFF_HS + NW * CB * 512; // [NW][512] transposition scratch of dS
-  static constexpr int OFF_PV = OFF_TR + NW * 512;      // [NW][64] f4: dv (at the end dW) partials
-  static constexpr int OFF_PF = OFF_PV + NW * 1024;     // [NW][16] float: df partials
+  // [NW][64] f4: dv (at the end dW) partials, over the stash, which nobody reads between a chunk's sweep
+  // and the barrier in front of the next chunk
+  static constexpr int OFF_PV = OFF_HS;
+  static constexpr int OFF_PF = OFF_TR + NW * 512;      // [NW][16] float: df partials
   static constexpr int BYTES = OFF_PF + NW * 64;
   // (K = 64, the paper's shape: three workgroups per CU)
   static_assert(BYTES <= kLdsLimit && (K > 64 || 3 * BYTES <= kLdsLimit), "LDS layout");
@@ -89,6 +94,18 @@ __device__ __forceinline__ h4_t cvt4_f16(const float (&x)[4]) {
   p.x = __builtin_bit_cast(uint32_t, __builtin_convertvector(a01, h2_t));
   p.y = __builtin_bit_cast(uint32_t, __builtin_convertvector(a23, h2_t));
   return __builtin_bit_cast(h4_t, p);
+}
+
+__device__ __forceinline__ h8_t join(h4_t lo, h4_t hi) { return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7); }
+
+// Two values per lane summed over pairs of lanes that differ in one bit, a for the lane with the bit
+// clear and b for the other: CTRL takes each lane to one that has the other bit.  Four levels of this
+// sum 16 values over 16 lanes with 45 instructions, where a 16x16x4 fp32 product against ones takes 32
+// cycles of the matrix core for each of them.
+template <int CTRL>
+__device__ __forceinline__ float lane_sum(float a, float b, bool bit) {
+  const float keep = bit ? b : a, give = bit ? a : b;
+  return keep + __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, give), CTRL, 0xF, 0xF, true));
 }
 
 template <typename RW, bool CLIP>
@@ -110,14 +127,15 @@ __global__ void __launch_bounds__(RW::THREADS, 3) rowwave_bwd_kernel(BwdArgs a, 
   lchar *const l0 = (lchar *)lds;
   float *qS = (float *)(lds + RW::OFF_Q);
   float *ckS = (float *)(lds + RW::OFF_CK);
-  _Float16 *kH = (_Float16 *)(lds + RW::OFF_KH);
   _Float16 *vH = (_Float16 *)(lds + RW::OFF_VH);
   float *dyS = (float *)(lds + RW::OFF_DY);
-  _Float16 *dyH = (_Float16 *)(lds + RW::OFF_DYH);
   float *fS = (float *)(lds + RW::OFF_F);
   f4_t *pv = (f4_t *)(lds + RW::OFF_PV);
   float *pf = (float *)(lds + RW::OFF_PF);
-  if (tid < 4) ((uint32_t *)(lds + RW::OFF_ZERO))[tid] = 0u;  // visible after the first barrier
+  // zeros: the pad, and the zero halves of the operand items, which stay (visible after the first barrier)
+  for (int i = tid; i < (RW::OFF_VH - RW::OFF_OP) / 16; i += THREADS)
+    *(u4_t *)(lds + RW::OFF_OP + 16 * i) = u4_t{0u, 0u, 0u, 0u};
+  __syncthreads();
 
   const bf16_raw *__restrict__ qg = (const bf16_raw *)a.q;
   const bf16_raw *__restrict__ kg = (const bf16_raw *)a.k;
@@ -186,6 +204,8 @@ __global__ void __launch_bounds__(RW::THREADS, 3) rowwave_bwd_kernel(BwdArgs a, 
   auto stage_wait = [&]() {  // (pins the point where the loads are waited for)
     asm volatile("" : "+v"(rqk), "+v"(rvd), "+v"(rf), "+v"(hck));
   };
+  // the value halves of a step's operand items (every second h4_t from here)
+  auto op_items = [&](int s, int off) { return (h4_t *)(lds + RW::OFF_OP + s * RW::OP_STEP + off + (s & 1) * 8); };
   auto stage_store = [&](int len) {
     float x[8];
     {
@@ -199,10 +219,10 @@ __global__ void __launch_bounds__(RW::THREADS, 3) rowwave_bwd_kernel(BwdArgs a, 
       const int e = tid - QI;
       *(f4_t *)&ckS[8 * e] = f4_t{x[0], x[1], x[2], x[3]} * kC;
       *(f4_t *)&ckS[8 * e + 4] = f4_t{x[4], x[5], x[6], x[7]} * kC;
-      h8_t hv;
-#pragma unroll
-      for (int i = 0; i < 8; ++i) hv[i] = (_Float16)x[i];
-      *(h8_t *)&kH[8 * e] = hv;
+      float x0[4] = {x[0], x[1], x[2], x[3]}, x1[4] = {x[4], x[5], x[6], x[7]};
+      h4_t *op = op_items(e / RL, RW::OP_K) + 4 * (e % RL);
+      op[0] = cvt4_f16(x0);
+      op[2] = cvt4_f16(x1);
     }
     if (tid < 64) {  // (wave 0: uniform)
       const int e = tid & 31;
@@ -215,18 +235,17 @@ __global__ void __launch_bounds__(RW::THREADS, 3) rowwave_bwd_kernel(BwdArgs a, 
       for (int i = 0; i < 8; ++i) mx = fmaxf(mx, fabsf(x[i]));
       const int ex = ilog2f(fminf(fmaxf(group_max_nonneg<2>(mx), 1e-30f), 1e30f));
       const float up = pow2i(10 - ex);
-      h8_t hv, hs;
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        hv[i] = (_Float16)x[i];
-        hs[i] = (_Float16)(x[i] * up);
-      }
+      const float sx = tid < 32 ? 1.f : up;
+      float x0[4] = {sx * x[0], sx * x[1], sx * x[2], sx * x[3]}, x1[4] = {sx * x[4], sx * x[5], sx * x[6], sx * x[7]};
+      const h4_t o0 = cvt4_f16(x0), o1 = cvt4_f16(x1);
+      h4_t *op = op_items(e >> 1, tid < 32 ? RW::OP_V : 0) + 4 * (e & 1);
+      op[0] = o0;
+      op[2] = o1;
       if (tid < 32) {
-        *(h8_t *)&vH[8 * e] = hv;
+        *(h8_t *)&vH[8 * e] = __builtin_shufflevector(o0, o1, 0, 1, 2, 3, 4, 5, 6, 7);
       } else {
         *(f4_t *)&dyS[8 * e] = f4_t{x[0], x[1], x[2], x[3]};
         *(f4_t *)&dyS[8 * e + 4] = f4_t{x[4], x[5], x[6], x[7]};
-        *(h8_t *)&dyH[8 * e] = hs;
         if ((e & 1) == 0) fS[(e >> 1) * 8 + 4] = pow2i(ex - 10);
       }
       if (tid < CB) {
@@ -329,12 +348,14 @@ __global__ void __launch_bounds__(RW::THREADS, 3) rowwave_bwd_kernel(BwdArgs a, 
     // is base + compile-time immediate.  The lane's column index is opaque as well: the
     // per-step masks (jl == s) are then built per step instead of being kept for every s.
     lchar *bRow4 = l0 + row * 4;            // q, c k (fp32) of this lane's row
-    lchar *bRow2 = l0 + (rb * 16 + 4 * ig) * 2;  // k (fp16) rows 4 ig .. of the block
-    lchar *bCol2 = l0 + 4 * ig * 2;         // v, dy (fp16) columns 4 ig ..
+    lchar *bOp = l0 + (jl * RW::OP_STEP + ig * 16 + RW::OFF_OP);  // operand items of step jl, columns (rows) 4 ig ..
+    lchar *bOp0 = l0 + (ig * 16 + RW::OFF_ZERO);                  // ... and the zeros in their place
+    lchar *bCol2 = l0 + 4 * ig * 2;         // v (fp16) columns 4 ig ..
     lchar *bCol4 = l0 + 4 * ig * 4;         // dy (fp32) columns 4 ig ..
-    lchar *bZero = l0;                      // wave-uniform reads (f), the zero pad
+    lchar *bZero = l0;                      // wave-uniform reads (f)
     int jlo = jl;
-    asm volatile("" : "+v"(bRow4), "+v"(bRow2), "+v"(bCol2), "+v"(bCol4), "+v"(bZero), "+v"(jlo));
+    asm volatile("" : "+v"(bRow4), "+v"(bOp), "+v"(bOp0), "+v"(bCol2), "+v"(bCol4), "+v"(bZero), "+v"(jlo));
+    auto op_base = [&](int s) __attribute__((always_inline)) { return jlo >> 1 == s >> 1 ? bOp : bOp0; };
 
     // ---- 1. recompute the chunk; the stash stays in registers
     h4_t zpS[CB];
@@ -364,20 +385,24 @@ __global__ void __launch_bounds__(RW::THREADS, 3) rowwave_bwd_kernel(BwdArgs a, 
             h[r] = fmaf(m2g, rr, t1);
           }
           zpS[s] = cvt4_f16(z);
+          const h4_t hbefore = hcur;
           hcur = cvt4_f16(h);
-          // dq_s = H_s dy_s: A[m = s][k = j] = dy_j (row s only), B[k = j][n = i] = H_s
-          const h4_t dyf = lds_ld<h4_t>(jlo == s ? bCol2 + (RW::OFF_DYH + s * V * 2) : bZero + RW::OFF_ZERO, 0);
-          dqacc = mfma_k16(dyf, hcur, dqacc);
+          // dq = H dy of two steps: A[m = s][k = j] = dy_j, B[k = j][n = i] = H_s in the first four
+          // slots for the even step, in the last four for the odd one; zeros in all other rows
+          if (s & 1) dqacc = mfma_k32(lds_ld<h8_t>(op_base(s), 0), join(hbefore, hcur), dqacc);
         }
         settle(dqacc);
       }
     }
 
     // ---- 2. sweep in reverse
-    f4_t dkacc = zero4, dvacc = zero4, dfacc = zero4;
+    f4_t dkacc = zero4, dvacc = zero4;
+    float dfb[CB / 4] = {};  // df: lane jl holds step 4 blk + jl % 4, summed over its quad of lanes
 #pragma unroll
     for (int blk = CB / 4 - 1; blk >= 0; --blk) {
       if (4 * blk < len) {
+        h4_t ds1, dT1, hT1;  // the odd step of a pair
+        float df1 = 0.f, dfp = 0.f;
 #pragma unroll
         for (int s4 = 3; s4 >= 0; --s4) {
           const int s = 4 * blk + s4;
@@ -392,9 +417,6 @@ __global__ void __launch_bounds__(RW::THREADS, 3) rowwave_bwd_kernel(BwdArgs a, 
           const h4_t zp = zpS[s];
           const h4_t hown = lds_ld<h4_t>(hsw, s * 512);
           const h4_t hT = lds_tr16(hsr, s * 512);
-          const bool mine = jlo == s;
-          const h4_t vfr = lds_ld<h4_t>(mine ? bCol2 + (RW::OFF_VH + s * V * 2) : bZero + RW::OFF_ZERO, 0);
-          const h4_t kfr = lds_ld<h4_t>(mine ? bRow2 + (RW::OFF_KH + s * K * 2) : bZero + RW::OFF_ZERO, 0);
           // H' - Z' and w = (1-f) Z^2 in packed fp16
           const h4_t hz = hown - zp;
           const h4_t ug = (zp * m4) * zp;  // = -w
@@ -411,8 +433,6 @@ __global__ void __launch_bounds__(RW::THREADS, 3) rowwave_bwd_kernel(BwdArgs a, 
           // off the chain: the two tiles with rows in the registers, for dW and dv
           lds_st<h4_t>(trw, 0, dsp);
           const h4_t dT = lds_tr16(trr, 0);
-          // dk_s = dS v_s: A[m = s][k = j] = v_j (row s only), B[k = j][n = i] = dS
-          dkacc = mfma_k16(vfr, dsp, dkacc);
 #pragma unroll
           for (int r = 0; r < 4; ++r) carry[r] = fmaf(f, G[r], d[r]);
           if constexpr (CLIP) {
@@ -421,17 +441,30 @@ __global__ void __launch_bounds__(RW::THREADS, 3) rowwave_bwd_kernel(BwdArgs a, 
 #pragma unroll
             for (int r = 0; r < 4; ++r) carry[r] = __builtin_amdgcn_fmed3f(carry[r], -cb, cb);
           }
-          // dW' += H'^T dS: A[m = j1][k = i] = H'[i][j1], B[k = i][n = j2] = dS[i][j2]
-          dWacc = mfma_k16(hT, dT, dWacc);
-          // dv_s = dS^T k_s: A[m = s][k = i] = k_i (row s only), B[k = i][n = j] = dS
-          dvacc = mfma_k16(kfr, dT, dvacc);
-          // df_s = sum G (H' - Z') / c: the fp32 MFMA against ones in column s adds the four lane
-          // groups; the 16 rows of that column are added at the end of the chunk
-          dfacc = __builtin_amdgcn_mfma_f32_16x16x4f32(dfl, mine ? 1.f : 0.f, dfacc, 0, 0, 0);
+          if (s & 1) {
+            ds1 = dsp;
+            dT1 = dT;
+            hT1 = hT;
+            df1 = dfl;
+          } else {
+            // two steps at once, the even one in the first four slots (half of a 16x16x32 product would
+            // be empty with one, at the same cost):
+            // dk = dS v:     A[m = s][k = j] = v_j,     B[k = j][n = i] = dS
+            // dv = dS^T k:   A[m = s][k = i] = k_i,     B[k = i][n = j] = dS
+            // dW' += H'^T dS: A[m = j1][k = i] = H'[i][j1], B[k = i][n = j2] = dS[i][j2]
+            const lchar *op = op_base(s);
+            const h8_t dT2 = join(dT, dT1);
+            dkacc = mfma_k32(lds_ld<h8_t>(op, RW::OP_V), join(dsp, ds1), dkacc);
+            dvacc = mfma_k32(lds_ld<h8_t>(op, RW::OP_K + rb * 64), dT2, dvacc);
+            dWacc = mfma_k32(join(hT, hT1), dT2, dWacc);
+            // df = sum G (H' - Z') / c over the lanes, each lane of a quad one step of the block
+            const float y = lane_sum<0xB1>(dfl, df1, jlo & 1);
+            if (s4 == 2) dfp = y;
+            else dfb[blk] = lane_sum<0x4E>(y, dfp, jlo & 2);
+          }
         }
         settle(dkacc);
         settle(dvacc);
-        settle(dfacc);
         settle(dWacc);
       }
     }
@@ -465,7 +498,9 @@ __global__ void __launch_bounds__(RW::THREADS, 3) rowwave_bwd_kernel(BwdArgs a, 
     // dv, df: partials of the row blocks meet in LDS
     pv[rb * 64 + lane] = dvacc * isc;
     {
-      float x = (dfacc[0] + dfacc[1]) + (dfacc[2] + dfacc[3]);
+      // (a rotation by 4 meets the other half's quad in place of the own half's: over the rotation by 8
+      //  every lane has met all four quads)
+      float x = lane_sum<0x128>(lane_sum<0x124>(dfb[0], dfb[1], jl & 4), lane_sum<0x124>(dfb[2], dfb[3], jl & 4), jl & 8);
       x += __shfl_xor(x, 16, 64);
       x += __shfl_xor(x, 32, 64);
       if (lane < 16) pf[rb * 16 + lane] = x * (kInvC * isc);
