@@ -72,9 +72,9 @@ struct RowWaveB {
                                                         //           1/(dy scale), 3 pad (8 floats)
   static constexpr int OFF_HS = OFF_F + CB * 32;        // [NW][CB][512] stash of H'_{t-1} (fp16 tiles)
   static constexpr int OFF_TR = OFF_HS + NW * CB * 512; // [NW][512] transposition scratch of dS
-  // [NW][64] f4: dv (at the end dW) partials, over the stash, which nobody reads between a chunk's sweep
-  // and the barrier in front of the next chunk
-  static constexpr int OFF_PV = OFF_HS;
+  // [NW] 64 f4, PV_WAVE apart: a wave's dv (at the end dW) partials, at the head of its own stash, which
+  // it does not read between a chunk's sweep and the barrier in front of the next chunk
+  static constexpr int OFF_PV = OFF_HS, PV_WAVE = CB * 512 / 16;
   static constexpr int OFF_PF = OFF_TR + NW * 512;      // [NW][16] float: df partials
   static constexpr int BYTES = OFF_PF + NW * 64;
   // (K = 64, the paper's shape: three workgroups per CU)
@@ -496,7 +496,7 @@ __global__ void __launch_bounds__(RW::THREADS, 3) rowwave_bwd_kernel(BwdArgs a, 
       }
     }
     // dv, df: partials of the row blocks meet in LDS
-    pv[rb * 64 + lane] = dvacc * isc;
+    pv[rb * RW::PV_WAVE + lane] = dvacc * isc;
     {
       // (a rotation by 4 meets the other half's quad in place of the own half's: over the rotation by 8
       //  every lane has met all four quads)
@@ -517,7 +517,7 @@ __global__ void __launch_bounds__(RW::THREADS, 3) rowwave_bwd_kernel(BwdArgs a, 
       // dv: accumulator [m = step][n = column]: lane (jl, ig) holds column jl, steps 4 ig + r
       f4_t d = pv[lane];
 #pragma unroll
-      for (int w = 1; w < NW; ++w) d += pv[w * 64 + lane];
+      for (int w = 1; w < NW; ++w) d += pv[w * RW::PV_WAVE + lane];
       float wr = 0.f;
       if (a.w_r) wr = bf16_to_f32(((const bf16_raw *)a.w_r)[n * V + jl]);
 #pragma unroll
@@ -541,13 +541,13 @@ __global__ void __launch_bounds__(RW::THREADS, 3) rowwave_bwd_kernel(BwdArgs a, 
   // ---- outputs of the whole sweep
   if (a.dH0) *(f4_t *)&a.dH0[st_off] = f4_t{carry[0], carry[1], carry[2], carry[3]} * isc;
   lds_barrier();  // wave 0 is done with the last chunk's partials
-  pv[rb * 64 + lane] = dWacc * (kInvC * isc);
+  pv[rb * RW::PV_WAVE + lane] = dWacc * (kInvC * isc);
   lds_barrier();
   if (rb == 0) {
     // dW: accumulator [m = j1][n = j2]: lane (jl, ig) holds dW[4 ig + r][jl]
     f4_t d = pv[lane];
 #pragma unroll
-    for (int w = 1; w < NW; ++w) d += pv[w * 64 + lane];
+    for (int w = 1; w < NW; ++w) d += pv[w * RW::PV_WAVE + lane];
     float *dst = ws.dWp + (size_t)unit * V * V;
 #pragma unroll
     for (int r = 0; r < 4; ++r) dst[(4 * ig + r) * V + jl] = d[r];
