@@ -614,7 +614,8 @@ __global__ void __launch_bounds__(2 * TL::THREADS, 2) mfma_bwd_overlap_kernel(Bw
 #pragma unroll
       for (int c2 = 0; c2 < CT; ++c2) dWacc[c2] *= ratio;
     }
-    f4_t dkacc = zero4, dvacc = zero4, dfacc = zero4;
+    f4_t dkacc = zero4, dvacc = zero4;
+    float dfacc = 0.f;  // df of step jl, summed over the rows and columns of the lane group
     float G[4] = {0.f, 0.f, 0.f, 0.f};
     float fprev = 0.f;
     // LDS addressing of this team: a few per-lane base offsets, made opaque once per chunk so
@@ -735,9 +736,11 @@ __global__ void __launch_bounds__(2 * TL::THREADS, 2) mfma_bwd_overlap_kernel(Bw
         dWacc[c2] = mfma_k16(hfr[c2], dsp, dWacc[c2]);
       }
       dvacc = mfma_k16(kfr, dsp, dvacc);
-      // df_s = sum G (H' - Z') / c: fp32 MFMA against ones in column s adds the four lane
-      // groups; the 16 rows of that column are added at the end of the chunk
-      dfacc = __builtin_amdgcn_mfma_f32_16x16x4f32(dfl, mine ? 1.f : 0.f, dfacc, 0, 0, 0);
+      // df_s = sum G (H' - Z') / c over the lane group, kept by one of its lanes; the four groups are
+      // added at the end of the chunk.  (A 16x16x4 fp32 product against ones takes the matrix core 32
+      // cycles, which the vector ALU of the SIMD spends waiting.)
+      const float dfs = row_sum(dfl);  // (in every lane: the exchange reads nothing from a lane that is switched off)
+      dfacc = mine ? dfs : dfacc;
       fprev = f;
     };
     // Super-step u sweeps chunk step len - 1 - u (E1) and finishes step len - u (R2).
@@ -808,7 +811,7 @@ __global__ void __launch_bounds__(2 * TL::THREADS, 2) mfma_bwd_overlap_kernel(Bw
     if (active) {
       if (ct < KS) fink[(rb * KS + ct) * 64 + ll] = dkacc * isc;
       finv[wave * 64 + ll] = dvacc * isc;
-      float x = (dfacc[0] + dfacc[1]) + (dfacc[2] + dfacc[3]);
+      float x = dfacc;
       x += __shfl_xor(x, 16, 64);
       x += __shfl_xor(x, 32, 64);
       if (ll < 16 && (int)jl2 < len) {

@@ -179,6 +179,15 @@ __device__ __forceinline__ float group_max_nonneg(float x) {
   }
   return __builtin_bit_cast(float, v);
 }
+// Sum over each group of 16 lanes, in all of them.
+__device__ __forceinline__ float row_sum(float x) {
+  auto add = [](float y, int moved) { return y + __builtin_bit_cast(float, moved); };
+  x = add(x, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0xB1, 0xF, 0xF, true));   // lane xor 1
+  x = add(x, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0x4E, 0xF, 0xF, true));   // lane xor 2
+  x = add(x, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0x124, 0xF, 0xF, true));  // rotated by 4
+  x = add(x, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0x128, 0xF, 0xF, true));  // rotated by 8
+  return x;
+}
 // eight bf16 values (one 16-byte load) widened to fp32
 __device__ __forceinline__ void bf16x8_to_f32(const u4_t &w, float (&x)[8]) {
 #pragma unroll
