@@ -20,11 +20,13 @@
 //        holds each row of W twice) -- these run on the matrix core while the
 //       vector ALU does E of the next tile.
 // Readout y_t = H_t^T q_t contracts over the rows, which are the lane index in
-// this layout.  The matrix core does the transpose: the tile's (hi, lo)
-// fragment times an identity fragment gives H' with rows in the registers and
-// columns across lanes, which (as fp16) is the A operand of a 16x16x16 MFMA
-// with q.  The K/16 row-block partials of a state are summed once per 16 steps
-// through LDS and stored as whole bf16 rows.
+// this layout.  The tile, rounded to fp16, takes a wave-private trip through LDS and comes
+// back by the transposing load with rows in the registers and columns across lanes, the A
+// operand of a 16x16x16 MFMA with q; that product follows in the middle of the next step.  (A
+// product with an identity fragment transposes as well, but takes 16 cycles of the matrix core a
+// tile, which add to the vector work: matrix and vector instructions of a SIMD hardly overlap.)
+// The K/16 row-block partials of a state are summed once per 16 steps through LDS and stored as
+// whole bf16 rows.
 #include "m2rnn_kernels.hpp"
 #include "m2rnn_mfma_common.hpp"
 
@@ -46,7 +48,8 @@ struct RowWave {
   static constexpr int OFF_V = OFF_Q + TB * K * 2;
   static constexpr int OFF_F = OFF_V + TB * V * 2;
   static constexpr int OFF_Y = 2 * STG;                          // [2][NW][TB][V] f32
-  static constexpr int BYTES = OFF_Y + 2 * NW * TB * V * 4;
+  static constexpr int OFF_T = OFF_Y + 2 * NW * TB * V * 4;      // [NW][CT] fp16 tiles on their way to the readout
+  static constexpr int BYTES = OFF_T + NW * CT * 512;
   static_assert(STG % 16 == 0 && BYTES <= kLdsLimit, "LDS layout");
 };
 
@@ -91,10 +94,11 @@ __global__ void __launch_bounds__(RW::THREADS, 2) rowwave_fwd_kernel(FwdArgs a) 
         for (int e = 0; e < 8; ++e)
           wf[jt][ct][e] = (_Float16)bf16_to_f32(Wn[(size_t)(16 * ct + 4 * ig + pair_row(e)) * V + 16 * jt + jl]);
   }
-  // identity fragment: B[slot][n] = 1 for both slots of a column when that column is n
-  h8_t ident;
-#pragma unroll
-  for (int e = 0; e < 8; ++e) ident[e] = (_Float16)(4 * ig + pair_row(e) == jl ? 1.f : 0.f);
+  // transposition of the readout's tiles: the 8-byte item (row, 4 columns) of a lane, and the one it
+  // addresses for the transposing load, placed so that both spread evenly over the banks
+  const int gs = jl & 3, is = 4 * ig + (jl >> 2);
+  lchar *const trw = (lchar *)lds + RW::OFF_T + rb * CT * 512 + (16 * ig + ((jl + 4 * ig) & 15)) * 8;
+  const lchar *const trr = (lchar *)lds + RW::OFF_T + rb * CT * 512 + (16 * gs + ((is + 4 * gs) & 15)) * 8;
 
   // ---- state: lane (row, ig) holds columns 16 ct + 4 ig + r, scaled by c
   const size_t st_off = (size_t)unit * K * V + (size_t)row * V + 4 * ig;
@@ -189,6 +193,18 @@ __global__ void __launch_bounds__(RW::THREADS, 2) rowwave_fwd_kernel(FwdArgs a) 
     const bool more = blk + 1 < nblk;
     if (more) stage_load(t0 + TB);
 
+    h4_t tr[CT], qtr;  // readout operands of the step before
+    // D[m = j][*] = c sum_i q_i H[i][j] of step s
+    auto readout = [&](int s) __attribute__((always_inline)) {
+      float *yrow = &yacc[((sb * NW + rb) * TB + s) * V + 4 * ig];
+      f4_t yv[CT];
+#pragma unroll
+      for (int ct = 0; ct < CT; ++ct) yv[ct] = mfma_k16(tr[ct], qtr, f4_t{0.f, 0.f, 0.f, 0.f});
+      if (jl == 0) {
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct) *(f4_t *)&yrow[16 * ct] = yv[ct];
+      }
+    };
     auto step = [&](int s) __attribute__((always_inline)) {
       const int t = t0 + s;
       if (a.ckpt && t == next_ck) {  // state before step t
@@ -213,13 +229,13 @@ __global__ void __launch_bounds__(RW::THREADS, 2) rowwave_fwd_kernel(FwdArgs a) 
       for (int ct = 0; ct < CT; ++ct) vfr[ct] = *(const h4_t *)&vH(sb)[s * V + 16 * ct + 4 * ig];
       h4_t qfr;
       if (DO_Y) qfr = *(const h4_t *)&qH(sb)[s * K + rb * 16 + 4 * ig];
-      float *yrow = &yacc[((sb * NW + rb) * TB + s) * V + 4 * ig];
 
       // last tile's slice of this step's contraction (tile 0 first: it is needed first)
 #pragma unroll
       for (int jt = 0; jt < CT; ++jt) acc[jt] = mfma_k32(wf[jt][CT - 1], hfL, acc[jt]);
 
-      f4_t nx[CT], tr[CT];
+      if (DO_Y && s > 0) readout(s - 1);
+      f4_t nx[CT];
 #pragma unroll
       for (int ct = 0; ct < CT; ++ct) {
         // E: tile ct
@@ -237,32 +253,21 @@ __global__ void __launch_bounds__(RW::THREADS, 2) rowwave_fwd_kernel(FwdArgs a) 
         } else {
           hfL = hf;
         }
-        // transpose on the matrix core: D[m = i][n = j] = hi + lo of H'[i][j]
-        if (DO_Y) tr[ct] = mfma_k32(hf, ident, f4_t{0.f, 0.f, 0.f, 0.f});
-      }
-      if (DO_Y) {
-        typedef float f2_t __attribute__((ext_vector_type(2)));
-        f4_t yv[CT];
-#pragma unroll
-        for (int ct = 0; ct < CT; ++ct) {
-          const f2_t a01 = {tr[ct][0], tr[ct][1]}, a23 = {tr[ct][2], tr[ct][3]};
-          uint2 tp;
-          tp.x = __builtin_bit_cast(uint32_t, __builtin_convertvector(a01, h2_t));
-          tp.y = __builtin_bit_cast(uint32_t, __builtin_convertvector(a23, h2_t));
-          // D[m = j][*] = c sum_i q_i H[i][j]
-          yv[ct] = mfma_k16(__builtin_bit_cast(h4_t, tp), qfr, f4_t{0.f, 0.f, 0.f, 0.f});
-        }
-        if (jl == 0) {
-#pragma unroll
-          for (int ct = 0; ct < CT; ++ct) *(f4_t *)&yrow[16 * ct] = yv[ct];
+        if (DO_Y) {
+          typedef float f2_t __attribute__((ext_vector_type(2)));
+          const f2_t a01 = {h[ct][0], h[ct][1]}, a23 = {h[ct][2], h[ct][3]};
+          lds_st<u2_t>(trw, ct * 512, u2_t{__builtin_bit_cast(uint32_t, __builtin_convertvector(a01, h2_t)),
+                                           __builtin_bit_cast(uint32_t, __builtin_convertvector(a23, h2_t))});
+          tr[ct] = lds_ld_tr(trr, ct * 512);
         }
       }
+      qtr = qfr;
 #pragma unroll
       for (int jt = 0; jt < CT; ++jt) acc[jt] = (CT > 1) ? nx[jt] : f4_t{0.f, 0.f, 0.f, 0.f};
       // scheduling hint: spread the matrix-core instructions between vector-ALU work
       // instead of issuing them back to back (a lone wave stalls behind a busy matrix core)
 #pragma unroll
-      for (int i = 0; i < (DO_Y ? 6 : 4) * CT; ++i) {
+      for (int i = 0; i < (DO_Y ? 5 : 4) * CT; ++i) {
         __builtin_amdgcn_sched_group_barrier(0x002, 6, 0);  // VALU
         __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // MFMA
       }
@@ -277,6 +282,7 @@ __global__ void __launch_bounds__(RW::THREADS, 2) rowwave_fwd_kernel(FwdArgs a) 
     } else {
       for (int s = 0; s < len; ++s) step(s);
     }
+    if (DO_Y) readout(len - 1);
     lds_barrier();  // y partials of this block and the next block's staging are complete
     if (DO_Y) {
       // flush: sum the row-block partials, store whole bf16 rows (4 values per thread)
