@@ -26,8 +26,8 @@
 //      split H' into (hi, lo), write the fragment to LDS, start the next step's
 //      contraction with the own tile; one barrier.
 //   Y  readout without leaving the step loop.  It contracts over the rows of H,
-//      which are spread over lanes here, so the tile is first transposed by an
-//      MFMA with an identity operand (exact), then one 16x16x16 MFMA with
+//      which are spread over lanes here, so the tile's hi parts take a way through
+//      LDS to the transposing load, then one 16x16x16 MFMA with
 //      A = hi of the transposed tile (k = rows) and B = q placed in column
 //      (t mod 16) only.  The accumulator is kept for 16 steps, so column s of
 //      it collects c sum_i q_i H[i][j] of step s; nothing is read back per step.
@@ -51,6 +51,7 @@ struct FwdSmem {
   alignas(16) float vS[2][TB][TL::V];
   alignas(16) float fS[2][TB][4];                  // f, c(1-f), unused, unused
   alignas(16) f4_t yB[TL::RB][TL::CT][64];         // readout accumulators of one block
+  alignas(16) u2_t tr[TL::WAVES][64];              // hi parts on their way to the readout
 };
 
 // (Second launch bound: at least two waves per SIMD, i.e. at most 256 registers.  With the
@@ -128,10 +129,11 @@ __global__ void __launch_bounds__(TL::THREADS, 2)
   int hx_off[CT];
 #pragma unroll
   for (int d = 0; d < CT; ++d) hx_off[d] = ((rb * CT + (ct + d) % CT) * 64 + lane) * 16;
-  // identity operand of the transposing MFMA: B[k = 4 ig + r][n = jl] = (k == n)
-  h4_t ident;
-#pragma unroll
-  for (int r = 0; r < 4; ++r) ident[r] = (_Float16)((4 * ig + r == jl) ? 1.f : 0.f);
+  // the tile's way through LDS for the readout: the 8-byte item (row, 4 columns) of a lane, and the one it
+  // addresses for the transposing load, placed so that both spread evenly over the banks
+  const int gs = jl & 3, is = 4 * ig + (jl >> 2);
+  lchar *const trw = (lchar *)&sm.tr[wave][0] + (16 * ig + ((jl + 4 * ig) & 15)) * 8;
+  const lchar *const trr = (lchar *)&sm.tr[wave][0] + (16 * gs + ((is + 4 * gs) & 15)) * 8;
 
   // ---- staging of q, k, v, f (TB steps per block)
   bf16_raw rq[NQ], rk[NQ], rv[NV];
@@ -246,31 +248,27 @@ __global__ void __launch_bounds__(TL::THREADS, 2)
     settle(x.acc);
   };
   // E: tanh, gate, split, fragment into exchange buffer `buf`, own-tile product of the next step
-  auto step_E = [&](const StepRegs &x, u4_t &fr, int buf) __attribute__((always_inline)) {
+  auto step_E = [&](const StepRegs &x, int buf) __attribute__((always_inline)) {
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const float sp = fmaf(x.kk, x.v4[r], x.acc[r]);
       h[r] = gate_tanh_step(x.f, x.gp, h[r], sp);
     }
-    fr = split4_hi_lo(h);
+    const u4_t fr = split4_hi_lo(h);
     lds_st<u4_t>(hx + hx_off[0], buf * HXBUF, fr);
+    if constexpr (DO_Y) lds_st<u2_t>(trw, 0, u2_t{fr[0], fr[2]});
     acc_own = mfma_k32(wf[0], __builtin_bit_cast(h8_t, fr), zero4);
   };
-  // Y: readout on the matrix core.  The tile's hi parts are the A operand [m = i][k = j] as
-  //    they stand; times the identity gives them back with rows in registers and columns in
-  //    lanes (exact: products with 1 and 0).  Then A[m = j][k = i] = hi(H'[i][j]);
-  //    B[k = i][n] = q_i for n == s, else 0: column s of yacc collects step s.
+  // Y: readout on the matrix core.  The tile's hi parts come back from LDS with rows in registers and
+  //    columns in lanes: A[m = j][k = i] = hi(H'[i][j]); B[k = i][n] = q_i for n == s, else 0: column s
+  //    of yacc collects step s.  (A product with the identity transposes too, for 16 more cycles of the
+  //    matrix core, which hardly overlap the SIMD's vector work.)
   //    (0 x NaN is NaN: a NaN that enters the state reaches the y of the earlier steps of its
   //    16-step block so.  V < 128 holds it back: q in every column, column s kept by selects.  At
   //    V = 128 those take 2.7 % of a 4 x 8192, 8-head training step, 10.88 -> 11.19 ms; transposed,
   //    with one select per step, 2.5 %.)
-  auto step_Y = [&](const StepRegs &x, const u4_t &fr, int s, f4_t &yacc)
-      __attribute__((always_inline)) {
-    // (masked up here: behind the transposing product it takes 8 % of the kernel at V = 128)
+  auto step_Y = [&](const StepRegs &x, h4_t ht, int s, f4_t &yacc) __attribute__((always_inline)) {
     const h4_t qf = V < 128 || jl == s ? x.qf : zero_h4;
-    const u2_t hv = {fr[0], fr[2]};
-    const f4_t tr = mfma_k16(__builtin_bit_cast(h4_t, hv), ident, zero4);
-    const h4_t ht = {(_Float16)tr[0], (_Float16)tr[1], (_Float16)tr[2], (_Float16)tr[3]};
     if constexpr (V < 128) {
       const f4_t yd = mfma_k16(ht, qf, zero4);
 #pragma unroll
@@ -329,12 +327,13 @@ __global__ void __launch_bounds__(TL::THREADS, 2)
         // through a block then uses the fetched registers, and the compiler puts no wait for
         // them -- which would also wait for the stores in flight -- at the head of the next.)
         if (s == TB / 2) stage_store(sb ^ 1);
-        u4_t fr;
-        step_E(x, fr, (s & 1) ^ 1);  // every block but the last has 16 steps: parity of s
+        step_E(x, (s & 1) ^ 1);  // every block but the last has 16 steps: parity of s
         lds_barrier();
-        // after the barrier: fetch the next step's operands, then the readout MFMAs
+        // after the barrier: fetch the next step's operands, then the readout MFMA
+        h4_t ht;
+        if constexpr (DO_Y) ht = lds_ld_tr(trr, 0);
         if (!last) step_L(nx, s + 1, sb, (s + 1) & 1);
-        if constexpr (DO_Y) step_Y(x, fr, s, yacc);
+        if constexpr (DO_Y) step_Y(x, ht, s, yacc);
       };
       if (len == TB) {
 #pragma unroll
