@@ -301,8 +301,10 @@ m2rnn_status m2rnn_fwd_static(const m2rnn_desc *desc, const m2rnn_opts *opts, co
     scratch_ptr = static_scratch_of_current_device();
     if (!scratch_ptr) return M2RNN_ERR_HIP;
   }
-  return fwd_impl(desc, opts, q, k, v, f, W, H0, y, HT, ckpt, scratch_ptr,
-                  scratch_ptr ? (size_t)M2RNN_STATIC_SCRATCH_BYTES : 0, hip_stream, scratch_ptr ? need : 0);
+  // (and one that only asks so that its workspace is never zero is not given room for finer parts)
+  const size_t room = fwd_family_of(desc) == kGeneric && need <= 256 ? need : (size_t)M2RNN_STATIC_SCRATCH_BYTES;
+  return fwd_impl(desc, opts, q, k, v, f, W, H0, y, HT, ckpt, scratch_ptr, scratch_ptr ? room : 0,
+                  hip_stream, scratch_ptr ? need : 0);
 }
 
 m2rnn_status m2rnn_bwd(const m2rnn_desc *desc, const void *q, const void *k, const void *v,

@@ -461,13 +461,16 @@ hipError_t generic_head_group_sum(const BwdArgs &a, const float *per_head, void 
 int generic_default_chunk(int, int) { return 16; }
 int generic_max_chunk(int, int) { return 256; }
 
+namespace {
+size_t quad_bytes(int B, int T, int N, int Nqk, int K, int V, int C, int bwd, bool may_split) {
+  // (never zero: a workspace that is plainly too small stays an error, whatever the shape)
+  const size_t need = quad_workspace_bytes(B, T, N, Nqk, K, V, C, bwd, may_split);
+  return need > 256 ? need : 256;
+}
+}  // namespace
 size_t generic_workspace_bytes(int B, int T, int N, int Nqk, int K, int V, int C, int bwd) {
-  if (quad_supported(K, V)) {
-    // (never zero: a workspace that is plainly too small stays an error, whatever the shape)
-    const size_t need = quad_workspace_bytes(B, T, N, Nqk, K, V, C, bwd);
-    return need > 256 ? need : 256;
-  }
-  return layout_ws(B, T, N, Nqk, K, V, C, bwd).total;
+  return quad_supported(K, V) ? quad_bytes(B, T, N, Nqk, K, V, C, bwd, true)
+                              : layout_ws(B, T, N, Nqk, K, V, C, bwd).total;
 }
 
 // V <= 64 can do with less than the query: without room for the partial sums of a state's parts they
@@ -476,8 +479,8 @@ size_t generic_workspace_bytes(int B, int T, int N, int Nqk, int K, int V, int C
 // It holds what the parts in turn need: carried gradients and inner states are at most
 // (C - 1) / 16 + 1 states of each recurrence against C + 1, the sums of dW and of shared heads are the same.
 size_t generic_least_bytes(int B, int T, int N, int Nqk, int K, int V, int C, int bwd) {
-  const size_t full = generic_workspace_bytes(B, T, N, Nqk, K, V, C, bwd);
   const size_t one = layout_ws(B, T, N, Nqk, K, V, C, bwd).total;
+  const size_t full = quad_supported(K, V) ? quad_bytes(B, T, N, Nqk, K, V, C, bwd, false) : one;
   return full < one ? full : one;
 }
 

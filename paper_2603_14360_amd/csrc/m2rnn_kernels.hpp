@@ -97,7 +97,8 @@ hipError_t generic_head_group_sum(const BwdArgs &a, const float *per_head, void 
 
 // fp32 kernels on the fp32 matrix instructions, V <= 64 (forward: fp32 io; backward: either io)
 bool quad_supported(int K, int V);
-size_t quad_workspace_bytes(int B, int T, int N, int Nqk, int K, int V, int C, int bwd);
+// may_split: with the room that a launch of few states likes to have for finer parts (not needed)
+size_t quad_workspace_bytes(int B, int T, int N, int Nqk, int K, int V, int C, int bwd, bool may_split);
 hipError_t quad_fwd(const FwdArgs &a, hipStream_t s);
 hipError_t quad_bwd(const BwdArgs &a, hipStream_t s);
 

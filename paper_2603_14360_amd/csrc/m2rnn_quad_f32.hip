@@ -13,29 +13,35 @@
 // V / 16 waves, with an exchange through LDS and a barrier in every step.
 // Layouts.  Accumulator ("D"): lane 4 b + n holds column 4 (b mod V/4) + n, register m row m of
 // the lane's group of 4 rows.  A operand: lane 4 b + m holds row m, register j column 4 b + j.
-// The two differ by a 4 x 4 transposition inside each group of four lanes (quad_transpose, eight
-// vector instructions).
+// The two differ by a 4 x 4 transposition inside each group of four lanes (quad_transpose).
+// Split (V = 32): both halves of a wave hold the SAME four rows and contract 16 of the 32 columns
+// each, half of the matrix instructions; the halves' sums meet by a lane swap that leaves two
+// of the four rows to each, half of the vector instructions.  Twice as many waves take part, which
+// pays as long as SIMDs are free (split_pays).
 //
 // Measured against the vector-ALU kernels that these replace (one workgroup per state, state and
 // W in LDS, three barriers per step): B = 4, N = 8, K = V = 32, T = 512 forward 1.13 -> 0.245 ms,
-// backward 4.34 -> 0.59 ms.  What bounds it there: 128 waves on 1024 SIMDs, each a chain of some
-// 1150 cycles per step (forward: 256 of matrix instructions, the rest the 165 vector instructions
-// of a lone wave); vector ALU 7 %, matrix cores 3 %, HBM 0.06 TB/s.
+// backward 4.34 -> 0.59 ms, and with split rows 0.173 and 0.443.  What bounds it there: waves alone on
+// their SIMD, each a chain of some 800 cycles per step (forward; 1100 with four rows per lane: 85 vector
+// instructions at 5.5 cycles for 165, 131 cycles of matrix instructions for 262).
 #include "m2rnn_io.hpp"
 #include "m2rnn_kernels.hpp"
 
+#include <type_traits>
 #include <utility>
 
 namespace m2rnn {
 namespace {
 
 constexpr int TB = 16;  // steps per staged block (forward), per on-chip stash (backward)
+typedef float f2_t __attribute__((ext_vector_type(2)));
 
-template <int K_, int V_>
-struct Quad {
-  static constexpr int K = K_, V = V_;
-  static constexpr int CB = V / 4;                     // 4-column blocks per row group
-  static constexpr int GR = 16 / CB;                   // row groups per wave
+template <int K_, int V_, int S_>
+struct QuadOf {
+  static constexpr int K = K_, V = V_, S = S_;         // S: lanes per column of a row group
+  static constexpr int E = 4 / S;                      // rows per lane
+  static constexpr int CB = V / 4 / S;                 // 4-column blocks that a lane's contraction runs over
+  static constexpr int GR = 64 / (V * S);              // row groups per wave
   static constexpr int RW = 4 * GR;                    // rows per wave
   static constexpr int CBSZ = CB == 16 ? 4 : (CB == 8 ? 3 : 2);
   static constexpr int NWU = K / RW;                   // waves per state
@@ -45,8 +51,15 @@ struct Quad {
   static constexpr int THREADS = NW * 64;
   static constexpr int NQ = TB * ROWS / THREADS;       // staged values per thread: q, k ...
   static constexpr int NV = (TB * V + THREADS - 1) / THREADS;  // ... v, dy
+  typedef float rows_t __attribute__((ext_vector_type(E)));  // a lane's elements
   static_assert(NWU >= 1 && NWU % NW == 0 && (TB * ROWS) % THREADS == 0, "quad tile");
+  static_assert(S == 1 || (S == 2 && V == 32 && K <= 32), "split");
 };
+template <int K_, int V_>
+struct Quad : QuadOf<K_, V_, 1> {};
+constexpr bool has_split(int K, int V) { return V == 32 && K <= 32; }
+template <int K_, int V_>
+struct Split : QuadOf<K_, V_, 2> {};
 
 // tanh.  Below 1 an odd polynomial x + x^3 p(x^2) (a minimax fit of (tanh x - x) / x^3 with every
 // coefficient a float, error 4.7e-9 relative to tanh); from 1 on 1 - 2 / (1 + e^(2 |x|)), whose
@@ -57,17 +70,31 @@ struct Quad {
 // state's error does not change, and a state that saturates pays: B 4, N 8, T 512, W of gain one, forward 246 ->
 // 292 us, although only waves that need it took it.)
 // Infinities give +-1; a NaN goes through the polynomial and stays one.
-__device__ __forceinline__ float tanh_f32(float x) {
+// All of a lane's elements at once, operation by operation: a lone wave issues an instruction every
+// 5.5 cycles, but one that needs the result of the one before it after 8.6.
+template <typename X>
+__device__ __forceinline__ X tanh_f32(X x) {
+  constexpr int E = sizeof(X) / 4;
   constexpr float c[7] = {-0.33333295583724976f, 0.13332346081733704f,  -0.05387984961271286f, 0.02148670330643654f,
                           -0.007946079596877098f, 0.0023012934252619743f, -0.0003584200458135456f};
-  const float x2 = x * x;
-  float p = c[6];
+  X e, p, near, far;
+  const X x2 = x * x, x3 = x * x2;
 #pragma unroll
-  for (int i = 5; i >= 0; --i) p = fmaf(x2, p, c[i]);
-  const float near = fmaf(x * x2, p, x);
-  const float e = __builtin_amdgcn_exp2f(2.885390081777927f * __builtin_fabsf(x));
-  const float far = __builtin_copysignf(fmaf(-2.f, __builtin_amdgcn_rcpf(1.f + e), 1.f), x);
-  return __builtin_fabsf(x) >= 1.f ? far : near;
+  for (int m = 0; m < E; ++m) {
+    e[m] = __builtin_amdgcn_exp2f(2.885390081777927f * __builtin_fabsf(x[m]));
+    p[m] = c[6];
+  }
+#pragma unroll
+  for (int i = 5; i >= 0; --i)
+#pragma unroll
+    for (int m = 0; m < E; ++m) p[m] = fmaf(x2[m], p[m], c[i]);
+#pragma unroll
+  for (int m = 0; m < E; ++m) {
+    near[m] = fmaf(x3[m], p[m], x[m]);
+    far[m] = __builtin_copysignf(fmaf(-2.f, __builtin_amdgcn_rcpf(1.f + e[m]), 1.f), x[m]);
+    p[m] = __builtin_fabsf(x[m]) >= 1.f ? far[m] : near[m];
+  }
+  return p;
 }
 
 template <int CTRL>
@@ -84,6 +111,27 @@ __device__ __forceinline__ f4_t quad_transpose(f4_t x, bool odd, bool high) {
   const float q0 = quad_perm<0x4E>(a0), q1 = quad_perm<0x4E>(a1);      // lane xor 2
   const float q2 = quad_perm<0x4E>(a2), q3 = quad_perm<0x4E>(a3);
   return f4_t{high ? q2 : a0, high ? q3 : a1, high ? a2 : q0, high ? a3 : q1};
+}
+
+// The same out of split rows (registers: rows 2 half, 2 half + 1 of column lane % 32): the half that
+// contracts columns 16 half .. gets all four rows of those, in both of its groups of 16 lanes.
+__device__ __forceinline__ f4_t quad_transpose(f2_t x, bool odd, bool high) {
+  const float p0 = quad_perm<0xB1>(x[0]), p1 = quad_perm<0xB1>(x[1]);
+  const float e[2] = {odd ? p1 : x[0], odd ? x[1] : p0};
+  float a[4];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    // groups of 16 lanes 0 1 2 3 -> 0 0 2 2 and 1 1 3 3 -> 0 0 1 1 (rows 0, 1) and 2 2 3 3 (rows 2, 3)
+    const uint32_t u = __builtin_bit_cast(uint32_t, e[i]);
+    const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+    const auto t = __builtin_amdgcn_permlane32_swap(r[0], r[1], false, false);
+    const uint32_t t0 = t[0], t1 = t[1];
+    a[i] = __builtin_bit_cast(float, t0);
+    a[2 + i] = __builtin_bit_cast(float, t1);
+  }
+  const float q0 = quad_perm<0x4E>(a[0]), q1 = quad_perm<0x4E>(a[1]);
+  const float q2 = quad_perm<0x4E>(a[2]), q3 = quad_perm<0x4E>(a[3]);
+  return f4_t{high ? q2 : a[0], high ? q3 : a[1], high ? a[2] : q0, high ? a[3] : q1};
 }
 
 // acc[k mod 4] += (column k of A) x (row k of B) for all k = 4 B0 + j of the blocks B0...: four
@@ -103,46 +151,83 @@ __device__ __forceinline__ f4_t contract_blocks(const f4_t &a, const float (&w)[
       ...);
   return (acc0 + acc1) + (acc2 + acc3);
 }
+// ... two chains (half the additions behind them), for the half as long sums of split rows
+template <int CBSZ, int V, int... B0>
+__device__ __forceinline__ f4_t contract_blocks2(const f4_t &a, const float (&w)[V],
+                                                 std::integer_sequence<int, B0...>) {
+  f4_t acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = acc0;
+  (
+      [&] {
+        acc0 = __builtin_amdgcn_mfma_f32_4x4x1f32(a[0], w[4 * B0 + 0], acc0, CBSZ, B0, 0);
+        acc1 = __builtin_amdgcn_mfma_f32_4x4x1f32(a[1], w[4 * B0 + 1], acc1, CBSZ, B0, 0);
+        acc0 = __builtin_amdgcn_mfma_f32_4x4x1f32(a[2], w[4 * B0 + 2], acc0, CBSZ, B0, 0);
+        acc1 = __builtin_amdgcn_mfma_f32_4x4x1f32(a[3], w[4 * B0 + 3], acc1, CBSZ, B0, 0);
+      }(),
+      ...);
+  return acc0 + acc1;
+}
+// a lane's rows of (rows of A) x W
 template <typename Q>
-__device__ __forceinline__ f4_t contract(const f4_t &a, const float (&w)[Q::V]) {
-  return contract_blocks<Q::CBSZ, Q::V>(a, w, std::make_integer_sequence<int, Q::CB>{});
+__device__ __forceinline__ typename Q::rows_t contract(const f4_t &a, const float (&w)[4 * Q::CB]) {
+  if constexpr (Q::S == 1) {
+    return contract_blocks<Q::CBSZ, Q::V>(a, w, std::make_integer_sequence<int, Q::CB>{});
+  } else {
+    const f4_t x = contract_blocks2<Q::CBSZ, 4 * Q::CB>(a, w, std::make_integer_sequence<int, Q::CB>{});
+    // both halves' sums: rows 0, 1 to the lower half, rows 2, 3 to the upper
+    typename Q::rows_t y;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const float lo = x[i], hi = x[2 + i];
+      const auto t = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, lo), __builtin_bit_cast(uint32_t, hi),
+                                                      false, false);
+      const uint32_t t0 = t[0], t1 = t[1];
+      y[i] = __builtin_bit_cast(float, t0) + __builtin_bit_cast(float, t1);
+    }
+    return y;
+  }
 }
 // Pre-activation of a step, H W + k v^T: the outer product joins last, by an FMA on the finished sum.
 // (As the start of one of the four chains it is rounded once more, and so is every sum behind it:
 // state error against 64 bits, 512 steps, 1.2e-7 for 0.9e-7 at V = 32, 1.4e-7 for 0.9e-7 at 64.)
 template <typename Q>
-__device__ __forceinline__ f4_t preactivation(const f4_t &ha, const float (&w)[Q::V], const f4_t &k4, float vj) {
-  f4_t sp = contract<Q>(ha, w);
+__device__ __forceinline__ typename Q::rows_t preactivation(const f4_t &ha, const float (&w)[4 * Q::CB],
+                                                            const typename Q::rows_t &kr, float vj) {
+  typename Q::rows_t sp = contract<Q>(ha, w);
 #pragma unroll
-  for (int m = 0; m < 4; ++m) sp[m] = fmaf(k4[m], vj, sp[m]);
+  for (int m = 0; m < Q::E; ++m) sp[m] = fmaf(kr[m], vj, sp[m]);
   return sp;
 }
 
 // Waits for a loaded value here: the first use sits in a loop, where the wait would be repeated
 // in every step, and would wait there for the prefetch as well.
-__device__ __forceinline__ void arrived(f4_t &x) { asm volatile("" : "+v"(x)); }
+template <typename X>
+__device__ __forceinline__ void arrived(X &x) { asm volatile("" : "+v"(x)); }
 
-// four elements of a column
-template <int V>
-__device__ __forceinline__ f4_t load_rows(const float *p) {
-  return f4_t{p[0], p[V], p[2 * V], p[3 * V]};
+// a lane's elements of a column
+template <typename Q>
+__device__ __forceinline__ typename Q::rows_t load_rows(const float *p) {
+  typename Q::rows_t x;
+#pragma unroll
+  for (int m = 0; m < Q::E; ++m) x[m] = p[m * Q::V];
+  return x;
 }
 
 // Per-lane position inside the workgroup's rows
 template <typename Q>
 struct LanePos {
-  int wave, lane, rg, col, row;  // row: first of the lane's 4 rows inside the workgroup
-  int arow, acol;                // row and first column of the lane's A operand
-  bool odd, high;
+  int wave, lane, col, row;  // row: first of the lane's E rows inside the workgroup
+  int arow, acol, slice;     // row and first column of the lane's A operand; first column of its contraction
+  bool odd, high, owner;     // owner: of the A operand, where two groups of lanes hold the same
   __device__ __forceinline__ LanePos() {
     lane = threadIdx.x & 63;
     wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int blk = lane >> 2;
-    rg = blk / Q::CB;
-    col = 4 * (blk % Q::CB) + (lane & 3);
-    row = wave * Q::RW + 4 * rg;
-    arow = row + (lane & 3);
-    acol = 4 * (blk % Q::CB);
+    const int group = lane / (Q::V * Q::S), part = lane / Q::V % Q::S;
+    col = lane % Q::V;
+    row = wave * Q::RW + 4 * group + Q::E * part;
+    arow = wave * Q::RW + 4 * group + (lane & 3);
+    slice = 4 * Q::CB * part;
+    acol = slice + 4 * ((lane >> 2) % Q::CB);
+    owner = Q::S == 1 || (lane & 16) == 0;
     odd = lane & 1;
     high = lane & 2;
   }
@@ -173,14 +258,14 @@ __device__ __forceinline__ void quad_fwd_part(const FwdArgs &a, float *__restric
   const float *fg = a.f + (size_t)b * T * N + n;
   const size_t qk_step = (size_t)a.Nqk * K, v_step = (size_t)N * V;
 
-  float w[V];
+  constexpr int E = Q::E;
+  typedef typename Q::rows_t rows_t;
+  float w[4 * Q::CB];
 #pragma unroll
-  for (int c = 0; c < V; ++c) w[c] = ((const float *)a.W)[((size_t)n * V + c) * V + p.col];
+  for (int c = 0; c < 4 * Q::CB; ++c) w[c] = ((const float *)a.W)[((size_t)n * V + p.slice + c) * V + p.col];
   const size_t st_off = ((size_t)unit * K + row_base + p.row) * V + p.col;
-  f4_t h = {0.f, 0.f, 0.f, 0.f};
-  if (a.H0)
-#pragma unroll
-    for (int m = 0; m < 4; ++m) h[m] = a.H0[st_off + m * V];
+  rows_t h = {};
+  if (a.H0) h = load_rows<Q>(a.H0 + st_off);
   arrived(h);
 
   float rq[NQ], rk[NQ], rv[NV], rf = 0.f;
@@ -219,7 +304,7 @@ __device__ __forceinline__ void quad_fwd_part(const FwdArgs &a, float *__restric
       const int s = idx / V, j = idx % V;
       float acc = 0.f;
 #pragma unroll
-      for (int i = 0; i < Q::NW * Q::GR; ++i) acc += (&sm.y[buf][s][0][0])[i * V + j];
+      for (int i = 0; i < Q::NW * 64 / V; ++i) acc += (&sm.y[buf][s][0][0])[i * V + j];
       const size_t off = (size_t)(t0 + s) * v_step + j;
       if constexpr (Q::P == 1 || SEQ) {
         float *dst = (float *)a.y + ((size_t)b * T * N + n) * V + off;
@@ -234,7 +319,7 @@ __device__ __forceinline__ void quad_fwd_part(const FwdArgs &a, float *__restric
   };
 
   const int nblk = (T + TB - 1) / TB, nck = (T + a.C - 1) / a.C;
-  int next_ck = 0;
+  int next_ck = a.ckpt ? 0 : -1;
   float *ckpt = a.ckpt ? a.ckpt + (size_t)unit * nck * K * V + (size_t)(row_base + p.row) * V + p.col : nullptr;
   if (nblk > 0) {
     load(0);
@@ -244,26 +329,38 @@ __device__ __forceinline__ void quad_fwd_part(const FwdArgs &a, float *__restric
   for (int blk = 0; blk < nblk; ++blk) {
     const int t0 = blk * TB, len = min(TB, T - t0), buf = blk & 1;
     if (blk + 1 < nblk) load(t0 + TB);
+    // a step's vectors are fetched during the one before (V = 16: no gain)
+    constexpr bool AHEAD = V > 16;
+    rows_t kr1, qr1;
+    float vj1, f1;
+    auto fetch = [&](int s) __attribute__((always_inline)) {
+      kr1 = *(const rows_t *)&sm.k[buf][s][p.row];
+      vj1 = sm.v[buf][s][p.col];
+      f1 = sm.f[buf][s];
+      if constexpr (DO_Y) qr1 = *(const rows_t *)&sm.q[buf][s][p.row];
+    };
+    if constexpr (AHEAD) fetch(0);
 #pragma nounroll
     for (int s = 0; s < len; ++s) {
-      if (ckpt && t0 + s == next_ck) {  // state before step t0 + s
+      if (t0 + s == next_ck) {  // state before step t0 + s
 #pragma unroll
-        for (int m = 0; m < 4; ++m) ckpt[m * V] = h[m];
+        for (int m = 0; m < E; ++m) ckpt[m * V] = h[m];
         ckpt += (size_t)K * V;
         next_ck += a.C;
       }
-      const f4_t k4 = *(const f4_t *)&sm.k[buf][s][p.row];
-      const float vj = sm.v[buf][s][p.col], f = sm.f[buf][s], gm = 1.f - f;
+      if constexpr (!AHEAD) fetch(s);
+      const rows_t kr = kr1, qr = qr1;
+      const float vj = vj1, f = f1, gm = 1.f - f;
+      if constexpr (AHEAD) fetch(min(s + 1, TB - 1));  // (behind the end: a step that is not used)
       const f4_t ha = quad_transpose(h, p.odd, p.high);
-      const f4_t sp = preactivation<Q>(ha, w, k4, vj);
+      const rows_t th = tanh_f32(preactivation<Q>(ha, w, kr, vj));
 #pragma unroll
-      for (int m = 0; m < 4; ++m) h[m] = fmaf(f, h[m], gm * tanh_f32(sp[m]));
+      for (int m = 0; m < E; ++m) h[m] = fmaf(f, h[m], gm * th[m]);
       if constexpr (DO_Y) {
-        const f4_t q4 = *(const f4_t *)&sm.q[buf][s][p.row];
-        float y = q4[0] * h[0];
+        float y = qr[0] * h[0];
 #pragma unroll
-        for (int m = 1; m < 4; ++m) y = fmaf(q4[m], h[m], y);
-        // lanes of a row group are consecutive, so lane order is [row group][column]
+        for (int m = 1; m < E; ++m) y = fmaf(qr[m], h[m], y);
+        // lanes that share rows are consecutive, so lane order is [rows][column]
         sm.y[buf][s][p.wave][p.lane] = y;
       }
     }
@@ -275,7 +372,7 @@ __device__ __forceinline__ void quad_fwd_part(const FwdArgs &a, float *__restric
   }
   if (a.HT)
 #pragma unroll
-    for (int m = 0; m < 4; ++m) a.HT[st_off + m * V] = h[m];
+    for (int m = 0; m < E; ++m) a.HT[st_off + m * V] = h[m];
 }
 
 template <typename Q, bool DO_Y, bool SEQ>
@@ -349,33 +446,35 @@ __global__ void __launch_bounds__(Q::THREADS, Q::V < 64 ? 2 : 1) quad_bwd_kernel
            *dyg = (const IO *)a.dy + v0;
   const float *fg = a.f + f0;
 
-  float w[V], wt[V];
+  constexpr int E = Q::E;
+  typedef typename Q::rows_t rows_t;
+  float w[4 * Q::CB], wt[4 * Q::CB];
 #pragma unroll
-  for (int c = 0; c < V; ++c) {
-    w[c] = to_f32<IO>(((const IO *)a.W)[((size_t)n * V + c) * V + p.col]);
-    wt[c] = to_f32<IO>(((const IO *)a.W)[((size_t)n * V + p.col) * V + c]);
+  for (int c = 0; c < 4 * Q::CB; ++c) {
+    w[c] = to_f32<IO>(((const IO *)a.W)[((size_t)n * V + p.slice + c) * V + p.col]);
+    wt[c] = to_f32<IO>(((const IO *)a.W)[((size_t)n * V + p.col) * V + p.slice + c]);
   }
   auto st_off = [&]() __attribute__((always_inline)) { return ((size_t)unit * K + row_base + p.row) * V + p.col; };
   // a part's slots in the workspace: a place that only the same lane reads again
   const int slots = SEQ ? ws.nsub + 1 : ws.nsub;
-  auto slot = [&](int i) __attribute__((always_inline)) { return (f4_t *)ws.sub + (((size_t)unit * Q::P + part) * slots + i) * THREADS + tid; };
+  auto slot = [&](int i) __attribute__((always_inline)) { return (rows_t *)ws.sub + (((size_t)unit * Q::P + part) * slots + i) * THREADS + tid; };
   auto turn = [&](int i) __attribute__((always_inline)) {
     if constexpr (SEQ) {
       part = i;
       row_base = i * ROWS;
     }
   };
-  f4_t carry = {0.f, 0.f, 0.f, 0.f};
+  rows_t carry = {};
   for (int i = 0; i < TURNS; ++i) {
     turn(i);
-    if (a.dHT) carry = load_rows<V>(a.dHT + st_off());
+    if (a.dHT) carry = load_rows<Q>(a.dHT + st_off());
     arrived(carry);
     if constexpr (SEQ) *slot(ws.nsub) = carry;
   }
 
   // dW tiles of 16 x 16: with at least one per wave, wave w owns the NTW tiles w NTW ..; with
-  // fewer tiles than waves (V = 16) every wave adds its own share of the rows to the one tile
-  constexpr int CT = V / 16, NT = CT * CT, NTW = NT >= NW ? NT / NW : 1, SPLIT = NT >= NW ? 1 : NW;
+  // fewer tiles than waves, SPLIT waves add their shares of the rows to the same tile
+  constexpr int CT = V / 16, NT = CT * CT, NTW = NT >= NW ? NT / NW : 1, SPLIT = NT >= NW ? 1 : NW / NT;
   f4_t dW[NTW];
 #pragma unroll
   for (int i = 0; i < NTW; ++i) dW[i] = f4_t{0.f, 0.f, 0.f, 0.f};
@@ -413,22 +512,42 @@ __global__ void __launch_bounds__(Q::THREADS, Q::V < 64 ? 2 : 1) quad_bwd_kernel
     if (tid < TB) sm.f[tid] = a.gate_alpha ? gate_psi(rf, a.gate_alpha[n], a.gate_beta[n]) : rf;
   };
   // one recomputed step of the recurrence; the state's A operand is returned for the stash
-  auto step = [&](f4_t &h, int s, f4_t &ha) __attribute__((always_inline)) {
-    const f4_t k4 = *(const f4_t *)&sm.k[s][p.row];
-    const float vj = sm.v[s][p.col], f = sm.f[s], gm = 1.f - f;
+  // (Of split rows, a step's vectors are fetched during the one before.  With four rows per lane the
+  // sweep is 1 % slower so: 64 x 64, 64 states, T = 512 983 -> 993 us.)
+  constexpr bool AHEAD = Q::S > 1;
+  rows_t kr1;
+  float vj1, f1;
+  auto fetch = [&](int s) __attribute__((always_inline)) {
+    kr1 = *(const rows_t *)&sm.k[s][p.row];
+    vj1 = sm.v[s][p.col];
+    f1 = sm.f[s];
+  };
+  auto step = [&](rows_t &h, int s, f4_t &ha) __attribute__((always_inline)) {
+    if constexpr (!AHEAD) fetch(s);
+    const rows_t kr = kr1;
+    const float vj = vj1, f = f1, gm = 1.f - f;
+    if constexpr (AHEAD) fetch(min(s + 1, TB - 1));
     ha = quad_transpose(h, p.odd, p.high);
-    const f4_t sp = preactivation<Q>(ha, w, k4, vj);
-    f4_t z;
+    rows_t z = preactivation<Q>(ha, w, kr, vj);
+    if constexpr (AHEAD) {
+      z = tanh_f32(z);
 #pragma unroll
-    for (int m = 0; m < 4; ++m) {
-      z[m] = tanh_f32(sp[m]);
-      h[m] = fmaf(f, h[m], gm * z[m]);
+      for (int m = 0; m < E; ++m) h[m] = fmaf(f, h[m], gm * z[m]);
+    } else {  // (element by element: 1 % here, the other way round in the forward)
+#pragma unroll
+      for (int m = 0; m < E; ++m) {
+        typedef float one_t __attribute__((ext_vector_type(1)));
+        z[m] = tanh_f32(one_t{z[m]})[0];
+        h[m] = fmaf(f, h[m], gm * z[m]);
+      }
     }
     return z;
   };
 
   const int nck = (T + C - 1) / C;
   const int a_off = sw<V>(p.arow, p.acol);
+  // Z of a step lies where its dS will: a wave's share of the rows, in the order of its lanes
+  rows_t *const zst = (rows_t *)&sm.D[0][0];
   if (!SEQ && nck > 0) {  // vectors of the last stash
     const int t0 = (nck - 1) * C, len = T - t0, sub = (len - 1) / TB;
     load(t0 + sub * TB, len - sub * TB);
@@ -436,11 +555,11 @@ __global__ void __launch_bounds__(Q::THREADS, Q::V < 64 ? 2 : 1) quad_bwd_kernel
   for (int ck = nck - 1; ck >= 0; --ck) {
     const int ck0 = ck * C, clen = min(C, T - ck0), nsub = (clen + TB - 1) / TB;
     auto checkpoint = [&]() __attribute__((always_inline)) {
-      f4_t h = load_rows<V>(a.ckpt + ((size_t)unit * nck + ck) * K * V + (size_t)(row_base + p.row) * V + p.col);
+      rows_t h = load_rows<Q>(a.ckpt + ((size_t)unit * nck + ck) * K * V + (size_t)(row_base + p.row) * V + p.col);
       arrived(h);
       return h;
     };
-    f4_t hck = {0.f, 0.f, 0.f, 0.f};
+    rows_t hck = {};
     if constexpr (!SEQ) hck = checkpoint();
     // checkpoints further apart than a stash: a first pass leaves the state in front of each
     // later stash in the workspace
@@ -448,12 +567,14 @@ __global__ void __launch_bounds__(Q::THREADS, Q::V < 64 ? 2 : 1) quad_bwd_kernel
       for (int i = 0; i < TURNS; ++i) {
         turn(i);
         if constexpr (SEQ) hck = checkpoint();
-        f4_t h = hck, ha;
+        rows_t h = hck;
+        f4_t ha;
         for (int sub = 0; sub + 1 < nsub; ++sub) {
           load(ck0 + sub * TB, TB);
           __syncthreads();
           store();
           __syncthreads();
+          if constexpr (AHEAD) fetch(0);
 #pragma nounroll
           for (int s = 0; s < TB; ++s) step(h, s, ha);
           *slot(sub) = h;
@@ -473,7 +594,8 @@ __global__ void __launch_bounds__(Q::THREADS, Q::V < 64 ? 2 : 1) quad_bwd_kernel
           if (sub == 0) hck = checkpoint();
         }
         store();
-        f4_t h = sub > 0 ? *slot(sub - 1) : hck, ha;
+        rows_t h = sub > 0 ? *slot(sub - 1) : hck;
+        f4_t ha;
         arrived(h);
         __syncthreads();
         // the next stash's vectors travel during this one
@@ -482,53 +604,65 @@ __global__ void __launch_bounds__(Q::THREADS, Q::V < 64 ? 2 : 1) quad_bwd_kernel
           else if (ck > 0 && C <= TB) load(ck0 - C, C);
         }
         // ---- recompute
+        if constexpr (AHEAD) fetch(0);
 #pragma nounroll
         for (int s = 0; s < len; ++s) {
-          const f4_t z = step(h, s, ha);
-          *(f4_t *)&sm.H[s][a_off] = ha;
-          ((f4_t *)sm.D[s])[tid] = z;  // (only this lane reads it again)
+          const rows_t z = step(h, s, ha);
+          if (p.owner) *(f4_t *)&sm.H[s][a_off] = ha;
+          zst[s * (ROWS * V / E) + tid] = z;  // (only this lane reads it again)
         }
-        *(f4_t *)&sm.H[len][a_off] = quad_transpose(h, p.odd, p.high);
+        ha = quad_transpose(h, p.odd, p.high);
+        if (p.owner) *(f4_t *)&sm.H[len][a_off] = ha;
         // ---- sweep
         float dfacc = 0.f;
+        rows_t q1, z1, h1;
+        float dy1;
+        auto fetch_sweep = [&](int s) __attribute__((always_inline)) {
+          q1 = *(const rows_t *)&sm.q[s][p.row];
+          dy1 = sm.dy[s][p.col];
+          f1 = sm.f[s];
+          z1 = zst[s * (ROWS * V / E) + tid];
+#pragma unroll
+          for (int m = 0; m < E; ++m) h1[m] = sm.H[s][sw<V>(p.row + m, p.col)];
+        };
+        if constexpr (AHEAD) fetch_sweep(len - 1);
 #pragma nounroll
         for (int s = len - 1; s >= 0; --s) {
-          const f4_t q4 = *(const f4_t *)&sm.q[s][p.row];
-          const float dyj = sm.dy[s][p.col], f = sm.f[s], gm = 1.f - f;
-          const f4_t z = ((const f4_t *)sm.D[s])[tid];
-          f4_t hp, G, dS;
+          if constexpr (!AHEAD) fetch_sweep(s);
+          const rows_t qr = q1, z = z1, hp = h1;
+          const float dyj = dy1, f = f1, gm = 1.f - f;
+          if constexpr (AHEAD) fetch_sweep(max(s - 1, 0));
+          rows_t G, dS;
           float dfl = 0.f;
 #pragma unroll
-          for (int m = 0; m < 4; ++m) hp[m] = sm.H[s][sw<V>(p.row + m, p.col)];
-#pragma unroll
-          for (int m = 0; m < 4; ++m) {
-            G[m] = fmaf(q4[m], dyj, carry[m]);
+          for (int m = 0; m < E; ++m) {
+            G[m] = fmaf(qr[m], dyj, carry[m]);
             dfl = fmaf(G[m], hp[m] - z[m], dfl);
             dS[m] = gm * G[m] * fmaf(-z[m], z[m], 1.f);
           }
           const f4_t da = quad_transpose(dS, p.odd, p.high);
-          *(f4_t *)&sm.D[s][a_off] = da;
+          if (p.owner) *(f4_t *)&sm.D[s][a_off] = da;
           const f4_t df4 = __builtin_amdgcn_mfma_f32_16x16x4f32(dfl, 1.f, f4_t{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
-          const f4_t d = contract<Q>(da, wt);
+          const rows_t d = contract<Q>(da, wt);
 #pragma unroll
-          for (int m = 0; m < 4; ++m) carry[m] = fmaf(f, G[m], d[m]);
+          for (int m = 0; m < E; ++m) carry[m] = fmaf(f, G[m], d[m]);
           // every column of df4 is the same: lane (j, i) holds the sums of 4 of the 16 rows i' = 4 i + r
           dfacc = (p.lane & 15) == s ? (df4[0] + df4[1]) + (df4[2] + df4[3]) : dfacc;
           if (a.clip > 0.f)
 #pragma unroll
-            for (int m = 0; m < 4; ++m) carry[m] = __builtin_amdgcn_fmed3f(carry[m], -a.clip, a.clip);
+            for (int m = 0; m < E; ++m) carry[m] = __builtin_amdgcn_fmed3f(carry[m], -a.clip, a.clip);
         }
         sm.df[p.wave * 4 + (p.lane >> 4)][p.lane & 15] = dfacc;  // lane (s, i): its rows' sum of step s
         __syncthreads();
         // ---- finish: dW, 4 rows of one step per product
 #pragma unroll
         for (int i = 0; i < NTW; ++i) {
-          const int tile = SPLIT > 1 ? 0 : p.wave * NTW + i, ci = tile / CT, cj = tile % CT;
+          const int tile = SPLIT > 1 ? p.wave / SPLIT : p.wave * NTW + i, ci = tile / CT, cj = tile % CT;
           const int kr = p.lane >> 4, c = p.lane & 15;
           // (summed per stash first: one running sum over all steps would lose two bits)
           f4_t acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = acc0;
-          const int r0 = SPLIT > 1 ? p.wave * Q::RW : 0;
-          constexpr int NR = SPLIT > 1 ? Q::RW : ROWS;
+          constexpr int NR = ROWS / SPLIT;
+          const int r0 = p.wave % SPLIT * NR;
           for (int s = 0; s < len; ++s) {
 #pragma unroll
             for (int r = 0; r < NR; r += 8) {
@@ -605,7 +739,7 @@ __global__ void __launch_bounds__(Q::THREADS, Q::V < 64 ? 2 : 1) quad_bwd_kernel
       turn(i);
       if constexpr (SEQ) carry = *slot(ws.nsub);
 #pragma unroll
-      for (int m = 0; m < 4; ++m) a.dH0[st_off() + m * V] = carry[m];
+      for (int m = 0; m < E; ++m) a.dH0[st_off() + m * V] = carry[m];
     }
   // dW of the workgroup: D layout of the 16x16 product, rows 4 (lane / 16) + r, column lane % 16
   float *dst = ws.dWp + (size_t)blockIdx.x * V * V;
@@ -614,12 +748,13 @@ __global__ void __launch_bounds__(Q::THREADS, Q::V < 64 ? 2 : 1) quad_bwd_kernel
     __syncthreads();
     red[tid] = dW[0];
     __syncthreads();
-    if (p.wave == 0) {
-      f4_t s = red[p.lane];
+    if (p.wave % SPLIT == 0) {
+      const int tile = p.wave / SPLIT, ci = tile / CT, cj = tile % CT;
+      f4_t s = red[tid];
 #pragma unroll
-      for (int i = 1; i < NW; ++i) s += red[i * 64 + p.lane];
+      for (int i = 1; i < SPLIT; ++i) s += red[i * 64 + tid];
 #pragma unroll
-      for (int r = 0; r < 4; ++r) dst[(4 * (p.lane >> 4) + r) * V + (p.lane & 15)] = s[r];
+      for (int r = 0; r < 4; ++r) dst[(16 * ci + 4 * (p.lane >> 4) + r) * V + 16 * cj + (p.lane & 15)] = s[r];
     }
   } else {
 #pragma unroll
@@ -690,13 +825,14 @@ hipError_t launch_fwd(const FwdArgs &a, hipStream_t s) {
   const int units = a.B * a.N;
   if (units == 0) return hipSuccess;
   float *ypart = (float *)a.ws;
-  const bool seq = Q::P > 1 && a.write_y && a.ws_bytes < fwd_parts_bytes<Q>(a.B, a.T, a.N);
+  constexpr bool turns = Q::P > 1 && Q::S == 1;  // (split parts are taken only with room for their sums)
+  const bool seq = turns && a.write_y && a.ws_bytes < fwd_parts_bytes<Q>(a.B, a.T, a.N);
   const dim3 grid(seq ? units : units * Q::P), block(Q::THREADS);
   if (!a.write_y)
     hipLaunchKernelGGL((quad_fwd_kernel<Q, false, false>), grid, block, 0, s, a, ypart);
   else if (!seq)
     hipLaunchKernelGGL((quad_fwd_kernel<Q, true, false>), grid, block, 0, s, a, ypart);
-  else if constexpr (Q::P > 1)
+  else if constexpr (turns)
     hipLaunchKernelGGL((quad_fwd_kernel<Q, true, true>), grid, block, 0, s, a, ypart);
   hipError_t e = hipGetLastError();
   if (seq) return e;
@@ -763,10 +899,10 @@ hipError_t launch_bwd_as(const BwdArgs &a, const QuadLayout &l, hipStream_t s) {
 }
 template <typename IO, typename Q>
 hipError_t launch_bwd(const BwdArgs &a, hipStream_t s) {
-  auto layout = [&](bool seq) { return quad_layout(a.B, a.T, a.N, a.Nqk, a.K, a.V, a.C, Q::P, Q::THREADS, seq); };
+  auto layout = [&](bool seq) { return quad_layout(a.B, a.T, a.N, a.Nqk, a.K, a.V, a.C, Q::P, Q::THREADS * Q::E / 4, seq); };
   const QuadLayout side = layout(false), turns = layout(true);
   if (a.ws_bytes >= side.total) return launch_bwd_as<IO, Q, false>(a, side, s);
-  if constexpr (Q::P > 1)
+  if constexpr (Q::P > 1 && Q::S == 1)
     if (a.ws_bytes >= turns.total) return launch_bwd_as<IO, Q, true>(a, turns, s);
   return hipErrorInvalidValue;
 }
@@ -778,21 +914,40 @@ hipError_t launch_bwd(const BwdArgs &a, hipStream_t s) {
 
 bool quad_supported(int, int V) { return V <= 64; }
 
-size_t quad_workspace_bytes(int B, int T, int N, int Nqk, int K, int V, int C, int bwd) {
-#define X(K_, V_)                                                                                  \
-  if (K == K_ && V == V_) {                                                                        \
-    using Q = Quad<K_, V_>;                                                                        \
-    if (!bwd) return fwd_parts_bytes<Q>(B, T, N);                                                   \
-    return quad_layout(B, T, N, Nqk, K, V, C, Q::P, Q::THREADS, false).total;                              \
-  }
+namespace {
+// the split kernel where there is one
+template <int K, int V>
+using QuadSplit = std::conditional_t<has_split(K, V), Split<K, V>, Quad<K, V>>;
+// As long as every wave has a SIMD (1024) for itself.  us, T = 512, forward / backward, 8 rows per wave -> split:
+// 32 x 32 8 states 245 / 588 -> 172 / 433, 128 states 249 / 605 -> 181 / 451, but 192 states 249 / 606 -> 267 / 626;
+// 16 x 32, T = 256 256 states 136 / 315 -> 95 / 227.
+bool split_pays(int K, int V, int units) { return has_split(K, V) && (long long)units * K <= 4096; }
+
+template <typename Q>
+size_t workspace_of(int B, int T, int N, int Nqk, int C, int bwd) {
+  if (!bwd) return fwd_parts_bytes<Q>(B, T, N);
+  return quad_layout(B, T, N, Nqk, Q::K, Q::V, C, Q::P, Q::THREADS * Q::E / 4, false).total;
+}
+}  // namespace
+
+size_t quad_workspace_bytes(int B, int T, int N, int Nqk, int K, int V, int C, int bwd, bool may_split) {
+  const bool split = may_split && split_pays(K, V, B * N);
+#define X(K_, V_)                                                                                       \
+  if (K == K_ && V == V_)                                                                               \
+    return split ? workspace_of<QuadSplit<K_, V_>>(B, T, N, Nqk, C, bwd)                                \
+                 : workspace_of<Quad<K_, V_>>(B, T, N, Nqk, C, bwd);
   M2RNN_QUAD_CASES(X)
 #undef X
   return 0;
 }
 
 hipError_t quad_fwd(const FwdArgs &a, hipStream_t s) {
-#define X(K_, V_) \
-  if (a.K == K_ && a.V == V_) return launch_fwd<Quad<K_, V_>>(a, s);
+  const size_t room = a.ws_bytes;
+  const bool split = split_pays(a.K, a.V, a.B * a.N) &&
+                     (!a.write_y || room >= quad_workspace_bytes(a.B, a.T, a.N, a.Nqk, a.K, a.V, a.C, 0, true));
+#define X(K_, V_)                                                                                       \
+  if (a.K == K_ && a.V == V_)                                                                           \
+    return split ? launch_fwd<QuadSplit<K_, V_>>(a, s) : launch_fwd<Quad<K_, V_>>(a, s);
   M2RNN_QUAD_CASES(X)
 #undef X
   return hipErrorInvalidValue;
@@ -802,14 +957,20 @@ hipError_t quad_fwd(const FwdArgs &a, hipStream_t s) {
 #define M2RNN_QUAD_BF16_CASES(X) X(16, 32) X(64, 32) X(128, 32) X(16, 64) X(32, 64) X(128, 64)
 
 hipError_t quad_bwd(const BwdArgs &a, hipStream_t s) {
+  const size_t room = a.ws_bytes;
+  const bool split = split_pays(a.K, a.V, a.B * a.N) &&
+                     room >= quad_workspace_bytes(a.B, a.T, a.N, a.Nqk, a.K, a.V, a.C, 1, true);
   if (a.io == 0) {
-#define X(K_, V_) \
-  if (a.K == K_ && a.V == V_) return launch_bwd<float, Quad<K_, V_>>(a, s);
+#define X(K_, V_)                                                                                   \
+  if (a.K == K_ && a.V == V_)                                                                       \
+    return split ? launch_bwd<float, QuadSplit<K_, V_>>(a, s) : launch_bwd<float, Quad<K_, V_>>(a, s);
     M2RNN_QUAD_CASES(X)
 #undef X
   } else {
-#define X(K_, V_) \
-  if (a.K == K_ && a.V == V_) return launch_bwd<__hip_bfloat16, Quad<K_, V_>>(a, s);
+#define X(K_, V_)                                                                                   \
+  if (a.K == K_ && a.V == V_)                                                                       \
+    return split ? launch_bwd<__hip_bfloat16, QuadSplit<K_, V_>>(a, s)                              \
+                 : launch_bwd<__hip_bfloat16, Quad<K_, V_>>(a, s);
     M2RNN_QUAD_BF16_CASES(X)
 #undef X
   }

@@ -160,6 +160,11 @@ def test_every_scan_kernel_has_a_parity_case():
         add(d(2, 35, 3, K, V, F32), bwd=True, ckpt=1)
     for K, V in quad.SHAPES:
         add(d(2, 35, 3, K, V, F32), bwd=True, route="")
+    for io, K, V, units in quad.MANY:
+        desc = d(units, 35, 1, K, V, F32 if io == "f32" else BF16)
+        add(desc, ckpt=1)
+        add(desc, bwd=True, ckpt=1)
+        add(desc, bwd=True, route="")
     for io, K, V, T, chunk, Nqk in quad.TURNS:
         desc = d(1, T, 4, K, V, F32 if io == "f32" else BF16, chunk=chunk, Nqk=Nqk)
         assert one_workgroup_per_state(desc, 1) < ws_bytes(desc, 1)

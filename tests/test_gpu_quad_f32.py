@@ -33,6 +33,59 @@ def test_lengths_and_intervals(K, V, T, chunk):
     _check(1, T, 4, K, V, chunk, Nqk=2, clip=0.5 if T == 33 else 0.0)
 
 
+# shapes whose rows are split between the halves of a wave as long as every wave has a SIMD for itself:
+# the last launch that is split, the first that is not
+MANY = [("f32", 32, 32, 128), ("f32", 32, 32, 129), ("f32", 16, 32, 256), ("f32", 16, 32, 258), ("bf16", 16, 32, 256),
+        ("bf16", 16, 32, 258)]
+
+
+@pytest.mark.parametrize("io,K,V,units", MANY)
+def test_split_rows_and_whole_rows(io, K, V, units):
+    """Both sides of the line, and the backward that recomputes the checkpoints: same bits as with them."""
+    T = 35
+    print("case split rows", io, K, V, units, flush=True)
+    inp = make_inputs(Workload("t", units, T, 1, K, V, io, 90 + K + units, K ** -0.5, 1.0, use_H0=True, use_dHT=True))
+    got, again = gu.run_gpu(inp, io), gu.run_gpu(inp, io, use_ckpt=False)
+    gu.compare(got, gu.run_oracle(inp), gu.TOL[io], label="split rows")
+    assert all((again[n] == got[n]).all() for n in got)
+
+
+@pytest.mark.parametrize("fwd", [True, False])
+def test_split_rows_need_no_more_room_than_whole_rows(fwd):
+    """32 x 32, few states: finer parts are taken with room for their sums only; the room of one workgroup
+    per state stays enough, and nothing is written behind it."""
+    import torch
+    from paper_2603_14360_amd import binding as mb
+    B, T, N, K, V = 2, 53, 3, 32, 32
+    desc = mb.make_desc(B, T, N, K, V, mb.M2RNN_F32)
+    full = mb.m2rnn_workspace_bytes(desc, 0 if fwd else 1)
+    al = lambda x: (x + 255) // 256 * 256
+    # one workgroup per state: nothing forward; a dW per state backward, and the options' sums
+    least = 256 if fwd else al(B * N * V * V * 4) + al(1024 * N * V * 4) + al(256 * 2 * N * 4)
+    assert least < full
+    print("case split rows, least room", fwd, flush=True)
+    inp = make_inputs(Workload("t", B, T, N, K, V, "f32", 31, K ** -0.5, 1.0, use_H0=True, use_dHT=True))
+    dev, ref = gu.to_device(inp, "f32"), gu.run_oracle(inp)
+    scan = mb.Scan(B, T, N, K, V, "f32")
+    args = [dev[n] for n in ("q", "k", "v", "f", "W", "H0")]
+    scan.fwd(*args)
+    new = lambda *s: torch.full(s, float("nan"), device="cuda")
+    for n in (full, least):
+        ws = torch.full((n + 4096,), 0xFF, dtype=torch.uint8, device="cuda")   # (a guard behind the workspace)
+        stream = torch.cuda.current_stream().cuda_stream
+        if fwd:
+            names, out = ("y", "HT"), [new(B, T, N, V), new(B, N, K, V)]
+            mb.m2rnn_fwd_opt(desc, mb.make_opts(), *args, *out, None, ws[:n], stream=stream)
+        else:
+            names = gu.GRAD_NAMES
+            out = [new(B, T, N, K), new(B, T, N, K), new(B, T, N, V), new(B, T, N), new(N, V, V), new(B, N, K, V)]
+            mb.m2rnn_bwd_opt(desc, mb.make_opts(), *args, scan.ckpt, dev["dy"], dev["dHT"], *out, ws[:n], stream=stream)
+        torch.cuda.synchronize()
+        assert (ws[n:] == 0xFF).all()
+        got = {name: gu.to_np(x) for name, x in zip(names, out)}
+        gu.compare(got, {name: ref[name] for name in got}, gu.TOL["f32"], label="room %d" % n)
+
+
 FORWARD_TURNS = [("f32", K, V) for K, V in ((128, 16), (64, 32), (128, 32), (32, 64), (64, 64), (128, 64))]
 
 
