@@ -97,6 +97,22 @@ def lib():
     return _lib
 
 
+_call_module = None
+
+
+def _call():
+    """The module that calls the library with the tensors themselves (csrc/py_call.cpp), with the entry
+    points of lib(); raises if it has not been built."""
+    global _call_module
+    if _call_module is None:
+        L = lib()
+        from paper_2603_14360_amd import _call as module
+        address = lambda f: ctypes.cast(f, ctypes.c_void_p).value
+        module.init(address(L.m2rnn_fwd_opt), address(L.m2rnn_bwd_opt))
+        _call_module = module
+    return _call_module
+
+
 def make_desc(B, T, N, K, V, io, Nqk=None, chunk=0, flags=0):
     return m2rnn_desc(B, T, N, N if Nqk is None else Nqk, K, V, io, chunk, flags)
 
@@ -126,16 +142,15 @@ def m2rnn_workspace_bytes(desc, bwd):
 
 
 def _ptr(x):
-    """Device (or raw integer) address of a tensor; None -> NULL."""
-    if x is None:
-        return None
-    if isinstance(x, int):
-        return ctypes.c_void_p(x)
-    return ctypes.c_void_p(x.data_ptr())
+    """Device (or raw integer) address of a tensor; None -> NULL.  (A plain int: the argument types make
+    a pointer of it, without an object of its own per argument.)"""
+    if x is None or isinstance(x, int):
+        return x
+    return x.data_ptr()
 
 
 def _nbytes(x):
-    return 0 if x is None else x.numel() * x.element_size()
+    return 0 if x is None else x.nbytes
 
 
 def m2rnn_fwd(desc, q, k, v, f, W, H0, y, HT, ckpt, workspace, stream=None, check=True):
@@ -143,7 +158,7 @@ def m2rnn_fwd(desc, q, k, v, f, W, H0, y, HT, ckpt, workspace, stream=None, chec
     header allows NULL); `stream` is a raw hipStream_t handle (int) or None."""
     rc = lib().m2rnn_fwd(ctypes.byref(desc), _ptr(q), _ptr(k), _ptr(v), _ptr(f), _ptr(W),
                          _ptr(H0), _ptr(y), _ptr(HT), _ptr(ckpt), _ptr(workspace),
-                         _nbytes(workspace), ctypes.c_void_p(stream or 0))
+                         _nbytes(workspace), stream or 0)
     if check and rc != 0:
         raise M2RNNError(rc, "m2rnn_fwd")
     return rc
@@ -154,7 +169,7 @@ def m2rnn_bwd(desc, q, k, v, f, W, H0, ckpt, dy, dHT, dq, dk, dv, df, dW, dH0, w
     rc = lib().m2rnn_bwd(ctypes.byref(desc), _ptr(q), _ptr(k), _ptr(v), _ptr(f), _ptr(W),
                          _ptr(H0), _ptr(ckpt), _ptr(dy), _ptr(dHT), _ptr(dq), _ptr(dk), _ptr(dv),
                          _ptr(df), _ptr(dW), _ptr(dH0), _ptr(workspace), _nbytes(workspace),
-                         ctypes.c_void_p(stream or 0))
+                         stream or 0)
     if check and rc != 0:
         raise M2RNNError(rc, "m2rnn_bwd")
     return rc
@@ -162,10 +177,9 @@ def m2rnn_bwd(desc, q, k, v, f, W, H0, ckpt, dy, dHT, dq, dk, dv, df, dW, dH0, w
 
 def make_opts(w_r=None, dw_r=None, grad_clip=0.0, gate=None, dgate=None):
     """m2rnn_opts from torch tensors (or None); gate = (alpha, beta), dgate = (dalpha, dbeta)."""
-    p = lambda x: None if x is None else x.data_ptr()
     ga, gb = gate if gate is not None else (None, None)
     da, db = dgate if dgate is not None else (None, None)
-    return m2rnn_opts(p(w_r), p(dw_r), float(grad_clip), p(ga), p(gb), p(da), p(db))
+    return m2rnn_opts(_ptr(w_r), _ptr(dw_r), float(grad_clip), _ptr(ga), _ptr(gb), _ptr(da), _ptr(db))
 
 
 def m2rnn_fwd_opt(desc, opts, q, k, v, f, W, H0, y, HT, ckpt, workspace, stream=None, check=True):
@@ -173,7 +187,7 @@ def m2rnn_fwd_opt(desc, opts, q, k, v, f, W, H0, y, HT, ckpt, workspace, stream=
     rc = lib().m2rnn_fwd_opt(ctypes.byref(desc), None if opts is None else ctypes.byref(opts),
                              _ptr(q), _ptr(k), _ptr(v), _ptr(f), _ptr(W), _ptr(H0), _ptr(y),
                              _ptr(HT), _ptr(ckpt), _ptr(workspace), _nbytes(workspace),
-                             ctypes.c_void_p(stream or 0))
+                             stream or 0)
     if check and rc != 0:
         raise M2RNNError(rc, "m2rnn_fwd_opt")
     return rc
@@ -183,7 +197,7 @@ def m2rnn_fwd_static(desc, opts, q, k, v, f, W, H0, y, HT, ckpt, stream=None, ch
     """m2rnn_fwd_opt on the library's own static scratch (no workspace argument)."""
     rc = lib().m2rnn_fwd_static(ctypes.byref(desc), None if opts is None else ctypes.byref(opts),
                                 _ptr(q), _ptr(k), _ptr(v), _ptr(f), _ptr(W), _ptr(H0), _ptr(y),
-                                _ptr(HT), _ptr(ckpt), ctypes.c_void_p(stream or 0))
+                                _ptr(HT), _ptr(ckpt), stream or 0)
     if check and rc != 0:
         raise M2RNNError(rc, "m2rnn_fwd_static")
     return rc
@@ -195,7 +209,7 @@ def m2rnn_bwd_opt(desc, opts, q, k, v, f, W, H0, ckpt, dy, dHT, dq, dk, dv, df, 
                              _ptr(q), _ptr(k), _ptr(v), _ptr(f), _ptr(W), _ptr(H0), _ptr(ckpt),
                              _ptr(dy), _ptr(dHT), _ptr(dq), _ptr(dk), _ptr(dv), _ptr(df),
                              _ptr(dW), _ptr(dH0), _ptr(workspace), _nbytes(workspace),
-                             ctypes.c_void_p(stream or 0))
+                             stream or 0)
     if check and rc != 0:
         raise M2RNNError(rc, "m2rnn_bwd_opt")
     return rc
@@ -220,7 +234,7 @@ def m2rnn_conv_silu_fwd(x, w, bias, out, stream=None, check=True):
     """out = SiLU(causal depthwise conv1d(4) of x [B,T,C]); w [C,4], bias [C] or None."""
     B, T, C = x.shape
     rc = lib().m2rnn_conv_silu_fwd(B, T, C, _io_code(x), _ptr(x), _ptr(w), _ptr(bias), _ptr(out),
-                                   ctypes.c_void_p(stream or 0))
+                                   stream or 0)
     return _check(rc, "m2rnn_conv_silu_fwd", check)
 
 
@@ -228,7 +242,7 @@ def m2rnn_conv_silu_bwd(x, w, bias, dout, dx, dw, dbias, workspace, stream=None,
     B, T, C = x.shape
     rc = lib().m2rnn_conv_silu_bwd(B, T, C, _io_code(x), _ptr(x), _ptr(w), _ptr(bias), _ptr(dout),
                                    _ptr(dx), _ptr(dw), _ptr(dbias), _ptr(workspace),
-                                   _nbytes(workspace), ctypes.c_void_p(stream or 0))
+                                   _nbytes(workspace), stream or 0)
     return _check(rc, "m2rnn_conv_silu_bwd", check)
 
 
@@ -240,7 +254,7 @@ def m2rnn_gated_rmsnorm_fwd(y, a, w, eps, out, s, stream=None, check=True):
     """out = RMSNorm(y (.) SiLU(a)) over the last axis of [B,T,D]; s [B,T] fp32 or None."""
     B, T, D = y.shape
     rc = lib().m2rnn_gated_rmsnorm_fwd(B, T, D, _io_code(y), _ptr(y), _ptr(a), _ptr(w), float(eps),
-                                       _ptr(out), _ptr(s), ctypes.c_void_p(stream or 0))
+                                       _ptr(out), _ptr(s), stream or 0)
     return _check(rc, "m2rnn_gated_rmsnorm_fwd", check)
 
 
@@ -249,7 +263,7 @@ def m2rnn_gated_rmsnorm_bwd(y, a, w, eps, s, dout, dy, da, dw, workspace, stream
     rc = lib().m2rnn_gated_rmsnorm_bwd(B, T, D, _io_code(y), _ptr(y), _ptr(a), _ptr(w), float(eps),
                                        _ptr(s), _ptr(dout), _ptr(dy), _ptr(da), _ptr(dw),
                                        _ptr(workspace), _nbytes(workspace),
-                                       ctypes.c_void_p(stream or 0))
+                                       stream or 0)
     return _check(rc, "m2rnn_gated_rmsnorm_bwd", check)
 
 
@@ -263,6 +277,7 @@ class Scan:
     def __init__(self, B, T, N, K, V, io, Nqk=None, chunk=0, backward=True, device="cuda"):
         import torch
         self.torch = torch
+        self._native = _call()
         self.desc = make_desc(B, T, N, K, V, M2RNN_BF16 if io in ("bf16", M2RNN_BF16) else M2RNN_F32,
                               Nqk=Nqk, chunk=chunk)
         d = self.desc
@@ -287,42 +302,41 @@ class Scan:
         self.workspace = torch.empty(max(ws, 256), dtype=torch.uint8, device=dev)
 
     def _stream(self):
-        return self.torch.cuda.current_stream().cuda_stream
+        # (torch.cuda.current_stream().cuda_stream without the object in between, 1 us of a call)
+        C = self.torch._C
+        return C._cuda_getCurrentRawStream(C._cuda_getDevice())
 
     def fwd(self, q, k, v, f, W, H0=None, w_r=None, gate=None):
         """w_r [N,V] (io dtype): adds the residual w_r (.) v_t to y_t.  gate = (alpha, beta)
         [N] fp32 each: f is the input of the forget-gate function."""
-        if w_r is None and gate is None:
-            m2rnn_fwd(self.desc, q, k, v, f, W, H0, self.y, self.HT, self.ckpt, self.workspace,
-                      stream=self._stream())
-        else:
-            m2rnn_fwd_opt(self.desc, make_opts(w_r=w_r, gate=gate), q, k, v, f, W, H0, self.y,
-                          self.HT, self.ckpt, self.workspace, stream=self._stream())
+        alpha, beta = gate if gate is not None else (None, None)
+        ws = self.workspace
+        rc = self._native.fwd(ctypes.addressof(self.desc), w_r, alpha, beta, q, k, v, f, W, H0, self.y, self.HT,
+                              self.ckpt, ws, self._stream(), _nbytes(ws))
+        if rc != 0:
+            raise M2RNNError(rc, "m2rnn_fwd" if w_r is None and gate is None else "m2rnn_fwd_opt")
         return self.y, self.HT
 
     def bwd(self, q, k, v, f, W, H0, dy, dHT=None, use_ckpt=True, w_r=None, grad_clip=0.0,
             gate=None):
         """With w_r the result has a further entry, dw_r [N,V] fp32; with gate two more,
         dalpha and dbeta [N] fp32 (and df is the gradient of the gate's input)."""
-        ck = self.ckpt if use_ckpt else None
-        if w_r is None and gate is None and not grad_clip > 0:
-            m2rnn_bwd(self.desc, q, k, v, f, W, H0, ck, dy, dHT, self.dq, self.dk, self.dv,
-                      self.df, self.dW, self.dH0, self.workspace, stream=self._stream())
-            return self.dq, self.dk, self.dv, self.df, self.dW, self.dH0
-        dw_r = None
+        out = (self.dq, self.dk, self.dv, self.df, self.dW, self.dH0)
+        plain = w_r is None and gate is None and not grad_clip > 0
+        alpha = beta = dw_r = dalpha = dbeta = None
         if w_r is not None:
             dw_r = self.torch.empty((self.desc.N, self.desc.V), dtype=self.torch.float32,
                                     device=self.dW.device)
-        dgate = None
-        if gate is not None:
-            dgate = tuple(self.torch.empty((self.desc.N,), dtype=self.torch.float32,
-                                           device=self.dW.device) for _ in range(2))
-        m2rnn_bwd_opt(self.desc, make_opts(w_r, dw_r, grad_clip, gate, dgate), q, k, v, f, W, H0,
-                      ck, dy, dHT, self.dq, self.dk, self.dv, self.df, self.dW, self.dH0,
-                      self.workspace, stream=self._stream())
-        out = (self.dq, self.dk, self.dv, self.df, self.dW, self.dH0)
-        if dw_r is not None:
             out = out + (dw_r,)
-        if dgate is not None:
-            out = out + dgate
+        if gate is not None:
+            alpha, beta = gate
+            dalpha, dbeta = (self.torch.empty((self.desc.N,), dtype=self.torch.float32,
+                                              device=self.dW.device) for _ in range(2))
+            out = out + (dalpha, dbeta)
+        ws = self.workspace
+        rc = self._native.bwd(ctypes.addressof(self.desc), w_r, dw_r, alpha, beta, dalpha, dbeta, q, k, v, f, W, H0,
+                              self.ckpt if use_ckpt else None, dy, dHT, self.dq, self.dk, self.dv, self.df, self.dW,
+                              self.dH0, ws, self._stream(), _nbytes(ws), 0.0 if plain else grad_clip)
+        if rc != 0:
+            raise M2RNNError(rc, "m2rnn_bwd" if plain else "m2rnn_bwd_opt")
         return out

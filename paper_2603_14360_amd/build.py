@@ -1,4 +1,5 @@
-"""Builds libm2rnn.so (the C-ABI library) in-tree with hipcc for gfx950.
+"""Builds libm2rnn.so (the C-ABI library) in-tree with hipcc for gfx950, and _call.so, the host-only
+Python module that the binding calls it with.
 
     python -m paper_2603_14360_amd.build
 
@@ -16,8 +17,10 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libm2rnn.so")
+CALL = os.path.join(HERE, "_call.so")
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+CXX = os.environ.get("CXX", "g++")
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
@@ -38,13 +41,33 @@ def _compile(src):
     return obj
 
 
+def _compile_call():
+    """csrc/py_call.cpp against the headers of the torch that is installed."""
+    import sysconfig
+    import torch
+    root = os.path.dirname(torch.__file__)
+    inc = [os.path.join(root, "include"), os.path.join(root, "include", "torch", "csrc", "api", "include"),
+           sysconfig.get_paths()["include"]]
+    tmp = CALL + ".tmp%d" % os.getpid()
+    cmd = [CXX, "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI] + ["-I" + i for i in inc]
+    cmd += [os.path.join(CSRC, "py_call.cpp"), "-o", tmp, "-L" + os.path.join(root, "lib"),
+            "-ltorch_python", "-ltorch_cpu", "-lc10"]
+    proc = subprocess.run(cmd, capture_output=True, text=True)
+    if proc.returncode != 0:
+        raise RuntimeError("%s failed on py_call.cpp:\n%s" % (CXX, proc.stderr))
+    os.replace(tmp, CALL)
+
+
 def build(verbose=True):
     os.makedirs(OBJ, exist_ok=True)
     sources = sorted(glob.glob(os.path.join(CSRC, "*.hip")))
     if not sources:
         raise RuntimeError("no HIP sources under " + CSRC)
     with concurrent.futures.ThreadPoolExecutor(max_workers=8) as pool:
+        call = pool.submit(_compile_call)
         objs = list(pool.map(_compile, sources))
+        call.result()
     tmp = LIB + ".tmp%d" % os.getpid()
     subprocess.check_call([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp] + objs)
     os.replace(tmp, LIB)

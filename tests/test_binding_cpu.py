@@ -1,0 +1,82 @@
+"""CPU-only: the module that hands a Scan's tensors to the library.  What arrives there is read with a
+recorder in the place of the library's entry points."""
+import ctypes
+
+import pytest
+import torch
+
+from paper_2603_14360_amd import binding as mb
+
+P = ctypes.c_void_p
+FWD = ctypes.CFUNCTYPE(ctypes.c_int, P, ctypes.POINTER(mb.m2rnn_opts), *[P] * 10, ctypes.c_size_t, P)
+BWD = ctypes.CFUNCTYPE(ctypes.c_int, P, ctypes.POINTER(mb.m2rnn_opts), *[P] * 16, ctypes.c_size_t, P)
+
+
+@pytest.fixture
+def recorded():
+    """(scan, calls): calls collects (name, options, arguments) instead of running them."""
+    calls = []
+
+    def record(name):
+        def f(desc, opts, *args):
+            calls.append((name, {n: getattr(opts[0], n) for n, _ in mb.m2rnn_opts._fields_}, (desc,) + args))
+            return 0 if len(calls) < 9 else 3
+        return f
+    fwd, bwd = FWD(record("fwd")), BWD(record("bwd"))
+    native, L = mb._call(), mb.lib()
+    address = lambda f: ctypes.cast(f, P).value
+    native.init(address(fwd), address(bwd))
+    try:
+        scan = mb.Scan(2, 3, 4, 16, 16, "bf16", device="cpu")
+        scan._stream = lambda: 77
+        yield scan, calls
+    finally:
+        native.init(address(L.m2rnn_fwd_opt), address(L.m2rnn_bwd_opt))
+
+
+def test_arguments_reach_their_places(recorded):
+    scan, calls = recorded
+    t = lambda: torch.zeros(8)
+    q, k, v, f, W, H0, dy, dHT, w_r, alpha, beta = (t() for _ in range(11))
+    a = lambda x: x.data_ptr()
+    ws, n = a(scan.workspace), scan.workspace.numel()
+    none = dict.fromkeys(("w_r", "dw_r", "gate_alpha", "gate_beta", "dgate_alpha", "dgate_beta"), None)
+    desc = ctypes.addressof(scan.desc)
+
+    assert scan.fwd(q, k, v, f, W, H0) == (scan.y, scan.HT)
+    args = tuple(map(a, (q, k, v, f, W, H0, scan.y, scan.HT, scan.ckpt))) + (ws, n, 77)
+    assert calls[-1] == ("fwd", dict(none, grad_clip=0.0), (desc,) + args)
+    scan.fwd(a(q), k, v, f, W, w_r=w_r, gate=(alpha, beta))   # (an address for a tensor; no H0)
+    opts = dict(none, grad_clip=0.0, w_r=a(w_r), gate_alpha=a(alpha), gate_beta=a(beta))
+    assert calls[-1] == ("fwd", opts, (desc,) + args[:5] + (None,) + args[6:])
+
+    outs = (scan.dq, scan.dk, scan.dv, scan.df, scan.dW, scan.dH0)
+    got = scan.bwd(q, k, v, f, W, H0, dy, dHT)
+    assert all(x is y for x, y in zip(got, outs)) and len(got) == 6
+    args = tuple(map(a, (q, k, v, f, W, H0, scan.ckpt, dy, dHT) + outs)) + (ws, n, 77)
+    assert calls[-1] == ("bwd", dict(none, grad_clip=0.0), (desc,) + args)
+    scan.bwd(q, k, v, f, W, H0, dy, grad_clip=-1.0)   # (off)
+    assert calls[-1][1]["grad_clip"] <= 0.0 and calls[-1][2][9] is None
+    got = scan.bwd(q, k, v, f, W, None, dy, dHT, use_ckpt=False, w_r=w_r, grad_clip=0.5, gate=(alpha, beta))
+    assert [tuple(x.shape) for x in got[6:]] == [(4, 16), (4,), (4,)]
+    opts = dict(w_r=a(w_r), dw_r=a(got[6]), grad_clip=0.5, gate_alpha=a(alpha), gate_beta=a(beta), dgate_alpha=a(got[7]),
+                dgate_beta=a(got[8]))
+    assert calls[-1] == ("bwd", opts, (desc,) + args[:5] + (None, None) + args[7:])
+
+
+def test_errors_are_exceptions(recorded):
+    scan, calls = recorded
+    x = torch.zeros(8)
+    with pytest.raises(TypeError):
+        scan.fwd([0], x, x, x, x)
+    with pytest.raises(RuntimeError):
+        scan.fwd(torch.empty(2, layout=torch.sparse_coo), x, x, x, x)
+    assert not calls
+    with pytest.raises(TypeError):
+        scan._native.fwd(x)
+    calls.extend([None] * 9)
+    with pytest.raises(mb.M2RNNError) as e:
+        scan.fwd(x, x, x, x, x)
+    assert e.value.code == 3 and "m2rnn_fwd failed" in str(e.value)
+    with pytest.raises(mb.M2RNNError, match="m2rnn_bwd_opt failed"):
+        scan.bwd(x, x, x, x, x, None, x, grad_clip=1.0)
