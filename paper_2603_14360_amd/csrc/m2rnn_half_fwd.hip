@@ -407,14 +407,27 @@ bool half_serves(int K, int V, int units, int T) {
   return V != 32 || load <= 4 || (K == 64 && load <= 6 && T >= 32);
 }
 
+namespace {
+// Which launches of this path run on one wave per 128 elements (m2rnn_pair_fwd.hip): those that leave every
+// wave a SIMD.  us, T = 2048, waves that share columns -> waves with whole rows: 64 x 64 4 states 420 -> 399,
+// 16 431 -> 410, 32 443 -> 424, but 128 (four waves a SIMD, with checkpoints, T = 4096) 1550 -> 2120; 32 x 32 16 states
+// 402 -> 334; 64 x 32 16 states 405 -> 339; 64 x 16 16 states 287 -> 300.
+// (By the states alone, not by the split that the room allows: y's bits do not depend on the room.)
+bool pair_serves(int K, int V, int units) {
+  return (V == 32 || V == 64) && half_load(K, V, units, 1) <= 1;
+}
+}  // namespace
 hipError_t half_fwd(const FwdArgs &a, hipStream_t s) {
   // (a pass that only writes checkpoints has no partial sums)
   const size_t part = a.write_y ? (size_t)a.B * a.T * a.N * a.V * 4 : 0;
   const int rb = half_pick_rb(a.K, a.V, a.B * a.N, part, a.ws_bytes, a.write_y ? a.T : INT_MAX);
-#define X(K_, V_, RB_) \
+  if (rb && pair_serves(a.K, a.V, a.B * a.N)) return pair_fwd(a, rb, s);
+#define H(K_, V_, RB_) \
   if (a.K == K_ && a.V == V_ && rb == RB_) return launch<Half<K_, V_, RB_>>(a, s);
-  M2RNN_HALF_CASES(X)
-#undef X
+#define W(K_, V_, RB_)
+  M2RNN_HALF_SPLITS(H, W)
+#undef H
+#undef W
   return hipErrorInvalidValue;
 }
 

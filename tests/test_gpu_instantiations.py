@@ -54,10 +54,13 @@ SPLITS = [
     (64, 16, 10, 4, 261, "half<64,16,2>"), (64, 16, 10, 8, 261, "half<64,16,4>"),
     (32, 16, 3, 5, 261, "half<32,16,1>"), (32, 16, 10, 8, 261, "half<32,16,2>"),
     (64, 32, 10, 4, 35, "half<64,32,2>"), (64, 32, 10, 9, 35, "half<64,32,4>"), (64, 32, 10, 21, 35, "half<64,32,8>"),
+    (32, 32, 20, 13, 261, "half<32,32,2>"), (64, 32, 10, 13, 261, "half<64,32,2>"), (64, 32, 10, 13, 35, "half<64,32,8>"),
+    (64, 64, 10, 7, 35, "half<64,64,1>"),
 ]
 # ... and that the checkpoint pass of the backward takes: (K, V, states)
 CHECKPOINT_PASS = [(16, 16, 200), (32, 16, 100), (32, 16, 300), (64, 16, 40), (64, 16, 100), (64, 16, 200), (64, 32, 40),
-                   (64, 32, 90), (64, 32, 210), (32, 32, 5), (32, 32, 100), (32, 32, 300), (64, 64, 40), (64, 64, 120)]
+                   (64, 32, 90), (64, 32, 210), (32, 32, 5), (32, 32, 100), (32, 32, 300), (64, 64, 40), (64, 64, 120),
+                   (64, 32, 130), (64, 64, 4), (64, 64, 70), (64, 32, 4)]
 DECODE = [(K, V) for V in (16, 32, 64) for K in (16, 32, 64, 128)]
 # V = 128 in fp32 on the vector ALUs, W beside the state in LDS (forward, backward) or not
 GENERIC_F32 = [(16, 128), (64, 128), (128, 128)]
