@@ -302,9 +302,10 @@ __device__ __forceinline__ void quad_fwd_part(const FwdArgs &a, float *__restric
   auto flush = [&](int t0, int len, int buf) {
     for (int idx = tid; idx < len * V; idx += THREADS) {
       const int s = idx / V, j = idx % V;
-      float acc = 0.f;
+      float acc = 0.f, acc1 = 0.f;
 #pragma unroll
-      for (int i = 0; i < Q::NW * 64 / V; ++i) acc += (&sm.y[buf][s][0][0])[i * V + j];
+      for (int i = 0; i < Q::NW * 64 / V; ++i) (Q::S > 1 && i % 2 ? acc1 : acc) += (&sm.y[buf][s][0][0])[i * V + j];
+      if constexpr (Q::S > 1) acc += acc1;  // (twice as many terms: two chains of them)
       const size_t off = (size_t)(t0 + s) * v_step + j;
       if constexpr (Q::P == 1 || SEQ) {
         float *dst = (float *)a.y + ((size_t)b * T * N + n) * V + off;
@@ -721,9 +722,10 @@ __global__ void __launch_bounds__(Q::THREADS, Q::V < 64 ? 2 : 1) quad_bwd_kernel
           for (int idx = tid; idx < len * V; idx += THREADS) finish_dv(idx, dvsum[0]);
         }
         if (tid < len) {
-          float acc = 0.f;
+          float acc = 0.f, acc1 = 0.f;
 #pragma unroll
-          for (int r = 0; r < NW * 4; ++r) acc += sm.df[r][tid];
+          for (int r = 0; r < NW * 4; ++r) (Q::S > 1 && r % 2 ? acc1 : acc) += sm.df[r][tid];
+          if constexpr (Q::S > 1) acc += acc1;
           const size_t o = f0 + (size_t)(t0 + tid) * N;
           if constexpr (SEQ) acc = dfsum = part ? dfsum + acc : acc;
           if (last_part) a.df[o] = acc;
