@@ -25,6 +25,8 @@
 //      is kept, one register of 16 lanes per step, so that 16 steps of y collect in four registers.
 //      (Kept by a select: with zeros in the other rows of A and a running sum, 0 x NaN would
 //      carry a NaN of the state into the y of earlier steps.)
+// Launches that leave every wave a SIMD run on waves with whole rows instead where V is 32 or 64
+// (m2rnn_pair_fwd.hip).
 // q, k, v, f for 16 steps at a time are staged through LDS, the next block's global loads in
 // flight behind the current block.
 #include "m2rnn_kernels.hpp"

@@ -18,10 +18,9 @@
 //   dS = (1-f) G (1 - Z^2)                       -> fp16, to LDS (row-major)
 //   dW' += H'_{t-1}^T dS       MFMA k = rows     (A = stash tiles, B = own dS)
 //   Ccarry = f G + dS W^T      MFMA k = columns  (A = dS rows from LDS, B = W^T)
-// The per-step vectors dq_t = H_t dy_t, dk_t = dS v_t, dv_t = dS^T k_t and the
-// scalar df_t = sum G (H_{t-1} - Z_t) never leave the matrix core during a
-// chunk: each is one more MFMA whose second operand (dy_t, v_t, k_t, ones) is
-// placed in column / row (t mod chunk) only, so a 16 x 16 accumulator collects
+// The per-step vectors dq_t = H_t dy_t, dk_t = dS v_t, dv_t = dS^T k_t never leave the matrix core
+// during a chunk (the scalar df_t = sum G (H_{t-1} - Z_t) is summed by lane exchanges): each
+// is one more MFMA whose second operand (dy_t, v_t, k_t) is placed in column / row (t mod chunk) only, so a 16 x 16 accumulator collects
 // the chunk's steps side by side and nothing is read back per step.  At the
 // end of a chunk the partial accumulators of the waves are added through LDS
 // in a fixed order and stored; nothing uses atomics.

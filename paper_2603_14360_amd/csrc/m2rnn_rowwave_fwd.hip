@@ -24,7 +24,8 @@
 // back by the transposing load with rows in the registers and columns across lanes, the A
 // operand of a 16x16x16 MFMA with q; that product follows in the middle of the next step.  (A
 // product with an identity fragment transposes as well, but takes 16 cycles of the matrix core a
-// tile, which add to the vector work: matrix and vector instructions of a SIMD hardly overlap.)
+// tile, which add to the vector work: matrix and vector instructions of a SIMD hardly overlap.  8 x 4096,
+// 84 heads of 64 x 16, a training step: 4817 -> 4741 us.)
 // The K/16 row-block partials of a state are summed once per 16 steps through LDS and stored as
 // whole bf16 rows.
 #include "m2rnn_kernels.hpp"
