@@ -65,12 +65,11 @@ struct RowWaveB {
   static constexpr int OFF_CK = OFF_Q + CB * K * 4;     // float c k   [CB][K]
   // Operands of the products over two steps: 16-byte items (4 values; zeros), in odd steps (zeros; 4
   // values), the items of a step's dy (scaled), v and k in a row.  A lane whose row of the operand is
-  // another step's reads zeros at the same offsets behind OFF_ZERO.
+  // another step's reads the zeros in front of them at the same offsets.
   static constexpr int OP_V = 64, OP_K = 128, OP_STEP = OP_K + 4 * K;
-  static constexpr int OFF_OP = OFF_CK + CB * K * 4;    // half dy, v, k [CB][OP_STEP bytes]
-  static constexpr int OFF_ZERO = OFF_OP + CB * OP_STEP;  // [OP_STEP] zero bytes
-  static constexpr int OFF_VH = OFF_ZERO + OP_STEP;     // half  v     [CB][V]
-  static constexpr int OFF_DY = OFF_VH + CB * V * 2;    // float dy    [CB][V]
+  static constexpr int OFF_ZERO = OFF_CK + CB * K * 4;  // [OP_STEP] zero bytes
+  static constexpr int OFF_OP = OFF_ZERO + OP_STEP;     // half dy, v, k [CB][OP_STEP bytes]
+  static constexpr int OFF_DY = OFF_OP + CB * OP_STEP;  // float dy    [CB][V]
   static constexpr int OFF_F = OFF_DY + CB * V * 4;     // per step: f, c(1-f), 1-f, f16x2 -(1-f)/c^2,
                                                         //           1/(dy scale), 3 pad (8 floats)
   static constexpr int OFF_HS = OFF_F + CB * 32;        // [NW][CB][512] stash of H'_{t-1} (fp16 tiles)
@@ -130,14 +129,13 @@ __global__ void __launch_bounds__(RW::THREADS, 3) rowwave_bwd_kernel(BwdArgs a, 
   lchar *const l0 = (lchar *)lds;
   float *qS = (float *)(lds + RW::OFF_Q);
   float *ckS = (float *)(lds + RW::OFF_CK);
-  _Float16 *vH = (_Float16 *)(lds + RW::OFF_VH);
   float *dyS = (float *)(lds + RW::OFF_DY);
   float *fS = (float *)(lds + RW::OFF_F);
   f4_t *pv = (f4_t *)(lds + RW::OFF_PV);
   float *pf = (float *)(lds + RW::OFF_PF);
   // zeros: the pad, and the zero halves of the operand items, which stay (visible after the first barrier)
-  for (int i = tid; i < (RW::OFF_VH - RW::OFF_OP) / 16; i += THREADS)
-    *(u4_t *)(lds + RW::OFF_OP + 16 * i) = u4_t{0u, 0u, 0u, 0u};
+  for (int i = tid; i < (RW::OFF_DY - RW::OFF_ZERO) / 16; i += THREADS)
+    *(u4_t *)(lds + RW::OFF_ZERO + 16 * i) = u4_t{0u, 0u, 0u, 0u};
   __syncthreads();
 
   const bf16_raw *__restrict__ qg = (const bf16_raw *)a.q;
@@ -240,13 +238,10 @@ __global__ void __launch_bounds__(RW::THREADS, 3) rowwave_bwd_kernel(BwdArgs a, 
       const float up = pow2i(10 - ex);
       const float sx = tid < 32 ? 1.f : up;
       float x0[4] = {sx * x[0], sx * x[1], sx * x[2], sx * x[3]}, x1[4] = {sx * x[4], sx * x[5], sx * x[6], sx * x[7]};
-      const h4_t o0 = cvt4_f16(x0), o1 = cvt4_f16(x1);
       h4_t *op = op_items(e >> 1, tid < 32 ? RW::OP_V : 0) + 4 * (e & 1);
-      op[0] = o0;
-      op[2] = o1;
-      if (tid < 32) {
-        *(h8_t *)&vH[8 * e] = __builtin_shufflevector(o0, o1, 0, 1, 2, 3, 4, 5, 6, 7);
-      } else {
+      op[0] = cvt4_f16(x0);
+      op[2] = cvt4_f16(x1);
+      if (tid >= 32) {
         *(f4_t *)&dyS[8 * e] = f4_t{x[0], x[1], x[2], x[3]};
         *(f4_t *)&dyS[8 * e + 4] = f4_t{x[4], x[5], x[6], x[7]};
         if ((e & 1) == 0) fS[(e >> 1) * 8 + 4] = pow2i(ex - 10);
@@ -351,14 +346,12 @@ __global__ void __launch_bounds__(RW::THREADS, 3) rowwave_bwd_kernel(BwdArgs a, 
     // is base + compile-time immediate.  The lane's column index is opaque as well: the
     // per-step masks (jl == s) are then built per step instead of being kept for every s.
     lchar *bRow4 = l0 + row * 4;            // q, c k (fp32) of this lane's row
-    lchar *bOp = l0 + (jl * RW::OP_STEP + ig * 16 + RW::OFF_OP);  // operand items of step jl, columns (rows) 4 ig ..
-    lchar *bOp0 = l0 + (ig * 16 + RW::OFF_ZERO);                  // ... and the zeros in their place
-    lchar *bCol2 = l0 + 4 * ig * 2;         // v (fp16) columns 4 ig ..
-    lchar *bCol4 = l0 + 4 * ig * 4;         // dy (fp32) columns 4 ig ..
+    lchar *bCol4 = l0 + 4 * ig * 4;         // dy (fp32) columns 4 ig .., operand items of columns (rows) 4 ig ..
+    lchar *bOp = bCol4 + (jl * RW::OP_STEP + RW::OFF_OP - RW::OFF_ZERO);  // OFF_ZERO behind it: the items of step jl
     lchar *bZero = l0;                      // wave-uniform reads (f)
     int jlo = jl;
-    asm volatile("" : "+v"(bRow4), "+v"(bOp), "+v"(bOp0), "+v"(bCol2), "+v"(bCol4), "+v"(bZero), "+v"(jlo));
-    auto op_base = [&](int s) __attribute__((always_inline)) { return jlo >> 1 == s >> 1 ? bOp : bOp0; };
+    asm volatile("" : "+v"(bRow4), "+v"(bOp), "+v"(bCol4), "+v"(bZero), "+v"(jlo));
+    auto op_base = [&](int s) __attribute__((always_inline)) { return jlo >> 1 == s >> 1 ? bOp : bCol4; };
 
     // ---- 1. recompute the chunk; the stash stays in registers
     h4_t zpS[CB];
@@ -374,7 +367,7 @@ __global__ void __launch_bounds__(RW::THREADS, 3) rowwave_bwd_kernel(BwdArgs a, 
           const float f = __builtin_bit_cast(float, (uint32_t)fg2.x), gp = __builtin_bit_cast(float, (uint32_t)fg2.y);
           const float m2g = -2.f * gp;
           const float cki = lds_ld<float>(bRow4, RW::OFF_CK + s * K * 4);
-          const h4_t v4 = lds_ld<h4_t>(bCol2, RW::OFF_VH + s * V * 2);
+          const h4_t v4 = lds_ld<h4_t>(bCol4, RW::OFF_OP + s * RW::OP_STEP + RW::OP_V + (s & 1) * 8);
           lds_st<h4_t>(hsw, s * 512, hcur);
           const f4_t acc = mfma_k32(wfT, __builtin_bit_cast(h8_t, split4_hi_lo(h)), zero4);
           float z[4];
@@ -392,7 +385,7 @@ __global__ void __launch_bounds__(RW::THREADS, 3) rowwave_bwd_kernel(BwdArgs a, 
           hcur = cvt4_f16(h);
           // dq = H dy of two steps: A[m = s][k = j] = dy_j, B[k = j][n = i] = H_s in the first four
           // slots for the even step, in the last four for the odd one; zeros in all other rows
-          if (s & 1) dqacc = mfma_k32(lds_ld<h8_t>(op_base(s), 0), join(hbefore, hcur), dqacc);
+          if (s & 1) dqacc = mfma_k32(lds_ld<h8_t>(op_base(s), RW::OFF_ZERO), join(hbefore, hcur), dqacc);
         }
         settle(dqacc);
       }
@@ -457,8 +450,8 @@ __global__ void __launch_bounds__(RW::THREADS, 3) rowwave_bwd_kernel(BwdArgs a, 
             // dW' += H'^T dS: A[m = j1][k = i] = H'[i][j1], B[k = i][n = j2] = dS[i][j2]
             const lchar *op = op_base(s);
             const h8_t dT2 = join(dT, dT1);
-            dkacc = mfma_k32(lds_ld<h8_t>(op, RW::OP_V), join(dsp, ds1), dkacc);
-            dvacc = mfma_k32(lds_ld<h8_t>(op, RW::OP_K + rb * 64), dT2, dvacc);
+            dkacc = mfma_k32(lds_ld<h8_t>(op, RW::OFF_ZERO + RW::OP_V), join(dsp, ds1), dkacc);
+            dvacc = mfma_k32(lds_ld<h8_t>(op + rb * 64, RW::OFF_ZERO + RW::OP_K), dT2, dvacc);
             dWacc = mfma_k32(join(hT, hT1), dT2, dWacc);
             // df = sum G (H' - Z') / c over the lanes, each lane of a quad one step of the block
             const float y = lane_sum<0xB1>(dfl, df1, jlo & 1);
