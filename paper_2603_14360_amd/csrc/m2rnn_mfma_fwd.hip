@@ -263,7 +263,7 @@ __global__ void __launch_bounds__(TL::THREADS, 2)
   //    columns in lanes: A[m = j][k = i] = hi(H'[i][j]); B[k = i][n] = q_i for n == s, else 0: column s
   //    of yacc collects step s.  (A product with the identity transposes too, for 16 more cycles of the
   //    matrix core, which hardly overlap the SIMD's vector work: 4 x 8192, 8 heads of 128 x 128, a training
-  //    step 10645 us so, 10394 through LDS.)
+  //    step 10585 us so, 10440 through LDS.)
   //    (0 x NaN is NaN: a NaN that enters the state reaches the y of the earlier steps of its
   //    16-step block so.  V < 128 holds it back: q in every column, column s kept by selects.  At
   //    V = 128 those take 2.7 % of a 4 x 8192, 8-head training step, 10.88 -> 11.19 ms; transposed,
