@@ -125,8 +125,8 @@ size_t m2rnn_ckpt_bytes(const m2rnn_desc *desc);
  *     query asks for 537 MB and 558 MB and takes 0.4 and 0.54 of the time.
  * fp32 with K = V = 32 and at most 128 states (B N): the query holds the partial sums of half states,
  * with which two thirds of the time suffice.  A third kind of call does without: the forward on 256
- * bytes, the backward on 4 B N (V^2 + ((C - 1) / 16) K V) [+ 8 B T N K] + 4096 N V + 2048 N bytes, all
- * its results the same to rounding. */
+ * bytes, the backward on 4 B N (V^2 + ((C - 1) / 16) K V) [+ 8 B T N K] + 4096 N V + 2048 N bytes, with
+ * the same results (dv, df and dW, whose sums take another order, to rounding). */
 size_t m2rnn_workspace_bytes(const m2rnn_desc *desc, int bwd);
 
 /*

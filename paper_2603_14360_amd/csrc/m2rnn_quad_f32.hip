@@ -17,7 +17,9 @@
 // Split (V = 32): both halves of a wave hold the SAME four rows and contract 16 of the 32 columns
 // each, half of the matrix instructions; the halves' sums meet by a lane swap that leaves two
 // of the four rows to each, half of the vector instructions.  Twice as many waves take part, which
-// pays as long as SIMDs are free (split_pays).
+// pays as long as SIMDs are free (split_pays).  A half contracts the columns of two of the four chains
+// (columns 4 i, 4 i + 1 or 4 i + 2, 4 i + 3), so that every sum has the order of the whole rows: states,
+// checkpoints, y and carried gradients have the same bits in both forms, whatever room a call has.
 //
 // Measured against the vector-ALU kernels that these replace (one workgroup per state, state and
 // W in LDS, three barriers per step): B = 4, N = 8, K = V = 32, T = 512 forward 1.13 -> 0.245 ms,
@@ -113,8 +115,8 @@ __device__ __forceinline__ f4_t quad_transpose(f4_t x, bool odd, bool high) {
   return f4_t{high ? q2 : a0, high ? q3 : a1, high ? a2 : q0, high ? a3 : q1};
 }
 
-// The same out of split rows (registers: rows 2 half, 2 half + 1 of column lane % 32): the half that
-// contracts columns 16 half .. gets all four rows of those, in both of its groups of 16 lanes.
+// The same out of split rows (registers: rows 2 half, 2 half + 1 of a column): half h gets all four rows
+// of the columns that the lanes 16 h .. + 15 of either half hold, in both of its groups of 16 lanes.
 __device__ __forceinline__ f4_t quad_transpose(f2_t x, bool odd, bool high) {
   const float p0 = quad_perm<0xB1>(x[0]), p1 = quad_perm<0xB1>(x[1]);
   const float e[2] = {odd ? p1 : x[0], odd ? x[1] : p0};
@@ -151,7 +153,7 @@ __device__ __forceinline__ f4_t contract_blocks(const f4_t &a, const float (&w)[
       ...);
   return (acc0 + acc1) + (acc2 + acc3);
 }
-// ... two chains (half the additions behind them), for the half as long sums of split rows
+// ... the two of the four chains that a half of a split row group takes
 template <int CBSZ, int V, int... B0>
 __device__ __forceinline__ f4_t contract_blocks2(const f4_t &a, const float (&w)[V],
                                                  std::integer_sequence<int, B0...>) {
@@ -173,7 +175,7 @@ __device__ __forceinline__ typename Q::rows_t contract(const f4_t &a, const floa
     return contract_blocks<Q::CBSZ, Q::V>(a, w, std::make_integer_sequence<int, Q::CB>{});
   } else {
     const f4_t x = contract_blocks2<Q::CBSZ, 4 * Q::CB>(a, w, std::make_integer_sequence<int, Q::CB>{});
-    // both halves' sums: rows 0, 1 to the lower half, rows 2, 3 to the upper
+    // both halves' sums, added as the chains of the whole rows are: rows 0, 1 to the lower half, rows 2, 3 to the upper
     typename Q::rows_t y;
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
@@ -216,20 +218,28 @@ __device__ __forceinline__ typename Q::rows_t load_rows(const float *p) {
 template <typename Q>
 struct LanePos {
   int wave, lane, col, row;  // row: first of the lane's E rows inside the workgroup
-  int arow, acol, slice;     // row and first column of the lane's A operand; first column of its contraction
-  bool odd, high, owner;     // owner: of the A operand, where two groups of lanes hold the same
+  int arow, acol, part;      // row of the lane's A operand, and the column from which on it stores it; half of a split row group
+  bool odd, high, second;    // second: of two groups of lanes that hold the same A operand
   __device__ __forceinline__ LanePos() {
     lane = threadIdx.x & 63;
     wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int group = lane / (Q::V * Q::S), part = lane / Q::V % Q::S;
-    col = lane % Q::V;
+    const int group = lane / (Q::V * Q::S);
+    part = lane / Q::V % Q::S;
+    col = Q::S == 1 ? lane % Q::V : slot(lane >> 4 & 1, lane & 15);
     row = wave * Q::RW + 4 * group + Q::E * part;
     arow = wave * Q::RW + 4 * group + (lane & 3);
-    slice = 4 * Q::CB * part;
-    acol = slice + 4 * ((lane >> 2) % Q::CB);
-    owner = Q::S == 1 || (lane & 16) == 0;
+    second = Q::S > 1 && (lane & 16);
+    acol = Q::S == 1 ? 4 * ((lane >> 2) % Q::CB) : column(4 * (lane >> 2 & 3) + 2 * second);
     odd = lane & 1;
     high = lane & 2;
+  }
+  // column of slot c of the contraction (of a half's contraction: the two chains that it takes)
+  static __device__ __forceinline__ int slot(int half, int c) { return Q::S == 1 ? c : 4 * (c >> 1) + 2 * half + (c & 1); }
+  __device__ __forceinline__ int column(int c) const { return slot(part, c); }
+  // the lane's share of the A operand to its place in LDS (of split rows, each group of lanes stores half)
+  __device__ __forceinline__ void store_operand(float *at, const f4_t &a) const {
+    if constexpr (Q::S == 1) *(f4_t *)at = a;
+    else *(f2_t *)at = f2_t{second ? a[2] : a[0], second ? a[3] : a[1]};
   }
 };
 
@@ -262,7 +272,7 @@ __device__ __forceinline__ void quad_fwd_part(const FwdArgs &a, float *__restric
   typedef typename Q::rows_t rows_t;
   float w[4 * Q::CB];
 #pragma unroll
-  for (int c = 0; c < 4 * Q::CB; ++c) w[c] = ((const float *)a.W)[((size_t)n * V + p.slice + c) * V + p.col];
+  for (int c = 0; c < 4 * Q::CB; ++c) w[c] = ((const float *)a.W)[((size_t)n * V + p.column(c)) * V + p.col];
   const size_t st_off = ((size_t)unit * K + row_base + p.row) * V + p.col;
   rows_t h = {};
   if (a.H0) h = load_rows<Q>(a.H0 + st_off);
@@ -302,10 +312,13 @@ __device__ __forceinline__ void quad_fwd_part(const FwdArgs &a, float *__restric
   auto flush = [&](int t0, int len, int buf) {
     for (int idx = tid; idx < len * V; idx += THREADS) {
       const int s = idx / V, j = idx % V;
+      const float *ys = &sm.y[buf][s][0][0] + j;
       float acc = 0.f, acc1 = 0.f;
+      // row groups in order; whole rows of a shape whose split form has two parts: as the two parts
+      constexpr int groups = Q::NW * Q::GR, half = has_split(K, V) && Q::S == 1 && K == 32 ? groups / 2 : groups;
 #pragma unroll
-      for (int i = 0; i < Q::NW * 64 / V; ++i) (Q::S > 1 && i % 2 ? acc1 : acc) += (&sm.y[buf][s][0][0])[i * V + j];
-      if constexpr (Q::S > 1) acc += acc1;  // (twice as many terms: two chains of them)
+      for (int i = 0; i < groups; ++i) (i < half ? acc : acc1) += Q::S == 1 ? ys[i * V] : ys[2 * i * V] + ys[(2 * i + 1) * V];
+      if constexpr (half < groups) acc += acc1;
       const size_t off = (size_t)(t0 + s) * v_step + j;
       if constexpr (Q::P == 1 || SEQ) {
         float *dst = (float *)a.y + ((size_t)b * T * N + n) * V + off;
@@ -359,10 +372,14 @@ __device__ __forceinline__ void quad_fwd_part(const FwdArgs &a, float *__restric
       for (int m = 0; m < E; ++m) h[m] = fmaf(f, h[m], gm * th[m]);
       if constexpr (DO_Y) {
         float y = qr[0] * h[0];
+        if constexpr (E == 4 && has_split(K, V)) {  // (as two lanes of a split row group do it)
+          y = fmaf(qr[1], h[1], y) + fmaf(qr[3], h[3], qr[2] * h[2]);
+        } else {
 #pragma unroll
-        for (int m = 1; m < E; ++m) y = fmaf(qr[m], h[m], y);
-        // lanes that share rows are consecutive, so lane order is [rows][column]
-        sm.y[buf][s][p.wave][p.lane] = y;
+          for (int m = 1; m < E; ++m) y = fmaf(qr[m], h[m], y);
+        }
+        // lanes that share rows are consecutive: [rows][column]
+        sm.y[buf][s][p.wave][p.lane - p.lane % V + p.col] = y;
       }
     }
     if (blk + 1 < nblk) store(buf ^ 1);
@@ -452,8 +469,8 @@ __global__ void __launch_bounds__(Q::THREADS, Q::V < 64 ? 2 : 1) quad_bwd_kernel
   float w[4 * Q::CB], wt[4 * Q::CB];
 #pragma unroll
   for (int c = 0; c < 4 * Q::CB; ++c) {
-    w[c] = to_f32<IO>(((const IO *)a.W)[((size_t)n * V + p.slice + c) * V + p.col]);
-    wt[c] = to_f32<IO>(((const IO *)a.W)[((size_t)n * V + p.col) * V + p.slice + c]);
+    w[c] = to_f32<IO>(((const IO *)a.W)[((size_t)n * V + p.column(c)) * V + p.col]);
+    wt[c] = to_f32<IO>(((const IO *)a.W)[((size_t)n * V + p.col) * V + p.column(c)]);
   }
   auto st_off = [&]() __attribute__((always_inline)) { return ((size_t)unit * K + row_base + p.row) * V + p.col; };
   // a part's slots in the workspace: a place that only the same lane reads again
@@ -609,11 +626,11 @@ __global__ void __launch_bounds__(Q::THREADS, Q::V < 64 ? 2 : 1) quad_bwd_kernel
 #pragma nounroll
         for (int s = 0; s < len; ++s) {
           const rows_t z = step(h, s, ha);
-          if (p.owner) *(f4_t *)&sm.H[s][a_off] = ha;
+          p.store_operand(&sm.H[s][a_off], ha);
           zst[s * (ROWS * V / E) + tid] = z;  // (only this lane reads it again)
         }
         ha = quad_transpose(h, p.odd, p.high);
-        if (p.owner) *(f4_t *)&sm.H[len][a_off] = ha;
+        p.store_operand(&sm.H[len][a_off], ha);
         // ---- sweep
         float dfacc = 0.f;
         rows_t q1, z1, h1;
@@ -642,7 +659,7 @@ __global__ void __launch_bounds__(Q::THREADS, Q::V < 64 ? 2 : 1) quad_bwd_kernel
             dS[m] = gm * G[m] * fmaf(-z[m], z[m], 1.f);
           }
           const f4_t da = quad_transpose(dS, p.odd, p.high);
-          if (p.owner) *(f4_t *)&sm.D[s][a_off] = da;
+          p.store_operand(&sm.D[s][a_off], da);
           const f4_t df4 = __builtin_amdgcn_mfma_f32_16x16x4f32(dfl, 1.f, f4_t{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
           const rows_t d = contract<Q>(da, wt);
 #pragma unroll

@@ -86,6 +86,66 @@ def test_split_rows_need_no_more_room_than_whole_rows(fwd):
         gu.compare(got, {name: ref[name] for name in got}, gu.TOL["f32"], label="room %d" % n)
 
 
+def test_split_rows_give_the_bits_of_whole_rows():
+    """32 x 32: neither the room nor the entry point shows in y, H_T or the checkpoints, nor, in the
+    backward, in what comes from the carried gradient; a pass that recomputes its checkpoints follows the
+    forward's trajectory on any room."""
+    import torch
+    from paper_2603_14360_amd import binding as mb
+    B, T, N, K, V = 2, 53, 3, 32, 32
+    desc = mb.make_desc(B, T, N, K, V, mb.M2RNN_F32)
+    al = lambda x: (x + 255) // 256 * 256
+    print("case split rows, bits", flush=True)
+    inp = make_inputs(Workload("t", B, T, N, K, V, "f32", 32, K ** -0.5, 1.0, use_H0=True, use_dHT=True))
+    dev = gu.to_device(inp, "f32")
+    args = [dev[n] for n in ("q", "k", "v", "f", "W", "H0")]
+    w_r, stream = torch.randn(N, V, device="cuda"), torch.cuda.current_stream().cuda_stream
+    new = lambda *s: torch.full(s, float("nan"), device="cuda")
+    room = lambda n: torch.full((n,), 0xFF, dtype=torch.uint8, device="cuda")
+    outs = []
+    for n in (mb.m2rnn_workspace_bytes(desc, 0), 256, None):
+        out = [new(B, T, N, V), new(B, N, K, V), new(mb.m2rnn_ckpt_bytes(desc) // 4)]
+        opts = mb.make_opts(w_r=w_r)
+        if n is None:
+            mb.m2rnn_fwd_static(desc, opts, *args, *out, stream=stream)
+        else:
+            mb.m2rnn_fwd_opt(desc, opts, *args, *out, room(n), stream=stream)
+        outs.append(out)
+    ckpt = outs[0][2]
+    least = al(B * N * V * V * 4) + al(1024 * N * V * 4) + al(256 * 2 * N * 4)
+    grads = []
+    for n, own in ((mb.m2rnn_workspace_bytes(desc, 1), 0), (least, 0), (least, al(ckpt.numel() * 4))):
+        out = [new(B, T, N, K), new(B, T, N, K), new(B, T, N, V), new(B, T, N), new(N, V, V), new(B, N, K, V)]
+        mb.m2rnn_bwd_opt(desc, mb.make_opts(), *args, None if own else ckpt, dev["dy"], dev["dHT"], *out, room(n + own),
+                         stream=stream)
+        grads.append(out)
+    torch.cuda.synchronize()
+    for out in outs:
+        assert all(torch.equal(a, b) and torch.isfinite(a).all() for a, b in zip(out, outs[0]))
+    assert all(torch.equal(a, b) and torch.isfinite(a).all() for a, b in zip(grads[1], grads[2]))
+    for name, a, b in zip(gu.GRAD_NAMES, grads[0], grads[1]):
+        assert name not in ("dq", "dk", "dH0") or torch.equal(a, b), name
+
+
+@pytest.mark.parametrize("K,most", [(32, 128), (16, 256)])
+def test_bits_do_not_depend_on_the_number_of_states(K, most):
+    """The last launch that is split and the first that is not: the same states, the same bits."""
+    import torch
+    from paper_2603_14360_amd import binding as mb
+    T, V = 35, 32
+    print("case split rows, states", K, most, flush=True)
+    dev = gu.to_device(make_inputs(Workload("t", most + 1, T, 1, K, V, "f32", 33, K ** -0.5, 1.0, use_H0=True, use_dHT=True)), "f32")
+    outs = []
+    for B in (most + 1, most):
+        args = [dev[n] if n == "W" else dev[n][:B].contiguous() for n in ("q", "k", "v", "f", "W", "H0")]
+        scan = mb.Scan(B, T, 1, K, V, "f32")
+        y, HT = scan.fwd(*args)
+        g = scan.bwd(*args, dev["dy"][:B].contiguous(), dev["dHT"][:B].contiguous())
+        outs.append([x[:most].clone() for x in (y, HT, g[0], g[1], g[5])])
+    torch.cuda.synchronize()
+    assert all(torch.equal(a, b) for a, b in zip(*outs))
+
+
 FORWARD_TURNS = [("f32", K, V) for K, V in ((128, 16), (64, 32), (128, 32), (32, 64), (64, 64), (128, 64))]
 
 
