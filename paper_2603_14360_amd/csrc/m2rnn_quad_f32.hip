@@ -72,24 +72,37 @@ struct Split : QuadOf<K_, V_, 2> {};
 // state's error does not change, and a state that saturates pays: B 4, N 8, T 512, W of gain one, forward 246 ->
 // 292 us, although only waves that need it took it.)
 // Infinities give +-1; a NaN goes through the polynomial and stays one.
-// All of a lane's elements at once, operation by operation: a lone wave issues an instruction every
-// 5.5 cycles, but one that needs the result of the one before it after 8.6.
+__device__ __forceinline__ constexpr float tanh_c(int i) {
+  constexpr float c[7] = {-0.33333295583724976f, 0.13332346081733704f,  -0.05387984961271286f, 0.02148670330643654f,
+                          -0.007946079596877098f, 0.0023012934252619743f, -0.0003584200458135456f};
+  return c[i];
+}
+__device__ __forceinline__ float tanh_f32(float x) {
+  const float x2 = x * x;
+  float p = tanh_c(6);
+#pragma unroll
+  for (int i = 5; i >= 0; --i) p = fmaf(x2, p, tanh_c(i));
+  const float near = fmaf(x * x2, p, x);
+  const float e = __builtin_amdgcn_exp2f(2.885390081777927f * __builtin_fabsf(x));
+  const float far = __builtin_copysignf(fmaf(-2.f, __builtin_amdgcn_rcpf(1.f + e), 1.f), x);
+  return __builtin_fabsf(x) >= 1.f ? far : near;
+}
+// The same of all of a lane's elements at once, operation by operation: a lone wave issues an instruction
+// every 5.5 cycles, but one that needs the result of the one before it after 8.6.
 template <typename X>
 __device__ __forceinline__ X tanh_f32(X x) {
   constexpr int E = sizeof(X) / 4;
-  constexpr float c[7] = {-0.33333295583724976f, 0.13332346081733704f,  -0.05387984961271286f, 0.02148670330643654f,
-                          -0.007946079596877098f, 0.0023012934252619743f, -0.0003584200458135456f};
   X e, p, near, far;
   const X x2 = x * x, x3 = x * x2;
 #pragma unroll
   for (int m = 0; m < E; ++m) {
     e[m] = __builtin_amdgcn_exp2f(2.885390081777927f * __builtin_fabsf(x[m]));
-    p[m] = c[6];
+    p[m] = tanh_c(6);
   }
 #pragma unroll
   for (int i = 5; i >= 0; --i)
 #pragma unroll
-    for (int m = 0; m < E; ++m) p[m] = fmaf(x2[m], p[m], c[i]);
+    for (int m = 0; m < E; ++m) p[m] = fmaf(x2[m], p[m], tanh_c(i));
 #pragma unroll
   for (int m = 0; m < E; ++m) {
     near[m] = fmaf(x3[m], p[m], x[m]);
@@ -218,24 +231,23 @@ __device__ __forceinline__ typename Q::rows_t load_rows(const float *p) {
 template <typename Q>
 struct LanePos {
   int wave, lane, col, row;  // row: first of the lane's E rows inside the workgroup
-  int arow, acol, part;      // row of the lane's A operand, and the column from which on it stores it; half of a split row group
+  int arow, acol, first;     // row of the lane's A operand, and the column from which on it stores it; first column of its contraction
   bool odd, high, second;    // second: of two groups of lanes that hold the same A operand
   __device__ __forceinline__ LanePos() {
     lane = threadIdx.x & 63;
     wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int group = lane / (Q::V * Q::S);
-    part = lane / Q::V % Q::S;
-    col = Q::S == 1 ? lane % Q::V : slot(lane >> 4 & 1, lane & 15);
+    const int group = lane / (Q::V * Q::S), part = lane / Q::V % Q::S;
+    first = Q::S == 1 ? 0 : 2 * part;
+    col = Q::S == 1 ? lane % Q::V : column(lane & 15) + (lane >> 3 & 2);
     row = wave * Q::RW + 4 * group + Q::E * part;
     arow = wave * Q::RW + 4 * group + (lane & 3);
     second = Q::S > 1 && (lane & 16);
-    acol = Q::S == 1 ? 4 * ((lane >> 2) % Q::CB) : column(4 * (lane >> 2 & 3) + 2 * second);
+    acol = Q::S == 1 ? 4 * ((lane >> 2) % Q::CB) : 8 * (lane >> 2 & 3) + (lane >> 2 & 4) + first;
     odd = lane & 1;
     high = lane & 2;
   }
-  // column of slot c of the contraction (of a half's contraction: the two chains that it takes)
-  static __device__ __forceinline__ int slot(int half, int c) { return Q::S == 1 ? c : 4 * (c >> 1) + 2 * half + (c & 1); }
-  __device__ __forceinline__ int column(int c) const { return slot(part, c); }
+  // column of slot c of the contraction, from `first` on (of a half's contraction: the two chains that it takes)
+  static __device__ __forceinline__ constexpr int column(int c) { return Q::S == 1 ? c : 4 * (c >> 1) + (c & 1); }
   // the lane's share of the A operand to its place in LDS (of split rows, each group of lanes stores half)
   __device__ __forceinline__ void store_operand(float *at, const f4_t &a) const {
     if constexpr (Q::S == 1) *(f4_t *)at = a;
@@ -271,8 +283,9 @@ __device__ __forceinline__ void quad_fwd_part(const FwdArgs &a, float *__restric
   constexpr int E = Q::E;
   typedef typename Q::rows_t rows_t;
   float w[4 * Q::CB];
+  const float *wp = (const float *)a.W + ((size_t)n * V + p.first) * V + p.col;
 #pragma unroll
-  for (int c = 0; c < 4 * Q::CB; ++c) w[c] = ((const float *)a.W)[((size_t)n * V + p.column(c)) * V + p.col];
+  for (int c = 0; c < 4 * Q::CB; ++c) w[c] = wp[p.column(c) * V];
   const size_t st_off = ((size_t)unit * K + row_base + p.row) * V + p.col;
   rows_t h = {};
   if (a.H0) h = load_rows<Q>(a.H0 + st_off);
@@ -333,7 +346,11 @@ __device__ __forceinline__ void quad_fwd_part(const FwdArgs &a, float *__restric
   };
 
   const int nblk = (T + TB - 1) / TB, nck = (T + a.C - 1) / a.C;
-  int next_ck = a.ckpt ? 0 : -1;
+  // V = 16: one row group's step by step order, and the loop without checkpoints apart from the one with
+  // them.  us, 512 steps, 4 states, as of the wider ones -> so: 16 x 16 212 -> 204, 32 x 16 217 -> 197,
+  // 64 x 16 200 -> 195; but 16 x 32 in split rows 165 -> 171 (300 states in whole rows 380 -> 386).
+  constexpr bool NARROW = V == 16;
+  int next_ck = a.ckpt || NARROW ? 0 : -1;
   float *ckpt = a.ckpt ? a.ckpt + (size_t)unit * nck * K * V + (size_t)(row_base + p.row) * V + p.col : nullptr;
   if (nblk > 0) {
     load(0);
@@ -343,34 +360,38 @@ __device__ __forceinline__ void quad_fwd_part(const FwdArgs &a, float *__restric
   for (int blk = 0; blk < nblk; ++blk) {
     const int t0 = blk * TB, len = min(TB, T - t0), buf = blk & 1;
     if (blk + 1 < nblk) load(t0 + TB);
-    // a step's vectors are fetched during the one before (V = 16: no gain)
-    constexpr bool AHEAD = V > 16;
+    // Of 64 columns and of split rows, a step's vectors are fetched during the one before.  (Whole rows of
+    // 32: 32 x 32, 64 states, 512 steps 236 us so, 240 with the fetch ahead; 128 x 32 240 and 249.)
+    constexpr bool AHEAD = V > 32 || Q::S > 1;
     rows_t kr1, qr1;
     float vj1, f1;
     auto fetch = [&](int s) __attribute__((always_inline)) {
       kr1 = *(const rows_t *)&sm.k[buf][s][p.row];
       vj1 = sm.v[buf][s][p.col];
       f1 = sm.f[buf][s];
-      if constexpr (DO_Y) qr1 = *(const rows_t *)&sm.q[buf][s][p.row];
+      if constexpr (DO_Y && AHEAD) qr1 = *(const rows_t *)&sm.q[buf][s][p.row];
     };
     if constexpr (AHEAD) fetch(0);
 #pragma nounroll
     for (int s = 0; s < len; ++s) {
-      if (t0 + s == next_ck) {  // state before step t0 + s
+      if ((!NARROW || ckpt) && t0 + s == next_ck) {  // state before step t0 + s
 #pragma unroll
         for (int m = 0; m < E; ++m) ckpt[m * V] = h[m];
         ckpt += (size_t)K * V;
         next_ck += a.C;
       }
       if constexpr (!AHEAD) fetch(s);
-      const rows_t kr = kr1, qr = qr1;
+      const rows_t kr = kr1;
+      rows_t qr = qr1;
       const float vj = vj1, f = f1, gm = 1.f - f;
       if constexpr (AHEAD) fetch(min(s + 1, TB - 1));  // (behind the end: a step that is not used)
       const f4_t ha = quad_transpose(h, p.odd, p.high);
-      const rows_t th = tanh_f32(preactivation<Q>(ha, w, kr, vj));
+      rows_t z = preactivation<Q>(ha, w, kr, vj);
+      if constexpr (!NARROW) z = tanh_f32(z);
 #pragma unroll
-      for (int m = 0; m < E; ++m) h[m] = fmaf(f, h[m], gm * th[m]);
+      for (int m = 0; m < E; ++m) h[m] = fmaf(f, h[m], gm * (NARROW ? tanh_f32((float)z[m]) : z[m]));
       if constexpr (DO_Y) {
+        if constexpr (!AHEAD) qr = *(const rows_t *)&sm.q[buf][s][p.row];
         float y = qr[0] * h[0];
         if constexpr (E == 4 && has_split(K, V)) {  // (as two lanes of a split row group do it)
           y = fmaf(qr[1], h[1], y) + fmaf(qr[3], h[3], qr[2] * h[2]);
@@ -467,10 +488,11 @@ __global__ void __launch_bounds__(Q::THREADS, Q::V < 64 ? 2 : 1) quad_bwd_kernel
   constexpr int E = Q::E;
   typedef typename Q::rows_t rows_t;
   float w[4 * Q::CB], wt[4 * Q::CB];
+  const IO *wp = (const IO *)a.W + (size_t)n * V * V;
 #pragma unroll
   for (int c = 0; c < 4 * Q::CB; ++c) {
-    w[c] = to_f32<IO>(((const IO *)a.W)[((size_t)n * V + p.column(c)) * V + p.col]);
-    wt[c] = to_f32<IO>(((const IO *)a.W)[((size_t)n * V + p.col) * V + p.column(c)]);
+    w[c] = to_f32<IO>(wp[p.first * V + p.col + p.column(c) * V]);
+    wt[c] = to_f32<IO>(wp[p.col * V + p.first + p.column(c)]);
   }
   auto st_off = [&]() __attribute__((always_inline)) { return ((size_t)unit * K + row_base + p.row) * V + p.col; };
   // a part's slots in the workspace: a place that only the same lane reads again
@@ -554,8 +576,7 @@ __global__ void __launch_bounds__(Q::THREADS, Q::V < 64 ? 2 : 1) quad_bwd_kernel
     } else {  // (element by element: 1 % here, the other way round in the forward)
 #pragma unroll
       for (int m = 0; m < E; ++m) {
-        typedef float one_t __attribute__((ext_vector_type(1)));
-        z[m] = tanh_f32(one_t{z[m]})[0];
+        z[m] = tanh_f32((float)z[m]);
         h[m] = fmaf(f, h[m], gm * z[m]);
       }
     }
