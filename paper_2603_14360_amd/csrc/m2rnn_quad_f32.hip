@@ -962,6 +962,11 @@ using QuadSplit = std::conditional_t<has_split(K, V), Split<K, V>, Quad<K, V>>;
 // 32 x 32 8 states 245 / 588 -> 172 / 433, 128 states 249 / 605 -> 181 / 451, but 192 states 249 / 606 -> 267 / 626;
 // 16 x 32, T = 256 256 states 136 / 315 -> 95 / 227.
 bool split_pays(int K, int V, int units) { return has_split(K, V) && (long long)units * K <= 4096; }
+// ... and the steps that repay what the split costs besides.  A 32-row state is two workgroups then, whose y
+// (dv, df) are summed by a launch (two) more.  us, whole / split, forward and backward, 32 x 32, 32 states:
+// T = 1 3.3 / 5.0 and 8.5 / 12.4, 8 6.5 / 7.4 and 15.2 / 16.8, 12 8.4 / 8.6 and 20.0 / 19.7, 16 10.2 / 9.9 and
+// 23.8 / 22.5.  16 x 32, 32 states: T = 1 3.2 / 3.3 and 8.1 / 8.4, 2 3.7 / 3.5 and 9.1 / 9.0.
+bool steps_repay(int K, int T) { return T >= (K == 32 ? 16 : 2); }
 
 template <typename Q>
 size_t workspace_of(int B, int T, int N, int Nqk, int C, int bwd) {
@@ -971,7 +976,7 @@ size_t workspace_of(int B, int T, int N, int Nqk, int C, int bwd) {
 }  // namespace
 
 size_t quad_workspace_bytes(int B, int T, int N, int Nqk, int K, int V, int C, int bwd, bool may_split) {
-  const bool split = may_split && split_pays(K, V, B * N);
+  const bool split = may_split && split_pays(K, V, B * N) && steps_repay(K, T);
 #define X(K_, V_)                                                                                       \
   if (K == K_ && V == V_)                                                                               \
     return split ? workspace_of<QuadSplit<K_, V_>>(B, T, N, Nqk, C, bwd)                                \
@@ -983,8 +988,10 @@ size_t quad_workspace_bytes(int B, int T, int N, int Nqk, int K, int V, int C, i
 
 hipError_t quad_fwd(const FwdArgs &a, hipStream_t s) {
   const size_t room = a.ws_bytes;
+  // (a pass without y has nothing to sum and needs no room)
   const bool split = split_pays(a.K, a.V, a.B * a.N) &&
-                     (!a.write_y || room >= quad_workspace_bytes(a.B, a.T, a.N, a.Nqk, a.K, a.V, a.C, 0, true));
+                     (!a.write_y || (steps_repay(a.K, a.T) &&
+                                     room >= quad_workspace_bytes(a.B, a.T, a.N, a.Nqk, a.K, a.V, a.C, 0, true)));
 #define X(K_, V_)                                                                                       \
   if (a.K == K_ && a.V == V_)                                                                           \
     return split ? launch_fwd<QuadSplit<K_, V_>>(a, s) : launch_fwd<Quad<K_, V_>>(a, s);
@@ -998,7 +1005,7 @@ hipError_t quad_fwd(const FwdArgs &a, hipStream_t s) {
 
 hipError_t quad_bwd(const BwdArgs &a, hipStream_t s) {
   const size_t room = a.ws_bytes;
-  const bool split = split_pays(a.K, a.V, a.B * a.N) &&
+  const bool split = split_pays(a.K, a.V, a.B * a.N) && steps_repay(a.K, a.T) &&
                      room >= quad_workspace_bytes(a.B, a.T, a.N, a.Nqk, a.K, a.V, a.C, 1, true);
   if (a.io == 0) {
 #define X(K_, V_)                                                                                   \

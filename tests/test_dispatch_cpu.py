@@ -124,6 +124,22 @@ def test_forward_kernel_choice(K, V, units, kernel, T):
     assert r["rc"] == 0
 
 
+# fp32 kernels of V = 32: states and steps around the lines from which on, and up to which, rows are split
+SPLIT_ROWS = [(32, 128, 16, "Split"), (32, 129, 16, "Quad"), (32, 8, 15, "Quad"), (32, 1, 1, "Quad"), (16, 256, 2, "Split"),
+              (16, 257, 2, "Quad"), (16, 8, 1, "Quad"), (64, 8, 40, "Quad"), (128, 2, 40, "Quad")]
+
+
+@pytest.mark.parametrize("K,units,T,form", SPLIT_ROWS)
+def test_rows_are_split_where_that_pays(K, units, T, form):
+    desc = d(units, T, 1, K, 32, F32)
+    calls = [dict(call=c, desc=desc, ws=WS, ws_bytes=ws_bytes(desc, int(c == "bwd")), ckpt=1) for c in ("fwd", "bwd")]
+    for r in lr.launches(calls):
+        kernel = r["launches"][0]["kernel"]
+        assert r["rc"] == 0 and "%s<%d, 32>" % (form, K) in kernel, kernel
+    if K == 32 and form == "Quad":   # nothing is asked for what is not used
+        assert ws_bytes(desc, 0) == 256
+
+
 SCAN_KERNELS = ("half_fwd", "mfma_fwd", "rowwave_fwd", "quad_fwd", "gen_fwd", "decode", "mfma_bwd_overlap", "rowwave_bwd",
                 "quad_bwd", "gen_bwd")
 
