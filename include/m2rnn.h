@@ -123,8 +123,8 @@ size_t m2rnn_ckpt_bytes(const m2rnn_desc *desc);
  *     query where that is less.  (C: the checkpoint interval; N V^2, N K V, B T N K terms each rounded
  *     up to 256 bytes.)  At B = 8, T = 4096, N = 16, K = V = 64 that is 0.5 MB and 42 MB, where the
  *     query asks for 537 MB and 558 MB and takes 0.4 and 0.54 of the time.
- * fp32 with K = V = 32 and at most 128 states (B N): the query holds the partial sums of half states,
- * with which two thirds of the time suffice.  A third kind of call does without: the forward on 256
+ * fp32 with K = V = 32, at most 128 states (B N) and T >= 16: the query holds the partial sums of half
+ * states, 8 B N T V bytes, as long as these are at most 64 MB; three quarters of the time suffice with them.  A third kind of call does without: the forward on 256
  * bytes, the backward on 4 B N (V^2 + ((C - 1) / 16) K V) [+ 8 B T N K] + 4096 N V + 2048 N bytes, with
  * the same results (dv, df and dW, whose sums take another order, to rounding). */
 size_t m2rnn_workspace_bytes(const m2rnn_desc *desc, int bwd);

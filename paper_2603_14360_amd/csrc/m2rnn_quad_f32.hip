@@ -966,7 +966,12 @@ bool split_pays(int K, int V, int units) { return has_split(K, V) && (long long)
 // (dv, df) are summed by a launch (two) more.  us, whole / split, forward and backward, 32 x 32, 32 states:
 // T = 1 3.3 / 5.0 and 8.5 / 12.4, 8 6.5 / 7.4 and 15.2 / 16.8, 12 8.4 / 8.6 and 20.0 / 19.7, 16 10.2 / 9.9 and
 // 23.8 / 22.5.  16 x 32, 32 states: T = 1 3.2 / 3.3 and 8.1 / 8.4, 2 3.7 / 3.5 and 9.1 / 9.0.
-bool steps_repay(int K, int T) { return T >= (K == 32 ? 16 : 2); }
+// And only while the two parts' sums stay small: the query is what a caller allocates unasked, and grows
+// with the steps (whole rows take none of it, and 1.4 times the time).
+constexpr size_t kMostParts = (size_t)64 << 20;
+bool steps_repay(int K, int V, int units, int T) {
+  return K == 32 ? T >= 16 && (size_t)units * T * V * 8 <= kMostParts : T >= 2;
+}
 
 template <typename Q>
 size_t workspace_of(int B, int T, int N, int Nqk, int C, int bwd) {
@@ -976,7 +981,7 @@ size_t workspace_of(int B, int T, int N, int Nqk, int C, int bwd) {
 }  // namespace
 
 size_t quad_workspace_bytes(int B, int T, int N, int Nqk, int K, int V, int C, int bwd, bool may_split) {
-  const bool split = may_split && split_pays(K, V, B * N) && steps_repay(K, T);
+  const bool split = may_split && split_pays(K, V, B * N) && steps_repay(K, V, B * N, T);
 #define X(K_, V_)                                                                                       \
   if (K == K_ && V == V_)                                                                               \
     return split ? workspace_of<QuadSplit<K_, V_>>(B, T, N, Nqk, C, bwd)                                \
@@ -990,7 +995,7 @@ hipError_t quad_fwd(const FwdArgs &a, hipStream_t s) {
   const size_t room = a.ws_bytes;
   // (a pass without y has nothing to sum and needs no room)
   const bool split = split_pays(a.K, a.V, a.B * a.N) &&
-                     (!a.write_y || (steps_repay(a.K, a.T) &&
+                     (!a.write_y || (steps_repay(a.K, a.V, a.B * a.N, a.T) &&
                                      room >= quad_workspace_bytes(a.B, a.T, a.N, a.Nqk, a.K, a.V, a.C, 0, true)));
 #define X(K_, V_)                                                                                       \
   if (a.K == K_ && a.V == V_)                                                                           \
@@ -1005,7 +1010,7 @@ hipError_t quad_fwd(const FwdArgs &a, hipStream_t s) {
 
 hipError_t quad_bwd(const BwdArgs &a, hipStream_t s) {
   const size_t room = a.ws_bytes;
-  const bool split = split_pays(a.K, a.V, a.B * a.N) && steps_repay(a.K, a.T) &&
+  const bool split = split_pays(a.K, a.V, a.B * a.N) && steps_repay(a.K, a.V, a.B * a.N, a.T) &&
                      room >= quad_workspace_bytes(a.B, a.T, a.N, a.Nqk, a.K, a.V, a.C, 1, true);
   if (a.io == 0) {
 #define X(K_, V_)                                                                                   \

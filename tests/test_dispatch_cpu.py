@@ -140,6 +140,18 @@ def test_rows_are_split_where_that_pays(K, units, T, form):
         assert ws_bytes(desc, 0) == 256
 
 
+@pytest.mark.parametrize("T,N,split", [(8192, 32, True), (8193, 32, False), (65536, 32, False), (2048, 128, True), (65536, 4, True)])
+def test_the_room_that_split_rows_ask_for_is_bounded(T, N, split):
+    desc = d(1, T, N, 32, 32, F32)
+    most, states = 64 << 20, N * 32 * 32 * 4
+    fwd, bwd = ws_bytes(desc, 0), ws_bytes(desc, 1)
+    assert fwd == (8 * N * T * 32 if split else 256) and fwd <= most
+    # (backward: dv as y, df, a dW per workgroup and the sums of the options' gradients)
+    assert bwd <= fwd + fwd // 32 + 2 * states + 4096 * N * 32 + 2048 * N + 1024
+    for r in lr.launches([dict(call=c, desc=desc, ws=WS, ws_bytes=n, ckpt=1) for c, n in (("fwd", fwd), ("bwd", bwd))]):
+        assert r["rc"] == 0 and ("Split<" in r["launches"][0]["kernel"]) == split
+
+
 SCAN_KERNELS = ("half_fwd", "mfma_fwd", "rowwave_fwd", "quad_fwd", "gen_fwd", "decode", "mfma_bwd_overlap", "rowwave_bwd",
                 "quad_bwd", "gen_bwd")
 
