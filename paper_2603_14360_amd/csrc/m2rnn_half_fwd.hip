@@ -25,8 +25,7 @@
 //      is kept, one register of 16 lanes per step, so that 16 steps of y collect in four registers.
 //      (Kept by a select: with zeros in the other rows of A and a running sum, 0 x NaN would
 //      carry a NaN of the state into the y of earlier steps.)
-// Launches that leave every wave a SIMD run on waves with whole rows instead where V is 32 or 64
-// (m2rnn_pair_fwd.hip).
+// Launches of few 32 x 32 or 64 x 64 states run on waves with whole rows instead (m2rnn_pair_fwd.hip).
 // q, k, v, f for 16 steps at a time are staged through LDS, the next block's global loads in
 // flight behind the current block.
 #include "m2rnn_kernels.hpp"
@@ -410,13 +409,16 @@ bool half_serves(int K, int V, int units, int T) {
 }
 
 namespace {
-// Which launches of this path run on one wave per 128 elements (m2rnn_pair_fwd.hip): those that leave every
-// wave a SIMD.  us, T = 2048, waves that share columns -> waves with whole rows: 64 x 64 4 states 420 -> 399,
-// 16 431 -> 410, 32 443 -> 424, but 128 (four waves a SIMD, with checkpoints, T = 4096) 1550 -> 2120; 32 x 32 16 states
-// 402 -> 334; 64 x 32 16 states 405 -> 339; 64 x 16 16 states 287 -> 300.
-// (By the states alone, not by the split that the room allows: y's bits do not depend on the room.)
+// Which launches of this path run on one wave per 128 elements (m2rnn_pair_fwd.hip): square states, as few as
+// leave every wave a SIMD on the finest split.  us, T = 2048, waves that share columns -> waves with whole rows: 64 x 64
+// 4 states 420 -> 399, 16 431 -> 410, 32 443 -> 424, but 128 (four waves a SIMD, with checkpoints, T = 4096) 1550 -> 2120;
+// 32 x 32 16 states 402 -> 334; 64 x 16 16 states 287 -> 300.  On the coarser splits that short sequences take they are
+// the faster ones too: 32 x 32, one workgroup per state (two waves a SIMD), 16 states, T = 8 6.4 -> 5.8 us, 44 15.6 -> 14.0.
+// (By the shape and the states alone, not by the split that the room allows: y's bits do not depend on the room.
+// So not 64 x 32: 405 -> 339 on the finest split, but without a workspace one workgroup holds the state, four waves
+// a SIMD, and 16 states take 661 -> 750 us, T = 16 9.2 -> 10.3.)
 bool pair_serves(int K, int V, int units) {
-  return (V == 32 || V == 64) && half_load(K, V, units, 1) <= 1;
+  return K == V && (V == 32 || V == 64) && half_load(K, V, units, 1) <= 1;
 }
 }  // namespace
 hipError_t half_fwd(const FwdArgs &a, hipStream_t s) {

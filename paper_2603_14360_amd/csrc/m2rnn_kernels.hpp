@@ -142,7 +142,7 @@ bool half_serves(int K, int V, int units, int T);
 // partial readouts (part_bytes for each of the K/(8 rb) parts of a state) must fit avail bytes
 int half_pick_rb(int K, int V, int units, size_t part_bytes, size_t avail, int T);
 hipError_t half_fwd(const FwdArgs &a, hipStream_t s);
-hipError_t pair_fwd(const FwdArgs &a, int rb, hipStream_t s);  // of launches whose waves have a SIMD each, V = 32, 64
+hipError_t pair_fwd(const FwdArgs &a, int rb, hipStream_t s);  // of few 32 x 32 or 64 x 64 states
 int mfma_pick_rb(int K, int V, int units);  // row blocks per workgroup of the tile serving a launch (0: none)
 
 // ---- register-resident path (bf16 io, V <= 64): one wave per 16 state rows ----

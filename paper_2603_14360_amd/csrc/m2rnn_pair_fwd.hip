@@ -1,5 +1,5 @@
-// The forward on blocks of eight state rows (m2rnn_half_fwd.hip) for launches whose waves have a SIMD each:
-// no wave waits for another one within 16 steps.
+// The forward on blocks of eight state rows (m2rnn_half_fwd.hip) for launches of few 32 x 32 or 64 x 64 states,
+// whose waves have a SIMD each: no wave waits for another one within 16 steps.
 //
 // What bounds it, and why this split: a wave alone on its SIMD issues an instruction every 5.5 cycles,
 // and a step is its chain; spread over V / 16 waves, a row block adds an LDS round trip and a barrier

@@ -124,6 +124,26 @@ def test_forward_kernel_choice(K, V, units, kernel, T):
     assert r["rc"] == 0
 
 
+# states on both sides of the line between the 8-row forwards on waves that share a row's columns and on waves
+# with whole rows; the choice looks at the shape and the states alone
+WHOLE_ROWS = [(64, 64, 1, "Pair"), (64, 64, 32, "Pair"), (64, 64, 33, "Half"), (32, 32, 1, "Pair"), (32, 32, 128, "Pair"),
+              (32, 32, 129, "Half"), (64, 32, 1, "Half"), (64, 32, 64, "Half"), (64, 16, 1, "Half"), (128, 128, 1, "Half")]
+
+
+@pytest.mark.parametrize("K,V,units,form", WHOLE_ROWS)
+def test_forward_on_waves_with_whole_rows(K, V, units, form):
+    for T in (2, 16, 44, 48, 600):
+        desc = d(units, T, 1, K, V, BF16)
+        full = ws_bytes(desc, 0)
+        calls = [dict(call="fwd", desc=desc, ws=WS, ws_bytes=n) for n in sorted({0, full // 4, full // 2, full})]
+        got = lr.launches(calls + [dict(call="static", desc=desc), dict(call="bwd", desc=desc, ws=WS, ws_bytes=ws_bytes(desc, 2))])
+        assert got[len(calls) - 1]["rc"] == got[-1]["rc"] == 0
+        for r in got:
+            assert r["rc"] in (0, 5)
+            for k in (l["kernel"] for l in r["launches"]):
+                assert not k.startswith("half_fwd_kernel") or "%s<%d, %d, " % (form, K, V) in k, (T, k)
+
+
 # fp32 kernels of V = 32: states and steps around the lines from which on, and up to which, rows are split
 SPLIT_ROWS = [(32, 128, 16, "Split"), (32, 129, 16, "Quad"), (32, 8, 15, "Quad"), (32, 1, 1, "Quad"), (16, 256, 2, "Split"),
               (16, 257, 2, "Quad"), (16, 8, 1, "Quad"), (64, 8, 40, "Quad"), (128, 2, 40, "Quad")]
