@@ -229,7 +229,7 @@ const char *m2rnn_route_string(const m2rnn_desc *desc, int bwd) {
   const int units = desc->B * desc->N;
   if (!bwd && half_serves(desc->K, desc->V, units, desc->T)) {
     const int rb = half_pick_rb(desc->K, desc->V, units, 0, 0, desc->T);
-#define X(K_, V_, RB_) \
+#define X(K_, V_, RB_, C_, R_) \
   if (desc->K == K_ && desc->V == V_ && rb == RB_) return "half<" #K_ "," #V_ "," #RB_ ">";
     M2RNN_HALF_CASES(X)
 #undef X

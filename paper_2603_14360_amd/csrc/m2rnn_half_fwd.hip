@@ -349,12 +349,14 @@ hipError_t launch(const FwdArgs &a, hipStream_t s) {
 // for the sum of their y, some 2.5 us, and save 0.01 us a step, 0.05 more for every wave that the fullest
 // SIMD has less: where one workgroup can hold a state, they are taken from the T on that repays the launch.
 // One part / parts, us: 64 x 32, 8 states, T = 4 8.2 / 11.2, 17 10.3 / 11.1, 24 13.4 / 11.1; 32 x 32, 8 states,
-// T = 32 11.3 / 11.2, 48 15.3 / 14.1, 200 53.9 / 43.6; 16 x 16, 8 states, T = 128 22.7 / 22.6, 256 46 / 40.1.
+// T = 32 11.3 / 11.2, 48 15.3 / 14.1, 200 53.9 / 43.6 (launches in a graph, on waves with whole rows: 16 states
+// T = 16 6.9 / 7.5, 24 9.4 / 9.4, 44 14.1 / 12.9, 128 states 24 9.7 / 10.2, 44 14.1 / 13.8); 16 x 16, 8 states, T = 128 22.7 / 22.6, 256 46 / 40.1.
 // Measured (us, forward, no checkpoints
 // unless stated, RB = 1 / 2 / 4 / 8):
-//   64 x 64, T 8192: 32 states 1772 / 2122 / 2938;  T 4096: 64 states 1105 / 1097 / 1491, 96 states
+//   64 x 64, T 8192: 32 states 1735 / 2134 (waves with whole rows; sharing columns 1772 / 2122 / 2938);  T 4096: 64 states 1105 / 1097 / 1491, 96 states
 //   1388 / 1518 / 1510;  T 2048 with checkpoints: 128 states 862 / 787 / 772
-//   32 x 32, with checkpoints: 16 states, T 333 69 / 74 / 85;  128, T 2048 458 / 431 / 499;
+//   32 x 32, with checkpoints: 16 states, T 333 60.8 / 61.3 / 75 (whole rows; 69 / 74 / 85);  128, T 2048
+//   sharing columns 458 / 431 / 499, whole rows RB = 2 365;
 //   512, T 1024 408 / 355 / 336
 //   64 x 16, T 777: 84 states 131 / 146 / 119 / 137;  336 252 / 233 / 184 / 216;  504 273 / 246 / 229 / 217
 namespace {
@@ -376,7 +378,7 @@ int half_pick_rb(int K, int V, int units, size_t part_bytes, size_t avail, int T
       best = rb, best_load = load, best_fits = groups <= 256;
     if (P == 1) whole = rb;
   };
-#define X(K_, V_, RB_) \
+#define X(K_, V_, RB_, C_, R_) \
   if (K == K_ && V == V_) consider(RB_);
   M2RNN_HALF_CASES(X)
 #undef X
@@ -426,12 +428,10 @@ hipError_t half_fwd(const FwdArgs &a, hipStream_t s) {
   const size_t part = a.write_y ? (size_t)a.B * a.T * a.N * a.V * 4 : 0;
   const int rb = half_pick_rb(a.K, a.V, a.B * a.N, part, a.ws_bytes, a.write_y ? a.T : INT_MAX);
   if (rb && pair_serves(a.K, a.V, a.B * a.N)) return pair_fwd(a, rb, s);
-#define H(K_, V_, RB_) \
-  if (a.K == K_ && a.V == V_ && rb == RB_) return launch<Half<K_, V_, RB_>>(a, s);
-#define W(K_, V_, RB_)
-  M2RNN_HALF_SPLITS(H, W)
-#undef H
-#undef W
+#define X(K_, V_, RB_, C_, R_) \
+  if constexpr (C_) if (a.K == K_ && a.V == V_ && rb == RB_) return launch<Half<K_, V_, RB_>>(a, s);
+  M2RNN_HALF_CASES(X)
+#undef X
   return hipErrorInvalidValue;
 }
 

@@ -302,18 +302,14 @@ inline int grid_blocks(int units, int P) { return 8 * P * ((units + 7) / 8); }
 #define M2RNN_TILE_CASES(X)                                                                      \
   X(64, 64, 2) X(64, 64, 1) X(128, 128, 1) X(32, 32, 2) X(32, 32, 1) X(16, 16, 1) X(64, 16, 1)
 
-// (K, V, RB) splits of the forward on 8-row blocks, per shape in increasing RB: those on waves that share
-// a row's columns (H) and those on waves with whole rows (W)
-#define M2RNN_HALF_SPLITS(H, W)                                                                      \
-  H(64, 64, 1) H(64, 64, 2) H(64, 64, 4) H(128, 128, 1) H(128, 128, 2) H(32, 32, 2) H(32, 32, 4)     \
-  H(16, 16, 1) H(16, 16, 2) H(64, 16, 1) H(64, 16, 2) H(64, 16, 4) H(64, 16, 8) H(32, 16, 1)         \
-  H(32, 16, 2) H(32, 16, 4) H(64, 32, 1) H(64, 32, 2) H(64, 32, 4) H(64, 32, 8)                      \
-  W(64, 64, 1) W(64, 64, 2) W(32, 32, 1) W(32, 32, 2) W(32, 32, 4)
-// all splits of a shape
-#define M2RNN_HALF_CASES(X)                                                                      \
-  X(64, 64, 1) X(64, 64, 2) X(64, 64, 4) X(128, 128, 1) X(128, 128, 2) X(32, 32, 1) X(32, 32, 2) \
-  X(32, 32, 4) X(16, 16, 1) X(16, 16, 2) X(64, 16, 1) X(64, 16, 2) X(64, 16, 4) X(64, 16, 8)                  \
-  X(32, 16, 1) X(32, 16, 2) X(32, 16, 4) X(64, 32, 1) X(64, 32, 2) X(64, 32, 4) X(64, 32, 8)
+// (K, V, RB) splits of the forward on 8-row blocks, per shape in increasing RB, and the forms that a launch
+// can take on them: waves that share a row's columns (C), waves with whole rows (R; few square states)
+#define M2RNN_HALF_CASES(X)  /* K, V, RB, C, R */                                                \
+  X(64, 64, 1, 1, 1) X(64, 64, 2, 1, 1) X(64, 64, 4, 1, 0) X(128, 128, 1, 1, 0) X(128, 128, 2, 1, 0) \
+  X(32, 32, 1, 0, 1) X(32, 32, 2, 1, 1) X(32, 32, 4, 1, 1) X(16, 16, 1, 1, 0) X(16, 16, 2, 1, 0) \
+  X(64, 16, 1, 1, 0) X(64, 16, 2, 1, 0) X(64, 16, 4, 1, 0) X(64, 16, 8, 1, 0) X(32, 16, 1, 1, 0) \
+  X(32, 16, 2, 1, 0) X(32, 16, 4, 1, 0) X(64, 32, 1, 1, 0) X(64, 32, 2, 1, 0) X(64, 32, 4, 1, 0) \
+  X(64, 32, 8, 1, 0)
 
 // (K, V) shapes of the register-resident (one wave per row block) kernels
 #define M2RNN_ROWWAVE_CASES(X)                                                                  \

@@ -322,12 +322,10 @@ hipError_t launch(const FwdArgs &a, hipStream_t s) {
 }  // namespace
 
 hipError_t pair_fwd(const FwdArgs &a, int rb, hipStream_t s) {
-#define H(K_, V_, RB_)
-#define W(K_, V_, RB_) \
-  if (a.K == K_ && a.V == V_ && rb == RB_) return launch<Pair<K_, V_, RB_>>(a, s);
-  M2RNN_HALF_SPLITS(H, W)
-#undef H
-#undef W
+#define X(K_, V_, RB_, C_, R_) \
+  if constexpr (R_) if (a.K == K_ && a.V == V_ && rb == RB_) return launch<Pair<K_, V_, RB_>>(a, s);
+  M2RNN_HALF_CASES(X)
+#undef X
   return hipErrorInvalidValue;
 }
 

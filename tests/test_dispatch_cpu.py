@@ -144,6 +144,25 @@ def test_forward_on_waves_with_whole_rows(K, V, units, form):
                 assert not k.startswith("half_fwd_kernel") or "%s<%d, %d, " % (form, K, V) in k, (T, k)
 
 
+HALF_SHAPES = [(64, 64), (128, 128), (32, 32), (16, 16), (64, 16), (32, 16), (64, 32)]
+
+
+@pytest.mark.parametrize("K,V", HALF_SHAPES)
+def test_every_split_that_is_chosen_is_built(K, V):
+    """Any number of states around the lines, any room, any length: a launch or a refusal, and in the
+    end the pass that recomputes checkpoints; never an instantiation that is missing."""
+    lines = [1, 2, 4, 8, 16, 32, 64, 128, 256, 512, 1024, 2048]
+    calls = []
+    for units in sorted({max(1, u + e) for u in lines for e in (-1, 0, 1)}):
+        for T in (2, 17, 46, 300):
+            desc = d(units, T, 1, K, V, BF16)
+            part = units * T * V * 4
+            calls += [dict(call="fwd", desc=desc, ws=WS, ws_bytes=P * part) for P in (16, 8, 4, 2, 1, 0)]
+            calls += [dict(call="static", desc=desc), dict(call="bwd", desc=desc, ws=WS, ws_bytes=ws_bytes(desc, 2))]
+    for c, r in zip(calls, lr.launches(calls)):
+        assert r["rc"] in (0, 5) and (r["rc"] == 0) == bool(r["launches"]), (c, r)
+
+
 # fp32 kernels of V = 32: states and steps around the lines from which on, and up to which, rows are split
 SPLIT_ROWS = [(32, 128, 16, "Split"), (32, 129, 16, "Quad"), (32, 8, 15, "Quad"), (32, 1, 1, "Quad"), (16, 256, 2, "Split"),
               (16, 257, 2, "Quad"), (16, 8, 1, "Quad"), (64, 8, 40, "Quad"), (128, 2, 40, "Quad")]
