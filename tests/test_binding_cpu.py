@@ -80,3 +80,29 @@ def test_errors_are_exceptions(recorded):
     assert e.value.code == 3 and "m2rnn_fwd failed" in str(e.value)
     with pytest.raises(mb.M2RNNError, match="m2rnn_bwd_opt failed"):
         scan.bwd(x, x, x, x, x, None, x, grad_clip=1.0)
+
+
+@pytest.mark.parametrize("fault", ["no compiler", "no torch"])
+def test_the_library_is_built_without_the_call_module(tmp_path, monkeypatch, fault):
+    """A missing host compiler or torch leaves libm2rnn.so built and in its place."""
+    import builtins
+    from paper_2603_14360_amd import build
+    (tmp_path / "a.hip").write_text("")
+    for name, value in (("CSRC", tmp_path), ("OBJ", tmp_path / "o"), ("LIB", tmp_path / "lib.so"), ("CALL", tmp_path / "call.so")):
+        monkeypatch.setattr(build, name, str(value))
+    monkeypatch.setattr(build, "_compile", lambda src: src + ".o")
+    monkeypatch.setattr(build.subprocess, "check_call", lambda cmd: open(cmd[cmd.index("-o") + 1], "w").close())
+    if fault == "no compiler":
+        monkeypatch.setattr(build, "CXX", str(tmp_path / "missing"))
+        with pytest.raises(RuntimeError, match="py_call"):
+            build.build(verbose=False)
+    else:
+        real = builtins.__import__
+
+        def without_torch(name, *args, **kw):
+            if name == "torch":
+                raise ImportError(name)
+            return real(name, *args, **kw)
+        monkeypatch.setattr(builtins, "__import__", without_torch)
+        assert build.build(verbose=False) == str(tmp_path / "lib.so")
+    assert (tmp_path / "lib.so").exists() and not (tmp_path / "call.so").exists()
