@@ -102,11 +102,20 @@ _call_module = None
 
 def _call():
     """The module that calls the library with the tensors themselves (csrc/py_call.cpp), with the entry
-    points of lib(); raises if it has not been built."""
+    points of lib(); raises if it has not been built for this Python and this torch."""
     global _call_module
     if _call_module is None:
         L = lib()
-        from paper_2603_14360_amd import _call as module
+        import torch
+        again = "; run `python -m paper_2603_14360_amd.build`. There is no fallback path."
+        try:
+            from paper_2603_14360_amd import _call as module
+        except ImportError as e:
+            raise RuntimeError("the module _call is not built for this Python and torch (%s)%s" % (e, again)) from e
+        built_for = getattr(module, "torch_version", "(unknown)")
+        if built_for != torch.__version__:
+            raise RuntimeError("the module _call is built for torch %s and this is %s%s"
+                               % (built_for, torch.__version__, again))
         address = lambda f: ctypes.cast(f, ctypes.c_void_p).value
         module.init(address(L.m2rnn_fwd_opt), address(L.m2rnn_bwd_opt))
         _call_module = module

@@ -1,5 +1,6 @@
-"""Builds libm2rnn.so (the C-ABI library) in-tree with hipcc for gfx950, and _call.so, the host-only
-Python module that the binding calls it with.
+"""Builds libm2rnn.so (the C-ABI library) in-tree with hipcc for gfx950, and _call, the host-only Python
+module that the binding calls it with (for the Python and the torch that build it: the file name says
+the one, the module the other).
 
     python -m paper_2603_14360_amd.build
 
@@ -12,12 +13,13 @@ import glob
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libm2rnn.so")
-CALL = os.path.join(HERE, "_call.so")
+CALL = os.path.join(HERE, "_call" + sysconfig.get_config_var("EXT_SUFFIX"))
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 CXX = os.environ.get("CXX", "g++")
@@ -43,14 +45,14 @@ def _compile(src):
 
 def _compile_call():
     """csrc/py_call.cpp against the headers of the torch that is installed."""
-    import sysconfig
     import torch
     root = os.path.dirname(torch.__file__)
     inc = [os.path.join(root, "include"), os.path.join(root, "include", "torch", "csrc", "api", "include"),
            sysconfig.get_paths()["include"]]
     tmp = CALL + ".tmp%d" % os.getpid()
     cmd = [CXX, "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden",
-           "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI] + ["-I" + i for i in inc]
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI,
+           '-DM2RNN_TORCH_VERSION="%s"' % torch.__version__] + ["-I" + i for i in inc]
     cmd += [os.path.join(CSRC, "py_call.cpp"), "-o", tmp, "-L" + os.path.join(root, "lib"),
             "-ltorch_python", "-ltorch_cpu", "-lc10"]
     try:
@@ -60,6 +62,9 @@ def _compile_call():
     if proc.returncode != 0:
         raise RuntimeError("%s failed on py_call.cpp:\n%s" % (CXX, proc.stderr))
     os.replace(tmp, CALL)
+    untagged = os.path.join(HERE, "_call.so")  # (one that any Python would take for its own)
+    if os.path.exists(untagged) and untagged != CALL:
+        os.remove(untagged)
 
 
 def build(verbose=True):

@@ -107,4 +107,9 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_call", nullptr, -1, methods, null
 
 }  // namespace
 
-extern "C" __attribute__((visibility("default"))) PyObject *PyInit__call() { return PyModule_Create(&module); }
+extern "C" __attribute__((visibility("default"))) PyObject *PyInit__call() {
+  PyObject *m = PyModule_Create(&module);
+  // (a tensor is read through torch's own headers: under another torch its layout may be another one)
+  if (m && PyModule_AddStringConstant(m, "torch_version", M2RNN_TORCH_VERSION) < 0) Py_CLEAR(m);
+  return m;
+}

@@ -106,3 +106,20 @@ def test_the_library_is_built_without_the_call_module(tmp_path, monkeypatch, fau
         monkeypatch.setattr(builtins, "__import__", without_torch)
         assert build.build(verbose=False) == str(tmp_path / "lib.so")
     assert (tmp_path / "lib.so").exists() and not (tmp_path / "call.so").exists()
+
+
+def test_a_call_module_of_another_torch_or_python_is_refused(monkeypatch):
+    import sys
+    import paper_2603_14360_amd as package
+    module = mb._call()
+    assert module.torch_version == torch.__version__ and module.__file__.endswith(".so") and "cpython" in module.__file__
+    monkeypatch.setattr(mb, "_call_module", None)
+    monkeypatch.setattr(torch, "__version__", "0.0")
+    with pytest.raises(RuntimeError, match="this is 0.0; run"):
+        mb._call()
+    monkeypatch.undo()
+    monkeypatch.setattr(mb, "_call_module", None)
+    monkeypatch.delattr(package, "_call", raising=False)
+    monkeypatch.setitem(sys.modules, "paper_2603_14360_amd._call", None)   # (as where no file has this Python's name)
+    with pytest.raises(RuntimeError, match="not built for this Python"):
+        mb._call()
