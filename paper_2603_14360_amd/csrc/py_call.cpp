@@ -43,6 +43,11 @@ bool addresses(PyObject *const *args, void *(&p)[n]) {
   return true;
 }
 
+bool ready(const void *entry) {
+  if (!entry) PyErr_SetString(PyExc_RuntimeError, "init has not been called");
+  return entry != nullptr;
+}
+
 bool arity(Py_ssize_t have, Py_ssize_t want) {
   if (have != want) PyErr_Format(PyExc_TypeError, "expected %zd arguments, got %zd", want, have);
   return have == want;
@@ -51,6 +56,10 @@ bool arity(Py_ssize_t have, Py_ssize_t want) {
 PyObject *init(PyObject *, PyObject *const *args, Py_ssize_t n) {
   void *p[2];
   if (!arity(n, 2) || !addresses(args, p)) return nullptr;
+  if (!p[0] || !p[1]) {
+    PyErr_SetString(PyExc_ValueError, "an entry point is NULL");
+    return nullptr;
+  }
   fwd_opt = (decltype(fwd_opt))p[0];
   bwd_opt = (decltype(bwd_opt))p[1];
   Py_RETURN_NONE;
@@ -59,7 +68,7 @@ PyObject *init(PyObject *, PyObject *const *args, Py_ssize_t n) {
 // fwd(desc, w_r, gate_alpha, gate_beta, q, k, v, f, W, H0, y, HT, ckpt, workspace, stream, bytes) -> status
 PyObject *fwd(PyObject *, PyObject *const *args, Py_ssize_t n) {
   void *p[15];
-  if (!arity(n, 16) || !addresses(args, p)) return nullptr;
+  if (!ready((const void *)fwd_opt) || !arity(n, 16) || !addresses(args, p)) return nullptr;
   const size_t bytes = PyLong_AsSize_t(args[15]);
   if (bytes == (size_t)-1 && PyErr_Occurred()) return nullptr;
   m2rnn_opts o = {};
@@ -78,7 +87,7 @@ PyObject *fwd(PyObject *, PyObject *const *args, Py_ssize_t n) {
 //     dq, dk, dv, df, dW, dH0, workspace, stream, bytes, grad_clip) -> status
 PyObject *bwd(PyObject *, PyObject *const *args, Py_ssize_t n) {
   void *p[24];
-  if (!arity(n, 26) || !addresses(args, p)) return nullptr;
+  if (!ready((const void *)bwd_opt) || !arity(n, 26) || !addresses(args, p)) return nullptr;
   const size_t bytes = PyLong_AsSize_t(args[24]);
   const double clip = PyFloat_AsDouble(args[25]);
   if (PyErr_Occurred()) return nullptr;

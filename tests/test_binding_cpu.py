@@ -123,3 +123,22 @@ def test_a_call_module_of_another_torch_or_python_is_refused(monkeypatch):
     monkeypatch.setitem(sys.modules, "paper_2603_14360_amd._call", None)   # (as where no file has this Python's name)
     with pytest.raises(RuntimeError, match="not built for this Python"):
         mb._call()
+
+
+def test_no_call_before_the_entry_points_are_known():
+    """In a process of its own: a call ahead of init, and an init without an entry point, are exceptions."""
+    import subprocess
+    import sys
+    code = """
+import torch
+from paper_2603_14360_amd import _call
+for call, error in ((lambda: _call.fwd(*[0] * 16), RuntimeError), (lambda: _call.bwd(*[0] * 26), RuntimeError),
+                    (lambda: _call.init(None, 1), ValueError), (lambda: _call.init(1, 0), ValueError),
+                    (lambda: _call.fwd(*[0] * 16), RuntimeError)):
+    try:
+        call()
+    except error:
+        continue
+    raise SystemExit("no %s" % error)
+"""
+    assert subprocess.run([sys.executable, "-c", code], cwd=mb.os.path.dirname(mb._HERE)).returncode == 0
