@@ -14,18 +14,29 @@ namespace {
 decltype(&m2rnn_fwd_opt) fwd_opt = nullptr;
 decltype(&m2rnn_bwd_opt) bwd_opt = nullptr;
 
-// None -> NULL, an int as it is, a tensor -> its address; false with a Python error set otherwise
+// None -> NULL, an int as it is, a tensor -> its address, anything else -> what its data_ptr() says (a
+// subclass of the tensor may have its own); false with a Python error set otherwise
 bool address(PyObject *o, void *&p) {
   if (o == Py_None) {
     p = nullptr;
-  } else if (THPVariable_Check(o)) {
+  } else if (THPVariable_CheckExact(o)) {
     p = THPVariable_Unpack(o).data_ptr();
   } else if (PyLong_Check(o)) {
     p = PyLong_AsVoidPtr(o);
     return !(p == nullptr && PyErr_Occurred());
   } else {
-    PyErr_SetString(PyExc_TypeError, "expected a tensor, an address or None");
-    return false;
+    PyObject *method = PyObject_GetAttrString(o, "data_ptr");
+    if (!method) {
+      if (PyErr_ExceptionMatches(PyExc_AttributeError))
+        PyErr_SetString(PyExc_TypeError, "expected a tensor, an address or None");
+      return false;
+    }
+    PyObject *number = PyObject_CallNoArgs(method);
+    Py_DECREF(method);
+    if (!number) return false;
+    p = PyLong_AsVoidPtr(number);
+    Py_DECREF(number);
+    return !(p == nullptr && PyErr_Occurred());
   }
   return true;
 }

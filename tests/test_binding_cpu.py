@@ -64,6 +64,29 @@ def test_arguments_reach_their_places(recorded):
     assert calls[-1] == ("bwd", opts, (desc,) + args[:5] + (None, None) + args[7:])
 
 
+def test_whatever_has_an_address_is_taken(recorded):
+    """As by the ctypes calls: a subclass of the tensor with a data_ptr of its own, a parameter, and any other
+    object that has the method; its exceptions come through."""
+    class Own(torch.Tensor):
+        def data_ptr(self):
+            return 4096
+
+    class Buffer:
+        def data_ptr(self):
+            return 8192
+
+    class Lost:
+        def data_ptr(self):
+            raise KeyError("lost")
+
+    scan, calls = recorded
+    x, w = torch.zeros(8), torch.nn.Parameter(torch.zeros(8))
+    scan.fwd(torch.zeros(8).as_subclass(Own), Buffer(), x, x, w)
+    assert calls[-1][2][1:6] == (4096, 8192, x.data_ptr(), x.data_ptr(), w.data_ptr())
+    with pytest.raises(KeyError):
+        scan.fwd(Lost(), x, x, x, w)
+
+
 def test_errors_are_exceptions(recorded):
     scan, calls = recorded
     x = torch.zeros(8)
