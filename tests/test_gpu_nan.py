@@ -67,3 +67,27 @@ def test_gradients_of_later_steps(io, K, V, t, bad):
     dq, dk, dv, df = got[:4]
     assert not df[0, :t + 1].isfinite().any() and not dv[0, :t, 0].isfinite().any()
     assert torch.equal(got[5][1:], clean[5][1:]) and not got[4].isfinite().any()
+
+
+@pytest.mark.parametrize("K,V,units", [(64, 64, 2), (64, 64, 130), (128, 128, 2), (32, 32, 3), (32, 32, 600), (16, 16, 3),
+                                       (32, 16, 3), (64, 16, 3), (64, 16, 300), (128, 16, 2)])
+@pytest.mark.parametrize("t", [5, 21, 36])
+def test_df_of_later_steps_in_the_matrix_core_backwards(K, V, units, t):
+    """dy of step t holds one NaN: df of the steps behind t keeps its bits, also within a chunk.  (dq, dk and
+    dv of a chunk are products that hold all its steps side by side, zeros in the places of the others.)"""
+    import torch
+    print("case df", K, V, units, t, flush=True)
+    dev = _device(K, V, units, "bf16")
+    scan = mb.Scan(units, T, 1, K, V, "bf16")
+    args = [dev[n] for n in ("q", "k", "v", "f", "W", "H0")]
+    scan.fwd(*args)
+    grads = lambda: [x.clone() for x in scan.bwd(*args, dev["dy"], dev["dHT"])]
+    clean = grads()
+    small = dev["dy"][0, t, 0].abs().argmin()   # (the largest entries set the scale of a chunk)
+    dev["dy"][0, t, 0, small] = float("nan")
+    got = grads()
+    torch.cuda.synchronize()
+    assert torch.equal(got[3][0, t + 1:], clean[3][0, t + 1:])
+    assert not got[3][0, :t + 1].isfinite().any()
+    for name, g, c in zip(gu.GRAD_NAMES, got, clean):
+        assert name == "dW" or torch.equal(g[1:], c[1:]), name
