@@ -95,6 +95,9 @@ int32_t m2rnn_max_chunk(const m2rnn_desc *desc);
  * "decode<K,V>" (T = 1: the single-launch latency kernel of recurrent inference),
  * "quad<K,V>" (fp32 throughout on the 4x4x1 matrix instructions, V <= 64), "generic<f32>" /
  * "generic<bf16>" (fp32 throughout on the vector ALUs, V = 128), or "invalid descriptor".
+ * "half" and "quad" name a shape and its split; few states run on another form of the kernel with the same
+ * name here (half_fwd_kernel<Pair<K,V,RB>>: waves with whole rows; quad_..._kernel<Split<K,V>>: rows split
+ * between the halves of a wave).
  * Static storage.  For profiling and for tests that must reach every variant. */
 const char *m2rnn_route_string(const m2rnn_desc *desc, int bwd);
 
