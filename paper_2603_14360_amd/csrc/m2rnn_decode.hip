@@ -8,7 +8,7 @@
 // y = H_1^T q is finished inside the kernel (row-block partials through LDS, one barrier),
 // and nothing needs a workspace.  The arithmetic is the register-resident forward's: the
 // problem is run transposed, S^T = W^T H^T, with the state as an fp16 (hi, lo) pair in
-// adjacent k-slots of the 16x16x32 MFMA against a W fragment that repeats each row of W.
+// two k-slots of the 16x16x32 MFMA (pair_slot) against a W fragment that repeats each row of W.
 #include "m2rnn_kernels.hpp"
 #include "m2rnn_mfma_common.hpp"
 
@@ -54,7 +54,7 @@ __global__ void __launch_bounds__(DC::THREADS, 2) decode_kernel(FwdArgs a) {
   uint2 vraw[CT];
 #pragma unroll
   for (int ct = 0; ct < CT; ++ct) vraw[ct] = *(const uint2 *)&vg[16 * ct + 4 * ig];
-  // W fragments (A operand of S^T = W^T H^T): slots 2e, 2e+1 of the MFMA for (jt, ct) hold
+  // W fragments (A operand of S^T = W^T H^T): slots pair_slot(e) and + 2 of the MFMA for (jt, ct) hold
   // W[16 ct + 4 ig + e][16 jt + jl]; they meet the (hi, lo) pair of that state element
   h8_t wf[CT][CT];
 #pragma unroll

@@ -19,8 +19,8 @@
 //      The state is exchanged as an fp16 pair (hi, lo) per element, hi + lo
 //      = H' to ~21 bits: the backward through this recurrence amplifies
 //      forward-trajectory errors by orders of magnitude at T = 4096, so a
-//      single fp16 operand (11 bits) is not enough.  The pair sits in adjacent
-//      k-slots of the MFMA and the W fragment repeats each row of W twice.
+//      single fp16 operand (11 bits) is not enough.  The pair sits in two
+//      k-slots of the MFMA (pair_slot) and the W fragment repeats each row of W twice.
 //   E  in registers, fp32:  s' = S' + (c k_i) v_j ; e = 2^{-|s'|} ; r = 1/(1+e) ;
 //      H' <- f H' + sign(s') c(1-f) (1-e) r   ( = c [f H + (1-f) tanh(s)], gate_tanh_step )
 //      split H' into (hi, lo), write the fragment to LDS, start the next step's

@@ -23,9 +23,9 @@
 //
 // Measured against the vector-ALU kernels that these replace (one workgroup per state, state and
 // W in LDS, three barriers per step): B = 4, N = 8, K = V = 32, T = 512 forward 1.13 -> 0.245 ms,
-// backward 4.34 -> 0.59 ms, and with split rows 0.173 and 0.443.  What bounds it there: waves alone on
-// their SIMD, each a chain of some 800 cycles per step (forward; 1100 with four rows per lane: 85 vector
-// instructions at 5.5 cycles for 165, 131 cycles of matrix instructions for 262).
+// backward 4.34 -> 0.59 ms, and with split rows 0.169 and 0.424.  What bounds it there: waves alone on
+// their SIMD, each a chain of some 800 cycles per step (forward; 1100 with four rows per lane: 86 vector
+// instructions at 5.5 cycles for 133, 131 cycles of matrix instructions for 262).
 #include "m2rnn_io.hpp"
 #include "m2rnn_kernels.hpp"
 
@@ -59,6 +59,9 @@ struct QuadOf {
 };
 template <int K_, int V_>
 struct Quad : QuadOf<K_, V_, 1> {};
+// The shapes that have split rows: those whose whole rows are one workgroup per state.  (64 x 32 and 128 x 32,
+// two and four of them, would gain as much, 16 states, T = 512 forward 232.5 -> 169.4 and 235.1 -> 174.0 us,
+// backward 589 -> 425 and 604 -> 433, with four and eight parts and twice the room; they are not built.)
 constexpr bool has_split(int K, int V) { return V == 32 && K <= 32; }
 template <int K_, int V_>
 struct Split : QuadOf<K_, V_, 2> {};
@@ -959,8 +962,8 @@ namespace {
 template <int K, int V>
 using QuadSplit = std::conditional_t<has_split(K, V), Split<K, V>, Quad<K, V>>;
 // As long as every wave has a SIMD (1024) for itself.  us, T = 512, forward / backward, 8 rows per wave -> split:
-// 32 x 32 8 states 245 / 588 -> 172 / 433, 128 states 249 / 605 -> 181 / 451, but 192 states 249 / 606 -> 267 / 626;
-// 16 x 32, T = 256 256 states 136 / 315 -> 95 / 227.
+// 32 x 32 8 states 230 / 583 -> 166 / 410, 128 states 233 / 601 -> 179 / 437, but 192 states 249 / 606 -> 267 / 626;
+// 16 x 32 256 states 240 / 618 -> 172 / 424.
 bool split_pays(int K, int V, int units) { return has_split(K, V) && (long long)units * K <= 4096; }
 // ... and the steps that repay what the split costs besides.  A 32-row state is two workgroups then, whose y
 // (dv, df) are summed by a launch (two) more.  us, whole / split, forward and backward, 32 x 32, 32 states:
