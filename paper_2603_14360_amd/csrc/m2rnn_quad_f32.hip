@@ -330,8 +330,9 @@ __device__ __forceinline__ void quad_fwd_part(const FwdArgs &a, float *__restric
       const int s = idx / V, j = idx % V;
       const float *ys = &sm.y[buf][s][0][0] + j;
       float acc = 0.f, acc1 = 0.f;
-      // row groups in order; whole rows of a shape whose split form has two parts: as the two parts
-      constexpr int groups = Q::NW * Q::GR, half = has_split(K, V) && Q::S == 1 && K == 32 ? groups / 2 : groups;
+      // Row groups in order; 32 rows of a shape with a split form as its two parts, 16 rows as two halves (with one chain
+      // the error of y against 64 bits was 0.5 % above that of four rows in one chain of FMAs per group).
+      constexpr int groups = Q::NW * Q::GR, half = has_split(K, V) && ROWS == K ? groups / 2 : groups;
 #pragma unroll
       for (int i = 0; i < groups; ++i) (i < half ? acc : acc1) += Q::S == 1 ? ys[i * V] : ys[2 * i * V] + ys[(2 * i + 1) * V];
       if constexpr (half < groups) acc += acc1;
@@ -763,10 +764,16 @@ __global__ void __launch_bounds__(Q::THREADS, Q::V < 64 ? 2 : 1) quad_bwd_kernel
           for (int idx = tid; idx < len * V; idx += THREADS) finish_dv(idx, dvsum[0]);
         }
         if (tid < len) {
-          float acc = 0.f, acc1 = 0.f;
+          float acc = 0.f;
+          if constexpr (Q::S == 1) {
 #pragma unroll
-          for (int r = 0; r < NW * 4; ++r) (Q::S > 1 && r % 2 ? acc1 : acc) += sm.df[r][tid];
-          if constexpr (Q::S > 1) acc += acc1;
+            for (int r = 0; r < NW * 4; ++r) acc += sm.df[r][tid];
+          } else {  // (twice as many terms: four chains of them)
+            f4_t x = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int r = 0; r < NW * 4; ++r) x[r % 4] += sm.df[r][tid];
+            acc = (x[0] + x[1]) + (x[2] + x[3]);
+          }
           const size_t o = f0 + (size_t)(t0 + tid) * N;
           if constexpr (SEQ) acc = dfsum = part ? dfsum + acc : acc;
           if (last_part) a.df[o] = acc;
