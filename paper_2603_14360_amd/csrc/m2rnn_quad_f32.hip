@@ -286,9 +286,8 @@ __device__ __forceinline__ void quad_fwd_part(const FwdArgs &a, float *__restric
   constexpr int E = Q::E;
   typedef typename Q::rows_t rows_t;
   float w[4 * Q::CB];
-  const float *wp = (const float *)a.W + ((size_t)n * V + p.first) * V + p.col;
 #pragma unroll
-  for (int c = 0; c < 4 * Q::CB; ++c) w[c] = wp[p.column(c) * V];
+  for (int c = 0; c < 4 * Q::CB; ++c) w[c] = ((const float *)a.W)[((size_t)n * V + p.first + p.column(c)) * V + p.col];
   const size_t st_off = ((size_t)unit * K + row_base + p.row) * V + p.col;
   rows_t h = {};
   if (a.H0) h = load_rows<Q>(a.H0 + st_off);
@@ -969,7 +968,7 @@ namespace {
 template <int K, int V>
 using QuadSplit = std::conditional_t<has_split(K, V), Split<K, V>, Quad<K, V>>;
 // As long as every wave has a SIMD (1024) for itself.  us, T = 512, forward / backward, 8 rows per wave -> split:
-// 32 x 32 8 states 230 / 583 -> 166 / 410, 128 states 233 / 601 -> 179 / 437, but 192 states 249 / 606 -> 267 / 626;
+// 32 x 32 8 states 230 / 583 -> 167 / 409, 128 states 233 / 601 -> 180 / 437, but 192 states 249 / 606 -> 267 / 626;
 // 16 x 32 256 states 240 / 618 -> 172 / 424.
 bool split_pays(int K, int V, int units) { return has_split(K, V) && (long long)units * K <= 4096; }
 // ... and the steps that repay what the split costs besides.  A 32-row state is two workgroups then, whose y
