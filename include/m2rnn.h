@@ -270,7 +270,8 @@ m2rnn_status m2rnn_gated_rmsnorm_bwd(int32_t B, int32_t T, int32_t D, int32_t io
  * its partial sums across workgroups is a device array inside the library, of
  * M2RNN_STATIC_SCRATCH_BYTES bytes, which every GPU the library runs on holds until the
  * process ends.  The call allocates nothing, frees nothing and synchronises nothing; it runs
- * the same kernels as m2rnn_fwd_opt and gives the same bits.
+ * what m2rnn_fwd_opt runs on as much room or less (fp32 with K = V = 32: on 256 bytes) and gives
+ * the same bits.
  *   - A descriptor whose forward cannot do with M2RNN_STATIC_SCRATCH_BYTES of scratch is
  *     rejected with M2RNN_ERR_WORKSPACE before anything is launched (e.g. B*T*N*V <= 2^19
  *     at K = V = 64 with few states; shapes whose forward needs no scratch always pass, and
